@@ -1,0 +1,280 @@
+"""The work that a user of this library has it do, as cases that can be timed and compared.
+
+Every case goes through the public binding (`paper_2511_05811_amd`).  Five kinds:
+
+  train      one optimizer step of one linear layer: two-level quantization of X and dY (both groupings), the
+             GEMMs Y, dX and dW, fused AdamW + automatic scaling + FP8 cast; `micro` micro-batches of `tokens`
+             tokens each, whose dW are accumulated in FP32.  Buffers and workspaces are kept, as a training
+             program keeps them.
+  forward    the layer without gradients (evaluation, generation): row grouping alone and one GEMM, any number
+             of tokens, outputs allocated by the call.
+  quantize   the quantizer alone, one or both groupings, on a dense or a strided tensor.
+  producers  the BF16 kernels in front of the quantizers, forward and backward, each followed by the quantizer
+             that takes the maximum they leave: SwiGLU (`what` = "swiglu") or residual add + RMSNorm ("norm").
+  optimizer  the fused weight step alone, on gradients that come from elsewhere (a reduce-scatter): FP32 or BF16
+             gradients, with or without the transposed codes.
+
+The layer shapes are those of a LLaMA-7B block (hidden 4096, FFN 11008, fused QKV 12288), of its small test
+version (hidden 256, FFN 512), and of the single-linear configuration (1024 -> 1024).
+"""
+import math
+
+import numpy as np
+import torch
+
+import paper_2511_05811_amd as moss
+
+DEV = "cuda:0"
+BOTH = moss.MOSS_Q_ROW | moss.MOSS_Q_COL
+EPS = 1e-5
+
+
+def listed():
+    return [
+        # the smallest training step of the repository's block test: latency and launches count
+        dict(name="train_small", kind="train", tokens=64, micro=1, n_in=256, n_out=512, ceil=False),
+        # a micro-batch run with gradient accumulation: the GEMMs have few rows, the optimizer all of W
+        dict(name="train_accumulate", kind="train", tokens=512, micro=2, n_in=4096, n_out=4096, ceil=False),
+        # one sequence of 2048 tokens through the fused QKV projection
+        dict(name="train_sequence", kind="train", tokens=2048, micro=1, n_in=4096, n_out=12288, ceil=False),
+        # the benchmark's batch of 8192 tokens: output projection, and one of the FFN projections (the largest)
+        dict(name="train_attn_out", kind="train", tokens=8192, micro=1, n_in=4096, n_out=4096, ceil=False),
+        dict(name="train_ffn", kind="train", tokens=8192, micro=1, n_in=4096, n_out=11008, ceil=False),
+        # a single linear layer, forward: 256 tokens, 1024 -> 1024
+        dict(name="forward_small", kind="forward", tokens=256, n_in=1024, n_out=1024, ceil=False),
+        # generation for a handful of sequences at once: every weight is read for few rows
+        dict(name="forward_generate", kind="forward", tokens=17, n_in=4096, n_out=11008, ceil=False),
+        # evaluation of a ragged batch through the down projection (long K), exponents rounded up
+        dict(name="forward_ragged", kind="forward", tokens=1333, n_in=11008, n_out=4096, ceil=True),
+        # the activation quantizer at 7B scale, both groupings
+        dict(name="quantize_both", kind="quantize", rows=8192, cols=4096, pad=0, row=True, col=True, ceil=False),
+        # what surrounds the linears of a block
+        dict(name="producers_swiglu", kind="producers", what="swiglu", rows=4096, cols=11008),
+        dict(name="producers_norm", kind="producers", what="norm", rows=8192, cols=4096),
+        # weight step fed by BF16 gradients
+        dict(name="optimizer_bf16_grad", kind="optimizer", rows=11008, cols=8192, grad_bf16=True, transpose=False),
+    ]
+
+
+def _between(rng, lo, hi, step):
+    """a multiple of `step` between lo and hi, spread over the logarithm"""
+    v = math.exp(rng.uniform(math.log(lo), math.log(hi)))
+    return max(lo, min(hi, int(round(v / step)) * step))
+
+
+def draw(rng):
+    kind = rng.choice(["train", "train", "train", "forward", "forward", "forward", "quantize", "producers", "optimizer"])
+    ceil = rng.random() < 0.3
+    if kind in ("train", "forward"):
+        # layer widths are nearly always multiples of 128; the library takes multiples of 32
+        step = 128 if rng.random() < 0.75 else 32
+        n_in, n_out = _between(rng, 256, 12288, step), _between(rng, 256, 12288, step)
+        most = 8192 * 4096 * 11008 // (n_in * n_out)
+        if n_in * n_out > 4096 * 11008:
+            n_out = max(256, 4096 * 11008 // n_in // step * step)
+            most = 8192
+        if kind == "train":
+            micro = 2 if rng.random() < 0.3 else 1
+            tokens = _between(rng, 32, max(32, min(16384, most // micro) // 32 * 32), 32)
+            return dict(kind=kind, tokens=tokens, micro=micro, n_in=n_in, n_out=n_out, ceil=ceil)
+        return dict(kind=kind, tokens=_between(rng, 1, min(16384, most), 1), n_in=n_in, n_out=n_out, ceil=ceil)
+    if kind == "quantize":
+        row = rng.random() < 0.8
+        col = not row or rng.random() < 0.7
+        rows = _between(rng, 32, 16384, 32) if col else _between(rng, 1, 16384, 1)
+        cols = _between(rng, 256, 12288, 32)
+        return dict(kind=kind, rows=rows, cols=cols, pad=64 if rng.random() < 0.2 else 0, row=row, col=col, ceil=ceil)
+    if kind == "producers":
+        what = rng.choice(["swiglu", "norm"])
+        return dict(kind=kind, what=what, rows=_between(rng, 32, 8192, 32), cols=_between(rng, 256, 11008 if what == "swiglu" else 8192, 32))
+    return dict(kind=kind, rows=_between(rng, 256, 11008, 32), cols=_between(rng, 256, 8192, 32), grad_bf16=rng.random() < 0.5,
+                transpose=rng.random() < 0.5)
+
+
+def _normal(gen, shape, scale):
+    return torch.randn(shape, generator=gen, device=DEV, dtype=torch.float32).mul_(scale)
+
+
+def _activation(gen, rows, cols, scale=1.0):
+    """N(0, 1) with 8 channels x 50: the outlier channels that activations of a trained model show"""
+    x = _normal(gen, (rows, cols), scale)
+    x[:, torch.randperm(cols, generator=gen, device=DEV)[:8]] *= 50.0
+    return x.to(torch.bfloat16)
+
+
+def _heavy_tailed(gen, rows, cols, ld):
+    """0.5 * Student-t(3) with 1 % of the channels x 100, in a tensor of row stride ld"""
+    z = _normal(gen, (rows, cols), 0.5)
+    chi = _normal(gen, (rows, cols), 1.0).square_()
+    for _ in range(2):
+        chi += _normal(gen, (rows, cols), 1.0).square_()
+    z /= chi.div_(3.0).sqrt_()
+    z[:, torch.randperm(cols, generator=gen, device=DEV)[:max(1, cols // 100)]] *= 100.0
+    x = torch.zeros((rows, ld), device=DEV, dtype=torch.bfloat16)
+    x[:, :cols] = z
+    return x[:, :cols]
+
+
+def _quant_buffers(rows, cols, row=True, col=True):
+    u8 = torch.uint8
+    out = dict(s=torch.empty(1, dtype=torch.float32, device=DEV))
+    if row:
+        out.update(q_row=torch.empty((rows, cols), dtype=u8, device=DEV), e_row=torch.empty((rows, cols // 32), dtype=u8, device=DEV))
+    if col:
+        out.update(q_col=torch.empty((cols, rows), dtype=u8, device=DEV), e_col=torch.empty((cols, rows // 32), dtype=u8, device=DEV))
+    return out
+
+
+def _quant_workspace(rows, cols):
+    return torch.zeros(max(16, moss.load().moss_quant_workspace_bytes(rows, cols, BOTH)), dtype=torch.uint8, device=DEV)
+
+
+class _Weight:
+    """FP32 master weights with their FP8 copies and optimizer state, and the buffers of the fused step."""
+
+    def __init__(self, gen, n_out, n_in, transpose=True):
+        u8 = torch.uint8
+        self.w = _normal(gen, (n_out, n_in), 0.02)
+        self.m, self.v = torch.zeros_like(self.w), torch.zeros_like(self.w)
+        self.state = moss.new_wscale_state(DEV)
+        self.wq = torch.empty((n_out, n_in), dtype=u8, device=DEV)
+        self.wq_t = torch.empty((n_in, n_out), dtype=u8, device=DEV) if transpose else None
+        self.ws = torch.empty(max(16, moss.load().moss_weight_workspace_bytes(n_out, n_in)), dtype=u8, device=DEV)
+        moss.weight_autoscale_init(self.w, self.state, wq=self.wq, wq_t=self.wq_t, workspace=self.ws)
+        self.s = self.state[4:8].view(torch.float32)
+        self.t = 0
+
+    def step(self, grad):
+        self.t += 1
+        t, b1, b2 = self.t, float(np.float32(0.9)), float(np.float32(0.95))
+        args = moss.AdamWArgs(3e-4, 0.9, 0.95, 1e-8, 0.1, 1.0 - b1, 1.0 - b2, 1.0 - b1 ** t, 1.0 - b2 ** t, 1.0, 500, t)
+        moss.weight_autoscale_cast(self.w, self.m, self.v, grad, args, self.state, wq=self.wq, wq_t=self.wq_t, workspace=self.ws)
+
+    def outputs(self):
+        out = dict(w=self.w, m=self.m, v=self.v, wq=self.wq, s=self.s)
+        if self.wq_t is not None:
+            out["wq_t"] = self.wq_t
+        return out
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    kind = case["kind"]
+    st = dict(case=case)
+    if kind == "train":
+        t, i, o = case["tokens"], case["n_in"], case["n_out"]
+        st["x"] = [_activation(gen, t, i) for _ in range(case["micro"])]
+        st["dy"] = [_normal(gen, (t, o), 1e-3).to(torch.bfloat16) for _ in range(case["micro"])]
+        st["y"] = [torch.empty((t, o), dtype=torch.bfloat16, device=DEV) for _ in range(case["micro"])]
+        st["dx"] = [torch.empty((t, i), dtype=torch.bfloat16, device=DEV) for _ in range(case["micro"])]
+        st["qx"], st["qdy"] = _quant_buffers(t, i), _quant_buffers(t, o)
+        st["ws"] = _quant_workspace(t, max(i, o))
+        st["dw"] = torch.empty((o, i), dtype=torch.float32, device=DEV)
+        st["weight"] = _Weight(gen, o, i)
+    elif kind == "forward":
+        st["x"] = _activation(gen, case["tokens"], case["n_in"])
+        st["weight"] = _Weight(gen, case["n_out"], case["n_in"], transpose=False)
+    elif kind == "quantize":
+        st["x"] = _heavy_tailed(gen, case["rows"], case["cols"], case["cols"] + case["pad"])
+        st["out"] = _quant_buffers(case["rows"], case["cols"], case["row"], case["col"])
+        st["ws"] = _quant_workspace(case["rows"], case["cols"])
+    elif kind == "producers":
+        r, c = case["rows"], case["cols"]
+        bf16 = torch.bfloat16
+        if case["what"] == "swiglu":
+            st["gate"], st["up"] = _normal(gen, (r, c), 2.0).to(bf16), _normal(gen, (r, c), 1.0).to(bf16)
+            st["dh"] = _normal(gen, (r, c), 1e-3).to(bf16)
+            st["q"] = [_quant_buffers(r, c) for _ in range(3)]
+        else:
+            st["x"], st["delta"] = _activation(gen, r, c), _normal(gen, (r, c), 0.5).to(bf16)
+            st["gamma"] = _normal(gen, (c,), 0.1).add_(1.0).to(bf16)
+            st["dy"], st["d_res"] = _normal(gen, (r, c), 1e-3).to(bf16), _normal(gen, (r, c), 1e-3).to(bf16)
+            st["q"] = [_quant_buffers(r, c) for _ in range(2)]
+    else:
+        st["weight"] = _Weight(gen, case["rows"], case["cols"], transpose=case["transpose"])
+        g = _normal(gen, (case["rows"], case["cols"]), 1e-3)
+        st["grad"] = g.to(torch.bfloat16) if case["grad_bf16"] else g
+    return st
+
+
+def run(st):
+    case = st["case"]
+    kind = case["kind"]
+    mode = moss.MOSS_EXP_CEIL if case.get("ceil") else moss.MOSS_EXP_NEAREST
+    if kind == "train":
+        qx, qdy, w = st["qx"], st["qdy"], st["weight"]
+        flags = BOTH | mode | moss.MOSS_WS_KEPT
+        for k in range(case["micro"]):
+            moss.quant_act_2level(st["x"][k], flags, out=qx, workspace=st["ws"])
+            moss.gemm_fp8_mx(qx["q_row"], qx["e_row"], qx["s"], w.wq, None, w.s, out=st["y"][k])
+            moss.quant_act_2level(st["dy"][k], flags, out=qdy, workspace=st["ws"])
+            moss.gemm_fp8_mx(qdy["q_row"], qdy["e_row"], qdy["s"], w.wq_t, None, w.s, out=st["dx"][k])
+            moss.gemm_fp8_mx(qdy["q_col"], qdy["e_col"], qdy["s"], qx["q_col"], qx["e_col"], qx["s"], out=st["dw"],
+                             accumulate=k > 0)
+        w.step(st["dw"])
+        return dict(y=st["y"], dx=st["dx"], dw=st["dw"], weight=w.outputs())
+    if kind == "forward":
+        w = st["weight"]
+        q = moss.quant_act_2level(st["x"], moss.MOSS_Q_ROW | mode)
+        y = moss.gemm_fp8_mx(q["q_row"], q["e_row"], q["s"], w.wq, None, w.s)
+        return dict(y=y, q=q["q_row"], e=q["e_row"], s=q["s"])
+    if kind == "quantize":
+        flags = (moss.MOSS_Q_ROW if case["row"] else 0) | (moss.MOSS_Q_COL if case["col"] else 0) | mode | moss.MOSS_WS_KEPT
+        moss.quant_act_2level(st["x"], flags, out=st["out"], workspace=st["ws"])
+        return st["out"]
+    if kind == "producers":
+        q = st["q"]
+        if case["what"] == "swiglu":
+            h, top = moss.swiglu_bf16(st["gate"], st["up"])
+            moss.quant_act_2level_given_max(h, top, BOTH, out=q[0])
+            d_gate, d_up, top_gate, top_up = moss.swiglu_bf16_backward(st["gate"], st["up"], st["dh"])
+            moss.quant_act_2level_given_max(d_gate, top_gate, BOTH, out=q[1])
+            moss.quant_act_2level_given_max(d_up, top_up, BOTH, out=q[2])
+            return dict(h=h, d_gate=d_gate, d_up=d_up, q=q)
+        h, y, top = moss.add_rmsnorm_bf16(st["x"], st["gamma"], EPS, delta=st["delta"])
+        moss.quant_act_2level_given_max(y, top, BOTH, out=q[0])
+        d_h, top_d = moss.rmsnorm_bf16_backward(h, st["gamma"], st["dy"], EPS, d_res=st["d_res"])
+        moss.quant_act_2level_given_max(d_h, top_d, BOTH, out=q[1])
+        return dict(h=h, y=y, d_h=d_h, q=q)
+    st["weight"].step(st["grad"])
+    return st["weight"].outputs()
+
+
+def work(case):
+    kind = case["kind"]
+    if kind == "train":
+        t, i, o, k = case["tokens"], case["n_in"], case["n_out"], case["micro"]
+        # X, dY in and Y, dX out in BF16; codes of W and of its transpose in and out; W, m, v in and out and dW out in FP32
+        return dict(bytes=4.0 * k * t * (i + o) + i * o * (4 + 24 + 4.0), flops=6.0 * k * t * i * o)
+    if kind == "forward":
+        t, i, o = case["tokens"], case["n_in"], case["n_out"]
+        return dict(bytes=t * i * (2 + 1.03125) + i * o + 2.0 * t * o, flops=2.0 * t * i * o)
+    if kind == "quantize":
+        return dict(bytes=case["rows"] * case["cols"] * (2.0 + 1.03125 * (case["row"] + case["col"])), flops=0)
+    n = case["rows"] * case["cols"]
+    if kind == "producers":
+        # the BF16 tensors in and out, and the codes of both groupings (the quantizer's reading of what was just
+        # written is not counted: a fused pass would not need it)
+        bf16_tensors, quantized = (8, 3) if case["what"] == "swiglu" else (8, 2)
+        return dict(bytes=n * (2.0 * bf16_tensors + 2.0625 * quantized), flops=0)
+    return dict(bytes=n * (24.0 + (2 if case["grad_bf16"] else 4) + 1 + case["transpose"]), flops=0)
+
+
+def tolerance(case):
+    """What a correct implementation of the same precision may differ by: about four times what the path differs by
+    from itself with the products, the SwiGLU and the norm evaluated in 64 bits (tokens 64 .. 2048, widths 256 .. 4096).
+
+    The quantizer and the weight step are specified to the bit.  The GEMMs sum in FP32 in an order of their own and
+    round Y and dX to BF16 (4.7e-4, one BF16 step of 2^-7 at most); dW differs by 1.5e-5, which the first AdamW step
+    turns into sign changes of a few updates (w: 6e-5, at most 0.03 of its RMS) and into 1.5e-5 of the codes.  The
+    producers evaluate in FP32 and round to BF16: 2.2e-5, one BF16 step, 1.5e-6 of the codes (one code is more than
+    that in a small tensor)."""
+    kind = case["kind"]
+    if kind in ("quantize", "optimizer"):
+        return "exact"
+    if kind == "producers":
+        return dict(rel=1e-4, max=0.03, differ=max(6e-6, 2.0 / (case["rows"] * case["cols"])))
+    if kind == "forward":
+        return dict(rel=2e-3, max=0.03, differ=0.0)
+    return dict(rel=2e-3, max=0.12, differ=max(6e-5, 2.0 / (case["n_in"] * case["n_out"])))
