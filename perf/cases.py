@@ -241,6 +241,77 @@ def run(st):
     return st["weight"].outputs()
 
 
+def _scale(top):
+    # (a division by a tensor: one by a Python number is carried out as a product with its reciprocal, which is not
+    # the FP32 quotient, and where amax/448 is a power of two every value halfway between two codes would move)
+    return top / torch.full_like(top, 448.0)
+
+
+def _quantized(x, ceil, by_columns=False):
+    """the values that X's codes stand for, in 64 bits: Q = e4m3(x / s * 2^-e), DQ = Q * 2^e * s, one s = amax/448
+    (FP32) per tensor, one e = round(log2(amax_i / amax)) (or its ceiling) per 32 values of a row or of a column"""
+    x = (x.t() if by_columns else x).float()
+    top = x.abs().max()
+    s = _scale(top)
+    groups = x.reshape(x.shape[0], -1, 32)
+    part, k = torch.frexp(groups.abs().amax(2, keepdim=True).double() / top.double())
+    e = (k - (part <= 0.5).int() if ceil else k - (part < math.sqrt(0.5)).int()).clamp(-127, 0)
+    power = torch.exp2(e.double())
+    q = (groups * (1.0 / s) / power.float()).clamp(-448.0, 448.0).to(torch.float8_e4m3fn)
+    return (q.double() * power * s.double()).reshape(x.shape)
+
+
+def _weight_values(w):
+    s = _scale(w.abs().max())
+    return (w * (1.0 / s)).clamp(-448.0, 448.0).to(torch.float8_e4m3fn).double() * s.double()
+
+
+def _adamw_first_step(weight, grad):
+    w, g = weight.w.double(), grad.double()
+    hp = [float(np.float32(v)) for v in (3e-4, 0.9, 0.95, 1e-8, 0.1)]
+    lr, b1, b2, eps, decay = hp
+    m, v = (1.0 - b1) * g, (1.0 - b2) * g * g
+    new = w - lr * (m / (1.0 - b1) / ((v / (1.0 - b2)).sqrt() + eps) + decay * w)
+    out = dict(w=new, m=m, v=v, wq=None, s=((w.abs().max() + lr) / 448.0).reshape(1))
+    if weight.wq_t is not None:
+        out["wq_t"] = None
+    return out
+
+
+def exact(case, seed):
+    """The numbers `run` computes, in 64 bits.  The specification fixes what is quantized or rounded on the way (the
+    codes, and the BF16 residual sum that the norm reads): that is kept.  Codes and exponents are compared as bytes."""
+    st = prepare(case, seed)
+    kind = case["kind"]
+    if kind == "train":
+        ceil, wv = case["ceil"], _weight_values(st["weight"].w)
+        out = dict(y=[], dx=[], dw=0.0)
+        for x, dy in zip(st["x"], st["dy"]):
+            out["y"].append(_quantized(x, ceil) @ wv.t())
+            out["dx"].append(_quantized(dy, ceil) @ wv)
+            out["dw"] = out["dw"] + _quantized(dy, ceil, True) @ _quantized(x, ceil, True).t()
+        return dict(out, weight=_adamw_first_step(st["weight"], out["dw"]))
+    if kind == "forward":
+        x = st["x"]
+        return dict(y=_quantized(x, case["ceil"]) @ _weight_values(st["weight"].w).t(), q=None, e=None,
+                    s=(x.abs().max().double() / 448.0).reshape(1))
+    if kind == "quantize":
+        return {k: (st["x"].abs().max().double() / 448.0).reshape(1) if k == "s" else None for k in st["out"]}
+    if kind == "producers":
+        q = [{k: None for k in one} for one in st["q"]]
+        if case["what"] == "swiglu":
+            g, u, dh = (st[k].double() for k in ("gate", "up", "dh"))
+            sig = torch.sigmoid(g)
+            return dict(h=g * sig * u, d_gate=dh * u * sig * (1.0 + g * (1.0 - sig)), d_up=dh * g * sig, q=q)
+        h = (st["x"].double() + st["delta"].double()).to(torch.bfloat16).double()
+        gamma = st["gamma"].double()
+        r = (h.square().mean(1, keepdim=True) + EPS).rsqrt()
+        n, g = h * r, st["dy"].double() * gamma
+        d_h = st["d_res"].double() + (g - n * (g * n).mean(1, keepdim=True)) * r
+        return dict(h=h, y=n * gamma, d_h=d_h, q=q)
+    return _adamw_first_step(st["weight"], st["grad"])
+
+
 def work(case):
     kind = case["kind"]
     if kind == "train":
