@@ -48,12 +48,9 @@
 #include <atomic>
 #include <type_traits>
 
-#include "moss_internal.h"
+#include "moss_gemm.h"
 
 namespace moss {
-
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int kBT = 256;                     // tile edge (rows of a and rows of b per workgroup)
 constexpr int kStageK = 128;                 // bytes of K per stage (one cache line per row)
@@ -65,56 +62,9 @@ constexpr int kBigLdsBytes = kDummyBase + 4 * 1024;              // 148 KiB
 
 extern __shared__ __attribute__((aligned(1024))) uint8_t big_smem[];
 
-// wave-wide direct global->LDS copy: every lane moves 16 bytes from base + off to
-// lds_addr + 16 * lane (lds_addr is wave-uniform and goes through M0)
-__device__ __forceinline__ void dma16(const uint8_t *base, uint32_t off, uint32_t lds_addr)
-{
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(off), "s"(base), "s"(lds_addr) : "memory", "m0");
-}
-
-template <int N> __device__ __forceinline__ void wait_vmcnt()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
-}
-
-__device__ __forceinline__ void wait_lds_and_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-// two FP32 -> two BF16 (round to nearest even), a in the low half: one V_CVT_PK_BF16_F32
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
-}
-
 struct Frags {
     v8i a[4], b[4];
 };
-
-// The block-scaled matrix instruction as volatile inline assembly: volatile asm statements keep
-// their program order, which is what pins "one matrix instruction, one LDS read, one global->LDS
-// copy" in the main loop (compiler scheduling hints did not survive: all 16 matrix instructions
-// of a substep were emitted first and the memory instructions after them in one burst).
-// SEL = 0 / 2 picks scale byte 0 / 2 of both scale registers.  Independent accumulators back to
-// back need no wait states; the places where results are consumed add their own (see callers).
-template <int SEL>
-__device__ __forceinline__ void mfma_scaled(v16f &acc, const v8i &x, const v8i &y, int sx, int sy)
-{
-    if (SEL == 0)
-        asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]"
-                     : "+a"(acc) : "v"(x), "v"(y), "v"(sx), "v"(sy));
-    else
-        asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[1,1,0]"
-                     : "+a"(acc) : "v"(x), "v"(y), "v"(sx), "v"(sy));
-}
-__device__ __forceinline__ void pin() { asm volatile("" ::: "memory"); }
 
 // What a wave needs to know about one output tile: wave-uniform bases (scalar registers) and
 // its lanes' byte offsets for the global->LDS copies.
@@ -479,6 +429,14 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
 
 }  // namespace moss
 
+bool moss_internal_gemm_big_ok(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int64_t ld_out)
+{
+    if (((M + 255) / 256) * ((N + 255) / 256) < 8) return false;
+    if (!a_e || ((uintptr_t)a_e & 3) || ((uintptr_t)b_e & 3)) return false;
+    if (K % 128 || K < 512 || K > (1 << 22)) return false;
+    return N % 8 == 0 && ld_out % 8 == 0;                      // the epilogue stores whole 16-byte pieces
+}
+
 // Returns MOSS_ERR_UNSUPPORTED when the shape does not fit the fast path (the caller then
 // uses the general kernel).
 int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, const uint8_t *a_e, const float *a_s,
@@ -486,8 +444,7 @@ int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, 
                            int64_t ld_out, int accumulate, hipStream_t st)
 {
     using namespace moss;
-    if (!a_e || K % 128 || K < 512 || K > (1 << 22)) return MOSS_ERR_UNSUPPORTED;
-    if (N % 8 || ld_out % 8) return MOSS_ERR_UNSUPPORTED;      // the epilogue stores whole 16-byte pieces
+    if (!moss_internal_gemm_big_ok(M, N, K, a_e, b_e, ld_out)) return MOSS_ERR_UNSUPPORTED;
     if ((int64_t)kBT * K >= ((int64_t)1 << 32)) return MOSS_ERR_UNSUPPORTED;
     int cus = moss_internal_cu_count();
     cus = cus >= 8 ? cus & ~7 : 8;

@@ -1,0 +1,492 @@
+// Block-scaled FP8 GEMM for problems that do not fill the machine with 256-wide tiles, and for every K that is not a
+// multiple of 128 (paper Sec. 3.1, Fig. 3b: only block-scaled matrix instructions in the main loop, the two FP32 scales
+// once in the epilogue).
+//
+// What bounds these problems is not the matrix pipe but how much of the operands is in flight: a compute unit takes
+// full 128-byte lines at about 62 B/clk, a miss takes some 2000 clocks, and with few tiles most compute units would
+// idle.  Hence
+//  * small tiles, so that there are enough workgroups, and the four waves of a workgroup split K as well (KS): each of
+//    the KS groups of WM x WN waves multiplies a contiguous part of K for the whole tile, and the partial sums meet in
+//    LDS at the end, in a fixed order.  A wave always computes (32 MI) x (32 NJ) outputs, so the LDS bytes read per
+//    matrix instruction do not grow as the tile shrinks.
+//  * SLOTS stages of K = 128 per group in flight as direct global->LDS copies of full lines.  A wave takes both
+//    substeps' fragments of a stage into registers, hands the slot straight back to the copies of stage + SLOTS and
+//    multiplies afterwards.  A group of one wave (WM = WN = 1) fills and reads slots of its own: its loop has no barrier.
+//  * the exponent bytes of the tile are brought to LDS ahead of the loop, as one dword (four groups, K = 128) per row
+//    and stage in [stage][row] order with a pitch of rows + 1 dwords, which neither the writes nor the reads find
+//    conflicts in.  A K range too long for that area is walked in several pieces.
+//  * K % 128 != 0: the copies of the last stage are clamped into the row, the missing part of the a fragments is zeroed
+//    and its exponents are 127 (rows of K / 32 exponents are then not dword aligned: they are cut out of two dwords).
+//
+// Operand layout of V_MFMA_SCALE_F32_32X32X64_F8F6F4 and the LDS swizzle are those of the large-tile kernel.
+#include <atomic>
+
+#include "moss_gemm.h"
+
+namespace moss {
+
+extern __shared__ __attribute__((aligned(1024))) uint8_t mid_smem[];
+
+constexpr int kMidThreads = 256;
+constexpr int kMidK = 128;            // bytes of K per stage: one line per row
+
+struct MidArgs {
+    int64_t M, N, K;
+    const uint8_t *a_q, *a_e;
+    const float *a_s;
+    const uint8_t *b_q, *b_e;
+    const float *b_s;
+    void *out;
+    int64_t ld_out;
+    int out_f32, accumulate;
+    int tiles_m, tiles_n;
+    int panel_stages;                 // stages whose exponents fit the LDS area
+    int e_dwords;                     // exponent rows are dword aligned
+};
+
+template <int MI, int NJ, int WM, int WN, int KS, int SLOTS>
+struct MidShape {
+    static constexpr int kBM = 32 * MI * WM, kBN = 32 * NJ * WN;
+    static constexpr int kRows = kBM + kBN;
+    static constexpr int kGroupBytes = kRows * kMidK;                  // one group's stage: a rows, then b rows
+    static constexpr int kSlot = KS * kGroupBytes;
+    static constexpr int kPanel = SLOTS * kSlot;                       // byte offset of the exponent area
+    static constexpr int kReduce = kBM * kBN * 4 * KS;                 // partial sums (they reuse the slots and the area)
+    static constexpr int kPieces = kRows / 8 / (WM * WN);              // 8-row copies per wave and stage
+    static_assert(WM * WN * KS * 64 == kMidThreads, "four waves");
+    static_assert(kRows % (16 * WM * WN) == 0, "an even number of whole copies per wave");
+};
+
+template <int MI, int NJ, int WM, int WN, int KS, int SLOTS, bool HAS_BE>
+__global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
+{
+    using S = MidShape<MI, NJ, WM, WN, KS, SLOTS>;
+    constexpr int kBM = S::kBM, kBN = S::kBN, kPieces = S::kPieces;
+    constexpr bool kAlone = WM * WN == 1;        // a group is one wave: nothing shared inside the loop
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ks = wave / (WM * WN), wg = wave % (WM * WN), wm = wg / WN, wn = wg % WN;
+    const int i32 = lane & 31, h = lane >> 5;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)mid_smem;
+    const int64_t M = p.M, N = p.N, K = p.K;
+    const int G = (int)(K >> 5);
+    const int C = (int)((K + kMidK - 1) / kMidK);     // stages of the whole K range
+
+    const float scale = (*p.a_s) * (*p.b_s);
+
+    // Workgroups are dealt round-robin to the 8 XCDs: each XCD gets a contiguous range of tiles, tile rows first, so that
+    // the tiles that share rows of b run behind one L2.
+    int tm, tn;
+    {
+        const uint32_t total = (uint32_t)p.tiles_m * (uint32_t)p.tiles_n, q = total >> 3, r = total & 7;
+        const uint32_t xcd = blockIdx.x & 7, pid = xcd * q + (xcd < r ? xcd : r) + (blockIdx.x >> 3);
+        tn = __builtin_amdgcn_readfirstlane((int)(pid / (uint32_t)p.tiles_m));
+        tm = (int)pid - tn * p.tiles_m;
+    }
+    const int64_t m0 = (int64_t)tm * kBM, n0 = (int64_t)tn * kBN;
+    const uint8_t *a_base = p.a_q + m0 * K, *b_base = p.b_q + n0 * K;
+    const int last_a = (int)(M - m0 < kBM ? M - m0 : kBM) - 1, last_b = (int)(N - n0 < kBN ? N - n0 : kBN) - 1;
+
+    // This lane's byte offsets of the wave's copies: piece x covers 8 rows of the group's stage (a rows first), the lane
+    // fetches the 16-byte chunk that its place in the swizzled row holds.  Rows beyond the matrix repeat the last row.
+    uint32_t off[kPieces];
+    uint32_t chunk[2];                           // (pieces of even and of odd number swizzle differently)
+#pragma unroll
+    for (int x = 0; x < 2; x++) chunk[x] = (uint32_t)((lane & 7) ^ ((x * 4 + (lane >> 4)) & 7)) * 16;
+#pragma unroll
+    for (int x = 0; x < kPieces; x++) {
+        const int pc = wg * kPieces + x, row = pc * 8 + (lane >> 3);
+        const bool is_a = pc * 8 < kBM;          // (kBM % 8 == 0: the same for all lanes)
+        const int r = is_a ? (row < last_a ? row : last_a) : (row - kBM < last_b ? row - kBM : last_b);
+        off[x] = (uint32_t)r * (uint32_t)K + chunk[x & 1];
+    }
+    // Copies of a stage into a slot: the bases are worked out once per stage, so that a copy is two instructions.  Stage
+    // C - 1 of a K that ends inside it is copied in one go, with offsets clamped into the row.
+    const uint32_t tail = (uint32_t)(K - (int64_t)(C - 1) * kMidK);      // bytes of the last stage that exist
+    struct Bases {
+        const uint8_t *a, *b;
+        uint32_t dst;
+    };
+    auto bases = [&](int c, int slot) {
+        return Bases{a_base + (int64_t)c * kMidK, b_base + (int64_t)c * kMidK,
+                     lds0 + (uint32_t)(slot * S::kSlot + ks * S::kGroupBytes + wg * kPieces * 1024)};
+    };
+    auto copy_piece = [&](const Bases &t, int x) { dma16((wg * kPieces + x) * 8 < kBM ? t.a : t.b, off[x], t.dst + x * 1024); };
+    auto copy_tail = [&](const Bases &t) {
+#pragma unroll
+        for (int x = 0; x < kPieces; x++)
+            dma16((wg * kPieces + x) * 8 < kBM ? t.a : t.b, chunk[x & 1] < tail ? off[x] : off[x] - chunk[x & 1], t.dst + x * 1024);
+    };
+    auto is_tail = [&](int c) { return tail < (uint32_t)kMidK && c == C - 1; };
+
+    // Exponents of stages [cb, cb + nc) into LDS: dword of (stage, row) at area[stage * (rows + 1) + row]
+    uint32_t *area_a = reinterpret_cast<uint32_t *>(mid_smem + S::kPanel);
+    uint32_t *area_b = area_a + p.panel_stages * (kBM + 1);
+    auto load_exponents = [&](const uint8_t *e, uint32_t *area, int rows, int64_t row0, int last, int64_t limit, int cb, int nc) {
+        const int per_row = kMidThreads / rows;              // threads that share a row (a power of two)
+        const int r = tid / per_row;
+        const int64_t at = (row0 + (r < last ? r : last)) * G + cb * 4;       // of this row's first dword, in bytes
+        const int first = tid % per_row;
+        constexpr int U = 8;
+        if (!e) {
+            for (int c = first; c < nc; c += per_row) area[c * (rows + 1) + r] = 0x7F7F7F7Fu;       // 2^0
+        } else if (p.e_dwords) {
+            const uint8_t *src = e + at;
+            for (int c0 = first; c0 < nc; c0 += per_row * U) {
+                uint32_t d[U];
+#pragma unroll
+                for (int u = 0; u < U; u++)
+                    if (c0 + u * per_row < nc) d[u] = *reinterpret_cast<const uint32_t *>(src + (c0 + u * per_row) * 4);
+#pragma unroll
+                for (int u = 0; u < U; u++)
+                    if (c0 + u * per_row < nc) area[(c0 + u * per_row) * (rows + 1) + r] = d[u];
+            }
+        } else {
+            // rows that are not dword aligned (e itself is): cut out of two neighbouring dwords where both lie inside the
+            // array, byte by byte at its end; 127 (2^0) beyond the row's end
+            const int64_t safe = limit * G - 8;
+            const int left = G - cb * 4, k = (int)(at & 3);
+            const uint8_t *src = e + (at - k);
+            constexpr int V = U / 2;
+            for (int c0 = first; c0 < nc; c0 += per_row * V) {
+                uint32_t lo[V], hi[V];
+#pragma unroll
+                for (int u = 0; u < V; u++) {
+                    const int c = c0 + u * per_row;
+                    lo[u] = hi[u] = 0;
+                    if (c < nc && at - k + c * 4 <= safe) {
+                        lo[u] = *reinterpret_cast<const uint32_t *>(src + c * 4);
+                        hi[u] = *reinterpret_cast<const uint32_t *>(src + c * 4 + 4);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < V; u++) {
+                    const int c = c0 + u * per_row;
+                    if (c >= nc) continue;
+                    uint32_t d = __builtin_amdgcn_alignbyte(hi[u], lo[u], (uint32_t)k);
+                    const int there = left - c * 4;          // bytes of this dword inside the row (at least one)
+                    if (at - k + c * 4 > safe) {
+                        d = 0;
+                        for (int b = 0; b < 4 && b < there; b++) d |= (uint32_t)src[k + c * 4 + b] << (8 * b);
+                    }
+                    if (there < 4) d = (d & (0xFFFFFFFFu >> (32 - 8 * there))) | (0x7F7F7F7Fu << (8 * there));
+                    area[c * (rows + 1) + r] = d;
+                }
+            }
+        }
+    };
+
+    v16f acc[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; i++)
+#pragma unroll
+        for (int j = 0; j < NJ; j++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
+
+    const int sw = (i32 >> 1) & 7;
+    const uint8_t *frag_a = mid_smem + ks * S::kGroupBytes + (wm * 32 * MI + i32) * kMidK;
+    const uint8_t *frag_b = mid_smem + ks * S::kGroupBytes + (kBM + wn * 32 * NJ + i32) * kMidK;
+    struct Stage {
+        v8i a[2][MI], b[2][NJ];
+        int sa[MI], sb[NJ];
+    };
+    // The assembly form of the instruction needs accumulators that are not named again before it has retired: with one or
+    // two accumulators the compiler pads the instructions instead.
+    auto multiply = [&](int s, v16f &d, const v8i &x, const v8i &y, int sx, int sy) {
+        if (MI * NJ >= 4) {
+            if (s == 0) mfma_scaled<0>(d, x, y, sx, sy);
+            else mfma_scaled<2>(d, x, y, sx, sy);
+        } else {
+            if (s == 0) d = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, d, 0, 0, 0, sx, 0, sy);
+            else d = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, d, 0, 0, 2, sx, 2, sy);
+            asm volatile("" : "+a"(d));          // (keeps the instruction here)
+        }
+    };
+    // 16-byte read number x of a stage's fragments (both substeps; a, then b; low and high half)
+    constexpr int kReads = 4 * (MI + NJ);
+    auto read_piece = [&](Stage &f, int so, int x) {
+        const int s = x / (2 * (MI + NJ)), fr = x % (2 * (MI + NJ)) / 2, half = x & 1;
+        const uint8_t *row = fr < MI ? frag_a + fr * 32 * kMidK : frag_b + (fr - MI) * 32 * kMidK;
+        const uint4 v = *reinterpret_cast<const uint4 *>(row + so + (((4 * s + 2 * half + h) ^ sw) << 4));
+        v8i &dst = fr < MI ? f.a[s][fr] : f.b[s][fr - MI];
+        dst[4 * half + 0] = (int)v.x; dst[4 * half + 1] = (int)v.y; dst[4 * half + 2] = (int)v.z; dst[4 * half + 3] = (int)v.w;
+    };
+    auto read_exponents = [&](uint32_t (&ra)[MI], uint32_t (&rb)[NJ], int c) {
+#pragma unroll
+        for (int i = 0; i < MI; i++) ra[i] = area_a[c * (kBM + 1) + wm * 32 * MI + i * 32 + i32];
+#pragma unroll
+        for (int j = 0; j < NJ; j++) rb[j] = HAS_BE ? area_b[c * (kBN + 1) + wn * 32 * NJ + j * 32 + i32] : 0x7F7F7F7Fu;
+    };
+    // byte 0 / 2 of a scale register = this lane's group in substep 0 / 1 (volatile: stays where it is put, away from
+    // the matrix instructions that read the registers)
+    const int sh8 = 8 * h;
+    auto shift_exponents = [&](Stage &f, const uint32_t (&ra)[MI], const uint32_t (&rb)[NJ]) {
+#pragma unroll
+        for (int i = 0; i < MI; i++) asm volatile("v_lshrrev_b32 %0, %1, %2" : "=v"(f.sa[i]) : "v"(sh8), "v"(ra[i]));
+#pragma unroll
+        for (int j = 0; j < NJ; j++) asm volatile("v_lshrrev_b32 %0, %1, %2" : "=v"(f.sb[j]) : "v"(sh8), "v"(rb[j]));
+    };
+
+    // all but the copies of the wave's `newer` latest stages (at most SLOTS - 2 are in flight behind the one waited for)
+    auto wait_newer = [&](int newer) {
+        if (SLOTS > 3 && newer >= 2) wait_vmcnt<2 * kPieces>();
+        else if (SLOTS > 2 && newer >= 1) wait_vmcnt<kPieces>();
+        else wait_vmcnt<0>();
+    };
+
+    for (int cb = 0; cb < C; cb += p.panel_stages) {
+        const int nc = C - cb < p.panel_stages ? C - cb : p.panel_stages;
+        // this group's contiguous part of the piece; `per` iterations for everyone (barriers)
+        const int per = (nc + KS - 1) / KS;
+        const int c0 = ks * per < nc ? ks * per : nc;
+        const int n = per < nc - c0 ? per : nc - c0;
+        if (cb > 0) __syncthreads();             // slots and exponents of the last piece have been read
+#pragma unroll
+        for (int s = 0; s < SLOTS; s++)
+            if (s < n) {
+                const Bases t = bases(cb + c0 + s, s);
+                if (is_tail(cb + c0 + s)) {
+                    copy_tail(t);
+                } else {
+#pragma unroll
+                    for (int x = 0; x < kPieces; x++) copy_piece(t, x);
+                }
+            }
+        load_exponents(p.a_e, area_a, kBM, m0, last_a, M, cb, nc);
+        if (HAS_BE) load_exponents(p.b_e, area_b, kBN, n0, last_b, N, cb, nc);
+        wait_vmcnt<0>();
+        __syncthreads();
+
+        // One barrier per stage.  At the top of iteration `it` the wave holds the fragments of its stage `it`: behind
+        // the barrier every wave of the group does, so that stage's slot may be refilled, and everyone's part of stage
+        // it + 1 has landed.  The reads of its fragments and the copies of stage it + SLOTS are dealt out between the
+        // matrix instructions of stage `it`.
+        Stage f0, f1;
+        int slot = 0;
+        if (n > 0) {
+            uint32_t ra[MI], rb[NJ];
+            read_exponents(ra, rb, c0);
+#pragma unroll
+            for (int x = 0; x < kReads; x++) read_piece(f0, 0, x);
+            shift_exponents(f0, ra, rb);
+        }
+        auto step = [&](Stage &f, Stage &next, int it) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            wait_newer(n - 2 - it);              // stage it + 1 has landed
+            if (!kAlone) {
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            const int after = slot + 1 == SLOTS ? 0 : slot + 1;
+            if (it < n) {
+                const int c = cb + c0 + it;
+                if (is_tail(c)) {
+#pragma unroll
+                    for (int s = 0; s < 2; s++)
+#pragma unroll
+                        for (int half = 0; half < 2; half++)
+                            if ((uint32_t)(4 * s + 2 * half + h) * 16 >= tail)
+#pragma unroll
+                                for (int i = 0; i < MI; i++)
+#pragma unroll
+                                    for (int v = 0; v < 4; v++) f.a[s][i][4 * half + v] = 0;
+                }
+                const bool last = it + SLOTS < n && is_tail(c + SLOTS), refill = it + SLOTS < n && !last;
+                const Bases t = bases(c + SLOTS, slot);
+                const int so = after * S::kSlot;
+                uint32_t ra[MI], rb[NJ];
+                read_exponents(ra, rb, it + 1 < n ? c0 + it + 1 : c0);
+                asm volatile("s_nop 4" ::: "memory");    // vector ALU write -> operand of a matrix instruction
+                constexpr int kMat = 2 * MI * NJ;
+#pragma unroll
+                for (int q = 0; q < kMat; q++) {
+                    const int s = q / (MI * NJ), i = q % (MI * NJ) / NJ, j = q % NJ;
+                    multiply(s, acc[i][j], f.b[s][j], f.a[s][i], f.sb[j], f.sa[i]);
+#pragma unroll
+                    for (int x = q * kReads / kMat; x < (q + 1) * kReads / kMat; x++) read_piece(next, so, x);   // (behind the last stage: read and not used)
+#pragma unroll
+                    for (int x = q * kPieces / kMat; x < (q + 1) * kPieces / kMat; x++)
+                        if (refill) copy_piece(t, x);
+                    if (q == kMat / 2) shift_exponents(next, ra, rb);
+                    pin();
+                }
+                if (last) copy_tail(t);
+            }
+            slot = after;
+        };
+        for (int it = 0; it < per; it += 2) {
+            step(f0, f1, it);
+            if (it + 1 < per) step(f1, f0, it + 1);
+        }
+    }
+
+    // Epilogue: every wave leaves its sums in LDS (row pitch 32 NJ floats, 16-byte chunks XOR-swizzled by row), then the
+    // workgroup walks the tile row by row, adds the KS parts in order, scales and stores.
+    // (accumulator register v of lane (i32, h) in fragment (i, j): row 32 i + i32, column 32 j + 8 (v / 4) + 4 h + v % 4)
+    constexpr int kChunks = 8 * NJ, kPart = 32 * MI * 32 * NJ;          // float4 per staged row; floats per wave
+#pragma unroll
+    for (int i = 0; i < MI; i++)
+#pragma unroll
+        for (int j = 0; j < NJ; j++) asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[i][j]));   // the last matrix instructions retire
+    __syncthreads();                             // slots and exponents have been read
+    float *part = reinterpret_cast<float *>(mid_smem);
+#pragma unroll
+    for (int i = 0; i < MI; i++)
+#pragma unroll
+        for (int j = 0; j < NJ; j++)
+#pragma unroll
+            for (int qd = 0; qd < 4; qd++)
+                *reinterpret_cast<float4 *>(part + wave * kPart + (i * 32 + i32) * 32 * NJ + (((8 * j + 2 * qd + h) ^ (i32 & (kChunks - 1))) << 2)) =
+                    make_float4(acc[i][j][4 * qd], acc[i][j][4 * qd + 1], acc[i][j][4 * qd + 2], acc[i][j][4 * qd + 3]);
+    __syncthreads();
+    const bool vec_ok = p.ld_out % 4 == 0;
+#pragma unroll 4
+    for (int id = tid; id < kBM * kBN / 4; id += kMidThreads) {
+        const int row = id / (kBN / 4), c4 = id % (kBN / 4);
+        const int rw = row / (32 * MI), rr = row % (32 * MI), cw = c4 / kChunks, cc = c4 % kChunks;
+        const float *src = part + (rw * WN + cw) * kPart + rr * 32 * NJ + ((cc ^ (rr & (kChunks - 1))) << 2);
+        float4 t = *reinterpret_cast<const float4 *>(src);
+#pragma unroll
+        for (int k = 1; k < KS; k++) {
+            const float4 u = *reinterpret_cast<const float4 *>(src + k * WM * WN * kPart);
+            t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+        }
+        const int64_t m = m0 + row, nn = n0 + 4 * c4;
+        if (m >= M || nn >= N) continue;
+        const float r[4] = {t.x * scale, t.y * scale, t.z * scale, t.w * scale};
+        if (p.out_f32) {
+            float *o = reinterpret_cast<float *>(p.out) + m * p.ld_out + nn;
+            if (vec_ok && nn + 3 < N) {
+                float4 v = make_float4(r[0], r[1], r[2], r[3]);
+                if (p.accumulate) {
+                    const float4 q = *reinterpret_cast<const float4 *>(o);
+                    v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+                }
+                *reinterpret_cast<float4 *>(o) = v;
+            } else {
+                for (int x = 0; x < 4 && nn + x < N; x++) o[x] = p.accumulate ? o[x] + r[x] : r[x];
+            }
+        } else {
+            uint16_t *o = reinterpret_cast<uint16_t *>(p.out) + m * p.ld_out + nn;
+            const uint32_t lo = pack_bf16(r[0], r[1]), hi = pack_bf16(r[2], r[3]);
+            if (vec_ok && nn + 3 < N) {
+                *reinterpret_cast<uint2 *>(o) = make_uint2(lo, hi);
+            } else {
+                for (int x = 0; x < 4 && nn + x < N; x++) o[x] = (uint16_t)((x & 2 ? hi : lo) >> (16 * (x & 1)));
+            }
+        }
+    }
+}
+
+// LDS for the exponents: what is left of `budget` behind the slots
+template <int MI, int NJ, int WM, int WN, int KS, int SLOTS>
+static int launch_mid(MidArgs p, int budget, hipStream_t st)
+{
+    using S = MidShape<MI, NJ, WM, WN, KS, SLOTS>;
+    const int64_t tiles_m = (p.M + S::kBM - 1) / S::kBM, tiles_n = (p.N + S::kBN - 1) / S::kBN;
+    if (tiles_m * tiles_n > 0x7FFFFFF) return MOSS_ERR_UNSUPPORTED;
+    const int stages = (int)((p.K + kMidK - 1) / kMidK);
+    const int per_stage = 4 * ((S::kBM + 1) + (p.b_e ? S::kBN + 1 : 0));
+    const int fit = (budget - S::kPanel) / per_stage;
+    if (fit < 1) return MOSS_ERR_UNSUPPORTED;
+    p.panel_stages = fit < stages ? fit : stages;
+    p.tiles_m = (int)tiles_m;
+    p.tiles_n = (int)tiles_n;
+    int lds = S::kPanel + p.panel_stages * per_stage;
+    if (lds < S::kReduce) lds = S::kReduce;
+    const int be = p.b_e ? 1 : 0;
+    const auto kern = be ? k_gemm_mx_mid<MI, NJ, WM, WN, KS, SLOTS, true> : k_gemm_mx_mid<MI, NJ, WM, WN, KS, SLOTS, false>;
+    static std::atomic<bool> attr_set[64][2];    // per device and kernel: the LDS size it may ask for has been raised
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MOSS_ERR_HIP;
+    if (!attr_set[dev][be].load()) {
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
+            (void)hipGetLastError();
+            return MOSS_ERR_UNSUPPORTED;
+        }
+        attr_set[dev][be].store(true);
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(kMidThreads), (size_t)lds, st, p);
+    if (hipGetLastError() != hipSuccess) return MOSS_ERR_HIP;
+    return MOSS_OK;
+}
+
+}  // namespace moss
+
+// Time of a problem in the kernels that could take it, in microseconds, from measurements on 256 compute units: a launch,
+// then per tile of the busiest compute unit a fixed part (first latency, exponents, epilogue) and a part per stage.
+//   tile        measured (M, N, K)                                                        model
+//   32 x 32     (64, 4096, 4096) 7.8, (512, 4096, 4096) 30.0, (256, 1024, 1024) 5.0       7.7, 30.5, 4.4
+//   64 x 64     (256, 4096, 4096) 12.7, (512, 4096, 4096) 23.3, (1024, 1024, 1024) 8.6    13.0, 23.8, 7.4
+//   64 x 128    (512, 4096, 4096) 16.5, (2048, 2048, 4096) 33.3, (512, 4096, 1024) 9.1    17.0, 32.0, 8.8
+//   128 x 128   (2048, 2048, 2080) 24.9, (4096, 4096, 2080) 92.8                          22.4, 83.0
+//   large       (64, 4096, 4096) 24.6, (1024, 4096, 4096) 27.4, (1333, 4096, 11008) 71    26, 30, 69
+//   general     (300, 1000, 2080) 22.5, (2048, 2048, 2080) 35.3, (64, 256, 512) 8.8       21, 35, 7.6
+namespace {
+
+struct MidPlan {
+    int kind;        // 0..3: the tiles above, -1: none of them
+    double us;
+};
+
+double per_cu(double tiles) { return tiles <= 256.0 ? 1.0 : (double)(((int64_t)tiles + 255) / 256); }
+double tiles_of(int64_t M, int64_t N, int bm, int bn) { return (double)((M + bm - 1) / bm) * (double)((N + bn - 1) / bn); }
+
+MidPlan plan_mid(int64_t M, int64_t N, int64_t K, bool b_exponents)
+{
+    const double C = (double)((K + 127) / 128), extra = b_exponents ? 0.5 : 0.0;
+    const double it4 = (double)(((int64_t)C + 3) / 4), it2 = (double)(((int64_t)C + 1) / 2);
+    const double t0 = tiles_of(M, N, 32, 32), t1 = tiles_of(M, N, 64, 64), t2 = tiles_of(M, N, 64, 128), t3 = tiles_of(M, N, 128, 128);
+    const double us[4] = {t0 <= 256.0 ? 3.9 + extra + 0.48 * it4 : 2.2 + per_cu(t0) * (0.9 + extra + 0.33 * it4),
+                          2.2 + per_cu(t1) * (3.3 + extra + 0.94 * it4),
+                          2.2 + per_cu(t2) * (3.9 + 2.0 * extra + 0.68 * it2),
+                          2.2 + per_cu(t3) * (8.0 + 3.0 * extra + 0.63 * C)};
+    MidPlan best{0, us[0]};
+    for (int k = 1; k < 4; k++)
+        if (us[k] < best.us) best = MidPlan{k, us[k]};
+    return best;
+}
+
+// k_gemm_mx_big, full or half tiles as moss_internal_gemm_big chooses them
+double us_big(int64_t M, int64_t N, int64_t K)
+{
+    const double C = (double)(K / 128), full = tiles_of(M, N, 256, 256), half = tiles_of(M, N, 128, 256);
+    const double cf = 2.2 + per_cu(full) * (8.0 + C * (0.9 + 0.6 * (full < 256.0 ? full / 256.0 : 1.0)));
+    const double ch = 2.2 + per_cu(half) * (6.0 + C * (0.55 + 0.22 * (half < 256.0 ? half / 256.0 : 1.0)));
+    return ch < cf ? ch : cf;
+}
+
+// k_gemm: up to four workgroups share a compute unit, every stage waits for its own loads
+double us_general(int64_t M, int64_t N, int64_t K)
+{
+    const double C = (double)((K + 127) / 128);
+    return 3.6 + C * (0.95 + 0.9 * tiles_of(M, N, 128, 128) / 256.0);
+}
+
+}  // namespace
+
+// Takes the problem if one of the tiles above is expected to be at least a tenth faster than the kernel that would have it
+// otherwise (large_ok: k_gemm_mx_big, else k_gemm), the accuracy of the model; MOSS_ERR_UNSUPPORTED leaves it to that one.
+int moss_internal_gemm_mid(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, const uint8_t *a_e, const float *a_s,
+                           const uint8_t *b_q, const uint8_t *b_e, const float *b_s, void *out, int out_f32, int64_t ld_out,
+                           int accumulate, bool large_ok, hipStream_t st)
+{
+    using namespace moss;
+    if (K > ((int64_t)1 << 22)) return MOSS_ERR_UNSUPPORTED;                 // 32-bit offsets inside a tile
+    if (((uintptr_t)a_e & 3) || ((uintptr_t)b_e & 3)) return MOSS_ERR_UNSUPPORTED;
+    const MidPlan plan = plan_mid(M, N, K, b_e != nullptr);
+    if (plan.us > 0.9 * (large_ok ? us_big(M, N, K) : us_general(M, N, K))) return MOSS_ERR_UNSUPPORTED;
+    MidArgs p{};
+    p.M = M; p.N = N; p.K = K;
+    p.a_q = a_q; p.a_e = a_e; p.a_s = a_s;
+    p.b_q = b_q; p.b_e = b_e; p.b_s = b_s;
+    p.out = out; p.ld_out = ld_out; p.out_f32 = out_f32; p.accumulate = accumulate;
+    p.e_dwords = K % 128 == 0;
+    switch (plan.kind) {
+        case 0: return launch_mid<1, 1, 1, 1, 4, 2>(p, 80 * 1024, st);       // two workgroups fit a compute unit
+        case 1: return launch_mid<2, 2, 1, 1, 4, 2>(p, 160 * 1024, st);
+        case 2: return launch_mid<2, 2, 1, 2, 2, 3>(p, 160 * 1024, st);
+        default: return launch_mid<2, 2, 2, 2, 1, 4>(p, 160 * 1024, st);
+    }
+}

@@ -27,6 +27,14 @@ int moss_internal_cu_count();
 int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, const uint8_t *a_e, const float *a_s,
                            const uint8_t *b_q, const uint8_t *b_e, const float *b_s, void *out, int out_f32,
                            int64_t ld_out, int accumulate, hipStream_t st);
+// whether the large-tile kernel takes the problem
+bool moss_internal_gemm_big_ok(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int64_t ld_out);
+
+// small tiles and split K for problems that leave the large tiles idle, and ragged K; MOSS_ERR_UNSUPPORTED if another kernel
+// is the better choice
+int moss_internal_gemm_mid(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, const uint8_t *a_e, const float *a_s,
+                           const uint8_t *b_q, const uint8_t *b_e, const float *b_s, void *out, int out_f32, int64_t ld_out,
+                           int accumulate, bool large_ok, hipStream_t st);
 
 namespace moss {
 

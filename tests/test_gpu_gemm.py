@@ -245,3 +245,26 @@ def test_bf16_baseline_gemm_matches_fp64_product():
         tol = np.outer(np.linalg.norm(af, axis=1), np.linalg.norm(bf, axis=1))
         err = np.abs(bf16_out_to_f64(out) - ref)
         assert (err <= 2.0 ** -8 * np.abs(ref) + 1e-5 * tol).all()
+
+
+@pytest.mark.parametrize("shape", [(33, 95, 160),          # 32 x 32 tiles: one row and one column over, two stages
+                                   (40, 60, 8224),         # ... exponents in two pieces, the second of few stages
+                                   (501, 2047, 1056),      # 64 x 64 tiles, N % 4 != 0
+                                   (500, 2000, 8224),      # ... exponents in two pieces
+                                   (512, 4000, 1056),      # 64 x 128 tiles, two K groups
+                                   (700, 2048, 4096),      # ... K % 128 == 0, three slots refilled many times
+                                   (1000, 4000, 1056)])    # 128 x 128 tiles
+def test_split_k_tiles(oracle, shape):
+    M, N, K = shape
+    rng = np.random.default_rng(M + N + K)
+    a, b = finite_codes(rng, (M, K)), finite_codes(rng, (N, K))
+    ae = rng.integers(110, 128, size=(M, K // 32), dtype=np.uint8)
+    be = rng.integers(110, 128, size=(N, K // 32), dtype=np.uint8)
+    a_s, b_s = np.float32(0.5), np.float32(0.25)
+    for exps in (None, be):
+        ref = oracle.gemm(a, ae, a_s, b, exps, b_s)
+        na, nb = oracle.row_norms(a, ae, a_s), oracle.row_norms(b, exps, b_s)
+        out = gpu_gemm(a, ae, a_s, b, exps, b_s, out_dtype=torch.float32)
+        assert_close(out.cpu().numpy().astype(np.float64), ref, na, nb, False, f"{shape} f32")
+        out = gpu_gemm(a, ae, a_s, b, exps, b_s, out_dtype=torch.bfloat16)
+        assert_close(bf16_out_to_f64(out), ref, na, nb, True, f"{shape} bf16")
