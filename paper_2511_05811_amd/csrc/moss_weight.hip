@@ -67,10 +67,11 @@ __device__ __forceinline__ WPartials ws_partials(void *ws, int64_t slots)
 }
 
 // Block-wide max / sums; the result is valid in thread 0 only.
+template <int THREADS>
 __device__ __forceinline__ void block_reduce(WCounts &c)
 {
-    __shared__ float r_amax[kWThreads / kWave];
-    __shared__ uint32_t r_over[kWThreads / kWave], r_clip[kWThreads / kWave];
+    __shared__ float r_amax[THREADS / kWave];
+    __shared__ uint32_t r_over[THREADS / kWave], r_clip[THREADS / kWave];
     c.amax = wave_max_f32(c.amax);
     c.over = wave_sum_u32(c.over);
     c.clip = wave_sum_u32(c.clip);
@@ -81,7 +82,7 @@ __device__ __forceinline__ void block_reduce(WCounts &c)
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < kWThreads / kWave; i++) {
+        for (int i = 1; i < THREADS / kWave; i++) {
             c.amax = fmaxf(c.amax, r_amax[i]);
             c.over += r_over[i];
             c.clip += r_clip[i];
@@ -91,7 +92,7 @@ __device__ __forceinline__ void block_reduce(WCounts &c)
 
 __device__ __forceinline__ void block_reduce_store(WCounts c, void *ws, int64_t slots)
 {
-    block_reduce(c);
+    block_reduce<kWThreads>(c);
     if (threadIdx.x == 0) {
         WPartials p = ws_partials(ws, slots);
         const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
@@ -141,6 +142,43 @@ __device__ __forceinline__ float scale_for_cast(const moss_wscale_state *st, int
     return (float)((double)st->s_base + cum / 448.0);
 }
 
+// One vector of four elements in the AdamW pass.
+struct StepVec {
+    float4 w, m, v, g;
+};
+
+__device__ __forceinline__ void load_step(StepVec &t, const float *w, const float *m, const float *v, const void *g, int64_t i4,
+                                          bool g_bf16)
+{
+    t.w = ld_stream_f4(reinterpret_cast<const float4 *>(w) + i4);
+    t.m = ld_stream_f4(reinterpret_cast<const float4 *>(m) + i4);
+    t.v = ld_stream_f4(reinterpret_cast<const float4 *>(v) + i4);
+    t.g = load_as_f32x4(g, i4, g_bf16);
+}
+
+__device__ __forceinline__ void step_and_store(StepVec &t, const AdamW &a, float *w, float *m, float *v, int64_t i4)
+{
+    adamw_elem(t.w.x, t.m.x, t.v.x, t.g.x, a);
+    adamw_elem(t.w.y, t.m.y, t.v.y, t.g.y, a);
+    adamw_elem(t.w.z, t.m.z, t.v.z, t.g.z, a);
+    adamw_elem(t.w.w, t.m.w, t.v.w, t.g.w, a);
+    st_stream_f4(reinterpret_cast<float4 *>(w) + i4, t.w);
+    st_stream_f4(reinterpret_cast<float4 *>(m) + i4, t.m);
+    st_stream_f4(reinterpret_cast<float4 *>(v) + i4, t.v);
+}
+
+__device__ __forceinline__ float absmax4(const float4 &t)
+{
+    return fmaxf(fmaxf(fabsf(t.x), fabsf(t.y)), fmaxf(fabsf(t.z), fabsf(t.w)));
+}
+
+// Bound: HBM (four streams in, three or four out).  All loads of kStepUnroll vectors are issued before the first
+// store: one vector at a time, a wave's loads queue behind its own stores and 11008 x 8192 with BF16 gradients took
+// 572 us (4.2 TB/s); two at a time 492 us, four 457 us (5.3 TB/s, the rate of the tile kernel below and of a plain copy).
+// (Contiguous ranges per workgroup instead of the grid-wide stride: 466 us; ordinary instead of streaming loads: 513
+// against 572 us with one vector, nothing on top of four.)
+constexpr int kStepUnroll = 4;
+
 template <bool G_BF16, bool DO_CAST>
 __global__ __launch_bounds__(kWThreads) void k_adamw_cast(float *__restrict__ w, float *__restrict__ m,
                                                           float *__restrict__ v, const void *__restrict__ g,
@@ -155,24 +193,26 @@ __global__ __launch_bounds__(kWThreads) void k_adamw_cast(float *__restrict__ w,
         limit = range_limit(s);
     }
     WCounts cnt;
-    const int64_t stride = (int64_t)gridDim.x * kWThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kWThreads + threadIdx.x; i < n4; i += stride) {
-        float4 wv = ld_stream_f4(reinterpret_cast<float4 *>(w) + i);
-        float4 mv = ld_stream_f4(reinterpret_cast<float4 *>(m) + i);
-        float4 vv = ld_stream_f4(reinterpret_cast<float4 *>(v) + i);
-        float4 gv = load_as_f32x4(g, i, G_BF16);
-        adamw_elem(wv.x, mv.x, vv.x, gv.x, a);
-        adamw_elem(wv.y, mv.y, vv.y, gv.y, a);
-        adamw_elem(wv.z, mv.z, vv.z, gv.z, a);
-        adamw_elem(wv.w, mv.w, vv.w, gv.w, a);
-        st_stream_f4(reinterpret_cast<float4 *>(w) + i, wv);
-        st_stream_f4(reinterpret_cast<float4 *>(m) + i, mv);
-        st_stream_f4(reinterpret_cast<float4 *>(v) + i, vv);
-        cnt.amax = fmaxf(cnt.amax, fmaxf(fmaxf(fabsf(wv.x), fabsf(wv.y)), fmaxf(fabsf(wv.z), fabsf(wv.w))));
-        if (DO_CAST) {
-            float y0 = wv.x * inv_s, y1 = wv.y * inv_s, y2 = wv.z * inv_s, y3 = wv.w * inv_s;
-            count4(cnt, wv, y0, y1, y2, y3, limit);
-            st_stream4(reinterpret_cast<uint32_t *>(wq) + i, cvt4_e4m3_sat(y0, y1, y2, y3));
+    const int64_t stride = (int64_t)gridDim.x * kWThreads * kStepUnroll;
+    for (int64_t i0 = (int64_t)blockIdx.x * kWThreads * kStepUnroll + threadIdx.x; i0 < n4; i0 += stride) {
+        StepVec t[kStepUnroll];
+#pragma unroll
+        for (int u = 0; u < kStepUnroll; u++) {
+            const int64_t i = i0 + u * kWThreads;
+            if (i < n4) load_step(t[u], w, m, v, g, i, G_BF16);
+        }
+#pragma unroll
+        for (int u = 0; u < kStepUnroll; u++) {
+            const int64_t i = i0 + u * kWThreads;
+            if (i >= n4) continue;
+            step_and_store(t[u], a, w, m, v, i);
+            const float4 &wv = t[u].w;
+            cnt.amax = fmaxf(cnt.amax, absmax4(wv));
+            if (DO_CAST) {
+                float y0 = wv.x * inv_s, y1 = wv.y * inv_s, y2 = wv.z * inv_s, y3 = wv.w * inv_s;
+                count4(cnt, wv, y0, y1, y2, y3, limit);
+                st_stream4(reinterpret_cast<uint32_t *>(wq) + i, cvt4_e4m3_sat(y0, y1, y2, y3));
+            }
         }
     }
     block_reduce_store(cnt, ws, slots);
@@ -211,11 +251,16 @@ __global__ __launch_bounds__(kWThreads) void k_weight_cast(const void *__restric
 }
 
 // 2-D variant used when the transposed codes are wanted as well: a workgroup owns a
-// 128 x 128 tile, walks it 8 rows at a time (32 lanes x float4 = one 512-byte row piece),
+// ROWS x 128 tile, walks it 8 rows at a time (32 lanes x float4 = one 512-byte row piece),
 // writes the codes row-major (128 bytes per row) and collects them transposed in LDS;
-// at the end 8 lanes write the 128 bytes of each transposed row.  STEP: apply AdamW first
+// at the end ROWS / 16 lanes write the ROWS bytes of each transposed row.  STEP: apply AdamW first
 // (fused optimizer step), otherwise cast only, with the scale already in the state.
-template <bool STEP, bool SRC_BF16>
+//
+// ROWS = 128 leaves whole lines of the transposed codes.  A weight of few such tiles is bound by the chain of 16
+// trips through memory of each workgroup, not by the rate: there ROWS = 32 has four times the workgroups with a
+// quarter of the trips.  BATCH vectors are loaded ahead of the first store, as in the flat pass; see tile_form for the
+// rule and what it measured.
+template <bool STEP, bool SRC_BF16, int ROWS, int BATCH>
 __global__ __launch_bounds__(kWThreads) void k_weight_tile(float *__restrict__ w, float *__restrict__ m,
                                                            float *__restrict__ v, const void *__restrict__ src,
                                                            int64_t rows, int64_t cols, AdamW a, double lr_term,
@@ -223,53 +268,53 @@ __global__ __launch_bounds__(kWThreads) void k_weight_tile(float *__restrict__ w
                                                            uint8_t *__restrict__ wq, uint8_t *__restrict__ wq_t,
                                                            void *ws, int64_t slots)
 {
-    constexpr int kPitch = kWTile + 4;
+    constexpr int kPitch = ROWS + 4;
     __shared__ __attribute__((aligned(16))) uint8_t tt[kWTile][kPitch];   // [column][row]
     const float s = scale_for_cast(st, STEP ? 1 : 0, lr_term);
     const float inv_s = s > 0.0f ? 1.0f / s : 0.0f;
     const float limit = range_limit(s);
     const int tid = threadIdx.x, rl = tid >> 5, c4 = (tid & 31) * 4;
-    const int64_t r0 = (int64_t)blockIdx.y * kWTile, c0 = (int64_t)blockIdx.x * kWTile;
+    const int64_t r0 = (int64_t)blockIdx.y * ROWS, c0 = (int64_t)blockIdx.x * kWTile;
     const int64_t col = c0 + c4;
     WCounts cnt;
-#pragma unroll 4
-    for (int it = 0; it < 16; it++) {
-        const int rr = it * 8 + rl;
-        const int64_t row = r0 + rr;
-        uint32_t code = 0;
-        if (row < rows && col < cols) {          // cols % 4 == 0: a float4 is inside or outside as a whole
-            const int64_t i4 = (row * cols + col) >> 2;
-            float4 wv;
-            if (STEP) {
-                wv = ld_stream_f4(reinterpret_cast<float4 *>(w) + i4);
-                float4 mv = ld_stream_f4(reinterpret_cast<float4 *>(m) + i4);
-                float4 vv = ld_stream_f4(reinterpret_cast<float4 *>(v) + i4);
-                float4 gv = load_as_f32x4(src, i4, SRC_BF16);
-                adamw_elem(wv.x, mv.x, vv.x, gv.x, a);
-                adamw_elem(wv.y, mv.y, vv.y, gv.y, a);
-                adamw_elem(wv.z, mv.z, vv.z, gv.z, a);
-                adamw_elem(wv.w, mv.w, vv.w, gv.w, a);
-                st_stream_f4(reinterpret_cast<float4 *>(w) + i4, wv);
-                st_stream_f4(reinterpret_cast<float4 *>(m) + i4, mv);
-                st_stream_f4(reinterpret_cast<float4 *>(v) + i4, vv);
-            } else {
-                wv = load_as_f32x4(src, i4, SRC_BF16);
+#pragma unroll (4 / BATCH)
+    for (int it0 = 0; it0 < ROWS / 8; it0 += BATCH) {
+        StepVec t[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; u++) {
+            const int64_t row = r0 + (it0 + u) * 8 + rl;
+            if (row < rows && col < cols) {          // cols % 4 == 0: a float4 is inside or outside as a whole
+                const int64_t i4 = (row * cols + col) >> 2;
+                if (STEP) load_step(t[u], w, m, v, src, i4, SRC_BF16);
+                else t[u].w = load_as_f32x4(src, i4, SRC_BF16);
             }
-            cnt.amax = fmaxf(cnt.amax, fmaxf(fmaxf(fabsf(wv.x), fabsf(wv.y)), fmaxf(fabsf(wv.z), fabsf(wv.w))));
-            const float y0 = wv.x * inv_s, y1 = wv.y * inv_s, y2 = wv.z * inv_s, y3 = wv.w * inv_s;
-            count4(cnt, wv, y0, y1, y2, y3, limit);
-            code = cvt4_e4m3_sat(y0, y1, y2, y3);
-            st_stream4(reinterpret_cast<uint32_t *>(wq) + i4, code);
         }
-        tt[c4][rr] = (uint8_t)code;
-        tt[c4 + 1][rr] = (uint8_t)(code >> 8);
-        tt[c4 + 2][rr] = (uint8_t)(code >> 16);
-        tt[c4 + 3][rr] = (uint8_t)(code >> 24);
+#pragma unroll
+        for (int u = 0; u < BATCH; u++) {
+            const int rr = (it0 + u) * 8 + rl;
+            const int64_t row = r0 + rr;
+            uint32_t code = 0;
+            if (row < rows && col < cols) {
+                const int64_t i4 = (row * cols + col) >> 2;
+                if (STEP) step_and_store(t[u], a, w, m, v, i4);
+                const float4 &wv = t[u].w;
+                cnt.amax = fmaxf(cnt.amax, absmax4(wv));
+                const float y0 = wv.x * inv_s, y1 = wv.y * inv_s, y2 = wv.z * inv_s, y3 = wv.w * inv_s;
+                count4(cnt, wv, y0, y1, y2, y3, limit);
+                code = cvt4_e4m3_sat(y0, y1, y2, y3);
+                st_stream4(reinterpret_cast<uint32_t *>(wq) + i4, code);
+            }
+            tt[c4][rr] = (uint8_t)code;
+            tt[c4 + 1][rr] = (uint8_t)(code >> 8);
+            tt[c4 + 2][rr] = (uint8_t)(code >> 16);
+            tt[c4 + 3][rr] = (uint8_t)(code >> 24);
+        }
     }
     __syncthreads();
+    constexpr int kPieces = ROWS / 16;               // 16-byte pieces of a transposed row
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-        const int idx = tid + k * kWThreads, c = idx >> 3, piece = idx & 7;
+    for (int k = 0; k < kWTile * kPieces / kWThreads; k++) {
+        const int idx = tid + k * kWThreads, c = idx / kPieces, piece = idx % kPieces;
         if (c0 + c < cols && r0 + piece * 16 < rows) {   // rows % 16 == 0: a 16-row piece is whole
             const uint32_t *p = reinterpret_cast<const uint32_t *>(&tt[c][piece * 16]);
             st_stream16(wq_t + (c0 + c) * rows + r0 + piece * 16, make_uint4(p[0], p[1], p[2], p[3]));
@@ -287,17 +332,23 @@ enum FinalizeMode {
 
 // `step`: the step number the caller says this call performs (only looked at by the two modes that
 // advance the step count): a caller whose count has drifted from the state's is flagged in the state.
-__global__ __launch_bounds__(kWThreads) void k_weight_finalize(moss_wscale_state *st, void *ws, int64_t slots,
+//
+// One workgroup, bound by the latency of its loads: 1024 threads, so that the up to 4096 partials of a large weight
+// are four per thread and in flight together.
+constexpr int kFinThreads = 1024;
+
+__global__ __launch_bounds__(kFinThreads) void k_weight_finalize(moss_wscale_state *st, void *ws, int64_t slots,
                                                                int n_partial, int mode, double lr_term, int64_t step)
 {
     WPartials p = ws_partials(ws, slots);
     WCounts c;
-    for (int i = threadIdx.x; i < n_partial; i += kWThreads) {
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n_partial; i += kFinThreads) {
         c.amax = fmaxf(c.amax, p.amax[i]);
         c.over += p.over[i];
         c.clip += p.clip[i];
     }
-    block_reduce(c);
+    block_reduce<kFinThreads>(c);
     if (threadIdx.x != 0) return;
     const float amax = c.amax;
     const uint32_t over = c.over, clip = c.clip;
@@ -394,9 +445,27 @@ namespace moss {
 // the 2-D kernel needs whole float4 per row and whole 16-row pieces per transposed row
 static bool tile_path_ok(int64_t rows, int64_t cols) { return cols % 4 == 0 && rows % 16 == 0; }
 
+// Form of k_weight_tile by the number of 128 x 128 tiles: step with FP32 gradients and transposed codes, in us,
+//                                tiles  8 (512 x 256)   64 (1024^2)   256 (2048^2)   512 (4096 x 2048)   1024 (4096^2)   2752 (11008 x 4096)
+//   32 rows, batches of 4               12.2            12.1          28.5           55.8                110
+//   128 rows, one vector at a time      18.1            26.8          31.6           52                  104             273 (BF16 gradients 256)
+//   128 rows, batches of 4              19.6            28.1          37.2           58                  104             264 (239)
+// Batches raise the rate (5.0 -> 5.2 TB/s) once three workgroups per compute unit overlap one's loads with another's stores.
+enum TileForm { kTile32, kTile128, kTile128Batched };
+
+static TileForm tile_form(int64_t rows, int64_t cols)
+{
+    const int64_t tiles = ((rows + kWTile - 1) / kWTile) * ((cols + kWTile - 1) / kWTile);
+    int64_t cus = moss_internal_cu_count();
+    if (cus <= 0) cus = 256;
+    if (tiles <= cus && tiles * 4 <= kWMaxBlocks) return kTile32;        // (four times the tiles have to fit the workspace)
+    return tiles < 3 * cus ? kTile128 : kTile128Batched;
+}
+
 struct WLaunch {
     int64_t rows, cols, n4, slots;
     int grid1d;
+    TileForm form;
     dim3 grid2d;
     hipStream_t st;
     void *ws;
@@ -405,10 +474,29 @@ struct WLaunch {
 
 static int finalize(const WLaunch &L, int n_partial, int mode, double lr_term, int64_t step = 0)
 {
-    hipLaunchKernelGGL(k_weight_finalize, dim3(1), dim3(kWThreads), 0, L.st, L.state, L.ws, L.slots, n_partial, mode, lr_term,
+    hipLaunchKernelGGL(k_weight_finalize, dim3(1), dim3(kFinThreads), 0, L.st, L.state, L.ws, L.slots, n_partial, mode, lr_term,
                        step);
     MOSS_LAUNCH_CHECK();
     return MOSS_OK;
+}
+
+template <bool STEP, bool SRC_BF16>
+static void launch_tile_of(const WLaunch &L, float *w, float *m, float *v, const void *src, const AdamW &a, double lr_term, uint8_t *wq,
+                           uint8_t *wq_t)
+{
+    const auto kern = L.form == kTile32    ? k_weight_tile<STEP, SRC_BF16, 32, 4>
+                      : L.form == kTile128 ? k_weight_tile<STEP, SRC_BF16, kWTile, 1>
+                                           : k_weight_tile<STEP, SRC_BF16, kWTile, 4>;
+    hipLaunchKernelGGL(kern, L.grid2d, dim3(kWThreads), 0, L.st, w, m, v, src, L.rows, L.cols, a, lr_term, L.state, wq, wq_t, L.ws,
+                       L.slots);
+}
+
+template <bool STEP>
+static void launch_tile(const WLaunch &L, bool src_bf16, float *w, float *m, float *v, const void *src, const AdamW &a, double lr_term,
+                        uint8_t *wq, uint8_t *wq_t)
+{
+    if (src_bf16) launch_tile_of<STEP, true>(L, w, m, v, src, a, lr_term, wq, wq_t);
+    else launch_tile_of<STEP, false>(L, w, m, v, src, a, lr_term, wq, wq_t);
 }
 
 // cast (and transposed copy) of the weights under the scale stored in the state
@@ -416,12 +504,7 @@ static int cast_only(const WLaunch &L, const void *w, bool bf16, uint8_t *wq, ui
 {
     const AdamW none{};
     if (wq_t && tile_path_ok(L.rows, L.cols)) {
-        if (bf16)
-            hipLaunchKernelGGL((k_weight_tile<false, true>), L.grid2d, dim3(kWThreads), 0, L.st, nullptr, nullptr, nullptr, w,
-                               L.rows, L.cols, none, 0.0, L.state, wq, wq_t, L.ws, L.slots);
-        else
-            hipLaunchKernelGGL((k_weight_tile<false, false>), L.grid2d, dim3(kWThreads), 0, L.st, nullptr, nullptr, nullptr, w,
-                               L.rows, L.cols, none, 0.0, L.state, wq, wq_t, L.ws, L.slots);
+        launch_tile<false>(L, bf16, nullptr, nullptr, nullptr, w, none, 0.0, wq, wq_t);
         MOSS_LAUNCH_CHECK();
         return finalize(L, (int)(L.grid2d.x * L.grid2d.y), kFinCastOnly, 0.0);
     }
@@ -440,7 +523,9 @@ static int make_launch(WLaunch &L, int64_t rows, int64_t cols, moss_wscale_state
 {
     L.rows = rows; L.cols = cols; L.n4 = rows * cols / 4; L.slots = partial_slots(rows, cols);
     L.grid1d = grid_for(L.n4);
-    const int64_t gx = (cols + kWTile - 1) / kWTile, gy = (rows + kWTile - 1) / kWTile;
+    L.form = tile_form(rows, cols);
+    const int64_t tile_rows = L.form == kTile32 ? 32 : kWTile;
+    const int64_t gx = (cols + kWTile - 1) / kWTile, gy = (rows + tile_rows - 1) / tile_rows;
     if (gy > 65535 || gx > 0x7FFFFFFF) return MOSS_ERR_SHAPE;
     L.grid2d = dim3((unsigned)gx, (unsigned)gy);
     L.st = (hipStream_t)stream; L.ws = ws; L.state = state;
@@ -505,10 +590,7 @@ extern "C" int moss_weight_autoscale_cast(float *w, float *m, float *v, const vo
         return cast_only(L, w, false, wq, wq_t);
     }
     if (wq_t && tile_path_ok(rows, cols)) {
-        if (gb)
-            hipLaunchKernelGGL((k_weight_tile<true, true>), L.grid2d, blk, 0, L.st, w, m, v, g, rows, cols, a, lr_term, state, wq, wq_t, workspace, L.slots);
-        else
-            hipLaunchKernelGGL((k_weight_tile<true, false>), L.grid2d, blk, 0, L.st, w, m, v, g, rows, cols, a, lr_term, state, wq, wq_t, workspace, L.slots);
+        launch_tile<true>(L, gb, w, m, v, g, a, lr_term, wq, wq_t);
         MOSS_LAUNCH_CHECK();
         return finalize(L, (int)(L.grid2d.x * L.grid2d.y), kFinStep, lr_term, args->step);
     }

@@ -77,6 +77,19 @@ def test_ragged_size_not_a_multiple_of_the_block(oracle):
     run_parity(oracle, 333, 52, 6, seed=6, interval=4)
 
 
+@pytest.mark.parametrize("rows,cols,transpose", [(16, 4, True),         # one piece of a 32-row tile
+                                                 (80, 132, True),       # 32-row tiles, ragged both ways
+                                                 (2064, 2052, True),    # 128-row tiles one vector at a time, ragged both ways
+                                                 (3088, 4100, True),    # 128-row tiles in batches, ragged both ways
+                                                 (1, 4, False),         # flat pass: one vector
+                                                 (36, 4100, False),     # ... a last trip that is not full
+                                                 (4097, 1028, False)])  # ... more trips than one
+@pytest.mark.parametrize("bf16_grad", [False, True])
+def test_tiles_and_trips_of_the_step(oracle, rows, cols, transpose, bf16_grad):
+    print(f"[weight parity] {rows}x{cols} transpose={transpose} bf16_grad={bf16_grad}", flush=True)
+    run_parity(oracle, rows, cols, 2, seed=9, interval=2, transpose=transpose, bf16_grad=bf16_grad)
+
+
 def test_broken_bound_saturates_and_counts(oracle):
     print("[weight parity] overflow path", flush=True)
     st = run_parity(oracle, 64, 64, 6, seed=7, lr=1e-2, margin=1e-4)
