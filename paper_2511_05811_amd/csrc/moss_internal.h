@@ -81,6 +81,19 @@ __device__ __forceinline__ void st_stream_f4(void *p, float4 v)
     __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4 *>(p));
 }
 
+// How a producer stores BF16 tensors that the next kernel (its quantizer) reads: through the caches from 32 MiB a tensor,
+// streaming below.  The eight L2s hold 32 MiB together and write what is dirty back when a kernel ends, which a small tensor
+// pays for in full (1024 x 11008 SwiGLU with its quantizers: 141 us through the caches, 140 streaming; 2048 x 4096
+// norm 90.5 and 89.4); a larger one leaves part of itself in the last-level cache (2048 x 11008: 189 and 196 us,
+// 4096 x 11008: 277 and 298; norm 4096 x 4096: 112.6 both, 8192 x 4096: 166 and 177, 8192 x 8192: 305 and 317).
+static inline int moss_stream_producer_stores(int64_t rows, int64_t cols) { return rows * cols <= ((int64_t)16 << 20); }
+
+__device__ __forceinline__ void st_producer16(void *p, uint4 v, int stream)
+{
+    if (stream) st_stream16(p, v);
+    else *reinterpret_cast<uint4 *>(p) = v;
+}
+
 // Two FP32 values -> two E4M3 bytes in the low half of the result.  The hardware
 // converter rounds to nearest even; values are clamped to +-448 first so that the
 // cast saturates instead of producing the NaN code.

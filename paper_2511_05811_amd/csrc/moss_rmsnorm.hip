@@ -79,7 +79,7 @@ __global__ void k_rmsnorm_clear(uint32_t *a)
 template <bool ADD, int CHUNKS>
 __global__ __launch_bounds__(kRnThreads) void k_add_rmsnorm(const uint16_t *__restrict__ x, const uint16_t *__restrict__ delta,
                                                             const uint16_t *__restrict__ gamma, float eps, int64_t rows,
-                                                            int chunks_per_row, int64_t ld, float inv_cols,
+                                                            int chunks_per_row, int64_t ld, float inv_cols, int stream,
                                                             uint16_t *__restrict__ h_out, uint16_t *__restrict__ y,
                                                             uint32_t *__restrict__ y_max)
 {
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kRnThreads) void k_add_rmsnorm(const uint16_t *__re
 #pragma unroll
                     for (int w = 0; w < 4; w++) o[w] = rn_pack(rn_lo(a[w]) + rn_lo(b[w]), rn_hi(a[w]) + rn_hi(b[w]));
                     hv[k] = make_uint4(o[0], o[1], o[2], o[3]);
-                    st_stream16(h_out + off, hv[k]);
+                    st_producer16(h_out + off, hv[k], stream);
                 }
             }
             const uint32_t a[4] = {hv[k].x, hv[k].y, hv[k].z, hv[k].w};
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(kRnThreads) void k_add_rmsnorm(const uint16_t *__re
                 o[w] = rn_pack((rn_lo(a[w]) * inv) * rn_lo(g[w]), (rn_hi(a[w]) * inv) * rn_hi(g[w]));
                 m = rn_pk_max_u16(m, o[w] & 0x7FFF7FFFu);
             }
-            st_stream16(y + r * ld + (int64_t)c * 8, make_uint4(o[0], o[1], o[2], o[3]));
+            st_producer16(y + r * ld + (int64_t)c * 8, make_uint4(o[0], o[1], o[2], o[3]), stream);
         }
     }
     merge_max(m, y_max, redm);
@@ -141,7 +141,7 @@ template <bool RES, int CHUNKS>
 __global__ __launch_bounds__(kRnThreads) void k_rmsnorm_backward(const uint16_t *__restrict__ h, const uint16_t *__restrict__ gamma,
                                                                  const uint16_t *__restrict__ dy, const uint16_t *__restrict__ d_res,
                                                                  float eps, int64_t rows, int chunks_per_row, int64_t ld,
-                                                                 float inv_cols, uint16_t *__restrict__ d_h,
+                                                                 float inv_cols, int stream, uint16_t *__restrict__ d_h,
                                                                  uint32_t *__restrict__ dh_max)
 {
     __shared__ float red[kRnThreads / kWave][2];
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(kRnThreads) void k_rmsnorm_backward(const uint16_t 
                 o[w] = rn_pack(lo, hi);
                 m = rn_pk_max_u16(m, o[w] & 0x7FFF7FFFu);
             }
-            st_stream16(d_h + off, make_uint4(o[0], o[1], o[2], o[3]));
+            st_producer16(d_h + off, make_uint4(o[0], o[1], o[2], o[3]), stream);
         }
     }
     merge_max(m, dh_max, redm);
@@ -237,12 +237,13 @@ extern "C" int moss_add_rmsnorm_bf16(const void *x, const void *delta, const voi
     hipStream_t st = (hipStream_t)stream;
     const int cpr = (int)(cols / 8), chunks = (cpr + kRnThreads - 1) / kRnThreads;
     const float inv_cols = 1.0f / (float)cols;
+    const int stream_out = moss_stream_producer_stores(rows, cols);
     const dim3 grid(rows_grid(rows)), block(kRnThreads);
     hipLaunchKernelGGL(k_rmsnorm_clear, dim3(1), dim3(64), 0, st, y_absmax_bits);
     MOSS_LAUNCH_CHECK();
 #define MOSS_RN_FWD(A, C)                                                                                                    \
     hipLaunchKernelGGL((k_add_rmsnorm<A, C>), grid, block, 0, st, (const uint16_t *)x, (const uint16_t *)delta,                \
-                       (const uint16_t *)gamma, eps, rows, cpr, ld, inv_cols, (uint16_t *)h_out, (uint16_t *)y, y_absmax_bits)
+                       (const uint16_t *)gamma, eps, rows, cpr, ld, inv_cols, stream_out, (uint16_t *)h_out, (uint16_t *)y, y_absmax_bits)
     if (delta) {
         if (chunks <= 1) MOSS_RN_FWD(true, 1); else if (chunks <= 2) MOSS_RN_FWD(true, 2); else if (chunks <= 4) MOSS_RN_FWD(true, 4); else MOSS_RN_FWD(true, 8);
     } else {
@@ -266,12 +267,13 @@ extern "C" int moss_rmsnorm_bf16_backward(const void *h, const void *gamma, cons
     hipStream_t st = (hipStream_t)stream;
     const int cpr = (int)(cols / 8), chunks = (cpr + kRnThreads - 1) / kRnThreads;
     const float inv_cols = 1.0f / (float)cols;
+    const int stream_out = moss_stream_producer_stores(rows, cols);
     const dim3 grid(rows_grid(rows)), block(kRnThreads);
     hipLaunchKernelGGL(k_rmsnorm_clear, dim3(1), dim3(64), 0, st, d_h_absmax_bits);
     MOSS_LAUNCH_CHECK();
 #define MOSS_RN_BWD(R, C)                                                                                                    \
     hipLaunchKernelGGL((k_rmsnorm_backward<R, C>), grid, block, 0, st, (const uint16_t *)h, (const uint16_t *)gamma,           \
-                       (const uint16_t *)dy, (const uint16_t *)d_res, eps, rows, cpr, ld, inv_cols, (uint16_t *)d_h,            \
+                       (const uint16_t *)dy, (const uint16_t *)d_res, eps, rows, cpr, ld, inv_cols, stream_out, (uint16_t *)d_h,            \
                        d_h_absmax_bits)
     if (d_res) {
         if (chunks <= 1) MOSS_RN_BWD(true, 1); else if (chunks <= 2) MOSS_RN_BWD(true, 2); else if (chunks <= 4) MOSS_RN_BWD(true, 4); else MOSS_RN_BWD(true, 8);

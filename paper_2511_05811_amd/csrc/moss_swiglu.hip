@@ -17,7 +17,10 @@ namespace moss {
 namespace {
 
 constexpr int kSwThreads = 256;
-constexpr int kSwUnroll = 2;
+// Chunks per thread whose loads are on the way together.  Forward 2 and backward 1 left too little in flight for tensors
+// of a trip or two per thread: 1024 x 11008 forward + backward + three quantizers took 142 us, 2 / 2 127, 4 / 2 115, 4 / 4 103;
+// 2048 x 11008 188 -> 162; 4096 x 11008, at the memory's rate, 278 either way.
+constexpr int kSwUnroll = 4;
 
 typedef unsigned short sw_u16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 sw_bf16x2 __attribute__((ext_vector_type(2)));
@@ -70,7 +73,7 @@ __device__ __forceinline__ int64_t chunk_offset(int64_t id, int chunks_per_row, 
 }
 
 __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restrict__ gate, const uint16_t *__restrict__ up,
-                                                       int64_t n_chunks, int chunks_per_row, int64_t ld, int dense,
+                                                       int64_t n_chunks, int chunks_per_row, int64_t ld, int dense, int stream,
                                                        uint16_t *__restrict__ h, uint32_t *__restrict__ h_max)
 {
     __shared__ uint32_t red[kSwThreads / kWave];
@@ -100,7 +103,7 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restric
                 o[w] = sw_pack((g0 * sigmoid(g0)) * lo_f32(uw[w]), (g1 * sigmoid(g1)) * hi_f32(uw[w]));
                 m = sw_pk_max_u16(m, o[w] & 0x7FFF7FFFu);
             }
-            st_stream16(h + off[k], make_uint4(o[0], o[1], o[2], o[3]));
+            st_producer16(h + off[k], make_uint4(o[0], o[1], o[2], o[3]), stream);
         }
     }
     fold_max(m, h_max, red);
@@ -108,36 +111,53 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restric
 
 __global__ __launch_bounds__(kSwThreads) void k_swiglu_backward(const uint16_t *__restrict__ gate, const uint16_t *__restrict__ up,
                                                                 const uint16_t *__restrict__ dh, int64_t n_chunks,
-                                                                int chunks_per_row, int64_t ld, int dense,
+                                                                int chunks_per_row, int64_t ld, int dense, int stream,
                                                                 uint16_t *__restrict__ d_gate, uint16_t *__restrict__ d_up,
                                                                 uint32_t *__restrict__ dg_max, uint32_t *__restrict__ du_max)
 {
     __shared__ uint32_t red[kSwThreads / kWave];
     uint32_t mg = 0, mu = 0;
-    const int64_t stride = (int64_t)gridDim.x * kSwThreads;
-    for (int64_t id = (int64_t)blockIdx.x * kSwThreads + threadIdx.x; id < n_chunks; id += stride) {
-        const int64_t off = chunk_offset(id, chunks_per_row, ld, dense);
-        const uint4 g = ld_stream16(gate + off), u = ld_stream16(up + off), d = ld_stream16(dh + off);
-        const uint32_t gw[4] = {g.x, g.y, g.z, g.w}, uw[4] = {u.x, u.y, u.z, u.w}, dw[4] = {d.x, d.y, d.z, d.w};
-        uint32_t og[4], ou[4];
+    const int64_t stride = (int64_t)gridDim.x * kSwThreads * kSwUnroll;
+    for (int64_t id0 = (int64_t)blockIdx.x * kSwThreads * kSwUnroll + threadIdx.x; id0 < n_chunks; id0 += stride) {
+        uint4 gc[kSwUnroll], uc[kSwUnroll], dc[kSwUnroll];
+        int64_t offs[kSwUnroll];
 #pragma unroll
-        for (int w = 0; w < 4; w++) {
-            float rg[2], ru[2];
-#pragma unroll
-            for (int e = 0; e < 2; e++) {
-                const float gv = e ? hi_f32(gw[w]) : lo_f32(gw[w]), uv = e ? hi_f32(uw[w]) : lo_f32(uw[w]);
-                const float dv = e ? hi_f32(dw[w]) : lo_f32(dw[w]);
-                const float sg = sigmoid(gv);
-                ru[e] = dv * (gv * sg);
-                rg[e] = (dv * uv) * (sg * (1.0f + gv * (1.0f - sg)));
+        for (int k = 0; k < kSwUnroll; k++) {
+            const int64_t id = id0 + (int64_t)k * kSwThreads;
+            offs[k] = -1;
+            if (id < n_chunks) {
+                offs[k] = chunk_offset(id, chunks_per_row, ld, dense);
+                gc[k] = ld_stream16(gate + offs[k]);
+                uc[k] = ld_stream16(up + offs[k]);
+                dc[k] = ld_stream16(dh + offs[k]);
             }
-            og[w] = sw_pack(rg[0], rg[1]);
-            ou[w] = sw_pack(ru[0], ru[1]);
-            mg = sw_pk_max_u16(mg, og[w] & 0x7FFF7FFFu);
-            mu = sw_pk_max_u16(mu, ou[w] & 0x7FFF7FFFu);
         }
-        st_stream16(d_gate + off, make_uint4(og[0], og[1], og[2], og[3]));
-        st_stream16(d_up + off, make_uint4(ou[0], ou[1], ou[2], ou[3]));
+#pragma unroll
+        for (int k = 0; k < kSwUnroll; k++) {
+            const int64_t off = offs[k];
+            if (off < 0) continue;
+            const uint4 &g = gc[k], &u = uc[k], &d = dc[k];
+            const uint32_t gw[4] = {g.x, g.y, g.z, g.w}, uw[4] = {u.x, u.y, u.z, u.w}, dw[4] = {d.x, d.y, d.z, d.w};
+            uint32_t og[4], ou[4];
+#pragma unroll
+            for (int w = 0; w < 4; w++) {
+                float rg[2], ru[2];
+#pragma unroll
+                for (int e = 0; e < 2; e++) {
+                    const float gv = e ? hi_f32(gw[w]) : lo_f32(gw[w]), uv = e ? hi_f32(uw[w]) : lo_f32(uw[w]);
+                    const float dv = e ? hi_f32(dw[w]) : lo_f32(dw[w]);
+                    const float sg = sigmoid(gv);
+                    ru[e] = dv * (gv * sg);
+                    rg[e] = (dv * uv) * (sg * (1.0f + gv * (1.0f - sg)));
+                }
+                og[w] = sw_pack(rg[0], rg[1]);
+                ou[w] = sw_pack(ru[0], ru[1]);
+                mg = sw_pk_max_u16(mg, og[w] & 0x7FFF7FFFu);
+                mu = sw_pk_max_u16(mu, ou[w] & 0x7FFF7FFFu);
+            }
+            st_producer16(d_gate + off, make_uint4(og[0], og[1], og[2], og[3]), stream);
+            st_producer16(d_up + off, make_uint4(ou[0], ou[1], ou[2], ou[3]), stream);
+        }
     }
     fold_max(mg, dg_max, red);
     fold_max(mu, du_max, red);
@@ -177,7 +197,8 @@ extern "C" int moss_swiglu_bf16(const void *gate, const void *up, int64_t rows, 
     hipLaunchKernelGGL(k_swiglu_clear, dim3(1), dim3(64), 0, st, h_absmax_bits, (uint32_t *)nullptr);
     MOSS_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_swiglu, dim3(grid_for(n_chunks, kSwUnroll)), dim3(kSwThreads), 0, st, (const uint16_t *)gate,
-                       (const uint16_t *)up, n_chunks, chunks_per_row, ld, (int)(ld == cols), (uint16_t *)h, h_absmax_bits);
+                       (const uint16_t *)up, n_chunks, chunks_per_row, ld, (int)(ld == cols),
+                       moss_stream_producer_stores(rows, cols), (uint16_t *)h, h_absmax_bits);
     MOSS_LAUNCH_CHECK();
     return MOSS_OK;
 }
@@ -199,9 +220,9 @@ extern "C" int moss_swiglu_bf16_backward(const void *gate, const void *up, const
     const int64_t n_chunks = rows * chunks_per_row;
     hipLaunchKernelGGL(k_swiglu_clear, dim3(1), dim3(64), 0, st, d_gate_absmax_bits, d_up_absmax_bits);
     MOSS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_swiglu_backward, dim3(grid_for(n_chunks, 1)), dim3(kSwThreads), 0, st, (const uint16_t *)gate,
+    hipLaunchKernelGGL(k_swiglu_backward, dim3(grid_for(n_chunks, kSwUnroll)), dim3(kSwThreads), 0, st, (const uint16_t *)gate,
                        (const uint16_t *)up, (const uint16_t *)dh, n_chunks, chunks_per_row, ld, (int)(ld == cols),
-                       (uint16_t *)d_gate, (uint16_t *)d_up, d_gate_absmax_bits, d_up_absmax_bits);
+                       moss_stream_producer_stores(rows, cols), (uint16_t *)d_gate, (uint16_t *)d_up, d_gate_absmax_bits, d_up_absmax_bits);
     MOSS_LAUNCH_CHECK();
     return MOSS_OK;
 }

@@ -63,6 +63,22 @@ def test_swiglu_forward_and_backward(oracle, shape):
     assert int(dumax.item()) == int((dub & 0x7FFF).max())
 
 
+def test_swiglu_of_more_than_32_mib_equals_its_parts():
+    # above 2^24 elements the outputs are stored through the caches: the same bits as in two parts below that
+    g, u, d = (bf16_to_gpu(a) for a in make_inputs(2049, 8200, 5))
+    h, hmax = moss.swiglu_bf16(g, u)
+    dg, du, dgmax, dumax = moss.swiglu_bf16_backward(g, u, d)
+    tops = [0, 0, 0]
+    for rows in (slice(0, 1000), slice(1000, 2049)):
+        ph, pm = moss.swiglu_bf16(g[rows], u[rows])
+        pg, pu, pgm, pum = moss.swiglu_bf16_backward(g[rows], u[rows], d[rows])
+        torch.cuda.synchronize()
+        for whole, part in ((h, ph), (dg, pg), (du, pu)):
+            assert np.array_equal(bits_of(whole[rows]), bits_of(part))
+        tops = [max(a, int(b.item())) for a, b in zip(tops, (pm, pgm, pum))]
+    assert tops == [int(t.item()) for t in (hmax, dgmax, dumax)]
+
+
 def test_swiglu_on_a_strided_view_and_zero_tensor(oracle):
     rows, cols, ld = 64, 96, 128
     gb, ub, _ = make_inputs(rows, ld, 7)

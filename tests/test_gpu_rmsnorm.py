@@ -81,6 +81,22 @@ def test_rmsnorm_forward_and_backward(oracle, shape):
         assert int(dhmax.item()) == int((dhb & 0x7FFF).max())
 
 
+def test_rmsnorm_of_more_than_32_mib_equals_its_parts():
+    # above 2^24 elements the outputs are stored through the caches: the same bits as in two parts below that
+    x, d, g, dy, dr = (bf16_to_gpu(a) for a in make(4097, 4104, 7))
+    h, y, ymax = moss.add_rmsnorm_bf16(x, g, EPS, delta=d)
+    dh, dhmax = moss.rmsnorm_bf16_backward(h, g, dy, EPS, d_res=dr)
+    tops = [0, 0]
+    for rows in (slice(0, 2000), slice(2000, 4097)):
+        ph, py, pm = moss.add_rmsnorm_bf16(x[rows], g, EPS, delta=d[rows])
+        pdh, pdm = moss.rmsnorm_bf16_backward(h[rows], g, dy[rows], EPS, d_res=dr[rows])
+        torch.cuda.synchronize()
+        for whole, part in ((h, ph), (y, py), (dh, pdh)):
+            assert np.array_equal(bits_of(whole[rows]), bits_of(part))
+        tops = [max(a, int(b.item())) for a, b in zip(tops, (pm, pdm))]
+    assert tops == [int(t.item()) for t in (ymax, dhmax)]
+
+
 def test_rmsnorm_on_a_strided_view_and_word_is_overwritten(oracle):
     rows, cols, ld = 40, 96, 128
     xb, db, gb, _, _ = make(rows, ld, 5)
