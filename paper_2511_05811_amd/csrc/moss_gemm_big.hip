@@ -60,6 +60,12 @@ constexpr int kScaleBase = 2 * kSlotBytes;             // 128 KiB
 constexpr int kDummyBase = kScaleBase + 2 * kScaleSlotBytes;     // 144 KiB: 1 KiB per wave that nobody reads
 constexpr int kBigLdsBytes = kDummyBase + 4 * 1024;              // 148 KiB
 
+// Rows (pairs of them) whose previous values an accumulating epilogue has on the way at a time.  Loaded one by one between
+// the stores, which may be the same memory as far as the compiler knows, every row waited out a trip to memory: 11008 x
+// 4096 x 2048 took 242 us, with 4 / 8 / 16 at a time 190 / 165 / 193 (16 spill registers that the main loop needs, which
+// costs a plain 4096 x 4096 x 8192 a fifth); 4096 x 4096 x 512 50 -> 41.5.
+constexpr int kAccBatch = 8;
+
 extern __shared__ __attribute__((aligned(1024))) uint8_t big_smem[];
 
 struct Frags {
@@ -405,18 +411,36 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
                                         acc[i][j][4 * qd + 2] * scale, acc[i][j][4 * qd + 3] * scale);
                 // 32 lanes cover one 512-byte row (128 floats), a wave instruction covers 2 rows
                 const int l32 = lane & 31, cc = l32 & 15;
-#pragma unroll 4
-                for (int k = 0; k < 16; k++) {
+                const int64_t n = nw + l32 * 4;
+                auto staged = [&](int k) {
                     const int rr = 2 * k + (lane >> 5);
-                    float4 v = *reinterpret_cast<const float4 *>(((l32 >> 4) ? pieceB : pieceA) + rr * 256 + ((cc ^ (rr & 15)) << 4));
-                    const int64_t m = mw + i * 32 + rr, n = nw + l32 * 4;
-                    if (m >= M || n >= N) continue;
-                    float *dst = o + m * ld_out + n;
-                    if (accumulate) {
-                        const float4 p = *reinterpret_cast<const float4 *>(dst);
-                        v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+                    return *reinterpret_cast<const float4 *>(((l32 >> 4) ? pieceB : pieceA) + rr * 256 + ((cc ^ (rr & 15)) << 4));
+                };
+                if (accumulate) {
+#pragma unroll 1
+                    for (int k0 = 0; k0 < 16; k0 += kAccBatch) {
+                        float4 prev[kAccBatch];
+#pragma unroll
+                        for (int k = 0; k < kAccBatch; k++) {
+                            const int64_t m = mw + i * 32 + 2 * (k0 + k) + (lane >> 5);
+                            prev[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+                            if (m < M && n < N) prev[k] = *reinterpret_cast<const float4 *>(o + m * ld_out + n);
+                        }
+#pragma unroll
+                        for (int k = 0; k < kAccBatch; k++) {
+                            const int64_t m = mw + i * 32 + 2 * (k0 + k) + (lane >> 5);
+                            if (m >= M || n >= N) continue;
+                            float4 v = staged(k0 + k);
+                            v.x += prev[k].x; v.y += prev[k].y; v.z += prev[k].z; v.w += prev[k].w;
+                            *reinterpret_cast<float4 *>(o + m * ld_out + n) = v;
+                        }
                     }
-                    *reinterpret_cast<float4 *>(dst) = v;
+                } else {
+#pragma unroll 4
+                    for (int k = 0; k < 16; k++) {
+                        const int64_t m = mw + i * 32 + 2 * k + (lane >> 5);
+                        if (m < M && n < N) *reinterpret_cast<float4 *>(o + m * ld_out + n) = staged(k);
+                    }
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }

@@ -268,3 +268,25 @@ def test_split_k_tiles(oracle, shape):
         assert_close(out.cpu().numpy().astype(np.float64), ref, na, nb, False, f"{shape} f32")
         out = gpu_gemm(a, ae, a_s, b, exps, b_s, out_dtype=torch.bfloat16)
         assert_close(bf16_out_to_f64(out), ref, na, nb, True, f"{shape} bf16")
+
+
+@pytest.mark.parametrize("shape", [(2049, 264, 512),       # 128 x 256 tiles: rows and columns over the edge of a tile
+                                   (1032, 2056, 640)])     # ... most tiles inside
+def test_accumulate_in_the_large_tiles(oracle, shape):
+    M, N, K = shape
+    rng = np.random.default_rng(M + N + K)
+    a, b = finite_codes(rng, (M, K)), finite_codes(rng, (N, K))
+    ae = rng.integers(110, 128, size=(M, K // 32), dtype=np.uint8)
+    be = rng.integers(110, 128, size=(N, K // 32), dtype=np.uint8)
+    a_s, b_s = np.float32(0.5), np.float32(0.25)
+    sa, sb = to_gpu(np.array([a_s], np.float32)), to_gpu(np.array([b_s], np.float32))
+    ops = (to_gpu(a), to_gpu(ae), sa, to_gpu(b), to_gpu(be), sb)
+    base = torch.from_numpy(rng.standard_normal((M, N + 8)).astype(np.float32)).to("cuda:0")
+    out = base.clone()
+    moss.gemm_fp8_mx(*ops, out=out[:, :N], accumulate=True)
+    plain = torch.zeros_like(out)
+    moss.gemm_fp8_mx(*ops, out=plain[:, :N])
+    torch.cuda.synchronize()
+    assert torch.equal(out, base + plain)                      # one FP32 addition per output, nothing beyond N
+    assert_close(plain[:, :N].cpu().numpy().astype(np.float64), oracle.gemm(a, ae, a_s, b, be, b_s),
+                 oracle.row_norms(a, ae, a_s), oracle.row_norms(b, be, b_s), False, f"{shape} accumulate")
