@@ -8,6 +8,8 @@
 //
 //  * One launch (k_quant_persist): tensors of up to four 128 x 128 tiles per workgroup of a
 //    co-resident grid stay in registers between the maximum and the codes; X is read once.
+//  * One launch (SCAN forms of the kernels below): tensors of at most kScanBytesRow / kScanBytesTile, where every workgroup reads the whole
+//    tensor for the maximum by itself.
 //  * Two launches: k_amax_bf16 leaves one partial maximum per workgroup in the workspace, and
 //    k_quant_row (row groups alone) or k_quant_tile (column groups, or both groupings from one
 //    fetch of X) folds the partials and converts.
@@ -266,28 +268,77 @@ __device__ __forceinline__ uint2 row_codes(const uint4 &r, float fused, uint32_t
     return make_uint2(out[0], out[1]);
 }
 
+// Small tensors: every workgroup takes the maximum over all of X itself, behind its L2, in place of the launch in front
+// that leaves partial maxima.  Both ways are a chain of latencies.  On the device, calls back to back, scan and two launches:
+//   row groups   32 KiB 3.4 / 5.4 us, 128 KiB 4.3 / 5.9, 256 KiB 5.8 / 5.8, 384 KiB 7.1 / 5.9
+//   both         32 KiB 6.9 / 8.3 us,  64 KiB 8.2 / 8.3, 128 KiB 10.6 / 8.5   (workgroups of a quarter of the threads)
+// and the host issues one launch less, about 2 us: 17 x 4096 and the GEMM behind it take 20 instead of 23 us, the smallest
+// training step 42 instead of 47.
+constexpr int64_t kScanBytesRow = 256 * 1024, kScanBytesTile = 64 * 1024;
+constexpr int kScanThreadsRow = 1024;
+constexpr int kScanUnroll = 8;
+
+template <bool CEIL, int THREADS>
+__device__ __forceinline__ GlobalScale scan_global_scale(const uint16_t *__restrict__ x, int n_chunks, int chunks_per_row, int64_t ld,
+                                                         int dense, uint32_t *red)
+{
+    uint32_t m = 0;
+    for (int id0 = threadIdx.x; id0 < n_chunks; id0 += THREADS * kScanUnroll) {
+        uint4 r[kScanUnroll];
+#pragma unroll
+        for (int u = 0; u < kScanUnroll; u++) {
+            const int id = id0 + u * THREADS;
+            r[u] = make_uint4(0, 0, 0, 0);
+            if (id < n_chunks) {
+                int64_t off = (int64_t)id * 8;
+                if (!dense) {
+                    const int row = id / chunks_per_row;
+                    off = row * ld + (id - row * chunks_per_row) * 8;
+                }
+                r[u] = *reinterpret_cast<const uint4 *>(x + off);     // (through the caches: every workgroup reads it)
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kScanUnroll; u++) {
+            const uint32_t c = chunk_absmax(r[u]);
+            m = c > m ? c : m;
+        }
+    }
+    m = wave_max_u32(m);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    m = red[0];
+    for (int i = 1; i < THREADS / kWave; i++) m = red[i] > m ? red[i] : m;
+    return make_global_scale<CEIL>(m);
+}
+
 // Row grouping: a group is 64 contiguous bytes = the 16-byte chunks of four
 // neighbouring lanes.  Each thread handles kRowUnroll chunks that are one block
-// stride apart so that all its loads are in flight together.
+// stride apart so that all its loads are in flight together.  SCAN: one chunk per thread of a larger workgroup, which
+// takes the maximum of X itself first.
 constexpr int kRowUnroll = 4;
+constexpr int row_threads(bool scan) { return scan ? kScanThreadsRow : kQuantThreads; }
+constexpr int row_unroll(bool scan) { return scan ? 1 : kRowUnroll; }
 
-template <bool CEIL>
-__global__ __launch_bounds__(kQuantThreads) void k_quant_row(const uint16_t *__restrict__ x, int64_t n_chunks,
+template <bool CEIL, bool SCAN>
+__global__ __launch_bounds__(row_threads(SCAN)) void k_quant_row(const uint16_t *__restrict__ x, int64_t n_chunks,
                                                              int chunks_per_row, int64_t ld, int dense,
                                                              const uint32_t *__restrict__ partial, int n_partial,
                                                              uint8_t *__restrict__ q, uint8_t *__restrict__ e,
                                                              float *__restrict__ s_global)
 {
-    __shared__ uint32_t red[kQuantThreads / kWave];
+    constexpr int kThreads = row_threads(SCAN), kUnroll = row_unroll(SCAN);
+    __shared__ uint32_t red[kThreads / kWave];
     converter_saturates();
-    const GlobalScale g = fold_global_scale<CEIL>(partial, n_partial, red);
+    const GlobalScale g = SCAN ? scan_global_scale<CEIL, kThreads>(x, (int)n_chunks, chunks_per_row, ld, dense, red)
+                               : fold_global_scale<CEIL>(partial, n_partial, red);
     if (blockIdx.x == 0 && threadIdx.x == 0) *s_global = g.s;
 
-    const int64_t base = (int64_t)blockIdx.x * (kQuantThreads * kRowUnroll) + threadIdx.x;
-    uint4 raw[kRowUnroll];
+    const int64_t base = (int64_t)blockIdx.x * (kThreads * kUnroll) + threadIdx.x;
+    uint4 raw[kUnroll];
 #pragma unroll
-    for (int u = 0; u < kRowUnroll; u++) {
-        int64_t id = base + (int64_t)u * kQuantThreads;
+    for (int u = 0; u < kUnroll; u++) {
+        int64_t id = base + (int64_t)u * kThreads;
         raw[u] = make_uint4(0, 0, 0, 0);
         if (id < n_chunks) {
             int64_t off;
@@ -300,11 +351,11 @@ __global__ __launch_bounds__(kQuantThreads) void k_quant_row(const uint16_t *__r
             raw[u] = ld_stream16(x + off);
         }
     }
-    float f[kRowUnroll];
-    uint32_t eb[kRowUnroll], gmax[kRowUnroll];
+    float f[kUnroll];
+    uint32_t eb[kUnroll], gmax[kUnroll];
     uint32_t sub_min = ~0u, min_fb = 255u;
 #pragma unroll
-    for (int u = 0; u < kRowUnroll; u++) {
+    for (int u = 0; u < kUnroll; u++) {
         // the four lanes of a quad hold one group; n_chunks % 4 == 0 keeps quads uniform
         gmax[u] = quad_max_u32(chunk_absmax(raw[u]));
         sub_min = gmax[u] - 1u < sub_min ? gmax[u] - 1u : sub_min;     // (a zero group wraps to the largest value)
@@ -315,7 +366,7 @@ __global__ __launch_bounds__(kQuantThreads) void k_quant_row(const uint16_t *__r
     if (__any(!g.fast || sub_min < 127u || (int)min_fb <= g.wide_at)) {
         bool wide = false;
 #pragma unroll
-        for (int u = 0; u < kRowUnroll; u++) {
+        for (int u = 0; u < kUnroll; u++) {
             const int ex = local_exponent<CEIL>(gmax[u], g);
             eb[u] = (uint32_t)(ex + 127);
             f[u] = group_factor(gmax[u], ex, g);
@@ -324,8 +375,8 @@ __global__ __launch_bounds__(kQuantThreads) void k_quant_row(const uint16_t *__r
         any_wide = __any(wide);
     }
 #pragma unroll
-    for (int u = 0; u < kRowUnroll; u++) {
-        const int64_t id = base + (int64_t)u * kQuantThreads;
+    for (int u = 0; u < kUnroll; u++) {
+        const int64_t id = base + (int64_t)u * kThreads;
         const uint2 out = any_wide ? row_codes<false>(raw[u], f[u], eb[u], g.inv_s) : row_codes<true>(raw[u], f[u], eb[u], g.inv_s);
         if (id < n_chunks) {
             st_stream8(q + id * 8, out);
@@ -650,7 +701,7 @@ __device__ __forceinline__ bool tile_of_workgroup(uint32_t id, int tiles_x, int 
     return tx < tiles_x && ty < tiles_y;
 }
 
-template <bool ROW, bool CEIL>
+template <bool ROW, bool CEIL, bool SCAN>
 __global__ __launch_bounds__(kQuantThreads, 4) void k_quant_tile(const uint16_t *__restrict__ x, int64_t rows, int64_t cols,
                                                                  int64_t ld, int tiles_x, int tiles_y,
                                                                  const uint32_t *__restrict__ partial,
@@ -665,7 +716,8 @@ __global__ __launch_bounds__(kQuantThreads, 4) void k_quant_tile(const uint16_t 
     if (!tile_of_workgroup(blockIdx.x, tiles_x, tiles_y, tx, ty)) return;     // (the whole workgroup, before any barrier)
     converter_saturates();
     if (threadIdx.x == 0) lds.redo = 0;
-    const GlobalScale g = fold_global_scale<CEIL>(partial, n_partial, red);
+    const GlobalScale g = SCAN ? scan_global_scale<CEIL, kQuantThreads>(x, (int)(rows * (cols / 8)), (int)(cols / 8), ld, ld == cols, red)
+                               : fold_global_scale<CEIL>(partial, n_partial, red);
     if (blockIdx.x == 0 && threadIdx.x == 0) *s_global = g.s;                 // (workgroup 0 has tile (0, 0))
 
     const TileShape sh = {rows, cols, ld};
@@ -673,7 +725,7 @@ __global__ __launch_bounds__(kQuantThreads, 4) void k_quant_tile(const uint16_t 
     uint4 raw[8];
     load_tile(raw, x, sh, r0, c0);
     bool general = true;
-    if (tile_is_full(sh, r0, c0)) {        // (lds.redo was cleared before the barrier inside fold_global_scale)
+    if (tile_is_full(sh, r0, c0)) {        // (lds.redo was cleared before the barrier inside fold_ / scan_global_scale)
         if (quant_tile_body<ROW, true, CEIL, true>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds) && (threadIdx.x & 63) == 0)
             atomicOr(&lds.redo, 1u);
         __syncthreads();
@@ -929,7 +981,8 @@ extern "C" size_t moss_quant_workspace_bytes(int64_t rows, int64_t cols, unsigne
 }
 
 // The launch that converts: k_quant_row for the row grouping alone, k_quant_tile as soon as the transposed
-// grouping is wanted.  `partial` holds n_partial candidate maxima (BF16 magnitude bits) that every workgroup folds.
+// grouping is wanted.  `partial` holds n_partial candidate maxima (BF16 magnitude bits) that every workgroup folds;
+// without any (n_partial == 0) the workgroups take the maximum over X themselves (the caller checks the size).
 static int launch_codes(const uint16_t *x, int64_t rows, int64_t cols, int64_t ld, bool want_row, bool want_col,
                         bool ceil_mode, const uint32_t *partial, int n_partial, uint8_t *q_row, uint8_t *e_row,
                         uint8_t *q_col, uint8_t *e_col, float *s_global, hipStream_t st)
@@ -938,27 +991,29 @@ static int launch_codes(const uint16_t *x, int64_t rows, int64_t cols, int64_t l
     const int chunks_per_row = (int)(cols / 8);
     const int64_t n_chunks = rows * chunks_per_row;
     const int dense = (ld == cols);
+    const bool scan = n_partial == 0;
     if (want_row && !want_col) {
-        const int64_t per_block = (int64_t)kQuantThreads * kRowUnroll;
+        const int threads = row_threads(scan);
+        const int64_t per_block = (int64_t)threads * row_unroll(scan);
         const int64_t blocks = (n_chunks + per_block - 1) / per_block;
         if (blocks > 0x7FFFFFFF) return MOSS_ERR_SHAPE;
-        if (ceil_mode)
-            hipLaunchKernelGGL(k_quant_row<true>, dim3((unsigned)blocks), dim3(kQuantThreads), 0, st, x, n_chunks,
-                               chunks_per_row, ld, dense, partial, n_partial, q_row, e_row, s_global);
-        else
-            hipLaunchKernelGGL(k_quant_row<false>, dim3((unsigned)blocks), dim3(kQuantThreads), 0, st, x, n_chunks,
-                               chunks_per_row, ld, dense, partial, n_partial, q_row, e_row, s_global);
+        const auto kern = ceil_mode ? (scan ? k_quant_row<true, true> : k_quant_row<true, false>)
+                                    : (scan ? k_quant_row<false, true> : k_quant_row<false, false>);
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), 0, st, x, n_chunks, chunks_per_row, ld, dense, partial,
+                           n_partial, q_row, e_row, s_global);
         MOSS_LAUNCH_CHECK();
     }
     if (want_col) {
         const int64_t gx = (cols + kTile - 1) / kTile, gy = (rows + kTile - 1) / kTile;
         if (gx > (1 << 24) || gy > (1 << 24) || tile_grid_size(gx, gy) > 0x7FFFFFFF) return MOSS_ERR_SHAPE;
         const dim3 grid((unsigned)tile_grid_size(gx, gy)), block(kQuantThreads);
-#define MOSS_LAUNCH_TILE(R, C)                                                                                          \
-    hipLaunchKernelGGL((k_quant_tile<R, C>), grid, block, 0, st, x, rows, cols, ld, (int)gx, (int)gy, partial, n_partial,  \
+#define MOSS_LAUNCH_TILE(R, C, S)                                                                                       \
+    hipLaunchKernelGGL((k_quant_tile<R, C, S>), grid, block, 0, st, x, rows, cols, ld, (int)gx, (int)gy, partial, n_partial, \
                        q_row, e_row, q_col, e_col, s_global)
-        if (want_row) { if (ceil_mode) MOSS_LAUNCH_TILE(true, true); else MOSS_LAUNCH_TILE(true, false); }
-        else          { if (ceil_mode) MOSS_LAUNCH_TILE(false, true); else MOSS_LAUNCH_TILE(false, false); }
+#define MOSS_LAUNCH_TILE_FORM(R, C) do { if (scan) MOSS_LAUNCH_TILE(R, C, true); else MOSS_LAUNCH_TILE(R, C, false); } while (0)
+        if (want_row) { if (ceil_mode) MOSS_LAUNCH_TILE_FORM(true, true); else MOSS_LAUNCH_TILE_FORM(true, false); }
+        else          { if (ceil_mode) MOSS_LAUNCH_TILE_FORM(false, true); else MOSS_LAUNCH_TILE_FORM(false, false); }
+#undef MOSS_LAUNCH_TILE_FORM
 #undef MOSS_LAUNCH_TILE
         MOSS_LAUNCH_CHECK();
     }
@@ -1004,6 +1059,10 @@ static int quant_with_workspace(const void *x_bf16, int64_t rows, int64_t cols, 
     const int chunks_per_row = (int)(cols / 8);
     const int64_t n_chunks = rows * chunks_per_row;
     const int dense = (ld == cols);
+
+    // Small tensors: one launch whose workgroups each read all of X for the maximum (the workspace is not touched)
+    if (n_chunks * 16 <= (want_col ? kScanBytesTile : kScanBytesRow))
+        return launch_codes(x, rows, cols, ld, want_row, want_col, ceil_mode, nullptr, 0, q_row, e_row, q_col, e_col, s_global, st);
 
     // Tensors of one to kKeep tiles per workgroup: one launch that keeps X in registers between the
     // maximum and the codes.

@@ -72,6 +72,22 @@ def test_ragged_shapes(oracle, shape):
     check_against_oracle(oracle, xb, 0, f"ragged {shape}")
 
 
+@pytest.mark.parametrize("rows,cols,ld", [(64, 512, 512),        # 64 KiB: the largest tensor whose tiles each look for the maximum
+                                          (96, 352, 352), (32, 1056, 1056),    # just above it: two launches
+                                          (96, 224, 320),        # ... a strided one below it, ragged tiles
+                                          (127, 1024, 1024), (128, 1024, 1024), (129, 1024, 1024),   # rows: around 256 KiB
+                                          (77, 1056, 1120), (1, 32, 32)])
+@pytest.mark.parametrize("flag", [0, CEIL])
+def test_small_tensors_where_every_workgroup_looks_for_the_maximum(oracle, rows, cols, ld, flag):
+    xb = mi.heavy_tailed_activation(rows, cols, seed=rows + cols)
+    for at in ((0, 0), (rows - 1, cols - 1)):                   # the maximum in the first and in the last place
+        big = xb.copy()
+        big[at] = 0xC700                                        # -32768
+        wide = np.full((rows, ld), 0x7F00, np.uint16)           # (what lies between the rows is larger still)
+        wide[:, :cols] = big
+        check_against_oracle(oracle, big, flag, f"max at {at} ld {ld}", x_dev=bf16_to_gpu(wide)[:, :cols])
+
+
 # Tensors with at least two 128 x 128 tiles per compute unit take the one-launch kernel (a bounded
 # grid that meets once for the global maximum and keeps its first tiles in registers).
 @pytest.mark.parametrize("shape,flag", [((4128, 2080), 0),      # ragged edges, every tile kept
