@@ -52,7 +52,7 @@ __device__ __forceinline__ void fold_max(uint32_t m, uint32_t *word, uint32_t *r
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int i = 1; i < kSwThreads / kWave; i++) m = red[i] > m ? red[i] : m;
-        if (m) __hip_atomic_fetch_max(word, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        merge_max_word(word, m);
     }
     __syncthreads();
 }
@@ -176,7 +176,9 @@ int grid_for(int64_t n_chunks, int per_thread)
     const int64_t want = (n_chunks + (int64_t)kSwThreads * per_thread - 1) / ((int64_t)kSwThreads * per_thread);
     int cus = moss_internal_cu_count();
     if (cus <= 0) cus = 256;
-    const int64_t cap = (int64_t)cus * 16;       // a few waves' worth of workgroups per compute unit, grid-stride beyond
+    // eight workgroups per compute unit, grid-stride beyond: every one ends on the caller's words (4096 x 11008 with the quantizers
+    // 259 us at 4, 8 and 16 per compute unit, 2048 x 11008 143 / 144 / 163)
+    const int64_t cap = (int64_t)cus * 8;
     return (int)(want < cap ? want : cap);
 }
 
