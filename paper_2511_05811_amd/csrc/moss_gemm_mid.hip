@@ -123,8 +123,9 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
     uint32_t *area_a = reinterpret_cast<uint32_t *>(mid_smem + S::kPanel);
     uint32_t *area_b = area_a + p.panel_stages * (kBM + 1);
     auto load_exponents = [&](const uint8_t *e, uint32_t *area, int rows, int64_t row0, int last, int64_t limit, int cb, int nc) {
-        const int per_row = kMidThreads / rows;              // threads that share a row (a power of two)
+        const int per_row = kMidThreads / rows;              // threads that share a row (192 rows: one, and 64 are left over)
         const int r = tid / per_row;
+        if (r >= rows) return;
         const int64_t at = (row0 + (r < last ? r : last)) * G + cb * 4;       // of this row's first dword, in bytes
         const int first = tid % per_row;
         constexpr int U = 8;
@@ -321,10 +322,12 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
         }
     }
 
-    // Epilogue: every wave leaves its sums in LDS (row pitch 32 NJ floats, 16-byte chunks XOR-swizzled by row), then the
+    // Epilogue: every wave leaves its sums in LDS (row pitch 32 NJ floats, 16-byte chunks XOR-swizzled by row within the
+    // largest power of two that divides their number), then the
     // workgroup walks the tile row by row, adds the KS parts in order, scales and stores.
     // (accumulator register v of lane (i32, h) in fragment (i, j): row 32 i + i32, column 32 j + 8 (v / 4) + 4 h + v % 4)
     constexpr int kChunks = 8 * NJ, kPart = 32 * MI * 32 * NJ;          // float4 per staged row; floats per wave
+    constexpr int kSwizzle = (kChunks & -kChunks) - 1;                   // (24 chunks: within each eight)
 #pragma unroll
     for (int i = 0; i < MI; i++)
 #pragma unroll
@@ -337,7 +340,7 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
         for (int j = 0; j < NJ; j++)
 #pragma unroll
             for (int qd = 0; qd < 4; qd++)
-                *reinterpret_cast<float4 *>(part + wave * kPart + (i * 32 + i32) * 32 * NJ + (((8 * j + 2 * qd + h) ^ (i32 & (kChunks - 1))) << 2)) =
+                *reinterpret_cast<float4 *>(part + wave * kPart + (i * 32 + i32) * 32 * NJ + (((8 * j + 2 * qd + h) ^ (i32 & kSwizzle)) << 2)) =
                     make_float4(acc[i][j][4 * qd], acc[i][j][4 * qd + 1], acc[i][j][4 * qd + 2], acc[i][j][4 * qd + 3]);
     __syncthreads();
     const bool vec_ok = p.ld_out % 4 == 0;
@@ -345,7 +348,7 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
     for (int id = tid; id < kBM * kBN / 4; id += kMidThreads) {
         const int row = id / (kBN / 4), c4 = id % (kBN / 4);
         const int rw = row / (32 * MI), rr = row % (32 * MI), cw = c4 / kChunks, cc = c4 % kChunks;
-        const float *src = part + (rw * WN + cw) * kPart + rr * 32 * NJ + ((cc ^ (rr & (kChunks - 1))) << 2);
+        const float *src = part + (rw * WN + cw) * kPart + rr * 32 * NJ + ((cc ^ (rr & kSwizzle)) << 2);
         float4 t = *reinterpret_cast<const float4 *>(src);
 #pragma unroll
         for (int k = 1; k < KS; k++) {
@@ -421,12 +424,20 @@ static int launch_mid(MidArgs p, int budget, hipStream_t st)
 //   64 x 64     (256, 4096, 4096) 12.7, (512, 4096, 4096) 23.3, (1024, 1024, 1024) 8.6    13.0, 23.8, 7.4
 //   64 x 128    (512, 4096, 4096) 16.5, (2048, 2048, 4096) 33.3, (512, 4096, 1024) 9.1    17.0, 32.0, 8.8
 //   128 x 128   (2048, 2048, 2080) 24.9, (4096, 4096, 2080) 92.8                          22.4, 83.0
+// K % 128 != 0: the rows no longer start on lines and the exponents are cut out of two dwords, so that a stage costs more
+// (more so with exponents of b); there 128 x 192 tiles pay as well, which read a third less per product
+// than 128 x 128 but leave no LDS for a fourth slot (with K % 128 == 0 the large tiles are better wherever they are):
+//   64 x 64     (600, 4096, 4128) 44.8, (2048, 2048, 2080) with b 54.1                     45, 53
+//   64 x 128    (8192, 2080, 4128) 193.6, (3072, 3072, 4128) with b 144.6                  198, 144
+//   128 x 128   (4096, 4096, 2080) 82.8, (3072, 3072, 4128) with b 112.9                   83, 110
+//   128 x 192   (1333, 4096, 4128) 47.3, (8192, 2080, 4128) 138.6, (3072, 3072, 4128) with b 108.6    46, 134, 108
+//   general     (1333, 4096, 4128) 62, (8192, 2080, 4128) 163, (3072, 3072, 4128) with b 123, (5000, 1056, 1056) 20.4
 //   large       (64, 4096, 4096) 24.6, (1024, 4096, 4096) 27.4, (1333, 4096, 11008) 71    26, 30, 69
 //   general     (300, 1000, 2080) 22.5, (2048, 2048, 2080) 35.3, (64, 256, 512) 8.8       21, 35, 7.6
 namespace {
 
 struct MidPlan {
-    int kind;        // 0..3: the tiles above, -1: none of them
+    int kind;        // 0 .. 4: the tiles above
     double us;
 };
 
@@ -435,15 +446,20 @@ double tiles_of(int64_t M, int64_t N, int bm, int bn) { return (double)((M + bm 
 
 MidPlan plan_mid(int64_t M, int64_t N, int64_t K, bool b_exponents)
 {
+    const bool ragged = K % 128 != 0;
     const double C = (double)((K + 127) / 128), extra = b_exponents ? 0.5 : 0.0;
     const double it4 = (double)(((int64_t)C + 3) / 4), it2 = (double)(((int64_t)C + 1) / 2);
-    const double t0 = tiles_of(M, N, 32, 32), t1 = tiles_of(M, N, 64, 64), t2 = tiles_of(M, N, 64, 128), t3 = tiles_of(M, N, 128, 128);
-    const double us[4] = {t0 <= 256.0 ? 3.9 + extra + 0.48 * it4 : 2.2 + per_cu(t0) * (0.9 + extra + 0.33 * it4),
-                          2.2 + per_cu(t1) * (3.3 + extra + 0.94 * it4),
-                          2.2 + per_cu(t2) * (3.9 + 2.0 * extra + 0.68 * it2),
-                          2.2 + per_cu(t3) * (8.0 + 3.0 * extra + 0.63 * C)};
+    const double t0 = tiles_of(M, N, 32, 32), t1 = tiles_of(M, N, 64, 64), t2 = tiles_of(M, N, 64, 128), t3 = tiles_of(M, N, 128, 128),
+                 t4 = tiles_of(M, N, 128, 192);
+    const double r01 = !ragged ? 1.0 : (b_exponents ? 1.85 : 1.33), r2 = !ragged ? 1.0 : (b_exponents ? 2.03 : 1.54),
+                 r3 = !ragged ? 1.0 : (b_exponents ? 1.2 : 1.14);
+    const double us[5] = {t0 <= 256.0 ? 3.9 + extra + 0.48 * r01 * it4 : 2.2 + per_cu(t0) * (0.9 + extra + 0.33 * r01 * it4),
+                          2.2 + per_cu(t1) * (3.3 + extra + 0.94 * r01 * it4),
+                          2.2 + per_cu(t2) * (3.9 + 2.0 * extra + 0.68 * r2 * it2),
+                          2.2 + per_cu(t3) * (8.0 + (ragged ? 6.0 : 3.0) * extra + 0.63 * r3 * C),
+                          2.2 + per_cu(t4) * (11.0 + (b_exponents ? 1.27 : 1.0) * C)};
     MidPlan best{0, us[0]};
-    for (int k = 1; k < 4; k++)
+    for (int k = 1; k < (ragged ? 5 : 4); k++)
         if (us[k] < best.us) best = MidPlan{k, us[k]};
     return best;
 }
@@ -487,6 +503,7 @@ int moss_internal_gemm_mid(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, 
         case 0: return launch_mid<1, 1, 1, 1, 4, 2>(p, 80 * 1024, st);       // two workgroups fit a compute unit
         case 1: return launch_mid<2, 2, 1, 1, 4, 2>(p, 160 * 1024, st);
         case 2: return launch_mid<2, 2, 1, 2, 2, 3>(p, 160 * 1024, st);
-        default: return launch_mid<2, 2, 2, 2, 1, 4>(p, 160 * 1024, st);
+        case 3: return launch_mid<2, 2, 2, 2, 1, 4>(p, 160 * 1024, st);
+        default: return launch_mid<2, 3, 2, 2, 1, 3>(p, 160 * 1024, st);
     }
 }

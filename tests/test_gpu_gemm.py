@@ -290,3 +290,8 @@ def test_accumulate_in_the_large_tiles(oracle, shape):
     assert torch.equal(out, base + plain)                      # one FP32 addition per output, nothing beyond N
     assert_close(plain[:, :N].cpu().numpy().astype(np.float64), oracle.gemm(a, ae, a_s, b, be, b_s),
                  oracle.row_norms(a, ae, a_s), oracle.row_norms(b, be, b_s), False, f"{shape} accumulate")
+
+
+def test_wide_tiles_where_k_ends_inside_a_stage(oracle):
+    # 128 x 192 tiles: rows and columns over the edge, N % 4 != 0, with exponents of b in two pieces
+    test_split_k_tiles(oracle, (2050, 2042, 4128))
