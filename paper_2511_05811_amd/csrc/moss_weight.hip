@@ -277,37 +277,62 @@ __global__ __launch_bounds__(kWThreads) void k_weight_tile(float *__restrict__ w
     const int64_t r0 = (int64_t)blockIdx.y * ROWS, c0 = (int64_t)blockIdx.x * kWTile;
     const int64_t col = c0 + c4;
     WCounts cnt;
-#pragma unroll (4 / BATCH)
-    for (int it0 = 0; it0 < ROWS / 8; it0 += BATCH) {
-        StepVec t[BATCH];
-#pragma unroll
-        for (int u = 0; u < BATCH; u++) {
-            const int64_t row = r0 + (it0 + u) * 8 + rl;
-            if (row < rows && col < cols) {          // cols % 4 == 0: a float4 is inside or outside as a whole
-                const int64_t i4 = (row * cols + col) >> 2;
-                if (STEP) load_step(t[u], w, m, v, src, i4, SRC_BF16);
-                else t[u].w = load_as_f32x4(src, i4, SRC_BF16);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < BATCH; u++) {
-            const int rr = (it0 + u) * 8 + rl;
+    // Casts the new weights of a vector and leaves the codes in the tile; 0 beyond the matrix.
+    auto cast_vector = [&](const float4 &wv, int64_t i4) {
+        cnt.amax = fmaxf(cnt.amax, absmax4(wv));
+        const float y0 = wv.x * inv_s, y1 = wv.y * inv_s, y2 = wv.z * inv_s, y3 = wv.w * inv_s;
+        count4(cnt, wv, y0, y1, y2, y3, limit);
+        const uint32_t code = cvt4_e4m3_sat(y0, y1, y2, y3);
+        st_stream4(reinterpret_cast<uint32_t *>(wq) + i4, code);
+        return code;
+    };
+    auto transpose_codes = [&](int rr, uint32_t code) {
+        tt[c4][rr] = (uint8_t)code;
+        tt[c4 + 1][rr] = (uint8_t)(code >> 8);
+        tt[c4 + 2][rr] = (uint8_t)(code >> 16);
+        tt[c4 + 3][rr] = (uint8_t)(code >> 24);
+    };
+    auto load_vector = [&](StepVec &t, int64_t i4) {
+        if (STEP) load_step(t, w, m, v, src, i4, SRC_BF16);
+        else t.w = load_as_f32x4(src, i4, SRC_BF16);
+    };
+    // (cols % 4 == 0: a float4 is inside or outside as a whole)
+    if (BATCH == 1) {
+#pragma unroll 4
+        for (int it = 0; it < ROWS / 8; it++) {
+            const int rr = it * 8 + rl;
             const int64_t row = r0 + rr;
             uint32_t code = 0;
             if (row < rows && col < cols) {
                 const int64_t i4 = (row * cols + col) >> 2;
-                if (STEP) step_and_store(t[u], a, w, m, v, i4);
-                const float4 &wv = t[u].w;
-                cnt.amax = fmaxf(cnt.amax, absmax4(wv));
-                const float y0 = wv.x * inv_s, y1 = wv.y * inv_s, y2 = wv.z * inv_s, y3 = wv.w * inv_s;
-                count4(cnt, wv, y0, y1, y2, y3, limit);
-                code = cvt4_e4m3_sat(y0, y1, y2, y3);
-                st_stream4(reinterpret_cast<uint32_t *>(wq) + i4, code);
+                StepVec t;
+                load_vector(t, i4);
+                if (STEP) step_and_store(t, a, w, m, v, i4);
+                code = cast_vector(t.w, i4);
             }
-            tt[c4][rr] = (uint8_t)code;
-            tt[c4 + 1][rr] = (uint8_t)(code >> 8);
-            tt[c4 + 2][rr] = (uint8_t)(code >> 16);
-            tt[c4 + 3][rr] = (uint8_t)(code >> 24);
+            transpose_codes(rr, code);
+        }
+    } else {
+#pragma unroll 1
+        for (int it0 = 0; it0 < ROWS / 8; it0 += BATCH) {
+            StepVec t[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; u++) {
+                const int64_t row = r0 + (it0 + u) * 8 + rl;
+                if (row < rows && col < cols) load_vector(t[u], (row * cols + col) >> 2);
+            }
+#pragma unroll
+            for (int u = 0; u < BATCH; u++) {
+                const int rr = (it0 + u) * 8 + rl;
+                const int64_t row = r0 + rr;
+                uint32_t code = 0;
+                if (row < rows && col < cols) {
+                    const int64_t i4 = (row * cols + col) >> 2;
+                    if (STEP) step_and_store(t[u], a, w, m, v, i4);
+                    code = cast_vector(t[u].w, i4);
+                }
+                transpose_codes(rr, code);
+            }
         }
     }
     __syncthreads();
@@ -450,7 +475,9 @@ static bool tile_path_ok(int64_t rows, int64_t cols) { return cols % 4 == 0 && r
 //   32 rows, batches of 4               12.2            12.1          28.5           55.8                110
 //   128 rows, one vector at a time      18.1            26.8          31.6           52                  104             273 (BF16 gradients 256)
 //   128 rows, batches of 4              19.6            28.1          37.2           58                  104             264 (239)
-// Batches raise the rate (5.0 -> 5.2 TB/s) once three workgroups per compute unit overlap one's loads with another's stores.
+// Batches raise the rate (5.0 -> 5.2 TB/s) once many rounds of workgroups overlap one's loads with another's stores.  Alone
+// they cost nothing from 1024 tiles on, but behind the GEMM that has just written the gradient they do (4096^2 in a
+// training step: + 5 us): from eight tiles per compute unit.
 enum TileForm { kTile32, kTile128, kTile128Batched };
 
 static TileForm tile_form(int64_t rows, int64_t cols)
@@ -459,7 +486,7 @@ static TileForm tile_form(int64_t rows, int64_t cols)
     int64_t cus = moss_internal_cu_count();
     if (cus <= 0) cus = 256;
     if (tiles <= cus && tiles * 4 <= kWMaxBlocks) return kTile32;        // (four times the tiles have to fit the workspace)
-    return tiles < 3 * cus ? kTile128 : kTile128Batched;
+    return tiles < 8 * cus ? kTile128 : kTile128Batched;
 }
 
 struct WLaunch {
@@ -486,7 +513,7 @@ static void launch_tile_of(const WLaunch &L, float *w, float *m, float *v, const
 {
     const auto kern = L.form == kTile32    ? k_weight_tile<STEP, SRC_BF16, 32, 4>
                       : L.form == kTile128 ? k_weight_tile<STEP, SRC_BF16, kWTile, 1>
-                                           : k_weight_tile<STEP, SRC_BF16, kWTile, 4>;
+                                           : k_weight_tile<STEP, SRC_BF16, kWTile, STEP ? 4 : 1>;   // (cast alone, 11008 x 4096: 61 us in batches, 54)
     hipLaunchKernelGGL(kern, L.grid2d, dim3(kWThreads), 0, L.st, w, m, v, src, L.rows, L.cols, a, lr_term, L.state, wq, wq_t, L.ws,
                        L.slots);
 }

@@ -80,7 +80,7 @@ def test_ragged_size_not_a_multiple_of_the_block(oracle):
 @pytest.mark.parametrize("rows,cols,transpose", [(16, 4, True),         # one piece of a 32-row tile
                                                  (80, 132, True),       # 32-row tiles, ragged both ways
                                                  (2064, 2052, True),    # 128-row tiles one vector at a time, ragged both ways
-                                                 (3088, 4100, True),    # 128-row tiles in batches, ragged both ways
+                                                 (5904, 5636, True),    # 128-row tiles in batches, ragged both ways
                                                  (1, 4, False),         # flat pass: one vector
                                                  (36, 4100, False),     # ... a last trip that is not full
                                                  (4097, 1028, False)])  # ... more trips than one
