@@ -88,6 +88,14 @@ __device__ __forceinline__ void st_stream_f4(void *p, float4 v)
 // 4096 x 11008: 277 and 298; norm 4096 x 4096: 112.6 both, 8192 x 4096: 166 and 177, 8192 x 8192: 305 and 317).
 static inline int moss_stream_producer_stores(int64_t rows, int64_t cols) { return rows * cols <= ((int64_t)16 << 20); }
 
+// One argument for both switches: the kernels hold it in a register for the stores, where an argument of its own for the
+// look would be fetched at the end of the kernel, in front of it (1536 x 256 norm backward 14.1 instead of 12.9 us).
+enum ProducerFlags { kProducerStream = 1, kProducerLook = 2 };
+static inline int producer_flags(int64_t rows, int64_t cols, bool look)
+{
+    return (moss_stream_producer_stores(rows, cols) ? kProducerStream : 0) | (look ? kProducerLook : 0);
+}
+
 __device__ __forceinline__ void st_producer16(void *p, uint4 v, int stream)
 {
     if (stream) st_stream16(p, v);
@@ -96,11 +104,17 @@ __device__ __forceinline__ void st_producer16(void *p, uint4 v, int stream)
 
 // Merges a workgroup's maximum into a word that only grows while the kernel runs.  Atomics on one address are carried out
 // one after the other, some 10 ns each: the 2048 of a norm of 2048 rows were 25 of its 30 us.  Looking first skips those that
-// would change nothing (SwiGLU 4096 x 11008 with its quantizers 278 -> 260 us, 1024 x 11008 103 -> 92).
-__device__ __forceinline__ void merge_max_word(uint32_t *word, uint32_t m)
+// would change nothing (SwiGLU 4096 x 11008 with its quantizers 278 -> 260 us, 1024 x 11008 103 -> 92), but it is a trip to
+// memory in front of the atomic, 0.4 to 0.9 us at the end of the kernel.  The launchers ask for it (`look`) from the number of
+// workgroups on at which the queue of atomics takes longer; each gives both sides at its rule.
+// The trip starts ahead of the workgroup's own reduction.
+__device__ __forceinline__ uint32_t look_at_word(const uint32_t *word, int look)
 {
-    if (m > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        __hip_atomic_fetch_max(word, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return look ? __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+}
+__device__ __forceinline__ void merge_max_word(uint32_t *word, uint32_t m, uint32_t seen)
+{
+    if (m > seen) __hip_atomic_fetch_max(word, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Two FP32 values -> two E4M3 bytes in the low half of the result.  The hardware

@@ -56,7 +56,7 @@ __device__ __forceinline__ void block_sum2(float &a, float &b, float (*red)[2])
     }
 }
 
-__device__ __forceinline__ void merge_max(uint32_t m, uint32_t *word, uint32_t *red)
+__device__ __forceinline__ void merge_max(uint32_t m, uint32_t *word, int look, uint32_t *red)
 {
     m = (m & 0xFFFFu) > (m >> 16) ? (m & 0xFFFFu) : (m >> 16);
     m = wave_max_u32(m);
@@ -64,8 +64,9 @@ __device__ __forceinline__ void merge_max(uint32_t m, uint32_t *word, uint32_t *
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
+        const uint32_t seen = look_at_word(word, look);
         for (int i = 1; i < kRnThreads / kWave; i++) m = red[i] > m ? red[i] : m;
-        merge_max_word(word, m);
+        merge_max_word(word, m, seen);
     }
 }
 
@@ -79,7 +80,7 @@ __global__ void k_rmsnorm_clear(uint32_t *a)
 template <bool ADD, int CHUNKS>
 __global__ __launch_bounds__(kRnThreads) void k_add_rmsnorm(const uint16_t *__restrict__ x, const uint16_t *__restrict__ delta,
                                                             const uint16_t *__restrict__ gamma, float eps, int64_t rows,
-                                                            int chunks_per_row, int64_t ld, float inv_cols, int stream,
+                                                            int chunks_per_row, int64_t ld, float inv_cols, int flags,
                                                             uint16_t *__restrict__ h_out, uint16_t *__restrict__ y,
                                                             uint32_t *__restrict__ y_max)
 {
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(kRnThreads) void k_add_rmsnorm(const uint16_t *__re
 #pragma unroll
                     for (int w = 0; w < 4; w++) o[w] = rn_pack(rn_lo(a[w]) + rn_lo(b[w]), rn_hi(a[w]) + rn_hi(b[w]));
                     hv[k] = make_uint4(o[0], o[1], o[2], o[3]);
-                    st_producer16(h_out + off, hv[k], stream);
+                    st_producer16(h_out + off, hv[k], flags & kProducerStream);
                 }
             }
             const uint32_t a[4] = {hv[k].x, hv[k].y, hv[k].z, hv[k].w};
@@ -129,10 +130,10 @@ __global__ __launch_bounds__(kRnThreads) void k_add_rmsnorm(const uint16_t *__re
                 o[w] = rn_pack((rn_lo(a[w]) * inv) * rn_lo(g[w]), (rn_hi(a[w]) * inv) * rn_hi(g[w]));
                 m = rn_pk_max_u16(m, o[w] & 0x7FFF7FFFu);
             }
-            st_producer16(y + r * ld + (int64_t)c * 8, make_uint4(o[0], o[1], o[2], o[3]), stream);
+            st_producer16(y + r * ld + (int64_t)c * 8, make_uint4(o[0], o[1], o[2], o[3]), flags & kProducerStream);
         }
     }
-    merge_max(m, y_max, redm);
+    merge_max(m, y_max, flags & kProducerLook, redm);
 }
 
 // d_h = d_res + (g - n mean(g n)) / rms with g = dy gamma, n = h / rms, rms = sqrt(mean(h^2) + eps).
@@ -141,7 +142,7 @@ template <bool RES, int CHUNKS>
 __global__ __launch_bounds__(kRnThreads) void k_rmsnorm_backward(const uint16_t *__restrict__ h, const uint16_t *__restrict__ gamma,
                                                                  const uint16_t *__restrict__ dy, const uint16_t *__restrict__ d_res,
                                                                  float eps, int64_t rows, int chunks_per_row, int64_t ld,
-                                                                 float inv_cols, int stream, uint16_t *__restrict__ d_h,
+                                                                 float inv_cols, int flags, uint16_t *__restrict__ d_h,
                                                                  uint32_t *__restrict__ dh_max)
 {
     __shared__ float red[kRnThreads / kWave][2];
@@ -200,10 +201,10 @@ __global__ __launch_bounds__(kRnThreads) void k_rmsnorm_backward(const uint16_t 
                 o[w] = rn_pack(lo, hi);
                 m = rn_pk_max_u16(m, o[w] & 0x7FFF7FFFu);
             }
-            st_producer16(d_h + off, make_uint4(o[0], o[1], o[2], o[3]), stream);
+            st_producer16(d_h + off, make_uint4(o[0], o[1], o[2], o[3]), flags & kProducerStream);
         }
     }
-    merge_max(m, dh_max, redm);
+    merge_max(m, dh_max, flags & kProducerLook, redm);
 }
 
 int check_rows(int64_t rows, int64_t cols, int64_t ld, float eps)
@@ -218,15 +219,32 @@ int rows_grid(int64_t rows)
 {
     int cus = moss_internal_cu_count();
     if (cus <= 0) cus = 256;
-    // Four workgroups per compute unit: each ends with a look at, and early on an atomic on, the caller's word, one after the
-    // other.  Norm forward and backward with their quantizers, 2 / 4 / 8 per compute unit: 2048 x 4096 63 / 68 / 88 us,
-    // 4096 x 4096 94 / 96 / 111, 8192 x 4096 168 / 154 / 165, 8192 x 8192 313 / 292 / 299.
+    // Four workgroups per compute unit: each ends on the caller's word, one after the other.  Norm forward and backward with
+    // their quantizers, 2 / 4 / 8 per compute unit: 2048 x 4096 63 / 68 / 88 us, 4096 x 4096 94 / 96 / 111, 8192 x 4096
+    // 168 / 154 / 165, 8192 x 8192 313 / 292 / 299.
     const int64_t cap = (int64_t)cus * 4;
     return (int)(rows < cap ? rows : cap);
 }
 
+// Look at the word before merging into it (merge_max_word): in wide rows from 3.5 rows per compute unit on, in narrow ones from 6.
+// The look costs every workgroup a trip and saves the queue behind it only if the ends of the workgroups are spread, so that
+// around the line it helps or hurts by which of them happen to end together.  Forward / backward alone, us, without and with,
+// means over eight inputs:
+//     256 x 4096  8.5 / 8.7 and  8.6 / 9.5      768 x 8192 17.6 / 15.0 and 18.7 / 22.2    1000 x 4096 18.1 / 13.7 and 18.7 / 19.4
+//    1200 x 8192 24.2 / 20.9 and 24.1 / 22.8   1400 x 4096 19.9 / 26.4 and 20.2 / 17.6    3072 x 4096 27.9 / 27.1 and 28.1 / 26.3
+//    1200 x 2048 17.7 / 18.9 and 17.8 / 13.1   1200 x 1024 17.1 / 21.5 and 17.2 / 21.1    1536 x 1024 17.5 / 14.7 and 17.5 / 16.1
+bool looks(int64_t rows, int64_t cols, bool backward)
+{
+    int64_t cus = moss_internal_cu_count();
+    if (cus <= 0) cus = 256;
+    return 2 * rows >= (cols >= (backward ? 2048 : 4096) ? 7 : 12) * cus;
+}
+
 }  // namespace
 }  // namespace moss
+
+// what the two entry points below choose for a tensor (the tests hold the rule by it)
+extern "C" int moss_internal_rmsnorm_looks(int64_t rows, int64_t cols, int64_t backward) { return moss::looks(rows, cols, backward != 0); }
 
 extern "C" int moss_add_rmsnorm_bf16(const void *x, const void *delta, const void *gamma, float eps, int64_t rows, int64_t cols,
                                      int64_t ld, void *h_out, void *y, uint32_t *y_absmax_bits, void *stream)
@@ -240,13 +258,13 @@ extern "C" int moss_add_rmsnorm_bf16(const void *x, const void *delta, const voi
     hipStream_t st = (hipStream_t)stream;
     const int cpr = (int)(cols / 8), chunks = (cpr + kRnThreads - 1) / kRnThreads;
     const float inv_cols = 1.0f / (float)cols;
-    const int stream_out = moss_stream_producer_stores(rows, cols);
+    const int flags = producer_flags(rows, cols, looks(rows, cols, false));
     const dim3 grid(rows_grid(rows)), block(kRnThreads);
     hipLaunchKernelGGL(k_rmsnorm_clear, dim3(1), dim3(64), 0, st, y_absmax_bits);
     MOSS_LAUNCH_CHECK();
 #define MOSS_RN_FWD(A, C)                                                                                                    \
     hipLaunchKernelGGL((k_add_rmsnorm<A, C>), grid, block, 0, st, (const uint16_t *)x, (const uint16_t *)delta,                \
-                       (const uint16_t *)gamma, eps, rows, cpr, ld, inv_cols, stream_out, (uint16_t *)h_out, (uint16_t *)y, y_absmax_bits)
+                       (const uint16_t *)gamma, eps, rows, cpr, ld, inv_cols, flags, (uint16_t *)h_out, (uint16_t *)y, y_absmax_bits)
     if (delta) {
         if (chunks <= 1) MOSS_RN_FWD(true, 1); else if (chunks <= 2) MOSS_RN_FWD(true, 2); else if (chunks <= 4) MOSS_RN_FWD(true, 4); else MOSS_RN_FWD(true, 8);
     } else {
@@ -270,13 +288,13 @@ extern "C" int moss_rmsnorm_bf16_backward(const void *h, const void *gamma, cons
     hipStream_t st = (hipStream_t)stream;
     const int cpr = (int)(cols / 8), chunks = (cpr + kRnThreads - 1) / kRnThreads;
     const float inv_cols = 1.0f / (float)cols;
-    const int stream_out = moss_stream_producer_stores(rows, cols);
+    const int flags = producer_flags(rows, cols, looks(rows, cols, true));
     const dim3 grid(rows_grid(rows)), block(kRnThreads);
     hipLaunchKernelGGL(k_rmsnorm_clear, dim3(1), dim3(64), 0, st, d_h_absmax_bits);
     MOSS_LAUNCH_CHECK();
 #define MOSS_RN_BWD(R, C)                                                                                                    \
     hipLaunchKernelGGL((k_rmsnorm_backward<R, C>), grid, block, 0, st, (const uint16_t *)h, (const uint16_t *)gamma,           \
-                       (const uint16_t *)dy, (const uint16_t *)d_res, eps, rows, cpr, ld, inv_cols, stream_out, (uint16_t *)d_h,            \
+                       (const uint16_t *)dy, (const uint16_t *)d_res, eps, rows, cpr, ld, inv_cols, flags, (uint16_t *)d_h,     \
                        d_h_absmax_bits)
     if (d_res) {
         if (chunks <= 1) MOSS_RN_BWD(true, 1); else if (chunks <= 2) MOSS_RN_BWD(true, 2); else if (chunks <= 4) MOSS_RN_BWD(true, 4); else MOSS_RN_BWD(true, 8);

@@ -44,15 +44,16 @@ __device__ __forceinline__ float sigmoid(float g)
     return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.44269504088896340736f));
 }
 
-__device__ __forceinline__ void fold_max(uint32_t m, uint32_t *word, uint32_t *red)
+__device__ __forceinline__ void fold_max(uint32_t m, uint32_t *word, int look, uint32_t *red)
 {
     m = (m & 0xFFFFu) > (m >> 16) ? (m & 0xFFFFu) : (m >> 16);
     m = wave_max_u32(m);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
+        const uint32_t seen = look_at_word(word, look);
         for (int i = 1; i < kSwThreads / kWave; i++) m = red[i] > m ? red[i] : m;
-        merge_max_word(word, m);
+        merge_max_word(word, m, seen);
     }
     __syncthreads();
 }
@@ -73,7 +74,7 @@ __device__ __forceinline__ int64_t chunk_offset(int64_t id, int chunks_per_row, 
 }
 
 __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restrict__ gate, const uint16_t *__restrict__ up,
-                                                       int64_t n_chunks, int chunks_per_row, int64_t ld, int dense, int stream,
+                                                       int64_t n_chunks, int chunks_per_row, int64_t ld, int dense, int flags,
                                                        uint16_t *__restrict__ h, uint32_t *__restrict__ h_max)
 {
     __shared__ uint32_t red[kSwThreads / kWave];
@@ -103,15 +104,15 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restric
                 o[w] = sw_pack((g0 * sigmoid(g0)) * lo_f32(uw[w]), (g1 * sigmoid(g1)) * hi_f32(uw[w]));
                 m = sw_pk_max_u16(m, o[w] & 0x7FFF7FFFu);
             }
-            st_producer16(h + off[k], make_uint4(o[0], o[1], o[2], o[3]), stream);
+            st_producer16(h + off[k], make_uint4(o[0], o[1], o[2], o[3]), flags & kProducerStream);
         }
     }
-    fold_max(m, h_max, red);
+    fold_max(m, h_max, flags & kProducerLook, red);
 }
 
 __global__ __launch_bounds__(kSwThreads) void k_swiglu_backward(const uint16_t *__restrict__ gate, const uint16_t *__restrict__ up,
                                                                 const uint16_t *__restrict__ dh, int64_t n_chunks,
-                                                                int chunks_per_row, int64_t ld, int dense, int stream,
+                                                                int chunks_per_row, int64_t ld, int dense, int flags,
                                                                 uint16_t *__restrict__ d_gate, uint16_t *__restrict__ d_up,
                                                                 uint32_t *__restrict__ dg_max, uint32_t *__restrict__ du_max)
 {
@@ -155,12 +156,12 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu_backward(const uint16_t *
                 mg = sw_pk_max_u16(mg, og[w] & 0x7FFF7FFFu);
                 mu = sw_pk_max_u16(mu, ou[w] & 0x7FFF7FFFu);
             }
-            st_producer16(d_gate + off, make_uint4(og[0], og[1], og[2], og[3]), stream);
-            st_producer16(d_up + off, make_uint4(ou[0], ou[1], ou[2], ou[3]), stream);
+            st_producer16(d_gate + off, make_uint4(og[0], og[1], og[2], og[3]), flags & kProducerStream);
+            st_producer16(d_up + off, make_uint4(ou[0], ou[1], ou[2], ou[3]), flags & kProducerStream);
         }
     }
-    fold_max(mg, dg_max, red);
-    fold_max(mu, du_max, red);
+    fold_max(mg, dg_max, flags & kProducerLook, red);
+    fold_max(mu, du_max, flags & kProducerLook, red);
 }
 
 int check_common(int64_t rows, int64_t cols, int64_t ld)
@@ -182,8 +183,20 @@ int grid_for(int64_t n_chunks, int per_thread)
     return (int)(want < cap ? want : cap);
 }
 
+// Look at the word before merging into it (merge_max_word) from 512 workgroups on.  Forward / backward (two words) alone, us,
+// without and with the look, by the number of workgroups:
+//     1 .. 63       5.2 / 6.0 and 5.4 / 6.6        64 .. 255   7.2 / 8.1 and 9.2 / 10.7
+//   256 .. 511     10.1 / 11.8 and 15.0 / 15.9    512 .. 1023  15.6 / 13.8 and 27.6 / 20.9       (2048: 41.4 / 34.9 and 80.3 / 61.6)
+bool looks(int grid) { return grid >= 512; }
+
 }  // namespace
 }  // namespace moss
+
+// what the two entry points below choose for a tensor (the tests hold the rules by it)
+extern "C" int moss_internal_swiglu_looks(int64_t rows, int64_t cols)
+{
+    return moss::looks(moss::grid_for(rows * (cols / 8), moss::kSwUnroll));
+}
 
 extern "C" int moss_swiglu_bf16(const void *gate, const void *up, int64_t rows, int64_t cols, int64_t ld,
                                 void *h, uint32_t *h_absmax_bits, void *stream)
@@ -198,9 +211,10 @@ extern "C" int moss_swiglu_bf16(const void *gate, const void *up, int64_t rows, 
     const int64_t n_chunks = rows * chunks_per_row;
     hipLaunchKernelGGL(k_swiglu_clear, dim3(1), dim3(64), 0, st, h_absmax_bits, (uint32_t *)nullptr);
     MOSS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_swiglu, dim3(grid_for(n_chunks, kSwUnroll)), dim3(kSwThreads), 0, st, (const uint16_t *)gate,
-                       (const uint16_t *)up, n_chunks, chunks_per_row, ld, (int)(ld == cols),
-                       moss_stream_producer_stores(rows, cols), (uint16_t *)h, h_absmax_bits);
+    const int grid = grid_for(n_chunks, kSwUnroll);
+    hipLaunchKernelGGL(k_swiglu, dim3(grid), dim3(kSwThreads), 0, st, (const uint16_t *)gate, (const uint16_t *)up, n_chunks,
+                       chunks_per_row, ld, (int)(ld == cols), producer_flags(rows, cols, looks(grid)),
+                       (uint16_t *)h, h_absmax_bits);
     MOSS_LAUNCH_CHECK();
     return MOSS_OK;
 }
@@ -222,9 +236,11 @@ extern "C" int moss_swiglu_bf16_backward(const void *gate, const void *up, const
     const int64_t n_chunks = rows * chunks_per_row;
     hipLaunchKernelGGL(k_swiglu_clear, dim3(1), dim3(64), 0, st, d_gate_absmax_bits, d_up_absmax_bits);
     MOSS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_swiglu_backward, dim3(grid_for(n_chunks, kSwUnroll)), dim3(kSwThreads), 0, st, (const uint16_t *)gate,
-                       (const uint16_t *)up, (const uint16_t *)dh, n_chunks, chunks_per_row, ld, (int)(ld == cols),
-                       moss_stream_producer_stores(rows, cols), (uint16_t *)d_gate, (uint16_t *)d_up, d_gate_absmax_bits, d_up_absmax_bits);
+    const int grid = grid_for(n_chunks, kSwUnroll);
+    hipLaunchKernelGGL(k_swiglu_backward, dim3(grid), dim3(kSwThreads), 0, st, (const uint16_t *)gate, (const uint16_t *)up,
+                       (const uint16_t *)dh, n_chunks, chunks_per_row, ld, (int)(ld == cols),
+                       producer_flags(rows, cols, looks(grid)), (uint16_t *)d_gate, (uint16_t *)d_up,
+                       d_gate_absmax_bits, d_up_absmax_bits);
     MOSS_LAUNCH_CHECK();
     return MOSS_OK;
 }

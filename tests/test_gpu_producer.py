@@ -63,6 +63,11 @@ def test_swiglu_forward_and_backward(oracle, shape):
     assert int(dumax.item()) == int((dub & 0x7FFF).max())
 
 
+@pytest.mark.parametrize("shape", [(511, 8192), (512, 8200)])
+def test_swiglu_on_both_sides_of_the_look_before_the_merge(oracle, shape):
+    test_swiglu_forward_and_backward(oracle, shape)
+
+
 def test_swiglu_of_more_than_32_mib_equals_its_parts():
     # above 2^24 elements the outputs are stored through the caches: the same bits as in two parts below that
     g, u, d = (bf16_to_gpu(a) for a in make_inputs(2049, 8200, 5))

@@ -81,6 +81,11 @@ def test_rmsnorm_forward_and_backward(oracle, shape):
         assert int(dhmax.item()) == int((dhb & 0x7FFF).max())
 
 
+@pytest.mark.parametrize("shape", [(1535, 72), (1536, 72)])      # (and more rows than workgroups)
+def test_rmsnorm_on_both_sides_of_the_look_before_the_merge(oracle, shape):
+    test_rmsnorm_forward_and_backward(oracle, shape)
+
+
 def test_rmsnorm_of_more_than_32_mib_equals_its_parts():
     # above 2^24 elements the outputs are stored through the caches: the same bits as in two parts below that
     x, d, g, dy, dr = (bf16_to_gpu(a) for a in make(4097, 4104, 7))

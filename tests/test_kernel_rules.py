@@ -1,0 +1,37 @@
+"""Which form of a kernel a call takes: the rules behind the entry points, asked on the host (256 compute units are
+assumed where there is no GPU), so that a change of a constant cannot move a size to another form unseen."""
+import ctypes as C
+
+import pytest
+
+import paper_2511_05811_amd as moss
+
+
+@pytest.fixture(scope="module")
+def L():
+    lib = moss.load()
+    if lib.moss_device_cu_count() not in (0, 256):
+        pytest.skip("the sizes below are those of 256 compute units")
+    return lib
+
+
+def ask(fn, *args):
+    fn.restype = C.c_int
+    return fn(*(C.c_int64(a) for a in args))
+
+
+@pytest.mark.parametrize("rows,cols,looks", [(1, 8, 0), (30, 1856, 0), (1024, 2056, 0), (511, 8192, 0), (512, 8192, 1),
+                                             (1024, 11008, 1), (8192, 11008, 1)])
+def test_swiglu_looks_before_it_merges_only_where_the_queue_of_atomics_is_longer(L, rows, cols, looks):
+    assert ask(L.moss_internal_swiglu_looks, rows, cols) == looks
+
+
+@pytest.mark.parametrize("rows,cols,looks", [(1, 8, 0), (16, 4096, 0), (895, 4096, 0), (896, 4096, 1), (1535, 2040, 0),
+                                             (1535, 72, 0), (1536, 72, 1), (8192, 4096, 1)])
+def test_norm_looks_before_it_merges_only_where_the_queue_of_atomics_is_longer(L, rows, cols, looks):
+    assert ask(L.moss_internal_rmsnorm_looks, rows, cols, 0) == looks
+    assert ask(L.moss_internal_rmsnorm_looks, rows, cols, 1) == looks
+
+
+def test_norm_rows_that_are_wide_for_the_backward_pass_alone(L):
+    assert [ask(L.moss_internal_rmsnorm_looks, 896, cols, back) for cols in (2048, 4088) for back in (0, 1)] == [0, 1, 0, 1]
