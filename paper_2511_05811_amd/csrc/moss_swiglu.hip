@@ -17,11 +17,6 @@ namespace moss {
 namespace {
 
 constexpr int kSwThreads = 256;
-// Chunks per thread whose loads are on the way together.  Forward 2 and backward 1 left too little in flight for tensors
-// of a trip or two per thread: 1024 x 11008 forward + backward + three quantizers took 142 us, 2 / 2 127, 4 / 2 115, 4 / 4 103;
-// 2048 x 11008 188 -> 162; 4096 x 11008, at the memory's rate, 278 either way.
-constexpr int kSwUnroll = 4;
-
 typedef unsigned short sw_u16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 sw_bf16x2 __attribute__((ext_vector_type(2)));
 typedef float sw_f32x2 __attribute__((ext_vector_type(2)));
@@ -73,18 +68,20 @@ __device__ __forceinline__ int64_t chunk_offset(int64_t id, int chunks_per_row, 
     return row * ld + (id - row * chunks_per_row) * 8;
 }
 
+// CHUNKS: 16-byte chunks of every input per thread whose loads are on the way together (chunks_per_thread has the rule)
+template <int CHUNKS>
 __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restrict__ gate, const uint16_t *__restrict__ up,
                                                        int64_t n_chunks, int chunks_per_row, int64_t ld, int dense, int flags,
                                                        uint16_t *__restrict__ h, uint32_t *__restrict__ h_max)
 {
     __shared__ uint32_t red[kSwThreads / kWave];
     uint32_t m = 0;
-    const int64_t stride = (int64_t)gridDim.x * kSwThreads * kSwUnroll;
-    for (int64_t id0 = (int64_t)blockIdx.x * kSwThreads * kSwUnroll + threadIdx.x; id0 < n_chunks; id0 += stride) {
-        uint4 g[kSwUnroll], u[kSwUnroll];
-        int64_t off[kSwUnroll];
+    const int64_t stride = (int64_t)gridDim.x * kSwThreads * CHUNKS;
+    for (int64_t id0 = (int64_t)blockIdx.x * kSwThreads * CHUNKS + threadIdx.x; id0 < n_chunks; id0 += stride) {
+        uint4 g[CHUNKS], u[CHUNKS];
+        int64_t off[CHUNKS];
 #pragma unroll
-        for (int k = 0; k < kSwUnroll; k++) {
+        for (int k = 0; k < CHUNKS; k++) {
             const int64_t id = id0 + (int64_t)k * kSwThreads;
             off[k] = -1;
             if (id < n_chunks) {
@@ -94,7 +91,7 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restric
             }
         }
 #pragma unroll
-        for (int k = 0; k < kSwUnroll; k++) {
+        for (int k = 0; k < CHUNKS; k++) {
             if (off[k] < 0) continue;
             const uint32_t gw[4] = {g[k].x, g[k].y, g[k].z, g[k].w}, uw[4] = {u[k].x, u[k].y, u[k].z, u[k].w};
             uint32_t o[4];
@@ -110,6 +107,7 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restric
     fold_max(m, h_max, flags & kProducerLook, red);
 }
 
+template <int CHUNKS>
 __global__ __launch_bounds__(kSwThreads) void k_swiglu_backward(const uint16_t *__restrict__ gate, const uint16_t *__restrict__ up,
                                                                 const uint16_t *__restrict__ dh, int64_t n_chunks,
                                                                 int chunks_per_row, int64_t ld, int dense, int flags,
@@ -118,12 +116,12 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu_backward(const uint16_t *
 {
     __shared__ uint32_t red[kSwThreads / kWave];
     uint32_t mg = 0, mu = 0;
-    const int64_t stride = (int64_t)gridDim.x * kSwThreads * kSwUnroll;
-    for (int64_t id0 = (int64_t)blockIdx.x * kSwThreads * kSwUnroll + threadIdx.x; id0 < n_chunks; id0 += stride) {
-        uint4 gc[kSwUnroll], uc[kSwUnroll], dc[kSwUnroll];
-        int64_t offs[kSwUnroll];
+    const int64_t stride = (int64_t)gridDim.x * kSwThreads * CHUNKS;
+    for (int64_t id0 = (int64_t)blockIdx.x * kSwThreads * CHUNKS + threadIdx.x; id0 < n_chunks; id0 += stride) {
+        uint4 gc[CHUNKS], uc[CHUNKS], dc[CHUNKS];
+        int64_t offs[CHUNKS];
 #pragma unroll
-        for (int k = 0; k < kSwUnroll; k++) {
+        for (int k = 0; k < CHUNKS; k++) {
             const int64_t id = id0 + (int64_t)k * kSwThreads;
             offs[k] = -1;
             if (id < n_chunks) {
@@ -134,7 +132,7 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu_backward(const uint16_t *
             }
         }
 #pragma unroll
-        for (int k = 0; k < kSwUnroll; k++) {
+        for (int k = 0; k < CHUNKS; k++) {
             const int64_t off = offs[k];
             if (off < 0) continue;
             const uint4 &g = gc[k], &u = uc[k], &d = dc[k];
@@ -172,8 +170,21 @@ int check_common(int64_t rows, int64_t cols, int64_t ld)
     return MOSS_OK;
 }
 
-int grid_for(int64_t n_chunks, int per_thread)
+// Chunks per thread.  One leaves too little in flight where the memory's rate counts, four leave small tensors to few
+// workgroups that each work through four chunks in a row.  Forward / backward alone, us, with 1, 2 and 4:
+//   chunks   2^10 (128 x 64)    4.6  5.0  5.6   and   5.1  5.6  6.5
+//            2^13               4.9  5.0  5.8         5.6  5.7  6.7
+//            2^14 (512 x 256)   5.5  5.2  5.8         6.2  5.9  6.8
+//            2^15               6.2  5.6  5.9         8.4  6.9  7.0
+//            2^16 (512 x 1024)  8.9  7.0  6.6        13.2  9.5  8.4
+//            2^18              19.9 12.8 10.1        34.5 21.1 15.0
+// (1024 x 11008 forward + backward + three quantizers 142 us with 2 forward and 1 backward, 103 with 4 and 4; at the memory's
+// rate, 4096 x 11008, 278 either way.)
+int chunks_per_thread(int64_t n_chunks) { return n_chunks < (1 << 14) ? 1 : n_chunks < (1 << 16) ? 2 : 4; }
+
+int grid_for(int64_t n_chunks)
 {
+    const int per_thread = chunks_per_thread(n_chunks);
     const int64_t want = (n_chunks + (int64_t)kSwThreads * per_thread - 1) / ((int64_t)kSwThreads * per_thread);
     int cus = moss_internal_cu_count();
     if (cus <= 0) cus = 256;
@@ -193,10 +204,8 @@ bool looks(int grid) { return grid >= 512; }
 }  // namespace moss
 
 // what the two entry points below choose for a tensor (the tests hold the rules by it)
-extern "C" int moss_internal_swiglu_looks(int64_t rows, int64_t cols)
-{
-    return moss::looks(moss::grid_for(rows * (cols / 8), moss::kSwUnroll));
-}
+extern "C" int moss_internal_swiglu_looks(int64_t rows, int64_t cols) { return moss::looks(moss::grid_for(rows * (cols / 8))); }
+extern "C" int moss_internal_swiglu_chunks(int64_t rows, int64_t cols) { return moss::chunks_per_thread(rows * (cols / 8)); }
 
 extern "C" int moss_swiglu_bf16(const void *gate, const void *up, int64_t rows, int64_t cols, int64_t ld,
                                 void *h, uint32_t *h_absmax_bits, void *stream)
@@ -211,8 +220,9 @@ extern "C" int moss_swiglu_bf16(const void *gate, const void *up, int64_t rows, 
     const int64_t n_chunks = rows * chunks_per_row;
     hipLaunchKernelGGL(k_swiglu_clear, dim3(1), dim3(64), 0, st, h_absmax_bits, (uint32_t *)nullptr);
     MOSS_LAUNCH_CHECK();
-    const int grid = grid_for(n_chunks, kSwUnroll);
-    hipLaunchKernelGGL(k_swiglu, dim3(grid), dim3(kSwThreads), 0, st, (const uint16_t *)gate, (const uint16_t *)up, n_chunks,
+    const int grid = grid_for(n_chunks), per_thread = chunks_per_thread(n_chunks);
+    const auto kern = per_thread == 1 ? k_swiglu<1> : per_thread == 2 ? k_swiglu<2> : k_swiglu<4>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kSwThreads), 0, st, (const uint16_t *)gate, (const uint16_t *)up, n_chunks,
                        chunks_per_row, ld, (int)(ld == cols), producer_flags(rows, cols, looks(grid)),
                        (uint16_t *)h, h_absmax_bits);
     MOSS_LAUNCH_CHECK();
@@ -236,8 +246,9 @@ extern "C" int moss_swiglu_bf16_backward(const void *gate, const void *up, const
     const int64_t n_chunks = rows * chunks_per_row;
     hipLaunchKernelGGL(k_swiglu_clear, dim3(1), dim3(64), 0, st, d_gate_absmax_bits, d_up_absmax_bits);
     MOSS_LAUNCH_CHECK();
-    const int grid = grid_for(n_chunks, kSwUnroll);
-    hipLaunchKernelGGL(k_swiglu_backward, dim3(grid), dim3(kSwThreads), 0, st, (const uint16_t *)gate, (const uint16_t *)up,
+    const int grid = grid_for(n_chunks), per_thread = chunks_per_thread(n_chunks);
+    const auto kern = per_thread == 1 ? k_swiglu_backward<1> : per_thread == 2 ? k_swiglu_backward<2> : k_swiglu_backward<4>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kSwThreads), 0, st, (const uint16_t *)gate, (const uint16_t *)up,
                        (const uint16_t *)dh, n_chunks, chunks_per_row, ld, (int)(ld == cols),
                        producer_flags(rows, cols, looks(grid)), (uint16_t *)d_gate, (uint16_t *)d_up,
                        d_gate_absmax_bits, d_up_absmax_bits);

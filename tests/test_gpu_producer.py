@@ -68,6 +68,12 @@ def test_swiglu_on_both_sides_of_the_look_before_the_merge(oracle, shape):
     test_swiglu_forward_and_backward(oracle, shape)
 
 
+@pytest.mark.parametrize("shape", [(3, 43688), (128, 1024), (257, 1032), (129, 4064), (64, 8192)])
+def test_swiglu_with_one_two_and_four_chunks_per_thread(oracle, shape):
+    # 2^14 and 2^16 chunks are the first tensors with two and four; below and above them, with trips that are not full
+    test_swiglu_forward_and_backward(oracle, shape)
+
+
 def test_swiglu_of_more_than_32_mib_equals_its_parts():
     # above 2^24 elements the outputs are stored through the caches: the same bits as in two parts below that
     g, u, d = (bf16_to_gpu(a) for a in make_inputs(2049, 8200, 5))

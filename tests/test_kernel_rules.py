@@ -26,6 +26,12 @@ def test_swiglu_looks_before_it_merges_only_where_the_queue_of_atomics_is_longer
     assert ask(L.moss_internal_swiglu_looks, rows, cols) == looks
 
 
+@pytest.mark.parametrize("rows,cols,chunks", [(1, 8, 1), (3, 8032, 1), (13, 2016, 1), (1024, 120, 1), (1, 131064, 1), (1, 131072, 2),
+                                              (1024, 504, 2), (1, 524280, 2), (1, 524288, 4), (8192, 11008, 4)])
+def test_swiglu_gives_small_tensors_more_workgroups_with_fewer_chunks(L, rows, cols, chunks):
+    assert ask(L.moss_internal_swiglu_chunks, rows, cols) == chunks
+
+
 @pytest.mark.parametrize("rows,cols,looks", [(1, 8, 0), (16, 4096, 0), (895, 4096, 0), (896, 4096, 1), (1535, 2040, 0),
                                              (1535, 72, 0), (1536, 72, 1), (8192, 4096, 1)])
 def test_norm_looks_before_it_merges_only_where_the_queue_of_atomics_is_longer(L, rows, cols, looks):
