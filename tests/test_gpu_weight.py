@@ -90,6 +90,11 @@ def test_tiles_and_trips_of_the_step(oracle, rows, cols, transpose, bf16_grad):
     run_parity(oracle, rows, cols, 2, seed=9, interval=2, transpose=transpose, bf16_grad=bf16_grad)
 
 
+def test_fold_of_as_many_partials_as_few_threads_take(oracle):
+    print("[weight parity] 4096x1024 flat: 1024 partials", flush=True)
+    run_parity(oracle, 4096, 1024, 2, seed=10, interval=2, transpose=False)
+
+
 def test_broken_bound_saturates_and_counts(oracle):
     print("[weight parity] overflow path", flush=True)
     st = run_parity(oracle, 64, 64, 6, seed=7, lr=1e-2, margin=1e-4)

@@ -41,3 +41,8 @@ def test_norm_looks_before_it_merges_only_where_the_queue_of_atomics_is_longer(L
 
 def test_norm_rows_that_are_wide_for_the_backward_pass_alone(L):
     assert [ask(L.moss_internal_rmsnorm_looks, 896, cols, back) for cols in (2048, 4088) for back in (0, 1)] == [0, 1, 0, 1]
+
+
+@pytest.mark.parametrize("partials,threads", [(1, 256), (256, 256), (1024, 256), (1025, 1024), (4096, 1024), (5504, 1024)])
+def test_few_partials_of_a_weight_are_folded_by_few_threads(L, partials, threads):
+    assert ask(L.moss_internal_weight_fold_threads, partials) == threads
