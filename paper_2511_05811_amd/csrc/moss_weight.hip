@@ -172,14 +172,11 @@ __device__ __forceinline__ float absmax4(const float4 &t)
     return fmaxf(fmaxf(fabsf(t.x), fabsf(t.y)), fmaxf(fabsf(t.z), fabsf(t.w)));
 }
 
-// Bound: HBM (four streams in, three or four out).  All loads of kStepUnroll vectors are issued before the first
-// store: one vector at a time, a wave's loads queue behind its own stores and 11008 x 8192 with BF16 gradients took
-// 572 us (4.2 TB/s); two at a time 492 us, four 457 us (5.3 TB/s, the rate of the tile kernel below and of a plain copy).
-// (Contiguous ranges per workgroup instead of the grid-wide stride: 466 us; ordinary instead of streaming loads: 513
-// against 572 us with one vector, nothing on top of four.)
-constexpr int kStepUnroll = 4;
-
-template <bool G_BF16, bool DO_CAST>
+// Bound: HBM (four streams in, three or four out).  BATCH vectors per thread are loaded ahead of the first store: one at a time,
+// a wave's loads queue behind its own stores and 11008 x 8192 with BF16 gradients took 572 us (4.2 TB/s); two at a time 492 us,
+// four 457 us (5.3 TB/s, the rate of the tile kernel below and of a plain copy).  (Contiguous ranges per workgroup: 466 us;
+// ordinary instead of streaming loads: 513 against 572 us with one vector, nothing on top of four.)  step_batch has the rule.
+template <bool G_BF16, bool DO_CAST, int BATCH>
 __global__ __launch_bounds__(kWThreads) void k_adamw_cast(float *__restrict__ w, float *__restrict__ m,
                                                           float *__restrict__ v, const void *__restrict__ g,
                                                           int64_t n4, AdamW a, double lr_term,
@@ -193,25 +190,31 @@ __global__ __launch_bounds__(kWThreads) void k_adamw_cast(float *__restrict__ w,
         limit = range_limit(s);
     }
     WCounts cnt;
-    const int64_t stride = (int64_t)gridDim.x * kWThreads * kStepUnroll;
-    for (int64_t i0 = (int64_t)blockIdx.x * kWThreads * kStepUnroll + threadIdx.x; i0 < n4; i0 += stride) {
-        StepVec t[kStepUnroll];
-#pragma unroll
-        for (int u = 0; u < kStepUnroll; u++) {
-            const int64_t i = i0 + u * kWThreads;
-            if (i < n4) load_step(t[u], w, m, v, g, i, G_BF16);
+    auto finish = [&](StepVec &t, int64_t i) {
+        step_and_store(t, a, w, m, v, i);
+        cnt.amax = fmaxf(cnt.amax, absmax4(t.w));
+        if (DO_CAST) {
+            const float y0 = t.w.x * inv_s, y1 = t.w.y * inv_s, y2 = t.w.z * inv_s, y3 = t.w.w * inv_s;
+            count4(cnt, t.w, y0, y1, y2, y3, limit);
+            st_stream4(reinterpret_cast<uint32_t *>(wq) + i, cvt4_e4m3_sat(y0, y1, y2, y3));
         }
+    };
+    const int64_t stride = (int64_t)gridDim.x * kWThreads * BATCH;
+    for (int64_t i0 = (int64_t)blockIdx.x * kWThreads * BATCH + threadIdx.x; i0 < n4; i0 += stride) {
+        StepVec t[BATCH];
+        if (BATCH == 1) {
+            load_step(t[0], w, m, v, g, i0, G_BF16);
+            finish(t[0], i0);
+        } else {
 #pragma unroll
-        for (int u = 0; u < kStepUnroll; u++) {
-            const int64_t i = i0 + u * kWThreads;
-            if (i >= n4) continue;
-            step_and_store(t[u], a, w, m, v, i);
-            const float4 &wv = t[u].w;
-            cnt.amax = fmaxf(cnt.amax, absmax4(wv));
-            if (DO_CAST) {
-                float y0 = wv.x * inv_s, y1 = wv.y * inv_s, y2 = wv.z * inv_s, y3 = wv.w * inv_s;
-                count4(cnt, wv, y0, y1, y2, y3, limit);
-                st_stream4(reinterpret_cast<uint32_t *>(wq) + i, cvt4_e4m3_sat(y0, y1, y2, y3));
+            for (int u = 0; u < BATCH; u++) {
+                const int64_t i = i0 + u * kWThreads;
+                if (i < n4) load_step(t[u], w, m, v, g, i, G_BF16);
+            }
+#pragma unroll
+            for (int u = 0; u < BATCH; u++) {
+                const int64_t i = i0 + u * kWThreads;
+                if (i < n4) finish(t[u], i);
             }
         }
     }
@@ -439,6 +442,23 @@ static int grid_for(int64_t n4)
     return (int)(blocks < kWMaxBlocks ? blocks : kWMaxBlocks);
 }
 
+// BATCH of k_adamw_cast: four vectors from two vectors per thread of the largest grid on (8M elements), and for a step with its
+// cast on up to one workgroup per compute unit.  Step alone, buffers that no cache holds, us, one vector and four:
+//   0.25M elements 10.2 and 9.7 (re-base 15.2, 15.6)    0.75M 11.2 and 10.7 (16.7, 16.9)    1.5M 13.7 and 15.1 (20.0, 22.3)
+//   2M 15.8 and 16.3    6M 40.0 and 41.5 (BF16 gradients 37.5, 40.0)    8M 52.0 and 51.7    12M 76.6 and 72.5    64M 401 and 361
+// The re-basing pass is followed by a cast of the same weights over the grid-wide stride, which finds them in the L2 of the XCD
+// that wrote them only if both passes give a vector to the same workgroup, as with one vector (64K elements 13.2, 14.5); few
+// workgroups are bound by the latency of their code, which is shorter with one.
+constexpr int kStepBatch = 4;
+
+static int step_batch(int64_t n4, int grid, bool cast)
+{
+    if (n4 >= 2 * (int64_t)kWMaxBlocks * kWThreads) return kStepBatch;
+    int cus = moss_internal_cu_count();
+    if (cus <= 0) cus = 256;
+    return cast && grid >= 32 && grid <= cus ? kStepBatch : 1;
+}
+
 static int launch_transpose(const uint8_t *src, int64_t rows, int64_t cols, uint8_t *dst, hipStream_t st)
 {
     int64_t gx = (cols + kTT - 1) / kTT, gy = (rows + kTT - 1) / kTT;
@@ -513,6 +533,16 @@ static int finalize(const WLaunch &L, int n_partial, int mode, double lr_term, i
     return MOSS_OK;
 }
 
+template <bool CAST>
+static void launch_flat(const WLaunch &L, bool grad_bf16, float *w, float *m, float *v, const void *g, const AdamW &a, double lr_term,
+                        uint8_t *wq)
+{
+    const auto kern = step_batch(L.n4, L.grid1d, CAST) == 1
+                          ? (grad_bf16 ? k_adamw_cast<true, CAST, 1> : k_adamw_cast<false, CAST, 1>)
+                          : (grad_bf16 ? k_adamw_cast<true, CAST, kStepBatch> : k_adamw_cast<false, CAST, kStepBatch>);
+    hipLaunchKernelGGL(kern, dim3(L.grid1d), dim3(kWThreads), 0, L.st, w, m, v, g, L.n4, a, lr_term, L.state, wq, L.ws, L.slots);
+}
+
 template <bool STEP, bool SRC_BF16>
 static void launch_tile_of(const WLaunch &L, float *w, float *m, float *v, const void *src, const AdamW &a, double lr_term, uint8_t *wq,
                            uint8_t *wq_t)
@@ -570,6 +600,11 @@ static int make_launch(WLaunch &L, int64_t rows, int64_t cols, moss_wscale_state
 // what the launches below choose (the tests hold the rules by it)
 extern "C" int moss_internal_weight_fold_threads(int64_t n_partial) { return moss::fold_threads((int)n_partial); }
 
+extern "C" int moss_internal_weight_step_batch(int64_t rows, int64_t cols, int64_t cast)
+{
+    return moss::step_batch(rows * cols / 4, moss::grid_for(rows * cols / 4), cast != 0);
+}
+
 extern "C" int moss_weight_autoscale_init(const void *w, int w_dtype, int64_t rows, int64_t cols,
                                           moss_wscale_state *state, uint8_t *wq, uint8_t *wq_t,
                                           void *workspace, size_t workspace_bytes, void *stream)
@@ -613,14 +648,10 @@ extern "C" int moss_weight_autoscale_cast(float *w, float *m, float *v, const vo
     const double lr_term = (double)args->margin * (double)args->lr;
     const bool rebase = args->interval > 0 && (args->step % args->interval) == 0;
     const bool gb = g_dtype == MOSS_DT_BF16;
-    const dim3 g1(L.grid1d), blk(kWThreads);
 
     if (rebase) {
         // AdamW alone (it yields amax(W_new)), re-base the scale from it, then cast with the new scale
-        if (gb)
-            hipLaunchKernelGGL((k_adamw_cast<true, false>), g1, blk, 0, L.st, w, m, v, g, L.n4, a, lr_term, state, wq, workspace, L.slots);
-        else
-            hipLaunchKernelGGL((k_adamw_cast<false, false>), g1, blk, 0, L.st, w, m, v, g, L.n4, a, lr_term, state, wq, workspace, L.slots);
+        launch_flat<false>(L, gb, w, m, v, g, a, lr_term, wq);
         MOSS_LAUNCH_CHECK();
         if ((rc = finalize(L, L.grid1d, kFinRebase, lr_term, args->step))) return rc;
         return cast_only(L, w, false, wq, wq_t);
@@ -630,10 +661,7 @@ extern "C" int moss_weight_autoscale_cast(float *w, float *m, float *v, const vo
         MOSS_LAUNCH_CHECK();
         return finalize(L, (int)(L.grid2d.x * L.grid2d.y), kFinStep, lr_term, args->step);
     }
-    if (gb)
-        hipLaunchKernelGGL((k_adamw_cast<true, true>), g1, blk, 0, L.st, w, m, v, g, L.n4, a, lr_term, state, wq, workspace, L.slots);
-    else
-        hipLaunchKernelGGL((k_adamw_cast<false, true>), g1, blk, 0, L.st, w, m, v, g, L.n4, a, lr_term, state, wq, workspace, L.slots);
+    launch_flat<true>(L, gb, w, m, v, g, a, lr_term, wq);
     MOSS_LAUNCH_CHECK();
     if ((rc = finalize(L, L.grid1d, kFinStep, lr_term, args->step))) return rc;
     if (wq_t) return launch_transpose(wq, rows, cols, wq_t, L.st);

@@ -90,6 +90,17 @@ def test_tiles_and_trips_of_the_step(oracle, rows, cols, transpose, bf16_grad):
     run_parity(oracle, rows, cols, 2, seed=9, interval=2, transpose=transpose, bf16_grad=bf16_grad)
 
 
+@pytest.mark.parametrize("rows,cols", [(31, 4096),          # one vector at a time: the largest before the first batches
+                                       (32, 4096),          # batches in the step, one at a time where the scale is re-based
+                                       (255, 4108),         # ... a last batch that is not full
+                                       (259, 4100),         # one at a time again, a last trip that is not full
+                                       (2049, 4100)])       # batches in both, likewise
+@pytest.mark.parametrize("bf16_grad", [False, True])
+def test_batches_of_the_flat_step(oracle, rows, cols, bf16_grad):
+    print(f"[weight parity] flat {rows}x{cols} bf16_grad={bf16_grad}", flush=True)
+    run_parity(oracle, rows, cols, 2, seed=11, interval=2, transpose=False, bf16_grad=bf16_grad)
+
+
 def test_fold_of_as_many_partials_as_few_threads_take(oracle):
     print("[weight parity] 4096x1024 flat: 1024 partials", flush=True)
     run_parity(oracle, 4096, 1024, 2, seed=10, interval=2, transpose=False)

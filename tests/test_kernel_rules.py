@@ -46,3 +46,10 @@ def test_norm_rows_that_are_wide_for_the_backward_pass_alone(L):
 @pytest.mark.parametrize("partials,threads", [(1, 256), (256, 256), (1024, 256), (1025, 1024), (4096, 1024), (5504, 1024)])
 def test_few_partials_of_a_weight_are_folded_by_few_threads(L, partials, threads):
     assert ask(L.moss_internal_weight_fold_threads, partials) == threads
+
+
+@pytest.mark.parametrize("rows,cols,step,rebase", [(1, 4, 1, 1), (31, 4096, 1, 1), (32, 4096, 4, 1), (256, 4096, 4, 1), (257, 4096, 1, 1),
+                                                   (2047, 4096, 1, 1), (2048, 4096, 4, 4), (11008, 8192, 4, 4)])
+def test_weight_step_takes_vectors_in_batches_where_they_pay(L, rows, cols, step, rebase):
+    assert ask(L.moss_internal_weight_step_batch, rows, cols, 1) == step
+    assert ask(L.moss_internal_weight_step_batch, rows, cols, 0) == rebase
