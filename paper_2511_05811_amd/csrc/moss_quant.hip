@@ -8,7 +8,7 @@
 //
 //  * One launch (k_quant_persist): tensors of up to four 128 x 128 tiles per workgroup of a
 //    co-resident grid stay in registers between the maximum and the codes; X is read once.
-//  * One launch (SCAN forms of the kernels below): tensors of at most kScanBytesRow / kScanBytesTile, where every workgroup reads the whole
+//  * One launch (SCAN forms of the kernels below): small tensors (kScanBytes*), where every workgroup reads the whole
 //    tensor for the maximum by itself.
 //  * Two launches: k_amax_bf16 leaves one partial maximum per workgroup in the workspace, and
 //    k_quant_row (row groups alone) or k_quant_tile (column groups, or both groupings from one
@@ -269,12 +269,16 @@ __device__ __forceinline__ uint2 row_codes(const uint4 &r, float fused, uint32_t
 }
 
 // Small tensors: every workgroup takes the maximum over all of X itself, behind its L2, in place of the launch in front
-// that leaves partial maxima.  Both ways are a chain of latencies.  On the device, calls back to back, scan and two launches:
-//   row groups   32 KiB 3.4 / 5.4 us, 128 KiB 4.3 / 5.9, 256 KiB 5.8 / 5.8, 384 KiB 7.1 / 5.9
-//   both         32 KiB 6.9 / 8.3 us,  64 KiB 8.2 / 8.3, 128 KiB 10.6 / 8.5   (workgroups of a quarter of the threads)
+// that leaves partial maxima.  Both ways are a chain of latencies.  On the device, calls back to back, scan and two launches;
+// with a row stride above the width every chunk of the scan costs a division, hence lower limits there:
+//   row groups   32 KiB 4.1 / 6.1 us, 128 KiB 4.8 / 6.5, 256 KiB 6.3 / 6.5, 362 KiB 7.6 / 6.5
+//     strided    32 KiB 4.4 / 6.9,    128 KiB 6.2 / 7.3, 181 KiB 7.1 / 7.3, 256 KiB 8.5 / 7.4
+//   both         32 KiB 6.8 / 8.0 us,  45 KiB 7.6 / 8.4,  64 KiB 8.5 / 8.6,  91 KiB 9.9 / 9.0  (workgroups of a quarter of the threads)
+//     strided    32 KiB 7.6 / 8.8,     45 KiB 8.3 / 8.8,  64 KiB 9.6 / 9.2
 // and the host issues one launch less, about 2 us: 17 x 4096 and the GEMM behind it take 20 instead of 23 us, the smallest
 // training step 42 instead of 47.
 constexpr int64_t kScanBytesRow = 256 * 1024, kScanBytesTile = 64 * 1024;
+constexpr int64_t kScanBytesRowStrided = 160 * 1024, kScanBytesTileStrided = 48 * 1024;
 constexpr int kScanThreadsRow = 1024;
 constexpr int kScanUnroll = 8;
 
@@ -980,6 +984,19 @@ extern "C" size_t moss_quant_workspace_bytes(int64_t rows, int64_t cols, unsigne
     return (size_t)(moss::kMaxPartials + moss::kSyncWords) * sizeof(uint32_t);
 }
 
+static bool scans(int64_t bytes, bool dense, bool want_col)
+{
+    using namespace moss;
+    if (want_col) return bytes <= (dense ? kScanBytesTile : kScanBytesTileStrided);
+    return bytes <= (dense ? kScanBytesRow : kScanBytesRowStrided);
+}
+
+// what quant_with_workspace chooses for a small tensor (the tests hold the rule by it)
+extern "C" int moss_internal_quant_scans(int64_t rows, int64_t cols, int64_t ld, int64_t want_col)
+{
+    return scans(rows * cols * 2, ld == cols, want_col != 0);
+}
+
 // The launch that converts: k_quant_row for the row grouping alone, k_quant_tile as soon as the transposed
 // grouping is wanted.  `partial` holds n_partial candidate maxima (BF16 magnitude bits) that every workgroup folds;
 // without any (n_partial == 0) the workgroups take the maximum over X themselves (the caller checks the size).
@@ -1061,7 +1078,7 @@ static int quant_with_workspace(const void *x_bf16, int64_t rows, int64_t cols, 
     const int dense = (ld == cols);
 
     // Small tensors: one launch whose workgroups each read all of X for the maximum (the workspace is not touched)
-    if (n_chunks * 16 <= (want_col ? kScanBytesTile : kScanBytesRow))
+    if (scans(n_chunks * 16, dense, want_col))
         return launch_codes(x, rows, cols, ld, want_row, want_col, ceil_mode, nullptr, 0, q_row, e_row, q_col, e_col, s_global, st);
 
     // Tensors of one to kKeep tiles per workgroup: one launch that keeps X in registers between the

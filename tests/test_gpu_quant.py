@@ -88,6 +88,14 @@ def test_small_tensors_where_every_workgroup_looks_for_the_maximum(oracle, rows,
         check_against_oracle(oracle, big, flag, f"max at {at} ld {ld}", x_dev=bf16_to_gpu(wide)[:, :cols])
 
 
+@pytest.mark.parametrize("rows,cols,ld", [(32, 768, 832),        # 48 KiB: the largest strided tensor whose tiles look for the maximum
+                                          (64, 512, 576),        # above it: two launches for column groups
+                                          (80, 1024, 1088), (96, 1024, 1032)])   # rows: around 160 KiB
+@pytest.mark.parametrize("flag", [0, CEIL])
+def test_strided_tensors_around_the_limit_of_the_scan(oracle, rows, cols, ld, flag):
+    test_small_tensors_where_every_workgroup_looks_for_the_maximum(oracle, rows, cols, ld, flag)
+
+
 # Tensors with at least two 128 x 128 tiles per compute unit take the one-launch kernel (a bounded
 # grid that meets once for the global maximum and keeps its first tiles in registers).
 @pytest.mark.parametrize("shape,flag", [((4128, 2080), 0),      # ragged edges, every tile kept

@@ -53,3 +53,11 @@ def test_few_partials_of_a_weight_are_folded_by_few_threads(L, partials, threads
 def test_weight_step_takes_vectors_in_batches_where_they_pay(L, rows, cols, step, rebase):
     assert ask(L.moss_internal_weight_step_batch, rows, cols, 1) == step
     assert ask(L.moss_internal_weight_step_batch, rows, cols, 0) == rebase
+
+
+@pytest.mark.parametrize("rows,cols,ld,row,col", [(1, 32, 32, 1, 1), (64, 512, 512, 1, 1), (65, 512, 512, 1, 0), (128, 1024, 1024, 1, 0),
+                                                  (129, 1024, 1024, 0, 0), (48, 512, 576, 1, 1), (49, 512, 576, 1, 0),
+                                                  (80, 1024, 1088, 1, 0), (81, 1024, 1088, 0, 0)])
+def test_every_workgroup_looks_for_the_maximum_of_a_small_tensor_only(L, rows, cols, ld, row, col):
+    assert ask(L.moss_internal_quant_scans, rows, cols, ld, 0) == row
+    assert ask(L.moss_internal_quant_scans, rows, cols, ld, 1) == col
