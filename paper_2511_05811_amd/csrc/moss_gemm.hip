@@ -240,6 +240,26 @@ extern "C" size_t moss_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
     return 0;
 }
 
+// Three kernels.  Small tiles, some with K split inside the workgroup, take any M, N and K for which a model of the three
+// expects them to be the fastest: problems that leave most compute units idle otherwise, most with K % 128 != 0, and many that
+// the large tiles cannot take.  256-wide tiles fed by direct global->LDS copies take the large problems with K % 128 == 0,
+// exponents of a and outputs in whole 16-byte pieces.  The general kernel takes the rest: tiny problems of many tiles (a short
+// K), large ones that do not fit the large tiles (K % 128 != 0, no exponents of a, odd N), exponents that are not dword aligned.
+//
+// The tile (rows * 1000 + columns) that moss_gemm_fp8_mx chooses for a problem whose exponents, where given, are aligned;
+// 0 for the general kernel (the tests hold the choice by it)
+extern "C" int moss_internal_gemm_tile(int64_t M, int64_t N, int64_t K, int64_t has_a_e, int64_t has_b_e, int64_t ld_out,
+                                       int64_t accumulate)
+{
+    static const uint8_t some[16] __attribute__((aligned(16))) = {};
+    const uint8_t *a_e = has_a_e ? some : nullptr, *b_e = has_b_e ? some : nullptr;
+    const bool large_ok = moss_internal_gemm_big_ok(M, N, K, a_e, b_e, ld_out);
+    static const int tiles[5] = {32032, 64064, 64128, 128128, 128192};
+    const int kind = moss_internal_gemm_mid_kind(M, N, K, a_e, b_e, (int)accumulate, large_ok);
+    if (kind >= 0) return tiles[kind];
+    return large_ok ? (moss_internal_gemm_big_narrow(M, N) ? 128256 : 256256) : 0;
+}
+
 extern "C" int moss_gemm_fp8_mx(int64_t M, int64_t N, int64_t K,
                                 const uint8_t *a_q, const uint8_t *a_e, const float *a_s,
                                 const uint8_t *b_q, const uint8_t *b_e, const float *b_s,
@@ -255,17 +275,15 @@ extern "C" int moss_gemm_fp8_mx(int64_t M, int64_t N, int64_t K,
     if (!moss_aligned16(a_q) || !moss_aligned16(b_q) || !moss_aligned16(out)) return MOSS_ERR_ALIGN;
     if (((uintptr_t)a_s & 3) || ((uintptr_t)b_s & 3)) return MOSS_ERR_ALIGN;
     if (K % 16) return MOSS_ERR_ALIGN;
-    // Three kernels: small tiles with K split inside the workgroup where the problem leaves most compute units idle
-    // otherwise, 256-wide tiles fed by direct global->LDS copies for the large problems, and the general kernel for the
-    // rest (many tiles with K % 128 != 0, operands that are not aligned for the copies).
     const int f32 = out_dtype == MOSS_DT_F32;
     const bool large_ok = moss_internal_gemm_big_ok(M, N, K, a_e, b_e, ld_out);
-    int rc = moss_internal_gemm_mid(M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, f32, ld_out, accumulate, large_ok, (hipStream_t)stream);
-    if (rc != MOSS_ERR_UNSUPPORTED) return rc;
-    if (large_ok) {
+    const int kind = moss_internal_gemm_mid_kind(M, N, K, a_e, b_e, accumulate, large_ok);
+    int rc = MOSS_ERR_UNSUPPORTED;
+    if (kind >= 0)
+        rc = moss_internal_gemm_mid(kind, M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, f32, ld_out, accumulate, (hipStream_t)stream);
+    if (rc == MOSS_ERR_UNSUPPORTED && large_ok)
         rc = moss_internal_gemm_big(M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, f32, ld_out, accumulate, (hipStream_t)stream);
-        if (rc != MOSS_ERR_UNSUPPORTED) return rc;
-    }
+    if (rc != MOSS_ERR_UNSUPPORTED) return rc;
     return launch_gemm<128, 128, 2, 2, kModeFp8Mx>(M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, out_dtype == MOSS_DT_F32,
                                                    ld_out, accumulate, (hipStream_t)stream);
 }

@@ -461,6 +461,25 @@ bool moss_internal_gemm_big_ok(int64_t M, int64_t N, int64_t K, const uint8_t *a
     return N % 8 == 0 && ld_out % 8 == 0;                      // the epilogue stores whole 16-byte pieces
 }
 
+// compute units of the persistent grid
+static int big_cus()
+{
+    const int cus = moss_internal_cu_count();
+    return cus <= 0 ? 256 : cus >= 8 ? cus & ~7 : 8;
+}
+
+// 256 x 256 tiles when they fill the machine, else 128 x 256 (twice the tiles, each at a somewhat
+// lower rate).  Time in units of one full tile on all compute units: rounds of full tiles, or rounds
+// of half tiles at 0.78 each (a half tile takes 0.76 of the time of a full one: 67 us against 88 us
+// for M = 4096, N = 2048, K = 7168), so the narrow tile pays only where it saves whole rounds.
+bool moss_internal_gemm_big_narrow(int64_t M, int64_t N)
+{
+    const int cus = big_cus();
+    const int64_t tiles_n = (N + moss::kBT - 1) / moss::kBT;
+    const int64_t full = ((M + moss::kBT - 1) / moss::kBT) * tiles_n, half = ((M + moss::kBT / 2 - 1) / (moss::kBT / 2)) * tiles_n;
+    return 0.78 * (double)((half + cus - 1) / cus) < (double)((full + cus - 1) / cus);
+}
+
 // Returns MOSS_ERR_UNSUPPORTED when the shape does not fit the fast path (the caller then
 // uses the general kernel).
 int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, const uint8_t *a_e, const float *a_s,
@@ -470,16 +489,9 @@ int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, 
     using namespace moss;
     if (!moss_internal_gemm_big_ok(M, N, K, a_e, b_e, ld_out)) return MOSS_ERR_UNSUPPORTED;
     if ((int64_t)kBT * K >= ((int64_t)1 << 32)) return MOSS_ERR_UNSUPPORTED;
-    int cus = moss_internal_cu_count();
-    cus = cus >= 8 ? cus & ~7 : 8;
-    // 256 x 256 tiles when they fill the machine, else 128 x 256 (twice the tiles, each at a somewhat
-    // lower rate).  Time in units of one full tile on all compute units: rounds of full tiles, or rounds
-    // of half tiles at 0.78 each (a half tile takes 0.76 of the time of a full one: 67 us against 88 us
-    // for M = 4096, N = 2048, K = 7168), so the narrow tile pays only where it saves whole rounds.
+    const int cus = big_cus();
+    const bool narrow = moss_internal_gemm_big_narrow(M, N);
     const int64_t tiles_n = (N + kBT - 1) / kBT;
-    const int64_t full = ((M + kBT - 1) / kBT) * tiles_n, half = ((M + kBT / 2 - 1) / (kBT / 2)) * tiles_n;
-    const double t_full = (double)((full + cus - 1) / cus), t_half = 0.78 * (double)((half + cus - 1) / cus);
-    const bool narrow = t_half < t_full;
     const int64_t tiles_m = narrow ? (M + kBT / 2 - 1) / (kBT / 2) : (M + kBT - 1) / kBT;
     if (tiles_m * tiles_n > 0x7FFFFFF) return MOSS_ERR_UNSUPPORTED;
     using Kern = void (*)(int64_t, int64_t, int64_t, const uint8_t *, const uint8_t *, const float *, const uint8_t *,

@@ -27,14 +27,17 @@ int moss_internal_cu_count();
 int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, const uint8_t *a_e, const float *a_s,
                            const uint8_t *b_q, const uint8_t *b_e, const float *b_s, void *out, int out_f32,
                            int64_t ld_out, int accumulate, hipStream_t st);
-// whether the large-tile kernel takes the problem
+// whether the large-tile kernel takes the problem, and in half tiles (128 x 256)
 bool moss_internal_gemm_big_ok(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int64_t ld_out);
+bool moss_internal_gemm_big_narrow(int64_t M, int64_t N);
 
-// small tiles and split K for problems that leave the large tiles idle, and ragged K; MOSS_ERR_UNSUPPORTED if another kernel
-// is the better choice
-int moss_internal_gemm_mid(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, const uint8_t *a_e, const float *a_s,
+// small tiles and split K for problems that leave the large tiles idle, and ragged K: the kind of tiles, or -1 if another kernel
+// is the better choice; MOSS_ERR_UNSUPPORTED if the device cannot launch them
+int moss_internal_gemm_mid_kind(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int accumulate,
+                                bool large_ok);
+int moss_internal_gemm_mid(int kind, int64_t M, int64_t N, int64_t K, const uint8_t *a_q, const uint8_t *a_e, const float *a_s,
                            const uint8_t *b_q, const uint8_t *b_e, const float *b_s, void *out, int out_f32, int64_t ld_out,
-                           int accumulate, bool large_ok, hipStream_t st);
+                           int accumulate, hipStream_t st);
 
 namespace moss {
 

@@ -61,3 +61,29 @@ def test_weight_step_takes_vectors_in_batches_where_they_pay(L, rows, cols, step
 def test_every_workgroup_looks_for_the_maximum_of_a_small_tensor_only(L, rows, cols, ld, row, col):
     assert ask(L.moss_internal_quant_scans, rows, cols, ld, 0) == row
     assert ask(L.moss_internal_quant_scans, rows, cols, ld, 1) == col
+
+
+# Tile (rows * 1000 + columns, 0 for the general kernel) that was the fastest, or within a few percent of it, when each
+# kernel ran the problem; without / with exponents of b.
+@pytest.mark.parametrize("M,N,K,b_e,tile", [(64, 256, 512, 0, 32032), (17, 11008, 4096, 0, 32032), (512, 256, 64, 1, 32032),
+                                            (256, 512, 64, 1, 32032), (256, 4096, 4096, 0, 64064), (1024, 1024, 1024, 0, 64064),
+                                            (512, 4096, 4096, 0, 64128), (512, 4096, 1024, 0, 64128),
+                                            (600, 4096, 4128, 0, 128128), (600, 4096, 4128, 1, 128128), (1000, 4000, 1056, 1, 128128),
+                                            (2048, 2048, 2080, 1, 128128), (1333, 4096, 4128, 0, 128192), (8192, 2080, 4128, 0, 128192),
+                                            (3072, 3072, 4128, 1, 128192), (2005, 2436, 3584, 0, 128192),
+                                            (1333, 4096, 11008, 0, 128256), (2005, 2440, 3584, 0, 128256), (8192, 4096, 4096, 0, 256256),
+                                            (4096, 4096, 8192, 1, 256256), (11008, 4096, 8192, 1, 256256),
+                                            (4096, 4096, 2080, 0, 0), (5000, 1056, 1056, 0, 0), (6321, 2424, 32, 0, 0), (2528, 2912, 8032, 1, 0)])
+def test_gemm_takes_the_kernel_that_measured_fastest(L, M, N, K, b_e, tile):
+    assert ask(L.moss_internal_gemm_tile, M, N, K, 1, b_e, N, 0) == tile
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(1341, 4234, 2944, 128192), (2085, 2656, 7168, 128192), (27, 512, 32, 32032), (8192, 4096, 4096, 0)])
+def test_gemm_without_exponents_of_a(L, M, N, K, tile):
+    assert ask(L.moss_internal_gemm_tile, M, N, K, 0, 0, N, 0) == tile
+
+
+@pytest.mark.parametrize("M,N,K,plain,accumulating", [(3520, 1536, 1184, 128192, 0), (12288, 672, 2144, 128192, 0), (4096, 4096, 512, 256256, 256256)])
+def test_gemm_that_accumulates(L, M, N, K, plain, accumulating):
+    assert ask(L.moss_internal_gemm_tile, M, N, K, 1, 1, N, 0) == plain
+    assert ask(L.moss_internal_gemm_tile, M, N, K, 1, 1, N, 1) == accumulating
