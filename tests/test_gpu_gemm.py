@@ -2,6 +2,8 @@
 against the CPU oracle's dequantize-then-FP64 GEMM (paper Sec. 3.1, Fig. 3b).
 Tolerance: |gpu - oracle| <= 1e-3 * |a_row|_2 * |b_row|_2 per output for FP32 outputs;
 BF16 outputs get the same bound plus one rounding step of the BF16 output format."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -28,6 +30,13 @@ def gpu_gemm(a_q, a_e, a_s, b_q, b_e, b_s, **kw):
     return out
 
 
+def tile_of(M, N, K, a_e, b_e, ld=None, accumulate=False):
+    """The tile (rows * 1000 + columns; 0: the general kernel) that the library chooses for a problem.  The tests below name
+    the kernel they are about and assert it by this."""
+    return moss.load().moss_internal_gemm_tile(*(C.c_int64(int(v)) for v in (M, N, K, a_e is not None, b_e is not None,
+                                                                            ld or N, accumulate)))
+
+
 def assert_close(got, ref, na, nb, bf16, tag):
     tol = REL * np.outer(na, nb) if ref.ndim == 2 else REL * na * nb
     err = np.abs(got - ref)
@@ -49,7 +58,7 @@ def assert_close(got, ref, na, nb, bf16, tag):
 
 @pytest.mark.parametrize("shape", [(16, 16, 32), (1, 1, 32), (5, 3, 64), (128, 128, 128), (200, 136, 96),
                                    (257, 129, 416), (130, 260, 1024), (64, 512, 160),
-                                   # >= 8 tiles of 256 x 256 with K % 128 == 0: the large-tile kernel
+                                   # K % 128 == 0 from 8 tiles of 256 x 256 on, where small tiles are still the faster ones
                                    (520, 776, 640), (1024, 2048, 512), (2049, 257, 1152), (512, 1024, 2176)])
 @pytest.mark.parametrize("exps", ["both", "a_only", "none"])
 def test_random_codes_all_tile_edges(oracle, shape, exps):
@@ -103,9 +112,9 @@ def test_one_hot_operands_pin_the_lane_and_scale_mapping(oracle):
         assert np.array_equal(out, ref), (m, n, k)
 
 
-@pytest.mark.parametrize("shape,ld", [((70, 52, 192), 64),          # general kernel
-                                      ((600, 1000, 512), 1004),     # ld_out % 8 != 0: the general kernel (the large-tile epilogue stores whole 16-byte pieces)
-                                      ((1024, 776, 640), 784)])     # large-tile kernel, vector stores, ragged N
+@pytest.mark.parametrize("shape,ld", [((70, 52, 192), 64),          # 32 x 32 tiles
+                                      ((600, 1000, 512), 1004),     # ... rows of the output not in whole 16-byte pieces
+                                      ((1024, 776, 640), 784)])     # 64 x 64 tiles, ragged N
 def test_fp32_accumulate_and_padded_output(oracle, shape, ld):
     M, N, K = shape
     rng = np.random.default_rng(9)
@@ -270,8 +279,8 @@ def test_split_k_tiles(oracle, shape):
         assert_close(bf16_out_to_f64(out), ref, na, nb, True, f"{shape} bf16")
 
 
-@pytest.mark.parametrize("shape", [(2049, 264, 512),       # 128 x 256 tiles: rows and columns over the edge of a tile
-                                   (1032, 2056, 640)])     # ... most tiles inside
+@pytest.mark.parametrize("shape", [(2049, 264, 512),       # 64 x 64 tiles: rows and columns over the edge of a tile
+                                   (1032, 2056, 640)])     # 128 x 256 tiles, an odd number of stages
 def test_accumulate_in_the_large_tiles(oracle, shape):
     M, N, K = shape
     rng = np.random.default_rng(M + N + K)
@@ -295,3 +304,123 @@ def test_accumulate_in_the_large_tiles(oracle, shape):
 def test_wide_tiles_where_k_ends_inside_a_stage(oracle):
     # 128 x 192 tiles: rows and columns over the edge, N % 4 != 0, with exponents of b in two pieces
     test_split_k_tiles(oracle, (2050, 2042, 4128))
+
+
+EDGES = [(16, 16, 32), (1, 1, 32), (5, 3, 64), (128, 128, 128), (200, 136, 96), (257, 129, 416), (130, 260, 1024), (64, 512, 160)]
+
+
+def odd_address(a):
+    """the array on the GPU, one byte behind an aligned address"""
+    buf = torch.zeros(a.size + 16, dtype=torch.uint8, device="cuda:0")
+    t = buf[1:1 + a.size].view(a.shape)
+    t.copy_(torch.from_numpy(a))
+    return t
+
+
+@pytest.mark.parametrize("shape", EDGES + [(70, 52, 192), (300, 263, 672)])
+@pytest.mark.parametrize("both", [True, False])
+def test_general_kernel_at_the_edges_of_its_tiles(oracle, shape, both):
+    # exponents that are not dword aligned go to the general kernel whatever the size
+    M, N, K = shape
+    rng = np.random.default_rng(M * 5 + N * 3 + K)
+    a, b = finite_codes(rng, (M, K)), finite_codes(rng, (N, K))
+    ae = rng.integers(100, 128, size=(M, K // 32), dtype=np.uint8)
+    be = rng.integers(100, 128, size=(N, K // 32), dtype=np.uint8) if both else None
+    a_s, b_s = np.float32(0.013), np.float32(1.7)
+    ref = oracle.gemm(a, ae, a_s, b, be, b_s)
+    na, nb = oracle.row_norms(a, ae, a_s), oracle.row_norms(b, be, b_s)
+    ops = (to_gpu(a), odd_address(ae), to_gpu(np.array([a_s])), to_gpu(b), odd_address(be) if both else None, to_gpu(np.array([b_s])))
+    base = rng.standard_normal((M, N + 5)).astype(np.float32)
+    buf = to_gpu(base)
+    moss.gemm_fp8_mx(*ops, out=buf[:, :N], accumulate=True)
+    plain = moss.gemm_fp8_mx(*ops, out_dtype=torch.float32)
+    half = moss.gemm_fp8_mx(*ops, out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    assert_close(plain.cpu().numpy().astype(np.float64), ref, na, nb, False, f"general {shape} f32")
+    assert_close(bf16_out_to_f64(half), ref, na, nb, True, f"general {shape} bf16")
+    res = buf.cpu().numpy()
+    assert np.array_equal(res[:, N:], base[:, N:])
+    assert np.array_equal(res[:, :N], base[:, :N] + plain.cpu().numpy())      # one FP32 addition per output
+
+
+def check_outputs(oracle, tag, outs, oa, ob, rng):
+    """Outputs against the oracle: all of them for small problems; for large ones the rows and columns on both sides of the
+    edges of tiles (32 .. 256), the last ones, and the random sample of check_sampled."""
+    (aq, ae, a_s), (bq, be, b_s) = oa, ob
+    M, N = aq.shape[0], bq.shape[0]
+    if M * N * aq.shape[1] <= 2 * 10 ** 9:
+        ref = oracle.gemm(aq, ae, a_s, bq, be, b_s)
+        na, nb = oracle.row_norms(aq, ae, a_s), oracle.row_norms(bq, be, b_s)
+        for out in outs:
+            assert_close(out.float().cpu().numpy().astype(np.float64), ref, na, nb, out.dtype == torch.bfloat16, tag)
+        return
+    edges = lambda n: sorted({i for i in (0, 31, 32, 63, 64, 127, 128, 191, 192, 255, 256, n - 2, n - 1) if 0 <= i < n})
+    ms = np.concatenate([np.full(N, r) for r in edges(M)] + [np.arange(M)] * len(edges(N)))
+    ns = np.concatenate([np.arange(N)] * len(edges(M)) + [np.full(M, c) for c in edges(N)])
+    more = sampled_pairs(rng, M, N, n_rows=4, n_cols=4, n_rand=65536)
+    ms, ns = np.concatenate([ms, more[0]]).astype(np.int64), np.concatenate([ns, more[1]]).astype(np.int64)
+    ref = oracle.gemm_sampled(aq, ae, a_s, bq, be, b_s, ms, ns)
+    na, nb = oracle.row_norms(aq, ae, a_s)[ms], oracle.row_norms(bq, be, b_s)[ns]
+    for out in outs:
+        got = out[torch.from_numpy(ms).to(out.device), torch.from_numpy(ns).to(out.device)]
+        assert_close(got.float().cpu().numpy().astype(np.float64), ref, na, nb, out.dtype == torch.bfloat16, tag)
+
+
+# (shape, exponents of b, tile): what the dispatch chooses, with sizes that go over the edges of that tile
+CHOSEN = [((2100, 2050, 64), True, 0),              # general: many tiles, short K
+          ((4104, 4100, 512), True, 0),             # ... N % 8 != 0 bars the large tiles
+          ((4104, 4100, 512), False, 0),
+          ((33, 95, 1056), True, 32032),            # K ends inside a stage, with exponents of b
+          ((65, 70, 288), True, 32032),
+          ((700, 2050, 512), True, 64128),          # whole stages, N % 4 != 0
+          ((700, 2050, 512), False, 64128),
+          ((600, 1400, 160), True, 64064),          # two stages for four K groups
+          ((601, 4098, 4128), True, 128128),        # exponents of 33 stages in two pieces, four slots
+          ((2005, 2436, 3584), False, 128192),      # whole stages
+          ((1341, 4234, 1184), True, 128192),       # K ends inside a stage
+          ((2050, 2042, 4128), True, 128192),       # ... exponents in two pieces, accumulating as well
+          ((2049, 2056, 512), True, 128256),        # the shortest K of the large tiles, one row and eight columns over
+          ((2049, 2056, 512), False, 128256),
+          ((1544, 3080, 640), True, 128256),        # an odd number of stages
+          ((4097, 4104, 512), True, 256256),
+          ((4097, 4104, 512), False, 256256),
+          ((2060, 4104, 640), False, 256256)]
+
+
+@pytest.mark.parametrize("shape,both,tile", CHOSEN)
+def test_every_kernel_of_the_dispatch(oracle, shape, both, tile):
+    """FP32 and BF16 outputs with rows of N + 8, overwritten and (FP32) accumulated into."""
+    M, N, K = shape
+    print(f"[gemm dispatch] {shape} both={both}: tile {tile}", flush=True)
+    rng = np.random.default_rng(M + N + K)
+    a, b = finite_codes(rng, (M, K)), finite_codes(rng, (N, K))
+    ae = rng.integers(110, 128, size=(M, K // 32), dtype=np.uint8)
+    be = rng.integers(110, 128, size=(N, K // 32), dtype=np.uint8) if both else None
+    assert tile_of(M, N, K, ae, be, N + 8) == tile
+    a_s, b_s = np.float32(0.5), np.float32(0.25)
+    ops = (to_gpu(a), to_gpu(ae), to_gpu(np.array([a_s])), to_gpu(b), to_gpu(be) if both else None, to_gpu(np.array([b_s])))
+    half = torch.full((M, N + 8), 3.0, dtype=torch.bfloat16, device="cuda:0")
+    moss.gemm_fp8_mx(*ops, out=half[:, :N])
+    plain = torch.full((M, N + 8), 3.0, dtype=torch.float32, device="cuda:0")
+    moss.gemm_fp8_mx(*ops, out=plain[:, :N])
+    torch.cuda.synchronize()
+    assert bool((half[:, N:] == 3.0).all()) and bool((plain[:, N:] == 3.0).all())
+    check_outputs(oracle, f"{shape} tile {tile}", (plain[:, :N], half[:, :N]), (a, ae, a_s), (b, be, b_s), rng)
+    if tile_of(M, N, K, ae, be, N + 8, accumulate=True) == tile:
+        base = torch.from_numpy(rng.standard_normal((M, N + 8)).astype(np.float32)).to("cuda:0")
+        out = base.clone()
+        moss.gemm_fp8_mx(*ops, out=out[:, :N], accumulate=True)
+        torch.cuda.synchronize()
+        assert torch.equal(out[:, N:], base[:, N:])
+        assert torch.equal(out[:, :N], base[:, :N] + plain[:, :N])            # one FP32 addition per output
+
+
+@pytest.mark.parametrize("shape,tile", [((1341, 4234, 2944), 128192), ((4097, 4104, 512), 0), ((27, 512, 32), 32032)])
+def test_dispatch_without_exponents_of_a(oracle, shape, tile):
+    M, N, K = shape
+    assert tile_of(M, N, K, None, None) == tile
+    rng = np.random.default_rng(M + N + K)
+    a, b = finite_codes(rng, (M, K)), finite_codes(rng, (N, K))
+    a_s, b_s = np.float32(0.5), np.float32(0.25)
+    out = gpu_gemm(a, None, a_s, b, None, b_s, out_dtype=torch.float32)
+    check_outputs(oracle, f"{shape} without exponents", (out,), (a, None, a_s), (b, None, b_s), rng)

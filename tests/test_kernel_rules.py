@@ -87,3 +87,22 @@ def test_gemm_without_exponents_of_a(L, M, N, K, tile):
 def test_gemm_that_accumulates(L, M, N, K, plain, accumulating):
     assert ask(L.moss_internal_gemm_tile, M, N, K, 1, 1, N, 0) == plain
     assert ask(L.moss_internal_gemm_tile, M, N, K, 1, 1, N, 1) == accumulating
+
+
+# what the GPU tests of the GEMM say about the kernel that a shape takes
+def test_gemm_tests_reach_the_kernels_they_name(L):
+    from test_gpu_gemm import CHOSEN
+    for (M, N, K), both, tile in CHOSEN:
+        assert ask(L.moss_internal_gemm_tile, M, N, K, 1, both, N + 8, 0) == tile, (M, N, K, both)
+    tiles = {t for _, _, t in CHOSEN}
+    assert tiles == {0, 32032, 64064, 64128, 128128, 128192, 128256, 256256}
+    accumulating = {ask(L.moss_internal_gemm_tile, M, N, K, 1, both, N + 8, 1) for (M, N, K), both, _ in CHOSEN}
+    assert accumulating == tiles
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(33, 95, 160, 32032), (40, 60, 8224, 32032), (501, 2047, 1056, 64064), (500, 2000, 8224, 64064),
+                                        (512, 4000, 1056, 64128), (700, 2048, 4096, 64128), (1000, 4000, 1056, 128128),
+                                        (2050, 2042, 4128, 128192), (4349, 4096, 512, 256256), (1032, 2056, 640, 128256)])
+def test_gemm_tests_of_one_kernel_each(L, M, N, K, tile):
+    for b_e in (0, 1):
+        assert ask(L.moss_internal_gemm_tile, M, N, K, 1, b_e, N, 0) == tile
