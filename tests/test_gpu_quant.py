@@ -132,6 +132,21 @@ def test_adversarial_blocks_inside_full_tiles_two_launch_path(oracle, flag):
     check_against_oracle(oracle, with_adversarial_blocks(384, 800, 52, scale=300.0), flag, "adversarial blocks, large maximum")
 
 
+# (Small tensors are quantized in one launch: these are above its limits, so that the launch that leaves partial maxima runs.)
+@pytest.mark.parametrize("name", ["zeros", "zero_groups", "one_outlier", "signed_zeros", "tiny", "tiny_zero_groups",
+                                  "subnormal", "tiny_groups_under_large_max", "big", "sqrt2_boundary", "wide_range"])
+def test_adversarial_tensors_two_launch_path(oracle, name):
+    xb = np.tile(mi.adversarial_activations(64, 128)[name], (9, 3))
+    for flag in (0, CEIL):
+        check_against_oracle(oracle, xb, flag, f"{name}, two launches")
+
+
+@pytest.mark.parametrize("rows,cols,ld", [(544, 288, 384), (161, 1056, 1120), (96, 2080, 2088)])
+@pytest.mark.parametrize("flag", [0, CEIL])
+def test_strided_tensors_two_launch_path(oracle, rows, cols, ld, flag):
+    test_small_tensors_where_every_workgroup_looks_for_the_maximum(oracle, rows, cols, ld, flag)
+
+
 def test_tensor_with_a_subnormal_maximum_in_full_tiles(oracle):
     rng = np.random.default_rng(53)
     xb = mi.f32_to_bf16_bits((rng.standard_normal((256, 384)) * 2.0 ** -129).astype(np.float32))
@@ -215,16 +230,17 @@ def test_one_launch_path_on_a_strided_view(oracle):
     check_against_oracle(oracle, xb, 0, "one-launch strided view", x_dev=x_view)
 
 
-def test_outputs_are_written_exactly_once_into_caller_buffers(oracle):
+@pytest.mark.parametrize("rows,cols", [(96, 160), (288, 480)])       # one launch, two launches
+def test_outputs_are_written_exactly_once_into_caller_buffers(oracle, rows, cols):
     # poison the output buffers: every byte must be overwritten, nothing beyond them touched
-    xb = mi.heavy_tailed_activation(96, 160, seed=33)
+    xb = mi.heavy_tailed_activation(rows, cols, seed=33)
     x = bf16_to_gpu(xb)
     d = x.device
     pad = 64
     bufs = {k: torch.full((n + 2 * pad,), 0xAB, dtype=torch.uint8, device=d)
-            for k, n in dict(q_row=96 * 160, e_row=96 * 5, q_col=96 * 160, e_col=160 * 3).items()}
-    out = dict(q_row=bufs["q_row"][pad:-pad].view(96, 160), e_row=bufs["e_row"][pad:-pad].view(96, 5),
-               q_col=bufs["q_col"][pad:-pad].view(160, 96), e_col=bufs["e_col"][pad:-pad].view(160, 3))
+            for k, n in dict(q_row=rows * cols, e_row=rows * cols // 32, q_col=rows * cols, e_col=rows * cols // 32).items()}
+    out = dict(q_row=bufs["q_row"][pad:-pad].view(rows, cols), e_row=bufs["e_row"][pad:-pad].view(rows, cols // 32),
+               q_col=bufs["q_col"][pad:-pad].view(cols, rows), e_col=bufs["e_col"][pad:-pad].view(cols, rows // 32))
     got = moss.quant_act_2level(x, ROW | COL, out=out)
     torch.cuda.synchronize()
     qr, er, s = oracle.quant_act_2level(xb, 0, 0)
