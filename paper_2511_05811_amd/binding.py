@@ -98,7 +98,10 @@ def _stream():
     import torch
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:      # a torch without these internal names
+        return torch.cuda.current_stream().cuda_stream
 
 
 def device_cu_count():

@@ -145,3 +145,15 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(binding, "_LIB_PATH", "/nonexistent/libmoss_hip.so")
     with pytest.raises(moss.MossError):
         binding.load()
+
+
+def test_stream_handle_without_the_internal_names_of_torch(monkeypatch):
+    import types
+
+    import torch
+    from paper_2511_05811_amd import binding
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1234))
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.delattr(torch._C, "_cuda_getDevice", raising=False)
+    assert binding._stream() == 0x1234
