@@ -226,25 +226,25 @@ int rows_grid(int64_t rows)
     return (int)(rows < cap ? rows : cap);
 }
 
-// Look at the word before merging into it (merge_max_word): in wide rows from 3.5 rows per compute unit on, in narrow ones from 6.
-// The look costs every workgroup a trip and saves the queue behind it only if the ends of the workgroups are spread, so that
-// around the line it helps or hurts by which of them happen to end together.  Forward / backward alone, us, without and with,
-// means over eight inputs:
-//     256 x 4096  8.5 / 8.7 and  8.6 / 9.5      768 x 8192 17.6 / 15.0 and 18.7 / 22.2    1000 x 4096 18.1 / 13.7 and 18.7 / 19.4
-//    1200 x 8192 24.2 / 20.9 and 24.1 / 22.8   1400 x 4096 19.9 / 26.4 and 20.2 / 17.6    3072 x 4096 27.9 / 27.1 and 28.1 / 26.3
-//    1200 x 2048 17.7 / 18.9 and 17.8 / 13.1   1200 x 1024 17.1 / 21.5 and 17.2 / 21.1    1536 x 1024 17.5 / 14.7 and 17.5 / 16.1
-bool looks(int64_t rows, int64_t cols, bool backward)
+// Look at the word before merging into it (merge_max_word): from 4.5 rows per compute unit on, in rows of 1024 and more from
+// 2.5.  The look costs every workgroup a trip and saves the queue behind it only if the ends of the workgroups are spread; near
+// the line it helps or hurts by which of them happen to end together.  Forward and backward with their quantizers, inputs that
+// no cache holds, us, without and with, means over three inputs:
+//      32 x 4096 24.3 / 24.7    256 x 2048 28.1 / 28.8    512 x 2048 36.0 / 37.9     768 x 256 41.5 / 46.0    1024 x 256  47.7 / 50.1
+//     640 x 1024 41.6 / 38.4    768 x 2048 46.8 / 44.3    768 x 8192 57.7 / 58.7     896 x 4096 54.1 / 49.5   1152 x 256  47.9 / 48.4
+//    1248 x 416  50.8 / 47.6   1248 x 4096 61.0 / 53.1   1536 x 4096 64.0 / 71.1    2048 x 4096 70.4 / 66.9   8192 x 4096 150.5 / 143.9
+bool looks(int64_t rows, int64_t cols)
 {
     int64_t cus = moss_internal_cu_count();
     if (cus <= 0) cus = 256;
-    return 2 * rows >= (cols >= (backward ? 2048 : 4096) ? 7 : 12) * cus;
+    return 2 * rows >= (cols >= 1024 ? 5 : 9) * cus;
 }
 
 }  // namespace
 }  // namespace moss
 
 // what the two entry points below choose for a tensor (the tests hold the rule by it)
-extern "C" int moss_internal_rmsnorm_looks(int64_t rows, int64_t cols, int64_t backward) { return moss::looks(rows, cols, backward != 0); }
+extern "C" int moss_internal_rmsnorm_looks(int64_t rows, int64_t cols) { return moss::looks(rows, cols); }
 
 extern "C" int moss_add_rmsnorm_bf16(const void *x, const void *delta, const void *gamma, float eps, int64_t rows, int64_t cols,
                                      int64_t ld, void *h_out, void *y, uint32_t *y_absmax_bits, void *stream)
@@ -258,7 +258,7 @@ extern "C" int moss_add_rmsnorm_bf16(const void *x, const void *delta, const voi
     hipStream_t st = (hipStream_t)stream;
     const int cpr = (int)(cols / 8), chunks = (cpr + kRnThreads - 1) / kRnThreads;
     const float inv_cols = 1.0f / (float)cols;
-    const int flags = producer_flags(rows, cols, looks(rows, cols, false));
+    const int flags = producer_flags(rows, cols, looks(rows, cols));
     const dim3 grid(rows_grid(rows)), block(kRnThreads);
     hipLaunchKernelGGL(k_rmsnorm_clear, dim3(1), dim3(64), 0, st, y_absmax_bits);
     MOSS_LAUNCH_CHECK();
@@ -288,7 +288,7 @@ extern "C" int moss_rmsnorm_bf16_backward(const void *h, const void *gamma, cons
     hipStream_t st = (hipStream_t)stream;
     const int cpr = (int)(cols / 8), chunks = (cpr + kRnThreads - 1) / kRnThreads;
     const float inv_cols = 1.0f / (float)cols;
-    const int flags = producer_flags(rows, cols, looks(rows, cols, true));
+    const int flags = producer_flags(rows, cols, looks(rows, cols));
     const dim3 grid(rows_grid(rows)), block(kRnThreads);
     hipLaunchKernelGGL(k_rmsnorm_clear, dim3(1), dim3(64), 0, st, d_h_absmax_bits);
     MOSS_LAUNCH_CHECK();
