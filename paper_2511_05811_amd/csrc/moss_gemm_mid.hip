@@ -424,8 +424,8 @@ static int launch_mid(MidArgs p, int budget, hipStream_t st)
 // two dwords, so that a stage costs more (more so with exponents of b).  128 x 192 tiles read a third less per product than
 // 128 x 128 but leave no LDS for a fourth slot: they pay where the large tiles cannot take the problem.  "b" marks exponents of b.
 //   tile        (M, N, K) measured / model
-//   32 x 32     (64, 4096, 4096) 9.9 / 7.7     (17, 11008, 4096) 12.4 / 9.3     (256, 1024, 1024) 5.3 / 4.9    (300, 1000, 2080) 8.0 / 8.4
-//               (64, 256, 512) 4.4 / 4.4       (512, 256, 64) b 5.7 / 5.3
+//   32 x 32     (64, 4096, 4096) 9.9 / 7.7     (17, 11008, 4096) 12.4 / 10.7    (256, 1024, 1024) 5.3 / 4.9    (300, 1000, 2080) 8.0 / 8.4
+//               (64, 256, 512) 4.4 / 4.4       (512, 256, 64) b 5.7 / 5.3     (512, 4096, 4096) 39 / 43       (9412, 144, 5504) 46 / 42
 //   64 x 64     (256, 4096, 4096) 16.0 / 13.0  (1024, 1024, 1024) 8.5 / 7.4     (600, 4096, 4128) 46 / 46      (2048, 2048, 2080) b 54 / 52
 //   64 x 128    (512, 4096, 4096) 21.3 / 17.0  (512, 4096, 1024) 10.4 / 8.8     (2048, 2048, 4096) 39 / 32     (8192, 2080, 4128) 200 / 198
 //               (3072, 3072, 4128) b 149 / 144
@@ -460,7 +460,9 @@ MidPlan plan_mid(int64_t M, int64_t N, int64_t K, bool b_exponents, bool accumul
                  n3 = rounds_of(tiles_of(M, N, 128, 128), cus), n4 = rounds_of(tiles_of(M, N, 128, 192), cus);
     const double r01 = !ragged ? 1.0 : (b_exponents ? 1.85 : 1.33), r2 = !ragged ? 1.0 : (b_exponents ? 2.03 : 1.54),
                  r3 = !ragged ? 1.0 : (b_exponents ? 1.2 : 1.14);
-    const double us[5] = {t0 <= cus ? 3.9 + extra + 0.48 * r01 * it4 : 2.2 + n0 * (0.9 + extra + 0.33 * r01 * it4),
+    // (two 32 x 32 workgroups fit a compute unit: a round that is half full costs less than a full one)
+    const double s0 = (ragged ? (b_exponents ? 0.34 : 0.24) : (b_exponents ? 0.24 : 0.2)) + (b_exponents && !ragged ? 0.32 : 0.34) * t0 / (n0 * cus);
+    const double us[5] = {t0 <= cus ? 3.9 + extra + 0.48 * r01 * it4 : 2.2 + n0 * ((b_exponents ? 1.25 : 0.8) + s0 * it4),
                           2.2 + n1 * (3.3 + extra + 0.94 * r01 * it4),
                           2.2 + n2 * (3.9 + 2.0 * extra + 0.68 * r2 * it2),
                           2.2 + n3 * (8.0 + (ragged ? 6.0 : 3.0) * extra + 0.63 * r3 * C),
@@ -493,7 +495,7 @@ double us_general(int64_t M, int64_t N, int64_t K, bool b_exponents, double cus)
 
 // The kind of tiles (0 .. 4) if one is expected to be at least a tenth faster than the kernel that would have the problem
 // otherwise (large_ok: k_gemm_mx_big, else k_gemm), -1 to leave it to that one.  With the tenth in hand, 2 of the 2300 problems
-// take longer than there, by 4 %; without it 11, by up to 20 %.
+// take longer than there, by 4 % (without it 11, by up to 20 %), and of 5000 others seven by 6 to 14 %.
 int moss_internal_gemm_mid_kind(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int accumulate,
                                 bool large_ok)
 {

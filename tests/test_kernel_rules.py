@@ -63,6 +63,7 @@ def test_every_workgroup_looks_for_the_maximum_of_a_small_tensor_only(L, rows, c
 @pytest.mark.parametrize("M,N,K,b_e,tile", [(64, 256, 512, 0, 32032), (17, 11008, 4096, 0, 32032), (512, 256, 64, 1, 32032),
                                             (256, 512, 64, 1, 32032), (256, 4096, 4096, 0, 64064), (1024, 1024, 1024, 0, 64064),
                                             (512, 4096, 4096, 0, 64128), (512, 4096, 1024, 0, 64128),
+                                            (9412, 144, 5504, 0, 64064), (2809, 256, 1216, 0, 64064), (64, 4224, 4864, 1, 32032),
                                             (600, 4096, 4128, 0, 128128), (600, 4096, 4128, 1, 128128), (1000, 4000, 1056, 1, 128128),
                                             (2048, 2048, 2080, 1, 128128), (1333, 4096, 4128, 0, 128192), (8192, 2080, 4128, 0, 128192),
                                             (3072, 3072, 4128, 1, 128192), (2005, 2436, 3584, 0, 128192),
