@@ -194,11 +194,15 @@ int grid_for(int64_t n_chunks)
     return (int)(want < cap ? want : cap);
 }
 
-// Look at the word before merging into it (merge_max_word) from 512 workgroups on.  Forward / backward (two words) alone, us,
+// Look at the word before merging into it (merge_max_word) from 384 workgroups on.  Forward / backward (two words) alone, us,
 // without and with the look, by the number of workgroups:
-//     1 .. 63       5.2 / 6.0 and 5.4 / 6.6        64 .. 255   7.2 / 8.1 and 9.2 / 10.7
-//   256 .. 511     10.1 / 11.8 and 15.0 / 15.9    512 .. 1023  15.6 / 13.8 and 27.6 / 20.9       (2048: 41.4 / 34.9 and 80.3 / 61.6)
-bool looks(int grid) { return grid >= 512; }
+//     1 .. 63     5.2 / 6.0 and 5.4 / 6.6      64 .. 255   7.2 / 8.1 and 9.2 / 10.7
+//   260           9.1 / 11.1 and 13.4 / 14.7     383      10.7 / 11.8 and 15.9 / 15.8
+//   420          11.2 / 11.6 and 16.9 / 15.5     500      12.4 / 11.4 and 19.3 / 13.6
+//   512 .. 1023  15.6 / 13.8 and 27.6 / 20.9     2048     41.4 / 34.9 and 80.3 / 61.6
+// and with the quantizers behind, on inputs that no cache holds: 256 workgroups (1024 x 2048) 51.0 / 51.8, 344 (256 x 11008)
+// 51.7 / 52.3, 512 (2048 x 2048) 64.1 / 60.0, 1024 (4096 x 2048) 88.9 / 74.4.
+bool looks(int grid) { return grid >= 384; }
 
 }  // namespace
 }  // namespace moss

@@ -63,31 +63,37 @@ def test_swiglu_forward_and_backward(oracle, shape):
     assert int(dumax.item()) == int((dub & 0x7FFF).max())
 
 
-@pytest.mark.parametrize("shape", [(511, 8192), (512, 8200)])
-def test_swiglu_on_both_sides_of_the_look_before_the_merge(oracle, shape):
-    test_swiglu_forward_and_backward(oracle, shape)
-
-
 @pytest.mark.parametrize("shape", [(3, 43688), (128, 1024), (257, 1032), (129, 4064), (64, 8192)])
 def test_swiglu_with_one_two_and_four_chunks_per_thread(oracle, shape):
     # 2^14 and 2^16 chunks are the first tensors with two and four; below and above them, with trips that are not full
     test_swiglu_forward_and_backward(oracle, shape)
 
 
-def test_swiglu_of_more_than_32_mib_equals_its_parts():
-    # above 2^24 elements the outputs are stored through the caches: the same bits as in two parts below that
-    g, u, d = (bf16_to_gpu(a) for a in make_inputs(2049, 8200, 5))
+def equals_its_parts(rows, cols, cut):
+    # the same bits as in two parts, which take other forms.  (A gate below -88.7, which the oracle's tests do not reach,
+    # overflows the exponential in FP32: those outputs, of less than 1e-35, are zero, and alike here.)
+    g, u, d = (bf16_to_gpu(a) for a in make_inputs(rows, cols, 5))
     h, hmax = moss.swiglu_bf16(g, u)
     dg, du, dgmax, dumax = moss.swiglu_bf16_backward(g, u, d)
     tops = [0, 0, 0]
-    for rows in (slice(0, 1000), slice(1000, 2049)):
-        ph, pm = moss.swiglu_bf16(g[rows], u[rows])
-        pg, pu, pgm, pum = moss.swiglu_bf16_backward(g[rows], u[rows], d[rows])
+    for part_rows in (slice(0, cut), slice(cut, rows)):
+        ph, pm = moss.swiglu_bf16(g[part_rows], u[part_rows])
+        pg, pu, pgm, pum = moss.swiglu_bf16_backward(g[part_rows], u[part_rows], d[part_rows])
         torch.cuda.synchronize()
         for whole, part in ((h, ph), (dg, pg), (du, pu)):
-            assert np.array_equal(bits_of(whole[rows]), bits_of(part))
+            assert np.array_equal(bits_of(whole[part_rows]), bits_of(part))
         tops = [max(a, int(b.item())) for a, b in zip(tops, (pm, pgm, pum))]
     assert tops == [int(t.item()) for t in (hmax, dgmax, dumax)]
+
+
+def test_swiglu_of_more_than_32_mib_equals_its_parts():
+    equals_its_parts(2049, 8200, 1000)         # above 2^24 elements the outputs are stored through the caches
+
+
+@pytest.mark.parametrize("rows,cols,cut", [(383, 8192, 100),     # the largest tensor whose workgroups merge without a look, ...
+                                           (384, 8200, 20)])     # ... and one whose workgroups look first
+def test_swiglu_on_both_sides_of_the_look_equals_its_parts(rows, cols, cut):
+    equals_its_parts(rows, cols, cut)
 
 
 def test_swiglu_on_a_strided_view_and_zero_tensor(oracle):

@@ -20,7 +20,7 @@ def ask(fn, *args):
     return fn(*(C.c_int64(a) for a in args))
 
 
-@pytest.mark.parametrize("rows,cols,looks", [(1, 8, 0), (30, 1856, 0), (1024, 2056, 0), (511, 8192, 0), (512, 8192, 1),
+@pytest.mark.parametrize("rows,cols,looks", [(1, 8, 0), (30, 1856, 0), (1024, 2056, 0), (383, 8192, 0), (384, 8192, 1),
                                              (1024, 11008, 1), (8192, 11008, 1)])
 def test_swiglu_looks_before_it_merges_only_where_the_queue_of_atomics_is_longer(L, rows, cols, looks):
     assert ask(L.moss_internal_swiglu_looks, rows, cols) == looks
