@@ -446,17 +446,21 @@ static int grid_for(int64_t n4)
 // cast on up to one workgroup per compute unit.  Step alone, buffers that no cache holds, us, one vector and four:
 //   0.25M elements 10.2 and 9.7 (re-base 15.2, 15.6)    0.75M 11.2 and 10.7 (16.7, 16.9)    1.5M 13.7 and 15.1 (20.0, 22.3)
 //   2M 15.8 and 16.3    6M 40.0 and 41.5 (BF16 gradients 37.5, 40.0)    8M 52.0 and 51.7    12M 76.6 and 72.5    64M 401 and 361
-// The re-basing pass is followed by a cast of the same weights over the grid-wide stride, which finds them in the L2 of the XCD
-// that wrote them only if both passes give a vector to the same workgroup, as with one vector (64K elements 13.2, 14.5); few
-// workgroups are bound by the latency of their code, which is shorter with one.
+// What reads the result next finds it in the L2 of the XCD that wrote it only if both give a vector to the same workgroup.  The
+// cast behind a re-basing pass walks the grid-wide stride, as the pass does with one vector (64K elements 13.2, 14.5); the byte
+// transpose behind a step (heights that the tile kernel does not take) walks 64 x 64 tiles, of which a workgroup of four writes
+// whole ones if rows are narrow (1038 x 64 18.2, 13.4; 427 x 192 17.0, 15.3; wider than 256 0.4 us more with four).  Otherwise
+// fewer than 32 workgroups are bound by the latency of their code, which is shorter with one.
 constexpr int kStepBatch = 4;
 
-static int step_batch(int64_t n4, int grid, bool cast)
+enum StepNext { kNextNothing, kNextCast, kNextNarrowTranspose };
+
+static int step_batch(int64_t n4, int grid, StepNext next)
 {
     if (n4 >= 2 * (int64_t)kWMaxBlocks * kWThreads) return kStepBatch;
     int cus = moss_internal_cu_count();
     if (cus <= 0) cus = 256;
-    return cast && grid >= 32 && grid <= cus ? kStepBatch : 1;
+    return next != kNextCast && grid <= cus && (grid >= 32 || next == kNextNarrowTranspose) ? kStepBatch : 1;
 }
 
 static int launch_transpose(const uint8_t *src, int64_t rows, int64_t cols, uint8_t *dst, hipStream_t st)
@@ -535,9 +539,9 @@ static int finalize(const WLaunch &L, int n_partial, int mode, double lr_term, i
 
 template <bool CAST>
 static void launch_flat(const WLaunch &L, bool grad_bf16, float *w, float *m, float *v, const void *g, const AdamW &a, double lr_term,
-                        uint8_t *wq)
+                        uint8_t *wq, StepNext next)
 {
-    const auto kern = step_batch(L.n4, L.grid1d, CAST) == 1
+    const auto kern = step_batch(L.n4, L.grid1d, next) == 1
                           ? (grad_bf16 ? k_adamw_cast<true, CAST, 1> : k_adamw_cast<false, CAST, 1>)
                           : (grad_bf16 ? k_adamw_cast<true, CAST, kStepBatch> : k_adamw_cast<false, CAST, kStepBatch>);
     hipLaunchKernelGGL(kern, dim3(L.grid1d), dim3(kWThreads), 0, L.st, w, m, v, g, L.n4, a, lr_term, L.state, wq, L.ws, L.slots);
@@ -600,9 +604,9 @@ static int make_launch(WLaunch &L, int64_t rows, int64_t cols, moss_wscale_state
 // what the launches below choose (the tests hold the rules by it)
 extern "C" int moss_internal_weight_fold_threads(int64_t n_partial) { return moss::fold_threads((int)n_partial); }
 
-extern "C" int moss_internal_weight_step_batch(int64_t rows, int64_t cols, int64_t cast)
+extern "C" int moss_internal_weight_step_batch(int64_t rows, int64_t cols, int64_t next)
 {
-    return moss::step_batch(rows * cols / 4, moss::grid_for(rows * cols / 4), cast != 0);
+    return moss::step_batch(rows * cols / 4, moss::grid_for(rows * cols / 4), (moss::StepNext)next);
 }
 
 extern "C" int moss_weight_autoscale_init(const void *w, int w_dtype, int64_t rows, int64_t cols,
@@ -651,7 +655,7 @@ extern "C" int moss_weight_autoscale_cast(float *w, float *m, float *v, const vo
 
     if (rebase) {
         // AdamW alone (it yields amax(W_new)), re-base the scale from it, then cast with the new scale
-        launch_flat<false>(L, gb, w, m, v, g, a, lr_term, wq);
+        launch_flat<false>(L, gb, w, m, v, g, a, lr_term, wq, kNextCast);
         MOSS_LAUNCH_CHECK();
         if ((rc = finalize(L, L.grid1d, kFinRebase, lr_term, args->step))) return rc;
         return cast_only(L, w, false, wq, wq_t);
@@ -661,7 +665,7 @@ extern "C" int moss_weight_autoscale_cast(float *w, float *m, float *v, const vo
         MOSS_LAUNCH_CHECK();
         return finalize(L, (int)(L.grid2d.x * L.grid2d.y), kFinStep, lr_term, args->step);
     }
-    launch_flat<true>(L, gb, w, m, v, g, a, lr_term, wq);
+    launch_flat<true>(L, gb, w, m, v, g, a, lr_term, wq, wq_t && cols <= 256 ? kNextNarrowTranspose : kNextNothing);
     MOSS_LAUNCH_CHECK();
     if ((rc = finalize(L, L.grid1d, kFinStep, lr_term, args->step))) return rc;
     if (wq_t) return launch_transpose(wq, rows, cols, wq_t, L.st);

@@ -101,6 +101,12 @@ def test_batches_of_the_flat_step(oracle, rows, cols, bf16_grad):
     run_parity(oracle, rows, cols, 2, seed=11, interval=2, transpose=False, bf16_grad=bf16_grad)
 
 
+@pytest.mark.parametrize("rows,cols", [(45, 96), (1038, 64), (1037, 1028)])     # (rows that the transposing tiles do not take)
+def test_flat_step_with_a_transpose_behind(oracle, rows, cols):
+    print(f"[weight parity] flat with transpose {rows}x{cols}", flush=True)
+    run_parity(oracle, rows, cols, 2, seed=12, interval=2, bf16_grad=True)
+
+
 def test_fold_of_as_many_partials_as_few_threads_take(oracle):
     print("[weight parity] 4096x1024 flat: 1024 partials", flush=True)
     run_parity(oracle, 4096, 1024, 2, seed=10, interval=2, transpose=False)

@@ -43,11 +43,11 @@ def test_few_partials_of_a_weight_are_folded_by_few_threads(L, partials, threads
     assert ask(L.moss_internal_weight_fold_threads, partials) == threads
 
 
-@pytest.mark.parametrize("rows,cols,step,rebase", [(1, 4, 1, 1), (31, 4096, 1, 1), (32, 4096, 4, 1), (256, 4096, 4, 1), (257, 4096, 1, 1),
-                                                   (2047, 4096, 1, 1), (2048, 4096, 4, 4), (11008, 8192, 4, 4)])
-def test_weight_step_takes_vectors_in_batches_where_they_pay(L, rows, cols, step, rebase):
-    assert ask(L.moss_internal_weight_step_batch, rows, cols, 1) == step
-    assert ask(L.moss_internal_weight_step_batch, rows, cols, 0) == rebase
+@pytest.mark.parametrize("rows,cols,step,rebase,transposed", [(1, 4, 1, 1, 4), (31, 4096, 1, 1, 4), (32, 4096, 4, 1, 4), (256, 4096, 4, 1, 4),
+                                                              (257, 4096, 1, 1, 1), (2047, 4096, 1, 1, 1), (2048, 4096, 4, 4, 4),
+                                                              (11008, 8192, 4, 4, 4)])
+def test_weight_step_takes_vectors_in_batches_where_they_pay(L, rows, cols, step, rebase, transposed):
+    assert [ask(L.moss_internal_weight_step_batch, rows, cols, following) for following in (0, 1, 2)] == [step, rebase, transposed]
 
 
 @pytest.mark.parametrize("rows,cols,ld,row,col", [(1, 32, 32, 1, 1), (64, 512, 512, 1, 1), (65, 512, 512, 1, 0), (128, 1024, 1024, 1, 0),
