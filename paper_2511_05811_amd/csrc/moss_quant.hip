@@ -8,12 +8,15 @@
 //
 //  * One launch (k_quant_persist): tensors of up to four 128 x 128 tiles per workgroup of a
 //    co-resident grid stay in registers between the maximum and the codes; X is read once.
-//  * One launch (SCAN forms of the kernels below): small tensors (kScanBytes*), where every workgroup reads the whole
-//    tensor for the maximum by itself.
-//  * Two launches: k_amax_bf16 leaves one partial maximum per workgroup in the workspace, and
+//  * One launch (k_quant_row_meet, k_quant_tile_meet): smaller tensors, a tile or up to 32 chunks per thread, in registers too.
+//  * One launch (SCAN forms of the kernels below): the smallest row groupings, and in captured calls all small tensors
+//    (kScanBytes*): every workgroup reads the whole tensor for the maximum by itself.
+//  * Two launches (above 64 MiB, and in captured calls): k_amax_bf16 leaves one partial maximum per workgroup in the workspace, and
 //    k_quant_row (row groups alone) or k_quant_tile (column groups, or both groupings from one
 //    fetch of X) folds the partials and converts.
 #include <atomic>
+#include <chrono>
+#include <random>
 
 #include "moss_internal.h"
 
@@ -282,9 +285,9 @@ constexpr int64_t kScanBytesRowStrided = 160 * 1024, kScanBytesTileStrided = 48 
 constexpr int kScanThreadsRow = 1024;
 constexpr int kScanUnroll = 8;
 
-template <bool CEIL, int THREADS>
-__device__ __forceinline__ GlobalScale scan_global_scale(const uint16_t *__restrict__ x, int n_chunks, int chunks_per_row, int64_t ld,
-                                                         int dense, uint32_t *red)
+template <int THREADS>
+__device__ __forceinline__ uint32_t scan_max(const uint16_t *__restrict__ x, int n_chunks, int chunks_per_row, int64_t ld, int dense,
+                                             uint32_t *red)
 {
     uint32_t m = 0;
     for (int id0 = threadIdx.x; id0 < n_chunks; id0 += THREADS * kScanUnroll) {
@@ -313,7 +316,68 @@ __device__ __forceinline__ GlobalScale scan_global_scale(const uint16_t *__restr
     __syncthreads();
     m = red[0];
     for (int i = 1; i < THREADS / kWave; i++) m = red[i] > m ? red[i] : m;
-    return make_global_scale<CEIL>(m);
+    return m;
+}
+
+// Meeting in slots: how the workgroups of a co-resident grid agree on the tensor's maximum inside one launch.  Every workgroup
+// leaves one 64-bit word, (number of the call) << 16 | its maximum, in a slot of the workspace, and every workgroup reads
+// all the slots until each holds this call's number: one trip to memory to leave a word, one or two to read the others'.
+// Only relaxed device-scope accesses, no fence (one writes back or invalidates the whole L2 of an XCD, ~60 us here), no
+// atomic that others queue behind, nothing to clear before or after: a word carries its own validity, and the number of a
+// call is never used again (a replay of a captured graph would use it again: captured calls take other paths).  The wait
+// is bounded: a workgroup that does not find a slot filled within poll_limit looks (the grid was not co-resident after all)
+// takes the maximum over X by itself, so every wave ends whatever the scheduler does, with the same outputs.
+constexpr int kMaxSlots = kMaxPartials / 2;      // they lie where the two-launch path has its partial maxima
+constexpr uint32_t kNotMet = ~0u;
+
+// m: this thread's maximum.  Returns the maximum over the grid in every thread, or kNotMet.  red: 2 * THREADS / 64 words.
+template <int THREADS>
+__device__ __forceinline__ uint32_t meet_in_slots(uint64_t *slots, int n, int mine, uint64_t call, uint32_t m, uint32_t poll_limit,
+                                                  uint32_t *red)
+{
+    constexpr int kWaves = THREADS / kWave, kLooks = 4;
+    m = wave_max_u32(m);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (n == 1) {                // nobody to meet
+        for (int i = 0; i < kWaves; i++) m = red[i] > m ? red[i] : m;
+        return m;
+    }
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kWaves; i++) m = red[i] > m ? red[i] : m;
+        __hip_atomic_store(slots + mine, call << 16 | m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    uint32_t top = 0;
+    for (int i0 = threadIdx.x; i0 < n; i0 += THREADS * kLooks) {
+        uint64_t w[kLooks];
+        for (uint32_t polls = 0;; polls++) {
+            bool there = true;
+#pragma unroll
+            for (int u = 0; u < kLooks; u++) {
+                w[u] = call << 16;
+                if (i0 + u * THREADS < n) w[u] = __hip_atomic_load(slots + i0 + u * THREADS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int u = 0; u < kLooks; u++) there = there && (w[u] >> 16) == call;
+            if (there) break;
+            if (polls >= poll_limit) {
+                top = kNotMet;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+#pragma unroll
+        for (int u = 0; u < kLooks; u++) {
+            const uint32_t v = (uint32_t)w[u] & 0xFFFFu;
+            top = v > top ? v : top;
+        }
+    }
+    top = wave_max_u32(top);
+    if ((threadIdx.x & 63) == 0) red[kWaves + (threadIdx.x >> 6)] = top;
+    __syncthreads();
+    top = red[kWaves];
+    for (int i = 1; i < kWaves; i++) top = red[kWaves + i] > top ? red[kWaves + i] : top;
+    return top;
 }
 
 // Row grouping: a group is 64 contiguous bytes = the 16-byte chunks of four
@@ -323,6 +387,47 @@ __device__ __forceinline__ GlobalScale scan_global_scale(const uint16_t *__restr
 constexpr int kRowUnroll = 4;
 constexpr int row_threads(bool scan) { return scan ? kScanThreadsRow : kQuantThreads; }
 constexpr int row_unroll(bool scan) { return scan ? 1 : kRowUnroll; }
+
+// Exponents and codes of N chunks per thread, chunk u being number base + u * stride.
+template <bool CEIL, int N>
+__device__ __forceinline__ void row_convert(const uint4 *raw, int64_t base, int stride, int64_t n_chunks, const GlobalScale &g,
+                                            uint8_t *__restrict__ q, uint8_t *__restrict__ e)
+{
+    float f[N];
+    uint32_t eb[N], gmax[N];
+    uint32_t sub_min = ~0u, min_fb = 255u;
+#pragma unroll
+    for (int u = 0; u < N; u++) {
+        // the four lanes of a quad hold one group; n_chunks % 4 == 0 keeps quads uniform
+        gmax[u] = quad_max_u32(chunk_absmax(raw[u]));
+        sub_min = gmax[u] - 1u < sub_min ? gmax[u] - 1u : sub_min;     // (a zero group wraps to the largest value)
+        fast_group(gmax[u], g, eb[u], f[u], min_fb);
+    }
+    // the integer form does not cover a subnormal tensor or group maximum, nor factors beyond the finite range
+    bool any_wide = false;
+    if (__any(!g.fast || sub_min < 127u || (int)min_fb <= g.wide_at)) {
+        bool wide = false;
+#pragma unroll
+        for (int u = 0; u < N; u++) {
+            const int ex = local_exponent<CEIL>(gmax[u], g);
+            eb[u] = (uint32_t)(ex + 127);
+            f[u] = group_factor(gmax[u], ex, g);
+            wide |= factor_is_wide(f[u]);
+        }
+        any_wide = __any(wide);
+    }
+#pragma unroll
+    for (int u = 0; u < N; u++) {
+        const int64_t id = base + (int64_t)u * stride;
+        // (through the caches, where the GEMM behind it finds them: it takes 69 us at 1333 x 4096 x 11008 instead of 81 behind
+        // streaming stores, which themselves are 1.5 of 15 us faster)
+        const uint2 out = any_wide ? row_codes<false>(raw[u], f[u], eb[u], g.inv_s) : row_codes<true>(raw[u], f[u], eb[u], g.inv_s);
+        if (id < n_chunks) {
+            *reinterpret_cast<uint2 *>(q + id * 8) = out;
+            if ((threadIdx.x & 3) == 0) e[id >> 2] = (uint8_t)eb[u];
+        }
+    }
+}
 
 template <bool CEIL, bool SCAN>
 __global__ __launch_bounds__(row_threads(SCAN)) void k_quant_row(const uint16_t *__restrict__ x, int64_t n_chunks,
@@ -334,7 +439,7 @@ __global__ __launch_bounds__(row_threads(SCAN)) void k_quant_row(const uint16_t 
     constexpr int kThreads = row_threads(SCAN), kUnroll = row_unroll(SCAN);
     __shared__ uint32_t red[kThreads / kWave];
     converter_saturates();
-    const GlobalScale g = SCAN ? scan_global_scale<CEIL, kThreads>(x, (int)n_chunks, chunks_per_row, ld, dense, red)
+    const GlobalScale g = SCAN ? make_global_scale<CEIL>(scan_max<kThreads>(x, (int)n_chunks, chunks_per_row, ld, dense, red))
                                : fold_global_scale<CEIL>(partial, n_partial, red);
     if (blockIdx.x == 0 && threadIdx.x == 0) *s_global = g.s;
 
@@ -355,38 +460,51 @@ __global__ __launch_bounds__(row_threads(SCAN)) void k_quant_row(const uint16_t 
             raw[u] = ld_stream16(x + off);
         }
     }
-    float f[kUnroll];
-    uint32_t eb[kUnroll], gmax[kUnroll];
-    uint32_t sub_min = ~0u, min_fb = 255u;
+    row_convert<CEIL, kUnroll>(raw, base, kThreads, n_chunks, g, q, e);
+}
+
+// Row grouping in one launch: U chunks per thread stay in registers while the workgroups meet.
+template <bool CEIL, int U>
+__global__ __launch_bounds__(kQuantThreads, U > 8 ? 2 : 4) void k_quant_row_meet(const uint16_t *__restrict__ x, int n_chunks,
+                                                                                  int chunks_per_row, int64_t ld, int dense,
+                                                                                  uint64_t *slots, uint64_t call, uint32_t poll_limit,
+                                                                                  uint8_t *__restrict__ q, uint8_t *__restrict__ e,
+                                                                                  float *__restrict__ s_global)
+{
+    __shared__ uint32_t red[2 * kQuantThreads / kWave];
+    converter_saturates();
+    const int base = (int)blockIdx.x * (kQuantThreads * U) + (int)threadIdx.x;
+    uint4 raw[U];
 #pragma unroll
-    for (int u = 0; u < kUnroll; u++) {
-        // the four lanes of a quad hold one group; n_chunks % 4 == 0 keeps quads uniform
-        gmax[u] = quad_max_u32(chunk_absmax(raw[u]));
-        sub_min = gmax[u] - 1u < sub_min ? gmax[u] - 1u : sub_min;     // (a zero group wraps to the largest value)
-        fast_group(gmax[u], g, eb[u], f[u], min_fb);
-    }
-    // the integer form does not cover a subnormal tensor or group maximum, nor factors beyond the finite range
-    bool any_wide = false;
-    if (__any(!g.fast || sub_min < 127u || (int)min_fb <= g.wide_at)) {
-        bool wide = false;
-#pragma unroll
-        for (int u = 0; u < kUnroll; u++) {
-            const int ex = local_exponent<CEIL>(gmax[u], g);
-            eb[u] = (uint32_t)(ex + 127);
-            f[u] = group_factor(gmax[u], ex, g);
-            wide |= factor_is_wide(f[u]);
-        }
-        any_wide = __any(wide);
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; u++) {
-        const int64_t id = base + (int64_t)u * kThreads;
-        const uint2 out = any_wide ? row_codes<false>(raw[u], f[u], eb[u], g.inv_s) : row_codes<true>(raw[u], f[u], eb[u], g.inv_s);
+    for (int u = 0; u < U; u++) {
+        const int id = base + u * kQuantThreads;
+        raw[u] = make_uint4(0, 0, 0, 0);
         if (id < n_chunks) {
-            st_stream8(q + id * 8, out);
-            if ((threadIdx.x & 3) == 0) e[id >> 2] = (uint8_t)eb[u];
+            int64_t off = (int64_t)id * 8;
+            if (!dense) {
+                const int row = id / chunks_per_row;
+                off = row * ld + (id - row * chunks_per_row) * 8;
+            }
+            raw[u] = ld_stream16(x + off);
         }
     }
+    uint32_t m = 0;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const uint32_t c = chunk_absmax(raw[u]);
+        m = c > m ? c : m;
+    }
+    m = meet_in_slots<kQuantThreads>(slots, (int)gridDim.x, (int)blockIdx.x, call, m, poll_limit, red);
+    if (m == kNotMet) {
+        __syncthreads();
+        m = scan_max<kQuantThreads>(x, n_chunks, chunks_per_row, ld, dense, red);
+    }
+    const GlobalScale g = make_global_scale<CEIL>(m);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *s_global = g.s;
+    constexpr int N = U < 4 ? U : 4;
+#pragma unroll
+    for (int u = 0; u < U; u += N)
+        row_convert<CEIL, N>(raw + u, (int64_t)base + (int64_t)u * kQuantThreads, kQuantThreads, n_chunks, g, q, e);
 }
 
 // Column grouping (groups of 32 along the rows, outputs stored transposed), optionally fused
@@ -403,16 +521,17 @@ __global__ __launch_bounds__(row_threads(SCAN)) void k_quant_row(const uint16_t 
 //    transposed output row; the pieces are collected in LDS and, after the only barrier,
 //    8 lanes write the 128 bytes of each transposed row.
 constexpr int kTile = 128;
-constexpr int kTilePitch = kTile + 8;   // bytes per staged output row (8-byte aligned pieces, some bank spread)
 
 // LDS of a workgroup that converts tiles: the transposed codes of the tile, and the exponent bytes of the tile's
 // 128 x 4 row groups and 4 x 128 column groups, which leave as one 4-byte store per row / per column (single-byte
 // stores from every lane cost several times the cache-line visits and were ~3.5 us of a 64 MiB tensor's 42 us).
+// W waves: 32 W rows; 8 bytes more per staged output row keep its pieces 8-byte aligned and spread the banks a little.
+template <int W>
 struct TileLds {
-    __attribute__((aligned(16))) uint8_t tt[kTile][kTilePitch];   // transposed codes [column][row]
-    __attribute__((aligned(8))) uint8_t te[4][kTile];             // row-group exponents [column group of the tile][row]
-    __attribute__((aligned(8))) uint8_t tc[4][kTile];             // column-group exponents [row group of the tile][column]
-    uint32_t redo;                                                // bit k: the workgroup's tile k needs the general form
+    __attribute__((aligned(16))) uint8_t tt[kTile][W * kGroup + 8];   // transposed codes [column][row]
+    __attribute__((aligned(8))) uint8_t te[4][W * kGroup];            // row-group exponents [column group of the tile][row]
+    __attribute__((aligned(8))) uint8_t tc[W][kTile];                 // column-group exponents [row group of the tile][column]
+    uint32_t redo;                                                    // bit k: the workgroup's tile k needs the general form
 };
 
 // The converter writes two bytes of its destination and keeps the other two, so its destination is also an
@@ -526,12 +645,15 @@ struct TileShape {
     int64_t rows, cols, ld;
 };
 
+// (a tile is 32 rows per wave of the workgroup high: W = 4 waves make the 128 x 128 tile)
+template <int W>
 __device__ __forceinline__ bool tile_is_full(const TileShape &sh, int64_t r0, int64_t c0)
 {
-    return r0 + kTile <= sh.rows && c0 + kTile <= sh.cols;
+    return r0 + W * kGroup <= sh.rows && c0 + kTile <= sh.cols;
 }
 
 // This lane's 8 x 16 bytes of the tile whose first element is (r0, c0); zeros outside X.
+template <int W>
 __device__ __forceinline__ void load_tile(uint4 (&raw)[8], const uint16_t *__restrict__ x, const TileShape &sh, int64_t r0,
                                           int64_t c0)
 {
@@ -539,7 +661,7 @@ __device__ __forceinline__ void load_tile(uint4 (&raw)[8], const uint16_t *__res
     const uint16_t *tile = x + r0 * sh.ld + c0;                                      // wave-uniform
     const uint32_t ld = (uint32_t)sh.ld;
     const uint32_t off = (uint32_t)(wave * kGroup + rl * 8) * ld + (uint32_t)ch * 8;  // elements, < 2^31 (host check)
-    if (tile_is_full(sh, r0, c0)) {
+    if (tile_is_full<W>(sh, r0, c0)) {
 #pragma unroll
         for (int it = 0; it < 8; it++) raw[it] = ld_stream16(tile + (off + (uint32_t)it * ld));
     } else {
@@ -566,8 +688,8 @@ __device__ __forceinline__ uint32_t tile_absmax(const uint4 (&raw)[8])
 }
 
 // Exponents and codes of one 128 x 128 tile from the registers that hold it, in one of two forms.
-//   FAST: for tiles that lie wholly inside X.  Nothing is predicated, the exponents come from the integer
-//         form (fast_group) and every code from one multiplication by 2^-e (1/s).  That form does not cover
+//   FAST: the exponents come from the integer form (fast_group) and every code from one multiplication by
+//         2^-e (1/s).  FULL: the tile lies wholly inside X and nothing is predicated.  The fast form does not cover
 //         a subnormal tensor or group maximum, nor a factor beyond the finite range (tiny nonzero groups under
 //         a small global maximum): the return value says whether this wave met one, and the tile then has to
 //         be done again in the general form (what was stored is overwritten).
@@ -575,13 +697,12 @@ __device__ __forceinline__ uint32_t tile_absmax(const uint4 (&raw)[8])
 // The two forms never sit side by side in a loop body: a kernel runs the fast form over its tiles and the
 // general form afterwards for the (rare) tiles that need it, so that the fast form's registers stay few.
 // The body contains one workgroup barrier; the LDS staging area stays in use until the caller's next barrier.
-template <bool ROW, bool COL, bool CEIL, bool FAST>
+template <bool ROW, bool COL, bool CEIL, bool FAST, bool FULL, int W>
 __device__ __forceinline__ bool quant_tile_body(const uint4 (&raw)[8], const TileShape &sh, int64_t r0, int64_t c0,
                                                 const GlobalScale &g, uint8_t *__restrict__ q_row,
                                                 uint8_t *__restrict__ e_row, uint8_t *__restrict__ q_col,
-                                                uint8_t *__restrict__ e_col, TileLds &lds)
+                                                uint8_t *__restrict__ e_col, TileLds<W> &lds)
 {
-    constexpr bool FULL = FAST;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rl = lane >> 4, ch = lane & 15;
     const int64_t rows = sh.rows, cols = sh.cols;
     const int row_in_tile = wave * kGroup + rl * 8;              // first of this lane's 8 rows
@@ -645,16 +766,17 @@ __device__ __forceinline__ bool quant_tile_body(const uint4 (&raw)[8], const Til
         uint8_t *q_col_tile = q_col + c0 * rows + r0;                                    // wave-uniform
 #pragma unroll
         for (int k = 0; k < 4; k++) {
-            const int idx = tid + k * kQuantThreads, c = idx >> 3, piece = idx & 7;
+            const int idx = tid + k * W * kWave, c = idx / (2 * W), piece = idx % (2 * W);
             if (FULL || (c0 + c < cols && r0 + piece * 16 < rows)) {
                 const uint32_t *src = reinterpret_cast<const uint32_t *>(&lds.tt[c][piece * 16]);
                 *reinterpret_cast<uint4 *>(q_col_tile + ((uint32_t)c * (uint32_t)rows + (uint32_t)piece * 16)) = make_uint4(src[0], src[1], src[2], src[3]);
             }
         }
     }
-    // Exponent bytes: threads 0..127 each own a row of the tile (its 4 row-group bytes are neighbours in e_row),
-    // threads 128..255 a column (its 4 column-group bytes are neighbours in e_col).
-    if (ROW && tid < kTile) {
+    // Exponent bytes: the first half of the threads own a row of the tile each (its 4 row-group bytes are neighbours in
+    // e_row), the second half 4 / W columns each (a column's W column-group bytes are neighbours in e_col).
+    constexpr int kHalf = W * kGroup;
+    if (ROW && tid < kHalf) {
         const int r = tid;
         const uint32_t word = (uint32_t)lds.te[0][r] | (uint32_t)lds.te[1][r] << 8 | (uint32_t)lds.te[2][r] << 16 | (uint32_t)lds.te[3][r] << 24;
         uint8_t *dst = e_row + (r0 + r) * n_cgroups + (c0 >> 5);
@@ -666,16 +788,22 @@ __device__ __forceinline__ bool quant_tile_body(const uint4 (&raw)[8], const Til
                 if (c0 + q * kGroup < cols) dst[q] = (uint8_t)(word >> (8 * q));
         }
     }
-    if (COL && tid >= kTile) {
-        const int c = tid - kTile;
-        const uint32_t word = (uint32_t)lds.tc[0][c] | (uint32_t)lds.tc[1][c] << 8 | (uint32_t)lds.tc[2][c] << 16 | (uint32_t)lds.tc[3][c] << 24;
-        uint8_t *dst = e_col + (c0 + c) * n_rgroups + (r0 >> 5);
-        if (FULL && (n_rgroups & 3) == 0) {
-            *reinterpret_cast<uint32_t *>(dst) = word;
-        } else if (c0 + c < cols) {
+    if (COL && tid >= kHalf) {
 #pragma unroll
-            for (int q = 0; q < 4; q++)
-                if (r0 + q * kGroup < rows) dst[q] = (uint8_t)(word >> (8 * q));
+        for (int c = tid - kHalf; c < kTile; c += kHalf) {
+            uint32_t word = 0;
+#pragma unroll
+            for (int q = 0; q < W; q++) word |= (uint32_t)lds.tc[q][c] << (8 * q);
+            uint8_t *dst = e_col + (c0 + c) * n_rgroups + (r0 >> 5);
+            if (W == 4 && FULL && (n_rgroups & 3) == 0) {
+                *reinterpret_cast<uint32_t *>(dst) = word;
+            } else if (W == 2 && FULL && (n_rgroups & 1) == 0) {
+                *reinterpret_cast<uint16_t *>(dst) = (uint16_t)word;
+            } else if (c0 + c < cols) {
+#pragma unroll
+                for (int q = 0; q < W; q++)
+                    if (r0 + q * kGroup < rows) dst[q] = (uint8_t)(word >> (8 * q));
+            }
         }
     }
     return redo;
@@ -705,6 +833,20 @@ __device__ __forceinline__ bool tile_of_workgroup(uint32_t id, int tiles_x, int 
     return tx < tiles_x && ty < tiles_y;
 }
 
+// A workgroup's only tile: the fast form, and the general one where that says so.  (lds.redo is zero, and a barrier ago.)
+template <bool ROW, bool CEIL, int W>
+__device__ __forceinline__ void quant_one_tile(const uint4 (&raw)[8], const TileShape &sh, int64_t r0, int64_t c0, const GlobalScale &g,
+                                               uint8_t *__restrict__ q_row, uint8_t *__restrict__ e_row,
+                                               uint8_t *__restrict__ q_col, uint8_t *__restrict__ e_col, TileLds<W> &lds)
+{
+    const bool redo = tile_is_full<W>(sh, r0, c0)
+                          ? quant_tile_body<ROW, true, CEIL, true, true, W>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds)
+                          : quant_tile_body<ROW, true, CEIL, true, false, W>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
+    if (redo && (threadIdx.x & 63) == 0) atomicOr(&lds.redo, 1u);
+    __syncthreads();
+    if (lds.redo) quant_tile_body<ROW, true, CEIL, false, false, W>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
+}
+
 template <bool ROW, bool CEIL, bool SCAN>
 __global__ __launch_bounds__(kQuantThreads, 4) void k_quant_tile(const uint16_t *__restrict__ x, int64_t rows, int64_t cols,
                                                                  int64_t ld, int tiles_x, int tiles_y,
@@ -714,28 +856,52 @@ __global__ __launch_bounds__(kQuantThreads, 4) void k_quant_tile(const uint16_t 
                                                                  uint8_t *__restrict__ e_col, float *__restrict__ s_global)
 {
     __shared__ uint32_t red[kQuantThreads / kWave];
-    __shared__ TileLds lds;
+    __shared__ TileLds<4> lds;
 
     int tx, ty;
     if (!tile_of_workgroup(blockIdx.x, tiles_x, tiles_y, tx, ty)) return;     // (the whole workgroup, before any barrier)
     converter_saturates();
     if (threadIdx.x == 0) lds.redo = 0;
-    const GlobalScale g = SCAN ? scan_global_scale<CEIL, kQuantThreads>(x, (int)(rows * (cols / 8)), (int)(cols / 8), ld, ld == cols, red)
+    const GlobalScale g = SCAN ? make_global_scale<CEIL>(scan_max<kQuantThreads>(x, (int)(rows * (cols / 8)), (int)(cols / 8), ld, ld == cols, red))
                                : fold_global_scale<CEIL>(partial, n_partial, red);
     if (blockIdx.x == 0 && threadIdx.x == 0) *s_global = g.s;                 // (workgroup 0 has tile (0, 0))
 
     const TileShape sh = {rows, cols, ld};
     const int64_t r0 = (int64_t)ty * kTile, c0 = (int64_t)tx * kTile;
     uint4 raw[8];
-    load_tile(raw, x, sh, r0, c0);
-    bool general = true;
-    if (tile_is_full(sh, r0, c0)) {        // (lds.redo was cleared before the barrier inside fold_ / scan_global_scale)
-        if (quant_tile_body<ROW, true, CEIL, true>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds) && (threadIdx.x & 63) == 0)
-            atomicOr(&lds.redo, 1u);
+    load_tile<4>(raw, x, sh, r0, c0);
+    quant_one_tile<ROW, CEIL, 4>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
+}
+
+// The same in one launch: a workgroup of W waves keeps its tile of 32 W rows x 128 columns in registers while the workgroups
+// meet.  Every workgroup of the grid has a tile; each XCD gets a contiguous range of them, so that the pieces of a line of
+// exponent bytes mostly meet in one L2.
+template <bool ROW, bool CEIL, int W>
+__global__ __launch_bounds__(W *kWave, 2) void k_quant_tile_meet(const uint16_t *__restrict__ x, int64_t rows, int64_t cols, int64_t ld,
+                                                                 int tiles_x, uint64_t *slots, uint64_t call, uint32_t poll_limit,
+                                                                 uint8_t *__restrict__ q_row, uint8_t *__restrict__ e_row,
+                                                                 uint8_t *__restrict__ q_col, uint8_t *__restrict__ e_col,
+                                                                 float *__restrict__ s_global)
+{
+    __shared__ uint32_t red[2 * W];
+    __shared__ TileLds<W> lds;
+    converter_saturates();
+    if (threadIdx.x == 0) lds.redo = 0;      // (read only behind the barriers of the meeting)
+    const uint32_t total = gridDim.x, per = total / kXcds, rest = total % kXcds, xcd = blockIdx.x % kXcds;
+    const int t = (int)(xcd * per + (xcd < rest ? xcd : rest) + blockIdx.x / kXcds);
+    const int ty = t / tiles_x;
+    const TileShape sh = {rows, cols, ld};
+    const int64_t r0 = (int64_t)ty * (W * kGroup), c0 = (int64_t)(t - ty * tiles_x) * kTile;
+    uint4 raw[8];
+    load_tile<W>(raw, x, sh, r0, c0);
+    uint32_t m = meet_in_slots<W * kWave>(slots, (int)total, t, call, tile_absmax(raw), poll_limit, red);
+    if (m == kNotMet) {
         __syncthreads();
-        general = lds.redo != 0;
+        m = scan_max<W * kWave>(x, (int)(rows * (cols / 8)), (int)(cols / 8), ld, ld == cols, red);
     }
-    if (general) quant_tile_body<ROW, true, CEIL, false>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
+    const GlobalScale g = make_global_scale<CEIL>(m);
+    if (t == 0 && threadIdx.x == 0) *s_global = g.s;
+    quant_one_tile<ROW, CEIL, W>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -745,8 +911,8 @@ __global__ __launch_bounds__(kQuantThreads, 4) void k_quant_tile(const uint16_t 
 // from memory once instead of twice: 128 KiB of registers per workgroup hold the tensor, the
 // other half of the register file does the arithmetic.
 //
-// Between the walks the workgroups agree on the global maximum through a few words of the
-// workspace.  Only relaxed device-scope atomics are used, no fences: a release or acquire fence
+// Between the walks the workgroups agree on the global maximum in slots (meet_in_slots), a captured call, which is
+// replayed, through a few counted words of the workspace.  Only relaxed device-scope atomics are used, no fences: a release or acquire fence
 // at device scope writes back / invalidates the whole L2 of the XCD and cost ~60 us per launch
 // here.  Everything that travels is a single word that carries its own validity:
 //   1. a workgroup merges its maximum into its group's word (atomic max) and only then -- the
@@ -788,15 +954,15 @@ __device__ __forceinline__ uint32_t after_value(uint32_t v, uint32_t after) { re
 template <bool ROW, bool COL, bool CEIL>
 __global__ __launch_bounds__(kQuantThreads, 2) void k_quant_persist(const uint16_t *__restrict__ x, int64_t rows,
                                                                     int64_t cols, int64_t ld, int tiles_x, int n_tiles,
-                                                                    uint32_t *sync, uint32_t poll_limit,
-                                                                    uint8_t *__restrict__ q_row,
+                                                                    uint32_t *sync, uint64_t *slots, uint64_t call,
+                                                                    uint32_t poll_limit, uint8_t *__restrict__ q_row,
                                                                     uint8_t *__restrict__ e_row,
                                                                     uint8_t *__restrict__ q_col,
                                                                     uint8_t *__restrict__ e_col,
                                                                     float *__restrict__ s_global)
 {
-    __shared__ uint32_t red[kQuantThreads / kWave + 1];
-    __shared__ TileLds lds;
+    __shared__ uint32_t red[2 * kQuantThreads / kWave];
+    __shared__ TileLds<4> lds;
 
     converter_saturates();
     if (threadIdx.x == 0) lds.redo = 0;      // (read only behind the barriers of the meeting point)
@@ -820,7 +986,7 @@ __global__ __launch_bounds__(kQuantThreads, 2) void k_quant_persist(const uint16
         if (t < n_tiles) {
             int64_t r0, c0;
             origin(t, r0, c0);
-            load_tile(keep[k], x, sh, r0, c0);
+            load_tile<4>(keep[k], x, sh, r0, c0);
         } else {
 #pragma unroll
             for (int it = 0; it < 8; it++) keep[k][it] = make_uint4(0, 0, 0, 0);
@@ -831,51 +997,57 @@ __global__ __launch_bounds__(kQuantThreads, 2) void k_quant_persist(const uint16
         const uint32_t c = tile_absmax(keep[k]);
         m = c > m ? c : m;
     }
-    // meeting point
-    uint32_t members = 0, my_use = 0;        // (thread 0's)
-    m = wave_max_u32(m);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < kQuantThreads / kWave; i++) m = red[i] > m ? red[i] : m;
-        uint32_t *grp_max = sync, *grp_cnt = sync + kSyncGroups * kSyncStride, *flags = sync + 2 * kSyncGroups * kSyncStride;
-        uint32_t *users = sync + 3 * kSyncGroups * kSyncStride;
-        uint32_t *all_max = sync + 4 * kSyncGroups * kSyncStride, *all_cnt = all_max + kSyncStride;
-        const int grp = first % kSyncGroups, n_grp = G < kSyncGroups ? G : kSyncGroups;
-        members = (uint32_t)((G - grp + kSyncGroups - 1) / kSyncGroups);
-        uint32_t old = atomicMax(&grp_max[grp * kSyncStride], m);
-        if (atomicAdd(&grp_cnt[grp * kSyncStride], after_value(1u, old)) == members - 1) {
-            const uint32_t gm = atomicExch(&grp_max[grp * kSyncStride], 0u);    // the group's maximum; word and count left at zero
-            __hip_atomic_store(&grp_cnt[grp * kSyncStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            old = atomicMax(all_max, gm);
-            if (atomicAdd(all_cnt, after_value(1u, old)) == (uint32_t)n_grp - 1) {
-                const uint32_t am = atomicExch(all_max, 0u);
-                __hip_atomic_store(all_cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                uint32_t was[kSyncGroups];
-#pragma unroll
-                for (int i = 0; i < kSyncGroups; i++)
-                    if (i < n_grp) was[i] = atomicExch(&flags[i * kSyncStride], 0x80000000u | am);
-                // the publisher is one more user of every flag: counted in once the flag is out
-#pragma unroll
-                for (int i = 0; i < kSyncGroups; i++)
-                    if (i < n_grp && atomicAdd(&users[i * kSyncStride], after_value(1u, was[i])) == (uint32_t)((G - i + kSyncGroups - 1) / kSyncGroups)) {
-                        __hip_atomic_store(&flags[i * kSyncStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        __hip_atomic_store(&users[i * kSyncStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
+    // meeting point: in slots, or (captured calls) over the counted words
+    uint32_t members = 0, my_use = ~0u;        // (thread 0's)
+    uint32_t amax_bits;
+    if (call != 0) {
+        amax_bits = meet_in_slots<kQuantThreads>(slots, G, first, call, m, poll_limit, red);
+        amax_bits = amax_bits == kNotMet ? 0 : amax_bits | 0x80000000u;
+    } else {
+        m = wave_max_u32(m);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int i = 1; i < kQuantThreads / kWave; i++) m = red[i] > m ? red[i] : m;
+            uint32_t *grp_max = sync, *grp_cnt = sync + kSyncGroups * kSyncStride, *flags = sync + 2 * kSyncGroups * kSyncStride;
+            uint32_t *users = sync + 3 * kSyncGroups * kSyncStride;
+            uint32_t *all_max = sync + 4 * kSyncGroups * kSyncStride, *all_cnt = all_max + kSyncStride;
+            const int grp = first % kSyncGroups, n_grp = G < kSyncGroups ? G : kSyncGroups;
+            members = (uint32_t)((G - grp + kSyncGroups - 1) / kSyncGroups);
+            uint32_t old = atomicMax(&grp_max[grp * kSyncStride], m);
+            if (atomicAdd(&grp_cnt[grp * kSyncStride], after_value(1u, old)) == members - 1) {
+                const uint32_t gm = atomicExch(&grp_max[grp * kSyncStride], 0u);    // the group's maximum; word and count left at zero
+                __hip_atomic_store(&grp_cnt[grp * kSyncStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                old = atomicMax(all_max, gm);
+                if (atomicAdd(all_cnt, after_value(1u, old)) == (uint32_t)n_grp - 1) {
+                    const uint32_t am = atomicExch(all_max, 0u);
+                    __hip_atomic_store(all_cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    uint32_t was[kSyncGroups];
+    #pragma unroll
+                    for (int i = 0; i < kSyncGroups; i++)
+                        if (i < n_grp) was[i] = atomicExch(&flags[i * kSyncStride], 0x80000000u | am);
+                    // the publisher is one more user of every flag: counted in once the flag is out
+    #pragma unroll
+                    for (int i = 0; i < kSyncGroups; i++)
+                        if (i < n_grp && atomicAdd(&users[i * kSyncStride], after_value(1u, was[i])) == (uint32_t)((G - i + kSyncGroups - 1) / kSyncGroups)) {
+                            __hip_atomic_store(&flags[i * kSyncStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_store(&users[i * kSyncStride], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                }
             }
+            uint32_t polls = 0, flag;
+            while (true) {
+                flag = relaxed_load(&flags[grp * kSyncStride]);
+                if (flag != 0 || polls >= poll_limit) break;
+                polls++;
+                __builtin_amdgcn_s_sleep(8);
+            }
+            my_use = atomicAdd(&users[grp * kSyncStride], 1u);      // done with the flag, seen or not
+            red[kQuantThreads / kWave] = flag;
         }
-        uint32_t polls = 0, flag;
-        while (true) {
-            flag = relaxed_load(&flags[grp * kSyncStride]);
-            if (flag != 0 || polls >= poll_limit) break;
-            polls++;
-            __builtin_amdgcn_s_sleep(8);
-        }
-        my_use = atomicAdd(&users[grp * kSyncStride], 1u);      // done with the flag, seen or not
-        red[kQuantThreads / kWave] = flag;
+        __syncthreads();
+        amax_bits = red[kQuantThreads / kWave];
     }
-    __syncthreads();
-    uint32_t amax_bits = red[kQuantThreads / kWave];
     if (amax_bits != 0) {
         amax_bits &= 0x7FFFu;
     } else {
@@ -885,11 +1057,12 @@ __global__ __launch_bounds__(kQuantThreads, 2) void k_quant_persist(const uint16
             uint4 ra[8];
             int64_t r0, c0;
             origin(t, r0, c0);
-            load_tile(ra, x, sh, r0, c0);
+            load_tile<4>(ra, x, sh, r0, c0);
             const uint32_t c = tile_absmax(ra);
             mm = c > mm ? c : mm;
         }
         mm = wave_max_u32(mm);
+        __syncthreads();
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mm;
         __syncthreads();
         amax_bits = red[0];
@@ -906,8 +1079,8 @@ __global__ __launch_bounds__(kQuantThreads, 2) void k_quant_persist(const uint16
         if (t < n_tiles) {
             int64_t r0, c0;
             origin(t, r0, c0);
-            if (tile_is_full(sh, r0, c0)) {
-                if (quant_tile_body<ROW, COL, CEIL, true>(keep[k], sh, r0, c0, g, q_row, e_row, q_col, e_col, lds) &&
+            if (tile_is_full<4>(sh, r0, c0)) {
+                if (quant_tile_body<ROW, COL, CEIL, true, true, 4>(keep[k], sh, r0, c0, g, q_row, e_row, q_col, e_col, lds) &&
                     (threadIdx.x & 63) == 0)
                     atomicOr(&lds.redo, 1u << k);
                 __syncthreads();
@@ -925,8 +1098,8 @@ __global__ __launch_bounds__(kQuantThreads, 2) void k_quant_persist(const uint16
         int64_t r0, c0;
         origin(kept_tile(k), r0, c0);
         uint4 ra[8];
-        load_tile(ra, x, sh, r0, c0);
-        quant_tile_body<ROW, COL, CEIL, false>(ra, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
+        load_tile<4>(ra, x, sh, r0, c0);
+        quant_tile_body<ROW, COL, CEIL, false, false, 4>(ra, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
         __syncthreads();
     }
     // the last of a flag's users (the group's members and the publisher) leaves flag and count at zero
@@ -944,7 +1117,7 @@ namespace {
 
 std::atomic<uint32_t> g_poll_limit{moss::kPollLimit};
 
-using PersistFn = void (*)(const uint16_t *, int64_t, int64_t, int64_t, int, int, uint32_t *, uint32_t, uint8_t *, uint8_t *,
+using PersistFn = void (*)(const uint16_t *, int64_t, int64_t, int64_t, int, int, uint32_t *, uint64_t *, uint64_t, uint32_t, uint8_t *, uint8_t *,
                            uint8_t *, uint8_t *, float *);
 
 PersistFn persist_kernel(bool row, bool col, bool ceil_mode)
@@ -955,23 +1128,44 @@ PersistFn persist_kernel(bool row, bool col, bool ceil_mode)
     return ceil_mode ? k_quant_persist<true, false, true> : k_quant_persist<true, false, false>;
 }
 
-// Workgroups of the one-launch kernel that one compute unit holds at a time, at most 2 (0: do not use it).
-int persist_groups_per_cu(PersistFn fn, int variant)
+// Workgroups of a kernel that one compute unit holds at a time (0: unknown, do not use it).  Asked for once per kernel: a
+// property of its register and LDS use on gfx950, the same on every device of the process.
+int groups_per_cu(const void *fn, int threads, std::atomic<int> &cached)
 {
-    // (a property of the kernel's register and LDS use on gfx950, the same on every device of the process)
-    static std::atomic<int> cached[8] = {{-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}, {-1}};
-    int v = cached[variant].load();
+    int v = cached.load() - 1;
     if (v < 0) {
-        int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(fn), moss::kQuantThreads, 0) !=
-            hipSuccess) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, fn, threads, 0) != hipSuccess) {
             (void)hipGetLastError();
-            n = 0;
+            v = 0;
         }
-        v = n > 2 ? 2 : n;
-        cached[variant].store(v);
+        cached.store(v + 1);
     }
     return v;
+}
+
+// The number of a call whose workgroups meet in slots: 48 bits, never zero, never used again by this process; it starts at a
+// random place, so that memory which another process left behind cannot hold it.
+uint64_t next_call()
+{
+    static std::atomic<uint64_t> last{[] {
+        std::random_device rd;
+        return ((uint64_t)rd() << 32) ^ rd() ^ (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();
+    }()};
+    uint64_t c;
+    do c = (last.fetch_add(1) + 1) & 0xFFFFFFFFFFFFull;
+    while (c == 0);
+    return c;
+}
+
+// A replay of a captured call would meet under the number of the capture, and find the slots of the replay before it.
+bool may_meet_in_slots(hipStream_t st)
+{
+    hipStreamCaptureStatus status;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusNone;
 }
 
 }  // namespace
@@ -991,10 +1185,54 @@ static bool scans(int64_t bytes, bool dense, bool want_col)
     return bytes <= (dense ? kScanBytesRow : kScanBytesRowStrided);
 }
 
-// what quant_with_workspace chooses for a small tensor (the tests hold the rule by it)
+// log2 of the chunks per thread of k_quant_row_meet, -1 if the tensor is too large for it.  One workgroup per compute unit of
+// the 256 up to 8 MiB, two above: fewer workgroups meet sooner (2 MiB 6.3 us with 256 of them, 7.2 with 512; 4 MiB 6.9 and 8.3,
+// with 1024 11.0), more of them load faster (16 MiB 11.1 either way, 28 MiB 15.8 and 14.5, 64 MiB 24.8 and 23.5).
+// Against the launches it replaces, calls back to back: 0.5 MiB 6.8 -> 4.8 us, 4 MiB 8.2 -> 6.9, 16 MiB 18.4 -> 11.3, 1333 x 11008
+// 23.8 -> 14.5 (and a clearing launch less where the workspace is not kept), 64 MiB 29.2 -> 23.5.
+static int row_meet_unroll_log2(int64_t n_chunks)
+{
+    int k = 0;
+    while (k < 6 && (n_chunks + (moss::kQuantThreads << k) - 1) / (moss::kQuantThreads << k) > (k < 4 ? 256 : 512)) k++;
+    if (k == 4 && (n_chunks + (moss::kQuantThreads << 3) - 1) / (moss::kQuantThreads << 3) <= 512) k = 3;
+    return k < 6 ? k : -1;
+}
+
+static int64_t meet_tiles(int64_t rows, int64_t cols, int k)
+{
+    using namespace moss;
+    return ((cols + kTile - 1) / kTile) * ((rows + (kGroup << k) - 1) / (kGroup << k));
+}
+
+// log2 of the waves (32-row groups) per workgroup of k_quant_tile_meet, -1 if the tensor is too large for it: the lowest tiles
+// that leave at most one workgroup per compute unit of the 256.  Lower ones spread a small tensor over more compute units
+// (64 x 256 5.0 us with one wave, 6.4 with four), more workgroups take longer to meet (512 x 4096: 10.0 / 9.0 / 7.8 us with 512 /
+// 256 / 128).  From 512 tiles of 128 x 128 on the kernel below, which keeps up to four, takes as long or less (2048 x 4096 17.0
+// against 16.2, 4096 x 4096 30 against 22).
+// Against the launches it replaces: 64 x 256 7.0 -> 5.0 us, 256 x 2048 10.2 -> 6.0, 1024 x 4096 15.3 -> 10.5, 1600 x 4160 19.5 -> 16.2.
+static int tile_meet_waves_log2(int64_t rows, int64_t cols)
+{
+    int k = 0;
+    while (k < 2 && meet_tiles(rows, cols, k) > 256) k++;
+    return meet_tiles(rows, cols, k) < 512 ? k : -1;
+}
+
+// Where the workgroups may meet, only the smallest row groupings still scan: 16 KiB 3.2 us scanned and 3.1 met, 64 KiB 3.6 both,
+// 96 KiB 3.9 and 4.2, 128 KiB 4.3 both, 256 KiB 6.3 and 4.4; strided 32 KiB 3.7 and 3.6, 128 KiB 5.4 and 4.3.
+static bool scans_rather_than_meet(int64_t bytes, bool dense, bool want_col)
+{
+    return !want_col && bytes <= (dense ? 96 : 24) * 1024;
+}
+
+// what quant_with_workspace chooses for a small tensor in a captured call (the tests hold the rules by these)
 extern "C" int moss_internal_quant_scans(int64_t rows, int64_t cols, int64_t ld, int64_t want_col)
 {
     return scans(rows * cols * 2, ld == cols, want_col != 0);
+}
+
+extern "C" int moss_internal_quant_meets(int64_t rows, int64_t cols, int64_t want_col)
+{
+    return want_col ? tile_meet_waves_log2(rows, cols) : row_meet_unroll_log2(rows * (cols / 8));
 }
 
 // The launch that converts: k_quant_row for the row grouping alone, k_quant_tile as soon as the transposed
@@ -1034,6 +1272,51 @@ static int launch_codes(const uint16_t *x, int64_t rows, int64_t cols, int64_t l
 #undef MOSS_LAUNCH_TILE
         MOSS_LAUNCH_CHECK();
     }
+    return MOSS_OK;
+}
+
+// The kernels that meet in slots, for tensors whose workgroups all run at once; MOSS_ERR_UNSUPPORTED if another form has it.
+static int launch_meeting(const uint16_t *x, int64_t rows, int64_t cols, int64_t ld, bool want_row, bool want_col, bool ceil_mode,
+                          uint64_t *slots, uint64_t call, uint8_t *q_row, uint8_t *e_row, uint8_t *q_col, uint8_t *e_col,
+                          float *s_global, hipStream_t st)
+{
+    using namespace moss;
+    const int64_t n_chunks = rows * (cols / 8), cus = moss_internal_cu_count();
+    const uint32_t polls = g_poll_limit.load();
+    if (!want_col) {
+        static std::atomic<int> cached[2][6];
+        const int k = row_meet_unroll_log2(n_chunks);
+        if (k < 0) return MOSS_ERR_UNSUPPORTED;
+        using Fn = void (*)(const uint16_t *, int, int, int64_t, int, uint64_t *, uint64_t, uint32_t, uint8_t *, uint8_t *, float *);
+        static const Fn fns[2][6] = {{k_quant_row_meet<false, 1>, k_quant_row_meet<false, 2>, k_quant_row_meet<false, 4>,
+                                      k_quant_row_meet<false, 8>, k_quant_row_meet<false, 16>, k_quant_row_meet<false, 32>},
+                                     {k_quant_row_meet<true, 1>, k_quant_row_meet<true, 2>, k_quant_row_meet<true, 4>,
+                                      k_quant_row_meet<true, 8>, k_quant_row_meet<true, 16>, k_quant_row_meet<true, 32>}};
+        const Fn fn = fns[ceil_mode][k];
+        const int64_t grid = (n_chunks + (kQuantThreads << k) - 1) / (kQuantThreads << k);
+        if (grid > cus * groups_per_cu(reinterpret_cast<const void *>(fn), kQuantThreads, cached[ceil_mode][k])) return MOSS_ERR_UNSUPPORTED;
+        hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kQuantThreads), 0, st, x, (int)n_chunks, (int)(cols / 8), ld, (int)(ld == cols),
+                           slots, call, polls, q_row, e_row, s_global);
+        MOSS_LAUNCH_CHECK();
+        return MOSS_OK;
+    }
+    static std::atomic<int> cached[2][2][3];
+    using Fn = void (*)(const uint16_t *, int64_t, int64_t, int64_t, int, uint64_t *, uint64_t, uint32_t, uint8_t *, uint8_t *, uint8_t *,
+                        uint8_t *, float *);
+    static const Fn fns[2][2][3] = {{{k_quant_tile_meet<false, false, 1>, k_quant_tile_meet<false, false, 2>, k_quant_tile_meet<false, false, 4>},
+                                     {k_quant_tile_meet<false, true, 1>, k_quant_tile_meet<false, true, 2>, k_quant_tile_meet<false, true, 4>}},
+                                    {{k_quant_tile_meet<true, false, 1>, k_quant_tile_meet<true, false, 2>, k_quant_tile_meet<true, false, 4>},
+                                     {k_quant_tile_meet<true, true, 1>, k_quant_tile_meet<true, true, 2>, k_quant_tile_meet<true, true, 4>}}};
+    const int64_t tiles_x = (cols + kTile - 1) / kTile;
+    const int k = tile_meet_waves_log2(rows, cols);
+    if (k < 0) return MOSS_ERR_UNSUPPORTED;
+    const Fn fn = fns[want_row][ceil_mode][k];
+    const int threads = kWave << k;
+    const int64_t tiles = meet_tiles(rows, cols, k);
+    if (tiles > cus * groups_per_cu(reinterpret_cast<const void *>(fn), threads, cached[want_row][ceil_mode][k])) return MOSS_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(fn, dim3((unsigned)tiles), dim3(threads), 0, st, x, rows, cols, ld, (int)tiles_x, slots, call, polls, q_row,
+                       e_row, q_col, e_col, s_global);
+    MOSS_LAUNCH_CHECK();
     return MOSS_OK;
 }
 
@@ -1078,8 +1361,16 @@ static int quant_with_workspace(const void *x_bf16, int64_t rows, int64_t cols, 
     const int dense = (ld == cols);
 
     // Small tensors: one launch whose workgroups each read all of X for the maximum (the workspace is not touched)
-    if (scans(n_chunks * 16, dense, want_col))
+    const bool tiny = scans_rather_than_meet(n_chunks * 16, dense, want_col);
+    const uint64_t call = !tiny && may_meet_in_slots(st) ? next_call() : 0;
+    if (tiny || (!call && scans(n_chunks * 16, dense, want_col)))
         return launch_codes(x, rows, cols, ld, want_row, want_col, ceil_mode, nullptr, 0, q_row, e_row, q_col, e_col, s_global, st);
+
+    if (call) {
+        const int rc = launch_meeting(x, rows, cols, ld, want_row, want_col, ceil_mode, (uint64_t *)workspace, call, q_row, e_row,
+                                      q_col, e_col, s_global, st);
+        if (rc != MOSS_ERR_UNSUPPORTED) return rc;
+    }
 
     // Tensors of one to kKeep tiles per workgroup: one launch that keeps X in registers between the
     // maximum and the codes.
@@ -1088,16 +1379,17 @@ static int quant_with_workspace(const void *x_bf16, int64_t rows, int64_t cols, 
         const int64_t n_tiles = tiles_x * tiles_y;
         const int variant = (want_row ? 1 : 0) | (want_col ? 2 : 0) | (ceil_mode ? 4 : 0);
         PersistFn fn = persist_kernel(want_row, want_col, ceil_mode);
-        const int per_cu = persist_groups_per_cu(fn, variant);
+        static std::atomic<int> cached[8];
+        const int held = groups_per_cu(reinterpret_cast<const void *>(fn), kQuantThreads, cached[variant]), per_cu = held > 2 ? 2 : held;
         const int64_t grid = (int64_t)per_cu * moss_internal_cu_count();
         if (per_cu > 0 && n_tiles >= grid && n_tiles <= grid * kKeep) {
             uint32_t *sync = partial + kMaxPartials;
-            if (!words_are_zero) {       // (the kernel leaves them at zero itself)
+            if (!call && !words_are_zero) {       // (the kernel leaves them at zero itself)
                 hipLaunchKernelGGL(k_quant_sync_reset, dim3(1), dim3(kQuantThreads), 0, st, sync);
                 MOSS_LAUNCH_CHECK();
             }
             hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kQuantThreads), 0, st, x, rows, cols, ld, (int)tiles_x,
-                               (int)n_tiles, sync, g_poll_limit.load(), q_row, e_row, q_col, e_col, s_global);
+                               (int)n_tiles, sync, (uint64_t *)workspace, call, g_poll_limit.load(), q_row, e_row, q_col, e_col, s_global);
             MOSS_LAUNCH_CHECK();
             return MOSS_OK;
         }

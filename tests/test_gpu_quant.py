@@ -249,3 +249,46 @@ def test_outputs_are_written_exactly_once_into_caller_buffers(oracle, rows, cols
     assert np.array_equal(u8(got["q_col"]), qc) and np.array_equal(u8(got["e_col"]), ec)
     for b in bufs.values():
         assert (b[:pad] == 0xAB).all() and (b[-pad:] == 0xAB).all()
+
+
+# One launch that meets in slots: one row, partial waves and workgroups, one chunk more than a grid holds at 1, 2, 4, 8 and 16
+# chunks per thread; tiles of 32, 64 and 128 rows at their first and last sizes, cut off at the right and below; strided.
+MEETS = [(1, 32, 0, False), (3, 96, 8, False), (49, 1024, 0, False), (255, 2048, 0, False), (257, 2048, 0, False), (513, 2048, 0, False),
+         (1025, 2048, 64, False), (2049, 2048, 0, False), (4097, 2048, 0, False), (1333, 11008, 0, False), (8192, 4096, 0, False),
+         (32, 32, 0, True), (32, 128, 0, True), (96, 160, 8, True), (256, 4096, 0, True), (288, 4096, 0, True), (544, 4096, 64, True),
+         (1056, 2080, 0, True), (2016, 4096, 0, True), (2048, 4096, 0, True), (4000, 4128, 0, True)]
+
+
+@pytest.mark.parametrize("rows,cols,pad,col", MEETS)
+def test_meeting_in_slots_gives_the_outputs_of_a_captured_call(rows, cols, pad, col):
+    """A captured call does not meet in slots: same bytes from both, for all groupings and rounding modes, on a workspace of
+    unknown contents, and with the wait switched off (every workgroup that came too early searches X itself)."""
+    x = bf16_to_gpu(mi.heavy_tailed_activation(rows, cols + pad, seed=rows + cols))[:, :cols]
+    x[rows // 2] = 0
+    for flags in ([ROW | COL, COL | CEIL] if col else [ROW, ROW | CEIL]):
+        ws = torch.full((moss.load().moss_quant_workspace_bytes(rows, cols, flags),), 0xA5, dtype=torch.uint8, device=x.device)
+        make = lambda: {k: torch.full(shape, 0xCD, dtype=torch.uint8, device=x.device) for k, shape in
+                        dict(q_row=(rows, cols), e_row=(rows, cols // 32), q_col=(cols, rows), e_col=(cols, rows // 32)).items()}
+        want = dict(make(), s=torch.zeros(1, device=x.device))
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            moss.quant_act_2level(x, flags, out=want, workspace=ws)
+        graph.replay()
+        torch.cuda.synchronize()
+        for polls in (32768, 32768, 0):
+            got = dict(make(), s=torch.zeros(1, device=x.device))
+            moss.quant_set_poll_limit(polls)
+            try:
+                moss.quant_act_2level(x, flags, out=got, workspace=ws)
+                torch.cuda.synchronize()
+            finally:
+                moss.quant_set_poll_limit(32768)
+            for k in want:
+                assert torch.equal(got[k], want[k]), (k, flags, polls)
+
+
+@pytest.mark.parametrize("name", ["zeros", "zero_groups", "signed_zeros", "tiny", "tiny_zero_groups", "subnormal", "tiny_groups_under_large_max"])
+@pytest.mark.parametrize("shape", [(64, 256), (96, 160)])       # whole tiles, tiles over the right edge
+def test_meeting_in_slots_on_tensors_that_the_fast_form_does_not_cover(oracle, name, shape):
+    check_against_oracle(oracle, mi.adversarial_activations(*shape)[name], 0, name)

@@ -102,3 +102,11 @@ def test_gemm_tests_reach_the_kernels_they_name(L):
 def test_gemm_tests_of_one_kernel_each(L, M, N, K, tile):
     for b_e in (0, 1):
         assert ask(L.moss_internal_gemm_tile, M, N, K, 1, b_e, N, 0) == tile
+
+
+@pytest.mark.parametrize("rows,cols,row,col", [(1, 32, 0, 0), (256, 2048, 0, 0), (257, 2048, 1, 0), (512, 2048, 1, 0), (513, 2048, 2, 1),
+                                               (1024, 2048, 2, 1), (1025, 2048, 3, 2), (3968, 2048, 3, 2), (3969, 2048, 3, -1),
+                                               (4096, 2048, 3, -1), (4097, 2048, 4, -1), (8192, 2048, 4, -1), (8192, 4096, 5, -1), (8193, 4096, -1, -1)])
+def test_workgroups_meet_where_their_tensor_fits_the_registers(L, rows, cols, row, col):
+    assert ask(L.moss_internal_quant_meets, rows, cols, 0) == row
+    assert ask(L.moss_internal_quant_meets, rows, cols, 1) == col
