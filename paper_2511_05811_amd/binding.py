@@ -1,5 +1,8 @@
 """ctypes binding of include/moss.h.  Argument marshalling only: every step of the
-path runs in the HIP kernels.  torch is used for device memory and streams."""
+path runs in the HIP kernels.  torch is used for device memory and streams.
+
+The calls that a training step or a forward pass makes go through _moss_calls first (csrc/moss_calls.cpp), which does in native
+code what the functions here do, for plain arguments, and answers None to anything else."""
 import ctypes as C
 import os
 import re
@@ -87,6 +90,27 @@ def _check(rc, what):
         raise MossError(f"{what}: {load().moss_status_string(rc).decode()} (status {rc})")
 
 
+_calls = None      # the native calls, bound to the library; False if they have not been built for this torch
+
+
+def _bind_calls():
+    global _calls
+    L = load()
+    import torch
+    try:
+        from . import _moss_calls as native
+        get_device, get_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    except (ImportError, AttributeError):
+        _calls = False
+        return _calls
+    names = ("moss_quant_workspace_bytes", "moss_quant_act_2level", "moss_quant_act_2level_given_max", "moss_gemm_fp8_mx",
+             "moss_weight_workspace_bytes", "moss_weight_autoscale_cast", "moss_swiglu_bf16", "moss_swiglu_bf16_backward",
+             "moss_add_rmsnorm_bf16", "moss_rmsnorm_bf16_backward")
+    native.bind(tuple(C.cast(getattr(L, n), C.c_void_p).value for n in names), _check, AdamWArgs, get_device, get_stream)
+    _calls = native
+    return _calls
+
+
 # What a call costs on the host decides the smallest problems (a GEMM of a few microseconds): pointers go to ctypes as plain
 # integers, and the current stream's handle is asked for directly, 0.2 us where a torch.cuda.Stream object takes 2.7 us
 # (a GEMM call 8.5 -> 4.6 us, of which 3.5 us are ctypes and the launch).
@@ -116,6 +140,11 @@ def _workspace(nbytes, device):
 def quant_act_2level(x, flags=MOSS_Q_ROW, out=None, workspace=None):
     """x: torch.bfloat16 [rows, cols] on the GPU (row stride may exceed cols).
     Returns dict(q_row, e_row, q_col, e_col, s) of device tensors (absent outputs are None)."""
+    native = _bind_calls() if _calls is None else _calls
+    if native:
+        done = native.quant_act_2level(x, flags, out, workspace)
+        if done is not None:
+            return done
     import torch
     L = load()
     rows, cols = x.shape
@@ -162,6 +191,11 @@ def quant_act_2level_noalloc(x, flags, out):
 def quant_act_2level_given_max(x, absmax_bits, flags=MOSS_Q_ROW, out=None):
     """quant_act_2level for a tensor whose producer left a bound of max|x| (BF16 magnitude bits) in the
     one-element int32 device tensor `absmax_bits`: one launch, x read once, no workspace."""
+    native = _bind_calls() if _calls is None else _calls
+    if native:
+        done = native.quant_act_2level_given_max(x, absmax_bits, flags, out)
+        if done is not None:
+            return done
     import torch
     L = load()
     rows, cols = x.shape
@@ -192,6 +226,11 @@ def quant_act_2level_given_max(x, absmax_bits, flags=MOSS_Q_ROW, out=None):
 
 def swiglu_bf16(gate, up, h=None, absmax_bits=None):
     """h = silu(gate) * up (BF16) and max|h| as BF16 magnitude bits in a one-element int32 tensor."""
+    native = _bind_calls() if _calls is None else _calls
+    if native:
+        done = native.swiglu_bf16(gate, up, h, absmax_bits)
+        if done is not None:
+            return done
     import torch
     L = load()
     rows, cols = gate.shape
@@ -209,6 +248,11 @@ def swiglu_bf16(gate, up, h=None, absmax_bits=None):
 
 def swiglu_bf16_backward(gate, up, dh, d_gate=None, d_up=None, d_gate_absmax_bits=None, d_up_absmax_bits=None):
     """(d_gate, d_up, their maximum words) for the upstream gradient dh of h = silu(gate) * up."""
+    native = _bind_calls() if _calls is None else _calls
+    if native:
+        done = native.swiglu_bf16_backward(gate, up, dh, d_gate, d_up, d_gate_absmax_bits, d_up_absmax_bits)
+        if done is not None:
+            return done
     import torch
     L = load()
     rows, cols = gate.shape
@@ -231,6 +275,11 @@ def swiglu_bf16_backward(gate, up, dh, d_gate=None, d_up=None, d_gate_absmax_bit
 
 def add_rmsnorm_bf16(x, gamma, eps, delta=None, h=None, y=None, absmax_bits=None):
     """(h, y, max word): h = x + delta (x itself if delta is None), y = rmsnorm(h) * gamma, max|y| as BF16 bits."""
+    native = _bind_calls() if _calls is None else _calls
+    if native:
+        done = native.add_rmsnorm_bf16(x, gamma, eps, delta, h, y, absmax_bits)
+        if done is not None:
+            return done
     import torch
     L = load()
     rows, cols = x.shape
@@ -252,6 +301,11 @@ def add_rmsnorm_bf16(x, gamma, eps, delta=None, h=None, y=None, absmax_bits=None
 
 def rmsnorm_bf16_backward(h, gamma, dy, eps, d_res=None, d_h=None, absmax_bits=None):
     """(d_h, max word) for the upstream gradient dy of rmsnorm(h) * gamma, plus the residual-path gradient d_res."""
+    native = _bind_calls() if _calls is None else _calls
+    if native:
+        done = native.rmsnorm_bf16_backward(h, gamma, dy, eps, d_res, d_h, absmax_bits)
+        if done is not None:
+            return done
     import torch
     L = load()
     rows, cols = h.shape
@@ -312,6 +366,11 @@ def weight_autoscale_init(w, state, wq=None, wq_t=None, want_transpose=False, wo
 
 def weight_autoscale_cast(w, m, v, g, args, state, wq=None, wq_t=None, want_transpose=False, workspace=None):
     """One fused AdamW + scale prediction + FP8 cast step; w, m, v float32 in place."""
+    native = _bind_calls() if _calls is None else _calls
+    if native:
+        done = native.weight_autoscale_cast(w, m, v, g, args, state, wq, wq_t, want_transpose, workspace)
+        if done is not None:
+            return done
     import torch
     L = load()
     rows, cols = w.shape
@@ -333,6 +392,11 @@ def weight_autoscale_cast(w, m, v, g, args, state, wq=None, wq_t=None, want_tran
 def gemm_fp8_mx(a_q, a_e, a_s, b_q, b_e, b_s, out=None, out_dtype=None, accumulate=False):
     """out[m,n] (+)= a_s*b_s*sum_k a[m,k] 2^(ae-127) b[n,k] 2^(be-127); a_q [M,K], b_q [N,K] uint8 device tensors,
     a_e/b_e uint8 [.,K/32] or None, a_s/b_s float32 device scalars."""
+    native = _bind_calls() if _calls is None else _calls
+    if native and (out_dtype is None or out is not None):
+        done = native.gemm_fp8_mx(a_q, a_e, a_s, b_q, b_e, b_s, out, accumulate)
+        if done is not None:
+            return done
     import torch
     L = load()
     M, K = a_q.shape

@@ -1,12 +1,15 @@
-"""Build libmoss_hip.so (gfx950) in-tree with hipcc.  `python -m paper_2511_05811_amd.build`."""
+"""Build libmoss_hip.so (gfx950) in-tree with hipcc, and the native calls of the binding, _moss_calls.so, with the host
+compiler.  `python -m paper_2511_05811_amd.build`."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(os.path.dirname(PKG), "include")
 LIB = os.path.join(PKG, "libmoss_hip.so")
+CALLS = os.path.join(PKG, "_moss_calls.so")
 SOURCES = ["moss_api.hip", "moss_quant.hip", "moss_weight.hip", "moss_gemm.hip", "moss_gemm_big.hip", "moss_gemm_mid.hip", "moss_swiglu.hip", "moss_rmsnorm.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -27,7 +30,22 @@ def build(verbose=False):
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err.strip():
         print(err, file=sys.stderr)
+    build_calls(verbose)
     return LIB
+
+
+def build_calls(verbose=False):
+    """_moss_calls.so: needs torch's headers and links against the torch that is installed here."""
+    import torch
+    home = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-I", INCLUDE, "-isystem", os.path.join(home, "include"), "-isystem", sysconfig.get_paths()["include"], "-o", CALLS,
+           os.path.join(CSRC, "moss_calls.cpp"), "-L", os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd))
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("building _moss_calls failed:\n" + res.stderr)
 
 
 if __name__ == "__main__":

@@ -16,7 +16,8 @@
 //    fetch of X) folds the partials and converts.
 #include <atomic>
 #include <chrono>
-#include <random>
+
+#include <unistd.h>
 
 #include "moss_internal.h"
 
@@ -1144,12 +1145,15 @@ int groups_per_cu(const void *fn, int threads, std::atomic<int> &cached)
 }
 
 // The number of a call whose workgroups meet in slots: 48 bits, never zero, never used again by this process; it starts at a
-// random place, so that memory which another process left behind cannot hold it.
+// place that depends on time and process (mixed as in splitmix64), so that memory which another process left behind does not
+// hold it.
 uint64_t next_call()
 {
     static std::atomic<uint64_t> last{[] {
-        std::random_device rd;
-        return ((uint64_t)rd() << 32) ^ rd() ^ (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();
+        uint64_t z = (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() + ((uint64_t)getpid() << 40);
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        return z ^ (z >> 31);
     }()};
     uint64_t c;
     do c = (last.fetch_add(1) + 1) & 0xFFFFFFFFFFFFull;
