@@ -15,6 +15,13 @@ __device__ __forceinline__ void dma16(const uint8_t *base, uint32_t off, uint32_
                  :: "v"(off), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
 
+// the same to lds_addr + at, which is added in the move to M0 (`at` is a constant once loops are unrolled)
+__device__ __forceinline__ void dma16_at(const uint8_t *base, uint32_t off, uint32_t lds_addr, int at)
+{
+    asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :: "v"(off), "s"(base), "s"(lds_addr), "i"(at) : "memory", "m0", "scc");
+}
+
 template <int N> __device__ __forceinline__ void wait_vmcnt()
 {
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");

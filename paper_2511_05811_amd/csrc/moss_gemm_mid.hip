@@ -53,16 +53,17 @@ struct MidShape {
     static constexpr int kSlot = KS * kGroupBytes;
     static constexpr int kPanel = SLOTS * kSlot;                       // byte offset of the exponent area
     static constexpr int kReduce = kBM * kBN * 4 * KS;                 // partial sums (they reuse the slots and the area)
-    static constexpr int kPieces = kRows / 8 / (WM * WN);              // 8-row copies per wave and stage
+    static constexpr int kPA = kBM / 8 / (WM * WN), kPB = kBN / 8 / (WM * WN);   // 8-row copies of a, of b per wave and stage
+    static constexpr int kPieces = kPA + kPB;
     static_assert(WM * WN * KS * 64 == kMidThreads, "four waves");
-    static_assert(kRows % (16 * WM * WN) == 0, "an even number of whole copies per wave");
+    static_assert(kBM % (16 * WM * WN) == 0 && kBN % (16 * WM * WN) == 0, "an even number of whole copies per wave and operand");
 };
 
 template <int MI, int NJ, int WM, int WN, int KS, int SLOTS, bool HAS_BE>
 __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
 {
     using S = MidShape<MI, NJ, WM, WN, KS, SLOTS>;
-    constexpr int kBM = S::kBM, kBN = S::kBN, kPieces = S::kPieces;
+    constexpr int kBM = S::kBM, kBN = S::kBN, kPA = S::kPA, kPieces = S::kPieces;
     constexpr bool kAlone = WM * WN == 1;        // a group is one wave: nothing shared inside the loop
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -75,48 +76,57 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
 
     const float scale = (*p.a_s) * (*p.b_s);
 
-    // Workgroups are dealt round-robin to the 8 XCDs: each XCD gets a contiguous range of tiles, tile rows first, so that
-    // the tiles that share rows of b run behind one L2.
+    // Workgroups are dealt round-robin to the 8 XCDs: each XCD gets a contiguous range of tiles, in bands of 8 tile rows walked
+    // column by column, so that the tiles it works on at a time form a block that shares rows of a and of b in its L2 (tile
+    // rows to the end first: 4096 x 2048 x 4096 in 128 x 128 tiles 55 us, in bands 47; one band where there are fewer).
     int tm, tn;
     {
         const uint32_t total = (uint32_t)p.tiles_m * (uint32_t)p.tiles_n, q = total >> 3, r = total & 7;
         const uint32_t xcd = blockIdx.x & 7, pid = xcd * q + (xcd < r ? xcd : r) + (blockIdx.x >> 3);
-        tn = __builtin_amdgcn_readfirstlane((int)(pid / (uint32_t)p.tiles_m));
-        tm = (int)pid - tn * p.tiles_m;
+        constexpr uint32_t kBand = 8;
+        const uint32_t rows = (uint32_t)p.tiles_m, band = pid / (kBand * (uint32_t)p.tiles_n), rem = pid - band * kBand * (uint32_t)p.tiles_n;
+        const uint32_t here = rows - band * kBand < kBand ? rows - band * kBand : kBand;
+        tn = __builtin_amdgcn_readfirstlane((int)(rem / here));
+        tm = __builtin_amdgcn_readfirstlane((int)(band * kBand + rem % here));
     }
     const int64_t m0 = (int64_t)tm * kBM, n0 = (int64_t)tn * kBN;
     const uint8_t *a_base = p.a_q + m0 * K, *b_base = p.b_q + n0 * K;
     const int last_a = (int)(M - m0 < kBM ? M - m0 : kBM) - 1, last_b = (int)(N - n0 < kBN ? N - n0 : kBN) - 1;
 
-    // This lane's byte offsets of the wave's copies: piece x covers 8 rows of the group's stage (a rows first), the lane
-    // fetches the 16-byte chunk that its place in the swizzled row holds.  Rows beyond the matrix repeat the last row.
+    // This lane's byte offsets of the wave's copies: piece x covers 8 rows of a (x < kPA) or of b, the lane fetches the 16-byte
+    // chunk that its place in the swizzled row holds.  Rows beyond the matrix repeat the last row.
     uint32_t off[kPieces];
     uint32_t chunk[2];                           // (pieces of even and of odd number swizzle differently)
 #pragma unroll
     for (int x = 0; x < 2; x++) chunk[x] = (uint32_t)((lane & 7) ^ ((x * 4 + (lane >> 4)) & 7)) * 16;
 #pragma unroll
     for (int x = 0; x < kPieces; x++) {
-        const int pc = wg * kPieces + x, row = pc * 8 + (lane >> 3);
-        const bool is_a = pc * 8 < kBM;          // (kBM % 8 == 0: the same for all lanes)
-        const int r = is_a ? (row < last_a ? row : last_a) : (row - kBM < last_b ? row - kBM : last_b);
-        off[x] = (uint32_t)r * (uint32_t)K + chunk[x & 1];
+        const int row = (x < kPA ? wg * kPA + x : wg * S::kPB + x - kPA) * 8 + (lane >> 3), last = x < kPA ? last_a : last_b;
+        off[x] = (uint32_t)(row < last ? row : last) * (uint32_t)K + chunk[x & 1];
     }
-    // Copies of a stage into a slot: the bases are worked out once per stage, so that a copy is two instructions.  Stage
-    // C - 1 of a K that ends inside it is copied in one go, with offsets clamped into the row.
+    // Copies of a stage into a slot.  Stage C - 1 of a K that ends inside it is copied in one go, with offsets clamped into the
+    // row.
     const uint32_t tail = (uint32_t)(K - (int64_t)(C - 1) * kMidK);      // bytes of the last stage that exist
     struct Bases {
         const uint8_t *a, *b;
-        uint32_t dst;
+        uint32_t dst_a, dst_b;
     };
-    auto bases = [&](int c, int slot) {
-        return Bases{a_base + (int64_t)c * kMidK, b_base + (int64_t)c * kMidK,
-                     lds0 + (uint32_t)(slot * S::kSlot + ks * S::kGroupBytes + wg * kPieces * 1024)};
+    const uint32_t dst_a0 = lds0 + (uint32_t)(ks * S::kGroupBytes + wg * kPA * 1024);
+    const uint32_t dst_b0 = lds0 + (uint32_t)(ks * S::kGroupBytes + kBM * kMidK + wg * S::kPB * 1024);
+    auto bases = [&](int c, uint32_t slot_at) {
+        return Bases{a_base + (int64_t)c * kMidK, b_base + (int64_t)c * kMidK, dst_a0 + slot_at, dst_b0 + slot_at};
     };
-    auto copy_piece = [&](const Bases &t, int x) { dma16((wg * kPieces + x) * 8 < kBM ? t.a : t.b, off[x], t.dst + x * 1024); };
+    auto copy_piece = [&](const Bases &t, int x) {
+        if (x < kPA) dma16_at(t.a, off[x], t.dst_a, x * 1024);
+        else dma16_at(t.b, off[x], t.dst_b, (x - kPA) * 1024);
+    };
     auto copy_tail = [&](const Bases &t) {
 #pragma unroll
-        for (int x = 0; x < kPieces; x++)
-            dma16((wg * kPieces + x) * 8 < kBM ? t.a : t.b, chunk[x & 1] < tail ? off[x] : off[x] - chunk[x & 1], t.dst + x * 1024);
+        for (int x = 0; x < kPieces; x++) {
+            const uint32_t o = chunk[x & 1] < tail ? off[x] : off[x] - chunk[x & 1];
+            if (x < kPA) dma16_at(t.a, o, t.dst_a, x * 1024);
+            else dma16_at(t.b, o, t.dst_b, (x - kPA) * 1024);
+        }
     };
     auto is_tail = [&](int c) { return tail < (uint32_t)kMidK && c == C - 1; };
 
@@ -247,7 +257,7 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
 #pragma unroll
         for (int s = 0; s < SLOTS; s++)
             if (s < n) {
-                const Bases t = bases(cb + c0 + s, s);
+                const Bases t = bases(cb + c0 + s, s * S::kSlot);
                 if (is_tail(cb + c0 + s)) {
                     copy_tail(t);
                 } else {
@@ -263,15 +273,75 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
         // One barrier per stage.  At the top of iteration `it` the wave holds the fragments of its stage `it`: behind
         // the barrier every wave of the group does, so that stage's slot may be refilled, and everyone's part of stage
         // it + 1 has landed.  The reads of its fragments and the copies of stage it + SLOTS are dealt out between the
-        // matrix instructions of stage `it`.
+        // matrix instructions of stage `it`, the reads over the first three quarters of them, so that the last have arrived
+        // at the next barrier.
+        //
+        // There are two copies of an iteration.  With one wave per SIMD whatever runs between two matrix instructions beyond
+        // their 64 clocks leaves the matrix pipe idle, and with everything that can happen at either end of K asked
+        // for on the way (a stage to refill with? which of the waits? the last stage?) that was as much again: 8 matrix
+        // instructions of 128 x 128 took 0.44 us without any reads and copies, of which they themselves are 0.21.  So the
+        // iterations in the middle, which always refill and never see the last stage, ask nothing.
         Stage f0, f1;
-        int slot = 0;
+        uint32_t slot_at = 0;                     // byte offset of the slot of stage `it`
+        constexpr uint32_t kEnd = SLOTS * S::kSlot;
         if (n > 0) {
             uint32_t ra[MI], rb[NJ];
             read_exponents(ra, rb, c0);
 #pragma unroll
             for (int x = 0; x < kReads; x++) read_piece(f0, 0, x);
             shift_exponents(f0, ra, rb);
+        }
+        constexpr int kMat = 2 * MI * NJ, kReadMat = kMat - kMat / 4;
+        // the matrix instructions of a stage, and between them what the next ones need
+        auto stage = [&](Stage &f, Stage &next, const Bases &t, uint32_t next_at, const uint32_t (&ra)[MI], const uint32_t (&rb)[NJ], bool refill) {
+#pragma unroll
+            for (int q = 0; q < kMat; q++) {
+                const int s = q / (MI * NJ), i = q % (MI * NJ) / NJ, j = q % NJ;
+                multiply(s, acc[i][j], f.b[s][j], f.a[s][i], f.sb[j], f.sa[i]);
+                if (q < kReadMat) {
+#pragma unroll
+                    for (int x = q * kReads / kReadMat; x < (q + 1) * kReads / kReadMat; x++) read_piece(next, (int)next_at, x);   // (behind the last stage: read and not used)
+                }
+#pragma unroll
+                for (int x = q * kPieces / kMat; x < (q + 1) * kPieces / kMat; x++)
+                    if (refill) copy_piece(t, x);
+                if (q == kMat / 2) shift_exponents(next, ra, rb);
+                pin();
+            }
+        };
+        // iterations that refill a slot with a whole stage, an even number of them
+        const bool ends_here = tail < (uint32_t)kMidK && cb + c0 + n == C;
+        int middle = n - SLOTS - (ends_here ? 1 : 0);
+        middle = middle > 0 ? middle & ~1 : 0;
+        Bases t = bases(cb + c0 + SLOTS, 0);
+        uint32_t at_a = (uint32_t)((c0 + 1) * (kBM + 1)), at_b = (uint32_t)((c0 + 1) * (kBN + 1));      // exponents of stage it + 1
+        auto middle_step = [&](Stage &f, Stage &next) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            wait_vmcnt<(SLOTS - 2) * kPieces>();
+            if (!kAlone) {
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            uint32_t ra[MI], rb[NJ];
+#pragma unroll
+            for (int i = 0; i < MI; i++) ra[i] = area_a[at_a + wm * 32 * MI + i * 32 + i32];
+#pragma unroll
+            for (int j = 0; j < NJ; j++) rb[j] = HAS_BE ? area_b[at_b + wn * 32 * NJ + j * 32 + i32] : 0x7F7F7F7Fu;
+            const uint32_t next_at = slot_at + S::kSlot == kEnd ? 0 : slot_at + S::kSlot;
+            t.dst_a = dst_a0 + slot_at;
+            t.dst_b = dst_b0 + slot_at;
+            asm volatile("s_nop 4" ::: "memory");    // vector ALU write -> operand of a matrix instruction
+            stage(f, next, t, next_at, ra, rb, true);
+            t.a += kMidK;
+            t.b += kMidK;
+            at_a += kBM + 1;
+            at_b += kBN + 1;
+            slot_at = next_at;
+        };
+        int it = 0;
+        for (; it < middle; it += 2) {
+            middle_step(f0, f1);
+            middle_step(f1, f0);
         }
         auto step = [&](Stage &f, Stage &next, int it) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -280,7 +350,7 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
             }
-            const int after = slot + 1 == SLOTS ? 0 : slot + 1;
+            const uint32_t next_at = slot_at + S::kSlot == kEnd ? 0 : slot_at + S::kSlot;
             if (it < n) {
                 const int c = cb + c0 + it;
                 if (is_tail(c)) {
@@ -295,29 +365,16 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
                                     for (int v = 0; v < 4; v++) f.a[s][i][4 * half + v] = 0;
                 }
                 const bool last = it + SLOTS < n && is_tail(c + SLOTS), refill = it + SLOTS < n && !last;
-                const Bases t = bases(c + SLOTS, slot);
-                const int so = after * S::kSlot;
+                const Bases t = bases(c + SLOTS, slot_at);
                 uint32_t ra[MI], rb[NJ];
                 read_exponents(ra, rb, it + 1 < n ? c0 + it + 1 : c0);
                 asm volatile("s_nop 4" ::: "memory");    // vector ALU write -> operand of a matrix instruction
-                constexpr int kMat = 2 * MI * NJ;
-#pragma unroll
-                for (int q = 0; q < kMat; q++) {
-                    const int s = q / (MI * NJ), i = q % (MI * NJ) / NJ, j = q % NJ;
-                    multiply(s, acc[i][j], f.b[s][j], f.a[s][i], f.sb[j], f.sa[i]);
-#pragma unroll
-                    for (int x = q * kReads / kMat; x < (q + 1) * kReads / kMat; x++) read_piece(next, so, x);   // (behind the last stage: read and not used)
-#pragma unroll
-                    for (int x = q * kPieces / kMat; x < (q + 1) * kPieces / kMat; x++)
-                        if (refill) copy_piece(t, x);
-                    if (q == kMat / 2) shift_exponents(next, ra, rb);
-                    pin();
-                }
+                stage(f, next, t, next_at, ra, rb, refill);
                 if (last) copy_tail(t);
             }
-            slot = after;
+            slot_at = next_at;
         };
-        for (int it = 0; it < per; it += 2) {
+        for (; it < per; it += 2) {
             step(f0, f1, it);
             if (it + 1 < per) step(f1, f0, it + 1);
         }

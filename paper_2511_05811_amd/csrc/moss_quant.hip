@@ -1217,7 +1217,7 @@ static int64_t meet_tiles(int64_t rows, int64_t cols, int k)
 static int tile_meet_waves_log2(int64_t rows, int64_t cols)
 {
     int k = 0;
-    while (k < 2 && meet_tiles(rows, cols, k) > 256) k++;
+    while (k < 2 && meet_tiles(rows, cols, k) > (k == 0 ? 256 : 192)) k++;
     return meet_tiles(rows, cols, k) < 512 ? k : -1;
 }
 
