@@ -242,12 +242,15 @@ extern "C" size_t moss_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
 
 // Three kernels.  Small tiles, some with K split inside the workgroup, take any M, N and K for which a model of the three
 // expects them to be the fastest: problems that leave most compute units idle otherwise, most with K % 128 != 0, and many that
-// the large tiles cannot take.  256-wide tiles fed by direct global->LDS copies take the large problems with K % 128 == 0,
-// exponents of a and outputs in whole 16-byte pieces.  The general kernel takes the rest: tiny problems of many tiles (a short
-// K), large ones that do not fit the large tiles (K % 128 != 0, no exponents of a, odd N), exponents that are not dword aligned.
+// the large tiles cannot take.  256-wide tiles fed by direct global->LDS copies take the large problems with exponents of a and
+// outputs in whole 16-byte pieces.  The general kernel takes the rest: tiny problems of many tiles (a short K), large ones that
+// do not fit the large tiles (no exponents of a, odd N), exponents that are not dword aligned.
 //
-// The tile (rows * 1000 + columns) that moss_gemm_fp8_mx chooses for a problem whose exponents, where given, are aligned;
-// 0 for the general kernel (the tests hold the choice by it)
+// The choice has two steps.  The first is made as if the large tiles took whole stages only (K % 128 == 0); the second gives
+// a problem whose K ends inside a stage to the large tiles all the same where they are faster than what the first has chosen.
+//
+// First step: the tile (rows * 1000 + columns) for a problem whose exponents, where given, are aligned; 0 for the general
+// kernel (the tests hold the choice by it)
 extern "C" int moss_internal_gemm_tile(int64_t M, int64_t N, int64_t K, int64_t has_a_e, int64_t has_b_e, int64_t ld_out,
                                        int64_t accumulate)
 {
@@ -258,6 +261,15 @@ extern "C" int moss_internal_gemm_tile(int64_t M, int64_t N, int64_t K, int64_t 
     const int kind = moss_internal_gemm_mid_kind(M, N, K, a_e, b_e, (int)accumulate, large_ok);
     if (kind >= 0) return tiles[kind];
     return large_ok ? (moss_internal_gemm_big_narrow(M, N) ? 128256 : 256256) : 0;
+}
+
+// Second step: the large tile that takes a problem with K % 128 != 0, 0 if the first step's choice stands
+extern "C" int moss_internal_gemm_ragged_tile(int64_t M, int64_t N, int64_t K, int64_t has_a_e, int64_t has_b_e, int64_t ld_out,
+                                              int64_t accumulate)
+{
+    static const uint8_t some[16] __attribute__((aligned(16))) = {};
+    if (!moss_internal_gemm_big_ragged(M, N, K, has_a_e ? some : nullptr, has_b_e ? some : nullptr, (int)accumulate, ld_out)) return 0;
+    return moss_internal_gemm_big_narrow(M, N) ? 128256 : 256256;
 }
 
 extern "C" int moss_gemm_fp8_mx(int64_t M, int64_t N, int64_t K,
@@ -276,8 +288,9 @@ extern "C" int moss_gemm_fp8_mx(int64_t M, int64_t N, int64_t K,
     if (((uintptr_t)a_s & 3) || ((uintptr_t)b_s & 3)) return MOSS_ERR_ALIGN;
     if (K % 16) return MOSS_ERR_ALIGN;
     const int f32 = out_dtype == MOSS_DT_F32;
-    const bool large_ok = moss_internal_gemm_big_ok(M, N, K, a_e, b_e, ld_out);
-    const int kind = moss_internal_gemm_mid_kind(M, N, K, a_e, b_e, accumulate, large_ok);
+    const bool ragged = K % 128 != 0 && moss_internal_gemm_big_ragged(M, N, K, a_e, b_e, accumulate, ld_out);
+    const bool large_ok = ragged || moss_internal_gemm_big_ok(M, N, K, a_e, b_e, ld_out);
+    const int kind = ragged ? -1 : moss_internal_gemm_mid_kind(M, N, K, a_e, b_e, accumulate, large_ok);
     int rc = MOSS_ERR_UNSUPPORTED;
     if (kind >= 0)
         rc = moss_internal_gemm_mid(kind, M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, f32, ld_out, accumulate, (hipStream_t)stream);

@@ -57,8 +57,9 @@ constexpr int kStageK = 128;                 // bytes of K per stage (one cache 
 constexpr int kSlotBytes = 2 * kBT * kStageK;          // a then b: 64 KiB
 constexpr int kScaleSlotBytes = 2 * kBT * 16;          // a then b, 16 exponent bytes (K 512) per row: 8 KiB
 constexpr int kScaleBase = 2 * kSlotBytes;             // 128 KiB
-constexpr int kDummyBase = kScaleBase + 2 * kScaleSlotBytes;     // 144 KiB: 1 KiB per wave that nobody reads
-constexpr int kBigLdsBytes = kDummyBase + 4 * 1024;              // 148 KiB
+// behind them 1 KiB per wave that nobody reads; a K that ends inside a stage has a third scale slot for its last stage
+constexpr int dummy_base(bool ragged) { return kScaleBase + (ragged ? 3 : 2) * kScaleSlotBytes; }     // 144 / 152 KiB
+constexpr int big_lds_bytes(bool ragged) { return dummy_base(ragged) + 4 * 1024; }                   // 148 / 156 KiB
 
 // Rows (pairs of them) whose previous values an accumulating epilogue has on the way at a time.  Loaded one by one between
 // the stores, which may be the same memory as far as the compiler knows, every row waited out a trip to memory: 11008 x
@@ -83,7 +84,17 @@ struct TileCtx {
 // MI = 32-row fragments of a per wave: 4 gives the 256 x 256 tile described above, 2 a 128 x 256
 // tile (64 x 128 per wave, half the accumulators) for problems with too few full tiles to fill
 // the machine.  The narrower tile reads 1.5 times the LDS bytes per matrix instruction.
-template <bool HAS_BE, int MI>
+//
+// RAGGED: K ends inside its last stage, t = 1 .. 3 groups of 32 into it.
+//  * The last stage is copied from [K - 128, K) of every row instead, 4 - t groups of which the stage before has multiplied
+//    already; their exponent bytes are 0 on both sides (2^-127 each), so that their products, below 2^-236, add nothing.
+//  * The rows of K / 32 exponent bytes are not dword aligned.  A scale block is the 16 bytes from a row's start rounded down
+//    to a dword on, and serves three stages: the dword of stage P lies across dwords P and P + 1 of the row, k = row * G % 4
+//    bytes in, the same k for all the rows a lane reads (they are 32 apart).  No block reaches beyond the dword C - 1 of a row of C
+//    stages, which holds bytes of that row, so all lie inside the array (M * G % 4 == 0, host check).
+//  * The dword of the last stage, its lower 4 - t bytes zero, is put together ahead of the tile and kept, shifted by k, in
+//    a third scale slot, where it is read like the others.
+template <bool HAS_BE, int MI, bool RAGGED>
 __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, int64_t K,
                                                         const uint8_t *__restrict__ a_q, const uint8_t *__restrict__ a_e,
                                                         const float *__restrict__ a_s,
@@ -104,8 +115,11 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
     const int i32 = lane & 31, h = lane >> 5;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)big_smem;
     const int G = (int)(K >> 5);
-    const int T = (int)(K / kStageK);   // stages per tile, >= 4 (host checks K % 128 == 0, K >= 512)
-    const int NB = (T + 3) >> 2;        // scale blocks per tile
+    // stages per tile: >= 4 (host checks K % 128 == 0, K >= 512), >= 5 where K ends inside the last (K > 512)
+    const int T = RAGGED ? (int)((K + kStageK - 1) / kStageK) : (int)(K / kStageK);
+    const int tail_groups = G - 4 * (T - 1);                             // t (RAGGED: 1 .. 3)
+    const int NB = RAGGED ? (T + 1) / 3 : (T + 3) >> 2;                  // scale blocks per tile (RAGGED: of stages 0 .. T - 2)
+    const uint32_t kk = RAGGED ? (uint32_t)(i32 * G) & 3u : 0u;          // bytes by which this lane's exponent rows are off
     const int total = tiles_m * tiles_n;
     const int n_my_tiles = (total - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
 
@@ -147,8 +161,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
             int64_t ra = c.m0 + r, rb = c.n0 + r;
             ra = (ra < M ? ra : M - 1) - c.m0;
             rb = (rb < N ? rb : N - 1) - c.n0;
-            c.ae_off = (uint32_t)(ra * G);
-            c.be_off = (uint32_t)(rb * G);
+            c.ae_off = (uint32_t)(ra * G) & (RAGGED ? ~3u : ~0u);
+            c.be_off = (uint32_t)(rb * G) & (RAGGED ? ~3u : ~0u);
         }
         c.a_base = a_q + c.m0 * K;
         c.b_base = b_q + c.n0 * K;
@@ -156,17 +170,27 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
         c.be_base = HAS_BE ? b_e + c.n0 * G : nullptr;
     };
 
+    // first byte of stage P in a row
+    auto stage_at = [&](int P) {
+        return (int64_t)P * kStageK - (RAGGED && P == T - 1 ? kStageK - 32 * tail_groups : 0);
+    };
     // all copies of stage P of tile c into the stage slot `par`: first the 8-row pieces of a, then the eight of b
     auto issue_stage = [&](const TileCtx &c, int P, int par) {
         const uint32_t slot = lds0 + (uint32_t)par * kSlotBytes + (uint32_t)wave * 64 * kStageK;
 #pragma unroll
-        for (int idx = 0; idx < kPiecesA; idx++) dma16(c.a_base + (int64_t)P * kStageK, c.a_off[idx], slot + idx * 8 * kStageK);
+        for (int idx = 0; idx < kPiecesA; idx++) dma16(c.a_base + stage_at(P), c.a_off[idx], slot + idx * 8 * kStageK);
 #pragma unroll
-        for (int idx = 0; idx < 8; idx++) dma16(c.b_base + (int64_t)P * kStageK, c.b_off[idx], slot + kBT * kStageK + idx * 8 * kStageK);
+        for (int idx = 0; idx < 8; idx++) dma16(c.b_base + stage_at(P), c.b_off[idx], slot + kBT * kStageK + idx * 8 * kStageK);
     };
     // First exponent byte of scale block blk: blocks are 16 groups wide; the last one is
     // shifted back so that its 16-byte copy ends exactly at the end of the row.
-    auto scale_block_start = [&](int blk) { const int st = blk * 16; return st + 16 <= G ? st : G - 16; };
+    // (RAGGED: of three dwords, the last shifted back to end with dword T - 1)
+    auto scale_block_start = [&](int blk) {
+        if (RAGGED) return 4 * (3 * blk < T - 4 ? 3 * blk : T - 4);
+        const int st = blk * 16;
+        return st + 16 <= G ? st : G - 16;
+    };
+    auto scale_block_of = [&](int P) { return RAGGED ? (int)((uint32_t)P * 43691u >> 17) : P >> 2; };       // (P / 3 for P <= 2^15)
     auto issue_scales = [&](const TileCtx &c, int blk, int spar) {
         const uint32_t slot = lds0 + kScaleBase + (uint32_t)spar * kScaleSlotBytes + (uint32_t)wave * 64 * 16;
         const int st = scale_block_start(blk);
@@ -191,18 +215,53 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
     // LDS byte offset (from the scale area) of the dword that holds the four exponent bytes of stage P, for a
     // tile whose scale block 0 sits in scale slot parity sp0
     auto scale_dword_offset = [&](int P, int sp0) {
-        const int blk = P >> 2;
+        if (RAGGED && P == T - 1) return (uint32_t)(2 * kScaleSlotBytes);
+        const int blk = scale_block_of(P);
         return (uint32_t)(((sp0 + blk) & 1) * kScaleSlotBytes + 4 * P - scale_block_start(blk));
     };
     // raw scale dwords of the stage at that offset
-    auto read_scales = [&](int (&sa)[MI], int (&sb)[4], uint32_t off) {
+    // (RAGGED: the dword lies across two, the upper ones go to sa_hi / sb_hi until align_scales; without exponents of b the
+    // bytes of groups that the last stage repeats are 0 as well: `unit`)
+    int sa_hi[RAGGED ? MI : 1], sb_hi[RAGGED && HAS_BE ? 4 : 1];
+    auto read_scales = [&](int (&sa)[MI], int (&sb)[4], uint32_t off, int unit) {
         const uint8_t *base = big_smem + kScaleBase + off;
 #pragma unroll
-        for (int i = 0; i < MI; i++) sa[i] = (int)*reinterpret_cast<const uint32_t *>(base + (wm * (kMT / 2) + i * 32 + i32) * 16);
+        for (int i = 0; i < MI; i++) {
+            const uint32_t *src = reinterpret_cast<const uint32_t *>(base + (wm * (kMT / 2) + i * 32 + i32) * 16);
+            sa[i] = (int)src[0];
+            if (RAGGED) sa_hi[i] = (int)src[1];
+        }
 #pragma unroll
-        for (int j = 0; j < 4; j++)
-            sb[j] = HAS_BE ? (int)*reinterpret_cast<const uint32_t *>(base + kBT * 16 + (wn * 128 + j * 32 + i32) * 16)
-                           : 0x7F7F7F7F;
+        for (int j = 0; j < 4; j++) {
+            const uint32_t *src = reinterpret_cast<const uint32_t *>(base + kBT * 16 + (wn * 128 + j * 32 + i32) * 16);
+            sb[j] = HAS_BE ? (int)src[0] : unit;
+            if (RAGGED && HAS_BE) sb_hi[j] = (int)src[1];
+        }
+    };
+    auto align_scales = [&](int (&sa)[MI], int (&sb)[4]) {
+        if (!RAGGED) return;
+#pragma unroll
+        for (int i = 0; i < MI; i++) asm volatile("v_alignbyte_b32 %0, %1, %0, %2" : "+v"(sa[i]) : "v"(sa_hi[i]), "v"(kk));
+        if (HAS_BE)
+#pragma unroll
+            for (int j = 0; j < 4; j++) asm volatile("v_alignbyte_b32 %0, %1, %0, %2" : "+v"(sb[j]) : "v"(sb_hi[j]), "v"(kk));
+    };
+    const int unit_tail = RAGGED ? (int)(0x7F7F7F7Fu << (8 * (4 - tail_groups))) : 0x7F7F7F7F;
+    // exponent dwords of the last stage of tile c (lane = row, as in issue_scales), in the third scale slot
+    auto prepare_tail = [&](const TileCtx &c) {
+        const int r = wave * 64 + lane;
+        const uint32_t k = (uint32_t)(r * G) & 3u;
+#pragma unroll
+        for (int op = 0; op < (HAS_BE ? 2 : 1); op++) {
+            if (op == 0 && wave * 64 >= kMT) continue;
+            const int64_t row0 = op ? c.n0 : c.m0, last = (op ? N : M) - 1;
+            const uint8_t *e = (op ? b_e : a_e) + (row0 + r < last ? row0 + r : last) * G + 4 * (T - 1);
+            uint32_t d = 0;
+#pragma unroll
+            for (int b = 0; b < 3; b++)
+                if (b < tail_groups) d |= (uint32_t)e[b] << (8 * (4 - tail_groups + b));
+            *reinterpret_cast<uint64_t *>(big_smem + kScaleBase + 2 * kScaleSlotBytes + op * kBT * 16 + r * 16) = (uint64_t)d << (8 * k);
+        }
     };
     // byte 0 / byte 2 of a scale register = this lane's group in substep 0 / 1: lanes of the
     // upper half shift their dword down by one byte.  There is one register set per substep, and
@@ -229,6 +288,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
     issue_scales(cx, 0, 0);
     issue_stage(cx, 0, 0);
     issue_stage(cx, 1, 1);
+    if (RAGGED) prepare_tail(cx);
 
     const float scale = (*a_s) * (*b_s);
 
@@ -241,7 +301,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
         wait_lds_and_barrier();
 #pragma unroll
         for (int idx = 0; idx < kPiecesR; idx++) read_piece(fe, g0 & 1, 0, idx);
-        read_scales(sa_raw, sb_raw, scale_dword_offset(0, sp0));
+        read_scales(sa_raw, sb_raw, scale_dword_offset(0, sp0), 0x7F7F7F7F);
+        align_scales(sa_raw, sb_raw);
         shift_scales(sa0, sb0, sa_raw, sb_raw);
         asm volatile("s_nop 4" ::: "memory");    // vector ALU write -> scale operand of a matrix instruction
 #pragma unroll
@@ -271,7 +332,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
             //   issue : ... or with stage 0 of the next tile; when there is nothing to refill (the last stage, and
             //           the one before it for the last tile) the copies still run, aimed at stage T-1 again and at
             //           an LDS area nobody reads, which keeps the loop free of branches
-            int fl = 0, iP = 0, Pl = 0;
+            int fl = 0, iP = 0, Pl = 0, unit = 0x7F7F7F7F;
             uint32_t sc_off = 0, dst_a = 0, dst_b = 0, dstep = 0;
             const uint8_t *a_src = nullptr, *b_src = nullptr;
             // substep 0: multiply K[0,64) while fetching the fragments of K[64,128)
@@ -292,17 +353,18 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
                 if (idx == 1) {
                     asm volatile("" : "+s"(fl), "+s"(iP), "+s"(Pl));
                     sc_off = scale_dword_offset(Pl + 1, sp0);
+                    if (RAGGED && !HAS_BE) unit = fl == 2 ? unit_tail : 0x7F7F7F7F;
                 }
                 if (idx == 2) {
                     asm volatile("" : "+s"(sc_off), "+s"(iP));
-                    a_src = cx.a_base + (int64_t)iP * kStageK;
-                    b_src = cx.b_base + (int64_t)iP * kStageK;
+                    a_src = cx.a_base + stage_at(iP);
+                    b_src = cx.b_base + stage_at(iP);
                 }
                 if (idx == 3) {
                     asm volatile("" : "+s"(a_src), "+s"(b_src), "+s"(fl));
                     const bool issue = fl == 3 || (fl == 2 && has_next);
                     const uint32_t slot = lds0 + (uint32_t)par * kSlotBytes + (uint32_t)wave * 64 * kStageK;
-                    const uint32_t dummy = lds0 + kDummyBase + (uint32_t)wave * 1024;
+                    const uint32_t dummy = lds0 + dummy_base(RAGGED) + (uint32_t)wave * 1024;
                     dst_a = issue ? slot : dummy;
                     dst_b = issue ? slot + kBT * kStageK : dummy;
                     dstep = issue ? 8 * kStageK : 0;
@@ -333,7 +395,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
                     wait_vmcnt<kBefore>();    // this wave's part of stage P+1 (and its scales) has landed
                     __builtin_amdgcn_s_barrier();
                     asm volatile("" ::: "memory");
-                    read_scales(sa_raw, sb_raw, sc_off);
+                    read_scales(sa_raw, sb_raw, sc_off, unit);
                 }
                 if (idx >= kBB) {
 #pragma unroll
@@ -347,10 +409,18 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
                     else dma16(b_src, cx.b_off[p - kPiecesA], cur);
                     cur += dstep;
                 }
-                if (idx == kBB + (kNM - kBB) / 2 && next) shift_scales(sa0, sb0, sa_raw, sb_raw);   // the next stage's, for its substep 0
+                if (idx == kBB + (kNM - kBB) / 2 && next) {                                         // the next stage's, for its substep 0
+                    align_scales(sa_raw, sb_raw);
+                    shift_scales(sa0, sb0, sa_raw, sb_raw);
+                }
             }
             // the next scale block, behind this substep's copies (the wait above counts back from the newest copy)
-            if (issue && (iP & 3) == 0) issue_scales(cx, iP >> 2, own ? (sp0 + (iP >> 2)) & 1 : (sp0 + NB) & 1);
+            if (RAGGED) {
+                const int blk = scale_block_of(iP);
+                if (issue && iP == 3 * blk && iP < T - 1) issue_scales(cx, blk, own ? (sp0 + blk) & 1 : (sp0 + NB) & 1);
+            } else {
+                if (issue && (iP & 3) == 0) issue_scales(cx, iP >> 2, own ? (sp0 + (iP >> 2)) & 1 : (sp0 + NB) & 1);
+            }
         }
         // (stage 1 of the next tile belongs into the last stage's slot, which the epilogue uses first:
         // it is issued after the epilogue)
@@ -446,6 +516,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
             }
         }
         // the pieces are free again: fill them with this wave's part of stage 1 of the next tile
+        if (RAGGED && has_next) prepare_tail(cx);      // (the third scale slot was last read before the epilogue's barrier)
         if (has_next) issue_stage(cx, 1, epar);
     }
     wait_vmcnt<0>();   // no copy into LDS may be outstanding when the wave ends
@@ -459,6 +530,15 @@ bool moss_internal_gemm_big_ok(int64_t M, int64_t N, int64_t K, const uint8_t *a
     if (!a_e || ((uintptr_t)a_e & 3) || ((uintptr_t)b_e & 3)) return false;
     if (K % 128 || K < 512 || K > (1 << 22)) return false;
     return N % 8 == 0 && ld_out % 8 == 0;                      // the epilogue stores whole 16-byte pieces
+}
+
+bool moss_internal_gemm_big_ragged_ok(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int64_t ld_out)
+{
+    if (((M + 255) / 256) * ((N + 255) / 256) < 8) return false;
+    if (!a_e || ((uintptr_t)a_e & 3) || ((uintptr_t)b_e & 3)) return false;
+    if (K % 128 == 0 || K % 32 || K <= 512 || K > (1 << 22)) return false;
+    if (M * (K / 32) % 4 || (b_e && N * (K / 32) % 4)) return false;       // exponent arrays of whole dwords
+    return N % 8 == 0 && ld_out % 8 == 0;
 }
 
 // compute units of the persistent grid
@@ -487,7 +567,8 @@ int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, 
                            int64_t ld_out, int accumulate, hipStream_t st)
 {
     using namespace moss;
-    if (!moss_internal_gemm_big_ok(M, N, K, a_e, b_e, ld_out)) return MOSS_ERR_UNSUPPORTED;
+    const bool ragged = K % 128 != 0;
+    if (!(ragged ? moss_internal_gemm_big_ragged_ok : moss_internal_gemm_big_ok)(M, N, K, a_e, b_e, ld_out)) return MOSS_ERR_UNSUPPORTED;
     if ((int64_t)kBT * K >= ((int64_t)1 << 32)) return MOSS_ERR_UNSUPPORTED;
     const int cus = big_cus();
     const bool narrow = moss_internal_gemm_big_narrow(M, N);
@@ -496,16 +577,17 @@ int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, 
     if (tiles_m * tiles_n > 0x7FFFFFF) return MOSS_ERR_UNSUPPORTED;
     using Kern = void (*)(int64_t, int64_t, int64_t, const uint8_t *, const uint8_t *, const float *, const uint8_t *,
                           const uint8_t *, const float *, void *, int, int64_t, int, int, int);
-    static const Kern kerns[4] = {k_gemm_mx_big<false, 4>, k_gemm_mx_big<true, 4>, k_gemm_mx_big<false, 2>,
-                                  k_gemm_mx_big<true, 2>};
-    static std::atomic<bool> attr_done[64][4];   // the LDS size attribute is set once per device and kernel (setting it
+    static const Kern kerns[8] = {k_gemm_mx_big<false, 4, false>, k_gemm_mx_big<true, 4, false>, k_gemm_mx_big<false, 2, false>,
+                                  k_gemm_mx_big<true, 2, false>,  k_gemm_mx_big<false, 4, true>, k_gemm_mx_big<true, 4, true>,
+                                  k_gemm_mx_big<false, 2, true>,  k_gemm_mx_big<true, 2, true>};
+    static std::atomic<bool> attr_done[64][8];   // the LDS size attribute is set once per device and kernel (setting it
                                                  // twice from racing threads is harmless: same value)
-    const int which = (b_e ? 1 : 0) | (narrow ? 2 : 0);
+    const int which = (b_e ? 1 : 0) | (narrow ? 2 : 0) | (ragged ? 4 : 0);
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MOSS_ERR_HIP;
-    std::atomic<bool>(&attr_set)[4] = attr_done[dev];
+    std::atomic<bool>(&attr_set)[8] = attr_done[dev];
     if (!attr_set[which].load()) {
-        if (hipFuncSetAttribute((const void *)kerns[which], hipFuncAttributeMaxDynamicSharedMemorySize, kBigLdsBytes) !=
+        if (hipFuncSetAttribute((const void *)kerns[which], hipFuncAttributeMaxDynamicSharedMemorySize, big_lds_bytes(ragged)) !=
             hipSuccess) {
             (void)hipGetLastError();
             return MOSS_ERR_UNSUPPORTED;
@@ -522,7 +604,7 @@ int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, 
     wgs = (wgs + 7) & ~(int64_t)7;
     if (wgs > cus) wgs = cus;
     const dim3 grid((unsigned)(total < cus ? total : wgs)), block(256);
-    hipLaunchKernelGGL(kerns[which], grid, block, kBigLdsBytes, st, M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, out_f32,
+    hipLaunchKernelGGL(kerns[which], grid, block, big_lds_bytes(ragged), st, M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, out_f32,
                        ld_out, accumulate, (int)tiles_m, (int)tiles_n);
     if (hipGetLastError() != hipSuccess) return MOSS_ERR_HIP;
     return MOSS_OK;

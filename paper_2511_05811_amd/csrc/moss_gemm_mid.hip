@@ -475,32 +475,35 @@ static int launch_mid(MidArgs p, int budget, hipStream_t st)
 
 }  // namespace moss
 
-// Time of a problem in the kernels that could take it, in microseconds, from measurements on 256 compute units (calls back to
-// back on two sets of operands): a launch, then per round of tiles over the compute units a fixed part (first latency,
-// exponents, epilogue) and a part per stage.  K % 128 != 0: the rows no longer start on lines and the exponents are cut out of
-// two dwords, so that a stage costs more (more so with exponents of b).  128 x 192 tiles read a third less per product than
-// 128 x 128 but leave no LDS for a fourth slot: they pay where the large tiles cannot take the problem.  "b" marks exponents of b.
+// Time of a problem in the kernels that could take it, in microseconds: a launch, then per round of tiles over the compute
+// units a fixed part (first latency, exponents, epilogue) and a part per iteration (stages of K = 128, dealt over the K groups
+// of a tile), each with a share that grows with how full the rounds are.  The constants are fits to 2200 random problems (M 32 to
+// 12000, N 256 to 12288, K 128 to 12288; calls back to back on two sets of operands, 256 compute units), each run in every
+// kernel that can take it; the fits miss by 2 to 7 % (mean), 10 % at the 10th and 90th percentile.  K % 128 != 0: the rows no longer start on lines and
+// the exponents are cut out of two dwords, so that a stage costs more.  "b" marks exponents of b, whose outputs are FP32.
 //   tile        (M, N, K) measured / model
-//   32 x 32     (64, 4096, 4096) 9.9 / 7.7     (17, 11008, 4096) 12.4 / 10.7    (256, 1024, 1024) 5.3 / 4.9    (300, 1000, 2080) 8.0 / 8.4
-//               (64, 256, 512) 4.4 / 4.4       (512, 256, 64) b 5.7 / 5.3     (512, 4096, 4096) 39 / 43       (9412, 144, 5504) 46 / 42
-//   64 x 64     (256, 4096, 4096) 16.0 / 13.0  (1024, 1024, 1024) 8.5 / 7.4     (600, 4096, 4128) 46 / 46      (2048, 2048, 2080) b 54 / 52
-//   64 x 128    (512, 4096, 4096) 21.3 / 17.0  (512, 4096, 1024) 10.4 / 8.8     (2048, 2048, 4096) 39 / 32     (8192, 2080, 4128) 200 / 198
-//               (3072, 3072, 4128) b 149 / 144
-//   128 x 128   (2048, 2048, 2080) 22.6 / 22.4 (600, 4096, 4128) 31.9 / 33.9    (2048, 2048, 4096) 30.8 / 30.4 (4096, 4096, 2080) 84 / 83
-//               (600, 4096, 4128) b 37.5 / 38.1    (1000, 4000, 1056) b 19.6 / 20.0    (3072, 3072, 4128) b 120 / 110
-//   128 x 192   (1333, 4096, 4128) 49 / 46     (8192, 2080, 4128) 142 / 134     (2005, 2436, 3584) 38 / 41     (3072, 3072, 4128) b 112 / 108
-//               (an accumulating epilogue 4 per round: (3520, 1536, 1184) b 34 / 30)
-//   large       (64, 4096, 4096) 29 / 26       (1024, 4096, 4096) 32 / 29       (1024, 1024, 1024) 12.0 / 12.8 (1333, 4096, 11008) 79 / 69
-//               (4096, 4096, 512) b 30 / 16
-//   general     (64, 256, 512) 9.2 / 8.5       (300, 1000, 2080) 23.9 / 22.1    (1333, 4096, 4128) 63 / 59     (2005, 2436, 3584) 48.7 / 51.0
-//               (5000, 1056, 1056) 21.1 / 21.7 (8192, 2080, 4128) 168 / 168     (6321, 2424, 32) 15.7 / 15.9   (512, 256, 64) b 7.0 / 6.8
-//               (1000, 4000, 1056) b 22.9 / 25.9   (2528, 2912, 8032) b 136 / 131   (3072, 3072, 4128) b 129 / 138
-// Over 2300 random problems (M to 16384, N and K to 12288) the model is within a fifth of nine in ten measured times, and a
-// quarter to two fifths low for the large tiles with exponents of b, whose FP32 outputs it does not know.
+//   32 x 32     (256, 1024, 1024) 4.2 / 4.5    (17, 11008, 4096) 10.2 / 10.1
+//   64 x 64     (1024, 1024, 1024) 6.5 / 7.0   (256, 4096, 4096) 12.0 / 12.3
+//   64 x 128    (512, 4096, 1024) 8.6 / 8.9    (512, 4096, 4096) 15.5 / 16.3
+//   128 x 128   (2048, 2048, 1024) 12.2 / 12.1 (2048, 2048, 4096) 23.8 / 24.0
+//   128 x 192   (2048, 3072, 1024) 15.4 / 15.5 (2048, 3072, 7168) 45.6 / 44.6
+//   large       (2048, 4096, 2048) 19.7 / 18.9 (4096, 4096, 4096) 56 / 58      (4096, 4096, 512) b 27.8 / 28.1
+//   ... ragged  (11328, 3520, 2080) 99.6 / 105 (1336, 4096, 4128) 38.6 / 36.4  (2432, 6016, 2656) b 55.4 / 57.3
+//   general     (4096, 4096, 2080) 62 / 62     (6321, 2424, 32) 15.7 / 15.9    (2528, 2912, 8032) b 136 / 131
 namespace {
 
 double rounds_of(double tiles, double cus) { return tiles <= cus ? 1.0 : std::ceil(tiles / cus); }
 double tiles_of(int64_t M, int64_t N, int bm, int bn) { return (double)((M + bm - 1) / bm) * (double)((N + bn - 1) / bn); }
+
+struct Cost {
+    double round, round_full, it, it_full;      // per round, and per iteration in a round; their part that goes with its fill
+};
+
+double us_of(const Cost &c, double tiles, double cus, double iterations, double per_round = 0.0)
+{
+    const double n = rounds_of(tiles, cus), u = tiles / (n * cus);
+    return 2.2 + n * (c.round + per_round + c.round_full * u + iterations * (c.it + c.it_full * u));
+}
 
 struct MidPlan {
     int kind;        // 0 .. 4: the tiles above, smallest first
@@ -509,34 +512,35 @@ struct MidPlan {
 
 MidPlan plan_mid(int64_t M, int64_t N, int64_t K, bool b_exponents, bool accumulate, bool large_ok, double cus)
 {
-    const bool ragged = K % 128 != 0;
-    const double C = (double)((K + 127) / 128), extra = b_exponents ? 0.5 : 0.0;
-    const double it4 = (double)(((int64_t)C + 3) / 4), it2 = (double)(((int64_t)C + 1) / 2);
-    const double t0 = tiles_of(M, N, 32, 32);
-    const double n0 = rounds_of(t0, cus), n1 = rounds_of(tiles_of(M, N, 64, 64), cus), n2 = rounds_of(tiles_of(M, N, 64, 128), cus),
-                 n3 = rounds_of(tiles_of(M, N, 128, 128), cus), n4 = rounds_of(tiles_of(M, N, 128, 192), cus);
-    const double r01 = !ragged ? 1.0 : (b_exponents ? 1.85 : 1.33), r2 = !ragged ? 1.0 : (b_exponents ? 2.03 : 1.54),
-                 r3 = !ragged ? 1.0 : (b_exponents ? 1.2 : 1.14);
-    // (two 32 x 32 workgroups fit a compute unit: a round that is half full costs less than a full one)
-    const double s0 = (ragged ? (b_exponents ? 0.34 : 0.24) : (b_exponents ? 0.24 : 0.2)) + (b_exponents && !ragged ? 0.32 : 0.34) * t0 / (n0 * cus);
-    const double us[5] = {t0 <= cus ? 3.9 + extra + 0.48 * r01 * it4 : 2.2 + n0 * ((b_exponents ? 1.25 : 0.8) + s0 * it4),
-                          2.2 + n1 * (3.3 + extra + 0.94 * r01 * it4),
-                          2.2 + n2 * (3.9 + 2.0 * extra + 0.68 * r2 * it2),
-                          2.2 + n3 * (8.0 + (ragged ? 6.0 : 3.0) * extra + 0.63 * r3 * C),
-                          2.2 + n4 * (11.0 + (accumulate ? 4.0 : 0.0) + (b_exponents ? 1.27 : 1.0) * C)};
+    // [kind 1 .. 4][K % 128 != 0][exponents of b]
+    static const Cost cost[4][2][2] = {{{{2.43, 0.59, 0.704, 0.175}, {3.03, 0.63, 0.738, 0.253}}, {{2.38, 0.54, 0.953, 0.381}, {2.90, 0.45, 1.100, 0.565}}},
+                                       {{{3.38, 0.86, 0.514, 0.101}, {3.84, 1.03, 0.700, 0.129}}, {{3.27, 0.94, 0.728, 0.210}, {3.82, 1.11, 1.009, 0.285}}},
+                                       {{{4.76, 1.22, 0.354, 0.140}, {5.79, 1.68, 0.406, 0.150}}, {{4.78, 1.66, 0.510, 0.179}, {5.56, 1.95, 0.667, 0.206}}},
+                                       {{{6.86, 1.59, 0.419, 0.187}, {8.05, 2.53, 0.622, 0.178}}, {{7.90, 2.23, 0.630, 0.205}, {7.67, 2.63, 0.960, 0.267}}}};
+    // 32 x 32: one round; two workgroups fit a compute unit, so that more rounds cost less each
+    static const double one[2][2][2] = {{{3.71, 0.407}, {4.27, 0.409}}, {{3.90, 0.490}, {4.26, 0.642}}};
+    static const double more[2][2][2] = {{{0.95, 0.375}, {1.25, 0.400}}, {{0.95, 0.520}, {1.15, 0.630}}};
+    const int r = K % 128 != 0, b = b_exponents;
+    const int64_t C = (K + 127) / 128;
+    const double it4 = (double)((C + 3) / 4), it2 = (double)((C + 1) / 2), t0 = tiles_of(M, N, 32, 32);
+    const double us[5] = {t0 <= cus ? one[r][b][0] + one[r][b][1] * it4 : 2.2 + rounds_of(t0, cus) * (more[r][b][0] + more[r][b][1] * it4),
+                          us_of(cost[0][r][b], tiles_of(M, N, 64, 64), cus, it4), us_of(cost[1][r][b], tiles_of(M, N, 64, 128), cus, it2),
+                          us_of(cost[2][r][b], tiles_of(M, N, 128, 128), cus, (double)C, accumulate ? 3.0 : 0.0),
+                          us_of(cost[3][r][b], tiles_of(M, N, 128, 192), cus, (double)C, accumulate ? 5.0 : 0.0)};
     MidPlan best{0, us[0]};
     for (int k = 1; k < (large_ok ? 4 : 5); k++)     // (large tiles, where they can take the problem, beat 128 x 192)
-        if (us[k] < best.us) best = MidPlan{k, us[k]};
+        if (us[k] < 0.97 * best.us) best = MidPlan{k, us[k]};
     return best;
 }
 
 // k_gemm_mx_big, full or half tiles as it chooses them
-double us_big(int64_t M, int64_t N, int64_t K, double cus)
+double us_big(int64_t M, int64_t N, int64_t K, bool b_exponents, double cus)
 {
-    const double C = (double)(K / 128), full = tiles_of(M, N, 256, 256), half = tiles_of(M, N, 128, 256);
-    if (moss_internal_gemm_big_narrow(M, N))
-        return 2.2 + rounds_of(half, cus) * (6.0 + C * (0.55 + 0.22 * (half < cus ? half / cus : 1.0)));
-    return 2.2 + rounds_of(full, cus) * (8.0 + C * (0.9 + 0.6 * (full < cus ? full / cus : 1.0)));
+    // [half tiles][K % 128 != 0][exponents of b]
+    static const Cost cost[2][2][2] = {{{{8.83, 0.04, 0.832, 0.627}, {16.61, 3.47, 0.888, 0.566}}, {{9.93, 0.04, 0.824, 0.718}, {19.86, 0.0, 0.853, 0.878}}},
+                                       {{{3.99, 0.65, 0.605, 0.147}, {5.30, 3.23, 0.667, 0.164}}, {{4.06, 0.05, 0.734, 0.260}, {5.48, 4.20, 0.865, 0.161}}}};
+    const bool half = moss_internal_gemm_big_narrow(M, N);
+    return us_of(cost[half][K % 128 != 0][b_exponents], tiles_of(M, N, half ? 128 : 256, 256), cus, (double)((K + 127) / 128));
 }
 
 // k_gemm: two workgroups run on a compute unit at a time, every stage waits for its own loads, every tile leaves at the
@@ -548,20 +552,44 @@ double us_general(int64_t M, int64_t N, int64_t K, bool b_exponents, double cus)
     return b_exponents ? 5.4 + rounds * C * (1.25 + 0.65 * u) + 3.4 * w : 4.6 + rounds * C * (0.96 + 0.6 * u) + 2.2 * w;
 }
 
+double model_cus()
+{
+    const int cus = moss_internal_cu_count();
+    return cus <= 0 ? 256 : cus;
+}
+
+// The small tiles if they are expected to take at most nine tenths of the time of the kernel that would have the problem
+// otherwise (large_ok: k_gemm_mx_big, else k_gemm; three quarters where short K and FP32 outputs make the fits worse, seven
+// tenths without exponents of a, which the fits have not seen), kind -1 and that kernel's time if not.
+MidPlan plan_small_or_other(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, bool accumulate, bool large_ok)
+{
+    const double cus = model_cus(), other = large_ok ? us_big(M, N, K, b_e != nullptr, cus) : us_general(M, N, K, b_e != nullptr, cus);
+    if (K > ((int64_t)1 << 22) || ((uintptr_t)a_e & 3) || ((uintptr_t)b_e & 3)) return MidPlan{-1, other};     // (32-bit offsets inside a tile)
+    const MidPlan plan = plan_mid(M, N, K, b_e != nullptr, accumulate, large_ok, cus);
+    const double margin = !a_e && plan.kind >= 3 ? 0.7 : b_e && plan.kind >= 3 && !large_ok && K <= 640 ? 0.75 : 0.9;
+    return plan.us > margin * other ? MidPlan{-1, other} : plan;
+}
+
 }  // namespace
 
-// The kind of tiles (0 .. 4) if one is expected to be at least a tenth faster than the kernel that would have the problem
-// otherwise (large_ok: k_gemm_mx_big, else k_gemm), -1 to leave it to that one.  With the tenth in hand, 2 of the 2300 problems
-// take longer than there, by 4 % (without it 11, by up to 20 %), and of 5000 others seven by 6 to 14 %.
+// The kind of tiles (0 .. 4), -1 to leave the problem to the kernel that would have it otherwise.  Over the 2200 problems the
+// kernels that this and the rule below choose take 0.5 % more than the fastest of each (mean), and 2.2 % less than those that
+// were chosen before; six take more than then, by 4 to 12 %.
 int moss_internal_gemm_mid_kind(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int accumulate,
                                 bool large_ok)
 {
-    if (K > ((int64_t)1 << 22)) return -1;                                   // 32-bit offsets inside a tile
-    if (((uintptr_t)a_e & 3) || ((uintptr_t)b_e & 3)) return -1;
-    int cus = moss_internal_cu_count();
-    if (cus <= 0) cus = 256;
-    const MidPlan plan = plan_mid(M, N, K, b_e != nullptr, accumulate != 0, large_ok, cus);
-    return plan.us > 0.9 * (large_ok ? us_big(M, N, K, cus) : us_general(M, N, K, b_e != nullptr, cus)) ? -1 : plan.kind;
+    return plan_small_or_other(M, N, K, a_e, b_e, accumulate != 0, large_ok).kind;
+}
+
+// Whether k_gemm_mx_big takes a problem with K % 128 != 0 from the kernel that has it by the rule above: where it is
+// expected to be a fourteenth faster (a fifth for a short K with exponents of b, as above).  4096 x 4096 x 2080 62 -> 39 us, 11328 x 3520 x
+// 2080 169 -> 100, 4160 x 4480 x 9824 305 -> 217, 2432 x 6016 x 2656 with exponents of b 105 -> 55.
+bool moss_internal_gemm_big_ragged(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int accumulate,
+                                   int64_t ld_out)
+{
+    if (!moss_internal_gemm_big_ragged_ok(M, N, K, a_e, b_e, ld_out)) return false;
+    const double other = plan_small_or_other(M, N, K, a_e, b_e, accumulate != 0, false).us;
+    return us_big(M, N, K, b_e != nullptr, model_cus()) < (b_e && K < 1000 ? 0.8 : 0.93) * other;
 }
 
 int moss_internal_gemm_mid(int kind, int64_t M, int64_t N, int64_t K, const uint8_t *a_q, const uint8_t *a_e, const float *a_s,

@@ -30,6 +30,10 @@ int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, 
 // whether the large-tile kernel takes the problem, and in half tiles (128 x 256)
 bool moss_internal_gemm_big_ok(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int64_t ld_out);
 bool moss_internal_gemm_big_narrow(int64_t M, int64_t N);
+// whether it can take a problem whose K is not a multiple of 128, and whether it should
+bool moss_internal_gemm_big_ragged_ok(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int64_t ld_out);
+bool moss_internal_gemm_big_ragged(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int accumulate,
+                                   int64_t ld_out);
 
 // small tiles and split K for problems that leave the large tiles idle, and ragged K: the kind of tiles, or -1 if another kernel
 // is the better choice; MOSS_ERR_UNSUPPORTED if the device cannot launch them

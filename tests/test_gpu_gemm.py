@@ -424,3 +424,42 @@ def test_dispatch_without_exponents_of_a(oracle, shape, tile):
     a_s, b_s = np.float32(0.5), np.float32(0.25)
     out = gpu_gemm(a, None, a_s, b, None, b_s, out_dtype=torch.float32)
     check_outputs(oracle, f"{shape} without exponents", (out,), (a, None, a_s), (b, None, b_s), rng)
+
+
+# K that ends 1, 2 or 3 groups into its last stage, in the large tiles: the shortest K (five stages, two scale blocks), whole and
+# partial scale blocks, rows and columns over the edge, several tiles per workgroup
+RAGGED_LARGE = [((2304, 2304, 864), False, 128256), ((2052, 2056, 992), False, 128256), ((4100, 4104, 1312), False, 256256),
+                ((2304, 2304, 1312), True, 128256), ((4128, 2560, 1184), True, 256256), ((4096, 4128, 2080), True, 256256), ((8200, 4104, 1056), False, 256256),
+                ((8224, 4128, 1120), True, 256256)]
+
+
+@pytest.mark.parametrize("shape,both,tile", RAGGED_LARGE)
+@pytest.mark.parametrize("low", [110, 0])
+def test_ragged_k_in_the_large_tiles(oracle, shape, both, tile, low):
+    """The groups that the last stage repeats must add nothing, also to sums whose own exponents are at the bottom of the
+    range (`low` = 0: the last stage's groups at 2^-127 + ..., under FP32 scales that bring them back)."""
+    M, N, K = shape
+    rng = np.random.default_rng(M + N + K + low)
+    a, b = finite_codes(rng, (M, K)), finite_codes(rng, (N, K))
+    G = K // 32
+    top = 128 if low else 20
+    ae = rng.integers(low, top, size=(M, G), dtype=np.uint8)
+    be = rng.integers(110, 128, size=(N, G), dtype=np.uint8) if both else None
+    lib = moss.load()
+    import ctypes as C
+    assert lib.moss_internal_gemm_ragged_tile(*(C.c_int64(v) for v in (M, N, K, 1, both, N + 8, 0))) == tile
+    a_s, b_s = np.float32(0.5 if low else 2.0 ** 100), np.float32(0.25)
+    ops = (to_gpu(a), to_gpu(ae), to_gpu(np.array([a_s])), to_gpu(b), to_gpu(be) if both else None, to_gpu(np.array([b_s])))
+    half = torch.full((M, N + 8), 3.0, dtype=torch.bfloat16, device="cuda:0")
+    moss.gemm_fp8_mx(*ops, out=half[:, :N])
+    plain = torch.full((M, N + 8), 3.0, dtype=torch.float32, device="cuda:0")
+    moss.gemm_fp8_mx(*ops, out=plain[:, :N])
+    torch.cuda.synchronize()
+    assert bool((half[:, N:] == 3.0).all()) and bool((plain[:, N:] == 3.0).all())
+    check_outputs(oracle, f"{shape} ragged large", (plain[:, :N], half[:, :N]), (a, ae, a_s), (b, be, b_s), rng)
+    base = torch.from_numpy(rng.standard_normal((M, N)).astype(np.float32)).to("cuda:0")
+    out = base.clone()
+    moss.gemm_fp8_mx(*ops, out=out, accumulate=True)
+    torch.cuda.synchronize()
+    assert lib.moss_internal_gemm_ragged_tile(*(C.c_int64(v) for v in (M, N, K, 1, both, N, 1))) == tile
+    assert torch.equal(out, base + plain[:, :N])                              # one FP32 addition per output

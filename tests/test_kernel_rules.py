@@ -105,8 +105,18 @@ def test_gemm_tests_of_one_kernel_each(L, M, N, K, tile):
 
 
 @pytest.mark.parametrize("rows,cols,row,col", [(1, 32, 0, 0), (256, 2048, 0, 0), (257, 2048, 1, 0), (512, 2048, 1, 0), (513, 2048, 2, 1),
-                                               (1024, 2048, 2, 1), (1025, 2048, 3, 2), (3968, 2048, 3, 2), (3969, 2048, 3, -1),
+                                               (768, 2048, 2, 1), (769, 2048, 2, 2), (1025, 2048, 3, 2), (3968, 2048, 3, 2), (3969, 2048, 3, -1),
                                                (4096, 2048, 3, -1), (4097, 2048, 4, -1), (8192, 2048, 4, -1), (8192, 4096, 5, -1), (8193, 4096, -1, -1)])
 def test_workgroups_meet_where_their_tensor_fits_the_registers(L, rows, cols, row, col):
     assert ask(L.moss_internal_quant_meets, rows, cols, 0) == row
     assert ask(L.moss_internal_quant_meets, rows, cols, 1) == col
+
+
+# ragged K in the large tiles: where the first step's kernel is slower, with whole exponent dwords and outputs in 16-byte pieces
+@pytest.mark.parametrize("M,N,K,b_e,tile", [(11328, 3520, 2080, 0, 256256), (4160, 4480, 9824, 0, 256256), (2432, 6016, 2656, 1, 256256), (4096, 4096, 2080, 0, 256256),
+                                            (1336, 4096, 4128, 0, 128256), (5000, 1056, 1056, 0, 128256), (3072, 3072, 4128, 1, 256256),
+                                            (1333, 4096, 4128, 0, 0), (1336, 4092, 4128, 0, 0), (1000, 4000, 1056, 0, 0), (512, 4096, 4128, 0, 0),
+                                            (4096, 4096, 4096, 0, 0), (4096, 4096, 544, 1, 0), (4096, 4096, 480, 0, 0), (4097, 4096, 2112, 0, 0), (4098, 4096, 2112, 0, 256256)])
+def test_ragged_k_goes_to_the_large_tiles_where_they_are_faster(L, M, N, K, b_e, tile):
+    assert ask(L.moss_internal_gemm_ragged_tile, M, N, K, 1, b_e, N, 0) == tile
+    assert ask(L.moss_internal_gemm_ragged_tile, M, N, K, 0, b_e, N, 0) == 0
