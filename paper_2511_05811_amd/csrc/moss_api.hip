@@ -1,5 +1,8 @@
-// Status strings and cached device properties of libmoss_hip.so.
+// Status strings, cached device properties and call numbers of libmoss_hip.so.
 #include <atomic>
+#include <chrono>
+
+#include <unistd.h>
 
 #include "moss_internal.h"
 
@@ -15,6 +18,32 @@ int moss_internal_cu_count()
         g_cu_count[dev].store(n);
     }
     return n;
+}
+
+// The numbers start at a place that depends on time and process (mixed as in splitmix64), so that memory which another
+// process left behind does not hold them.
+uint64_t moss_next_call()
+{
+    static std::atomic<uint64_t> last{[] {
+        uint64_t z = (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() + ((uint64_t)getpid() << 40);
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        return z ^ (z >> 31);
+    }()};
+    uint64_t c;
+    do c = (last.fetch_add(1) + 1) & 0xFFFFFFFFFFFFull;
+    while (c == 0);
+    return c;
+}
+
+bool moss_may_number_calls(hipStream_t st)
+{
+    hipStreamCaptureStatus status;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusNone;
 }
 
 extern "C" int moss_device_cu_count(void) { return moss_internal_cu_count(); }

@@ -22,6 +22,13 @@ static inline bool moss_aligned16(const void *p) { return (reinterpret_cast<uint
 
 int moss_internal_cu_count();
 
+// Numbers of calls, for words in a workspace of unknown contents that carry their own validity: a word that holds the number of
+// the call in its upper 48 bits has been written by that call.  Never zero, never used again by this process.
+uint64_t moss_next_call();
+// false where a launch on the stream is being captured: a replay would use the number again, and find the words of the replay
+// before it.
+bool moss_may_number_calls(hipStream_t st);
+
 // 256 x 256 tile fast path of the block-scaled GEMM; MOSS_ERR_UNSUPPORTED if the shape or
 // operands do not qualify (the caller falls back to the general kernel).
 int moss_internal_gemm_big(int64_t M, int64_t N, int64_t K, const uint8_t *a_q, const uint8_t *a_e, const float *a_s,

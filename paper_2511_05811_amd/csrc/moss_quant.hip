@@ -15,9 +15,6 @@
 //    k_quant_row (row groups alone) or k_quant_tile (column groups, or both groupings from one
 //    fetch of X) folds the partials and converts.
 #include <atomic>
-#include <chrono>
-
-#include <unistd.h>
 
 #include "moss_internal.h"
 
@@ -1144,34 +1141,6 @@ int groups_per_cu(const void *fn, int threads, std::atomic<int> &cached)
     return v;
 }
 
-// The number of a call whose workgroups meet in slots: 48 bits, never zero, never used again by this process; it starts at a
-// place that depends on time and process (mixed as in splitmix64), so that memory which another process left behind does not
-// hold it.
-uint64_t next_call()
-{
-    static std::atomic<uint64_t> last{[] {
-        uint64_t z = (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() + ((uint64_t)getpid() << 40);
-        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-        return z ^ (z >> 31);
-    }()};
-    uint64_t c;
-    do c = (last.fetch_add(1) + 1) & 0xFFFFFFFFFFFFull;
-    while (c == 0);
-    return c;
-}
-
-// A replay of a captured call would meet under the number of the capture, and find the slots of the replay before it.
-bool may_meet_in_slots(hipStream_t st)
-{
-    hipStreamCaptureStatus status;
-    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return status == hipStreamCaptureStatusNone;
-}
-
 }  // namespace
 
 extern "C" void moss_quant_set_poll_limit(unsigned polls) { g_poll_limit.store(polls); }
@@ -1366,7 +1335,7 @@ static int quant_with_workspace(const void *x_bf16, int64_t rows, int64_t cols, 
 
     // Small tensors: one launch whose workgroups each read all of X for the maximum (the workspace is not touched)
     const bool tiny = scans_rather_than_meet(n_chunks * 16, dense, want_col);
-    const uint64_t call = !tiny && may_meet_in_slots(st) ? next_call() : 0;
+    const uint64_t call = !tiny && moss_may_number_calls(st) ? moss_next_call() : 0;
     if (tiny || (!call && scans(n_chunks * 16, dense, want_col)))
         return launch_codes(x, rows, cols, ld, want_row, want_col, ceil_mode, nullptr, 0, q_row, e_row, q_col, e_col, s_global, st);
 
