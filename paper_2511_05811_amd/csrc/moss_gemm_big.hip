@@ -28,9 +28,9 @@
 //  * E8M0 scale bytes travel the same way in blocks of 16 bytes (16 groups = K 512) per
 //    row into a small LDS ring; a lane reads one dword per fragment and stage and the
 //    instruction's byte selector picks the group of the substep.
-//  * Epilogue: accumulators times s_a*s_b are staged through the wave's own part of the last
+//  * Epilogue: accumulators times s_a*s_b; BF16 outputs are staged through the wave's own part of the last
 //    stage slot (16-byte chunks XOR-swizzled by row) so that every global store instruction
-//    writes whole 256-byte row pieces.
+//    writes whole 256-byte row pieces, FP32 outputs are stored from the registers.
 //  * Persistent workgroups, one per compute unit; the first two stages of a workgroup's next
 //    tile are already in flight while it writes out the current one.
 //  * A second instantiation with half the rows of a (128 x 256 tile, 64 x 128 per wave) serves
@@ -60,12 +60,6 @@ constexpr int kScaleBase = 2 * kSlotBytes;             // 128 KiB
 // behind them 1 KiB per wave that nobody reads; a K that ends inside a stage has a third scale slot for its last stage
 constexpr int dummy_base(bool ragged) { return kScaleBase + (ragged ? 3 : 2) * kScaleSlotBytes; }     // 144 / 152 KiB
 constexpr int big_lds_bytes(bool ragged) { return dummy_base(ragged) + 4 * 1024; }                   // 148 / 156 KiB
-
-// Rows (pairs of them) whose previous values an accumulating epilogue has on the way at a time.  Loaded one by one between
-// the stores, which may be the same memory as far as the compiler knows, every row waited out a trip to memory: 11008 x
-// 4096 x 2048 took 242 us, with 4 / 8 / 16 at a time 190 / 165 / 193 (16 spill registers that the main loop needs, which
-// costs a plain 4096 x 4096 x 8192 a fifth); 4096 x 4096 x 512 50 -> 41.5.
-constexpr int kAccBatch = 8;
 
 extern __shared__ __attribute__((aligned(1024))) uint8_t big_smem[];
 
@@ -427,7 +421,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
         asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");   // let the last matrix instructions retire
 
         // ---- epilogue.  Accumulator register v of lane (i32, h) in fragment (i, j) is out[m, n] with
-        // m = .. + 32 i + i32 and n = .. + 32 j + 8 (v / 4) + 4 h + v % 4.  Scale, convert, and stage
+        // m = .. + 32 i + i32 and n = .. + 32 j + 8 (v / 4) + 4 h + v % 4.  BF16 outputs: scale, convert, and stage
         // 16 KiB at a time through the two 8 KiB pieces of the last stage's slot that this wave itself
         // fills by copies (rows 64 wave .. of the a and of the b half), then store whole 256-byte row
         // pieces.  Inside a 256-byte staged row the 16-byte chunk c sits at c ^ (row & 15).
@@ -436,6 +430,10 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
         uint8_t *pieceA = big_smem + epar * kSlotBytes + wave * 64 * kStageK;
         uint8_t *pieceB = pieceA + kBT * kStageK;
         const int64_t mw = m0 + wm * (kMT / 2), nw = n0 + wn * 128;
+        auto next_stage_1 = [&]() {
+            if (RAGGED && has_next) prepare_tail(cx);      // (the third scale slot was last read before the epilogue's barrier)
+            if (has_next) issue_stage(cx, 1, epar);
+        };
         if (!out_f32) {
             uint16_t *o = reinterpret_cast<uint16_t *>(out);
 #pragma unroll
@@ -467,57 +465,19 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // staged rows consumed before they are overwritten
             }
+            next_stage_1();                // the pieces are free again: fill them with this wave's part of stage 1 of the next tile
         } else {
-            float *o = reinterpret_cast<float *>(out);
+            // FP32 outputs (weight gradients) leave straight from the registers: no LDS to wait for, and the next tile's stage 1 is
+            // on its way ahead of the stores instead of behind them (loads and stores complete in order on one counter).
+            // 12288 x 4096 x 2048 128 -> 117.6 us, 11008 x 4096 x 8192 337 -> 325, 4096 x 4096 x 512 28.4 -> 23.7, accumulating
+            // 40.2 -> 32.2.  (BF16 outputs this way lose to whole streamed rows: 8192 x 12288 x 4096 316 against 326.)
+            next_stage_1();
 #pragma unroll
-            for (int i = 0; i < MI; i++) {      // one 32-row block per round: 32 rows x 512 B, halves in the two pieces
+            for (int i = 0; i < MI; i++)
 #pragma unroll
                 for (int j = 0; j < 4; j++)
-#pragma unroll
-                    for (int qd = 0; qd < 4; qd++)
-                        *reinterpret_cast<float4 *>(((j >> 1) ? pieceB : pieceA) + i32 * 256 +
-                                                    ((((j & 1) * 8 + qd * 2 + h) ^ (i32 & 15)) << 4)) =
-                            make_float4(acc[i][j][4 * qd] * scale, acc[i][j][4 * qd + 1] * scale,
-                                        acc[i][j][4 * qd + 2] * scale, acc[i][j][4 * qd + 3] * scale);
-                // 32 lanes cover one 512-byte row (128 floats), a wave instruction covers 2 rows
-                const int l32 = lane & 31, cc = l32 & 15;
-                const int64_t n = nw + l32 * 4;
-                auto staged = [&](int k) {
-                    const int rr = 2 * k + (lane >> 5);
-                    return *reinterpret_cast<const float4 *>(((l32 >> 4) ? pieceB : pieceA) + rr * 256 + ((cc ^ (rr & 15)) << 4));
-                };
-                if (accumulate) {
-#pragma unroll 1
-                    for (int k0 = 0; k0 < 16; k0 += kAccBatch) {
-                        float4 prev[kAccBatch];
-#pragma unroll
-                        for (int k = 0; k < kAccBatch; k++) {
-                            const int64_t m = mw + i * 32 + 2 * (k0 + k) + (lane >> 5);
-                            prev[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-                            if (m < M && n < N) prev[k] = *reinterpret_cast<const float4 *>(o + m * ld_out + n);
-                        }
-#pragma unroll
-                        for (int k = 0; k < kAccBatch; k++) {
-                            const int64_t m = mw + i * 32 + 2 * (k0 + k) + (lane >> 5);
-                            if (m >= M || n >= N) continue;
-                            float4 v = staged(k0 + k);
-                            v.x += prev[k].x; v.y += prev[k].y; v.z += prev[k].z; v.w += prev[k].w;
-                            *reinterpret_cast<float4 *>(o + m * ld_out + n) = v;
-                        }
-                    }
-                } else {
-#pragma unroll 4
-                    for (int k = 0; k < 16; k++) {
-                        const int64_t m = mw + i * 32 + 2 * k + (lane >> 5);
-                        if (m < M && n < N) *reinterpret_cast<float4 *>(o + m * ld_out + n) = staged(k);
-                    }
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            }
+                    store_fragment(acc[i][j], scale, out, ld_out, mw + i * 32 + i32, nw + j * 32, h, M, N, true, accumulate);
         }
-        // the pieces are free again: fill them with this wave's part of stage 1 of the next tile
-        if (RAGGED && has_next) prepare_tail(cx);      // (the third scale slot was last read before the epilogue's barrier)
-        if (has_next) issue_stage(cx, 1, epar);
     }
     wait_vmcnt<0>();   // no copy into LDS may be outstanding when the wave ends
 }

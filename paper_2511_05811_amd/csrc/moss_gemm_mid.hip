@@ -52,7 +52,7 @@ struct MidShape {
     static constexpr int kGroupBytes = kRows * kMidK;                  // one group's stage: a rows, then b rows
     static constexpr int kSlot = KS * kGroupBytes;
     static constexpr int kPanel = SLOTS * kSlot;                       // byte offset of the exponent area
-    static constexpr int kReduce = kBM * kBN * 4 * KS;                 // partial sums (they reuse the slots and the area)
+    static constexpr int kReduce = KS == 1 ? 0 : kBM * kBN * 4 * KS;   // partial sums (they reuse the slots and the area)
     static constexpr int kPA = kBM / 8 / (WM * WN), kPB = kBN / 8 / (WM * WN);   // 8-row copies of a, of b per wave and stage
     static constexpr int kPieces = kPA + kPB;
     static_assert(WM * WN * KS * 64 == kMidThreads, "four waves");
@@ -380,7 +380,20 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
         }
     }
 
-    // Epilogue: every wave leaves its sums in LDS (row pitch 32 NJ floats, 16-byte chunks XOR-swizzled by row within the
+    // Epilogue with one K group: straight from the registers (see store_fragment)
+    if (KS == 1) {
+#pragma unroll
+        for (int i = 0; i < MI; i++)
+#pragma unroll
+            for (int j = 0; j < NJ; j++) {
+                asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[i][j]));   // the last matrix instructions retire
+                store_fragment(acc[i][j], scale, p.out, p.ld_out, m0 + (wm * MI + i) * 32 + i32, n0 + (wn * NJ + j) * 32, h, M, N, p.out_f32,
+                               p.accumulate);
+            }
+        return;
+    }
+
+    // Epilogue with several: every wave leaves its sums in LDS (row pitch 32 NJ floats, 16-byte chunks XOR-swizzled by row within the
     // largest power of two that divides their number), then the
     // workgroup walks the tile row by row, adds the KS parts in order, scales and stores.
     // (accumulator register v of lane (i32, h) in fragment (i, j): row 32 i + i32, column 32 j + 8 (v / 4) + 4 h + v % 4)
