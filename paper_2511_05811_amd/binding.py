@@ -97,16 +97,17 @@ def _bind_calls():
     global _calls
     L = load()
     import torch
+    names = ("moss_quant_workspace_bytes", "moss_quant_act_2level", "moss_quant_act_2level_given_max", "moss_gemm_fp8_mx",
+             "moss_weight_workspace_bytes", "moss_weight_autoscale_cast", "moss_internal_swiglu_bf16", "moss_internal_swiglu_bf16_backward",
+             "moss_internal_add_rmsnorm_bf16", "moss_internal_rmsnorm_bf16_backward")     # (these take scratch)
     try:
         from . import _moss_calls as native
         get_device, get_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+        addresses = tuple(C.cast(getattr(L, n), C.c_void_p).value for n in names)
     except (ImportError, AttributeError):
         _calls = False
         return _calls
-    names = ("moss_quant_workspace_bytes", "moss_quant_act_2level", "moss_quant_act_2level_given_max", "moss_gemm_fp8_mx",
-             "moss_weight_workspace_bytes", "moss_weight_autoscale_cast", "moss_swiglu_bf16", "moss_swiglu_bf16_backward",
-             "moss_add_rmsnorm_bf16", "moss_rmsnorm_bf16_backward")
-    native.bind(tuple(C.cast(getattr(L, n), C.c_void_p).value for n in names), _check, AdamWArgs, get_device, get_stream)
+    native.bind(addresses, _check, AdamWArgs, get_device, get_stream)
     _calls = native
     return _calls
 

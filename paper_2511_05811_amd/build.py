@@ -39,7 +39,7 @@ def build_calls(verbose=False):
     import torch
     home = os.path.dirname(torch.__file__)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
-           "-I", INCLUDE, "-isystem", os.path.join(home, "include"), "-isystem", sysconfig.get_paths()["include"], "-o", CALLS,
+           "-I", INCLUDE, "-I", CSRC, "-isystem", os.path.join(home, "include"), "-isystem", sysconfig.get_paths()["include"], "-o", CALLS,
            os.path.join(CSRC, "moss_calls.cpp"), "-L", os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd))

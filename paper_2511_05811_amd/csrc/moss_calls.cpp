@@ -16,6 +16,7 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 
 #include "moss.h"
+#include "moss_producer.h"
 
 namespace {
 
@@ -26,10 +27,10 @@ struct Library {
     decltype(&moss_gemm_fp8_mx) gemm_fp8_mx;
     decltype(&moss_weight_workspace_bytes) weight_workspace_bytes;
     decltype(&moss_weight_autoscale_cast) weight_autoscale_cast;
-    decltype(&moss_swiglu_bf16) swiglu_bf16;
-    decltype(&moss_swiglu_bf16_backward) swiglu_bf16_backward;
-    decltype(&moss_add_rmsnorm_bf16) add_rmsnorm_bf16;
-    decltype(&moss_rmsnorm_bf16_backward) rmsnorm_bf16_backward;
+    decltype(&moss_internal_swiglu_bf16) swiglu_bf16;
+    decltype(&moss_internal_swiglu_bf16_backward) swiglu_bf16_backward;
+    decltype(&moss_internal_add_rmsnorm_bf16) add_rmsnorm_bf16;
+    decltype(&moss_internal_rmsnorm_bf16_backward) rmsnorm_bf16_backward;
 };
 
 Library lib;
@@ -368,6 +369,9 @@ bool rows_out(PyObject *o, Output &out, const at::Tensor &like, bool check_strid
     return true;
 }
 
+// scratch of a producer: any contents, the call's own until it has run (the allocator hands it out again in stream order)
+at::Tensor producer_workspace(const at::Tensor &like) { return make({(int64_t)kProducerWorkspaceBytes}, at::kByte, like); }
+
 uint32_t *word_ptr(const Output &o) { return static_cast<uint32_t *>(ptr(&o.t)); }
 
 // (gate, up, h, absmax_bits)
@@ -383,7 +387,9 @@ PyObject *swiglu_bf16(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t rows = gate->size(0), cols = gate->size(1), ld = gate->stride(0);
         void *pg = ptr(gate), *pu = ptr(up), *ph = ptr(&h.t);
         uint32_t *w = word_ptr(top);
-        const int rc = without_gil([&] { return lib.swiglu_bf16(pg, pu, rows, cols, ld, ph, w, stream); });
+        const at::Tensor ws = producer_workspace(*gate);
+        void *pw = ws.data_ptr();
+        const int rc = without_gil([&] { return lib.swiglu_bf16(pg, pu, rows, cols, ld, ph, w, pw, kProducerWorkspaceBytes, stream); });
         return checked(rc, "moss_swiglu_bf16") ? PyTuple_Pack(2, h.o, top.o) : nullptr;
     });
 }
@@ -402,7 +408,9 @@ PyObject *swiglu_bf16_backward(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t rows = gate->size(0), cols = gate->size(1), ld = gate->stride(0);
         void *pg = ptr(gate), *pu = ptr(up), *pd = ptr(dh), *og = ptr(&dg.t), *ou = ptr(&du.t);
         uint32_t *wg = word_ptr(tg), *wu = word_ptr(tu);
-        const int rc = without_gil([&] { return lib.swiglu_bf16_backward(pg, pu, pd, rows, cols, ld, og, ou, wg, wu, stream); });
+        const at::Tensor ws = producer_workspace(*gate);
+        void *pw = ws.data_ptr();
+        const int rc = without_gil([&] { return lib.swiglu_bf16_backward(pg, pu, pd, rows, cols, ld, og, ou, wg, wu, pw, kProducerWorkspaceBytes, stream); });
         return checked(rc, "moss_swiglu_bf16_backward") ? PyTuple_Pack(4, dg.o, du.o, tg.o, tu.o) : nullptr;
     });
 }
@@ -429,7 +437,9 @@ PyObject *add_rmsnorm_bf16(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t rows = x->size(0), cols = x->size(1), ld = x->stride(0);
         void *px = ptr(x), *pd = ptr(delta), *pg = ptr(gamma), *ph = delta ? ptr(&h.t) : nullptr, *py = ptr(&y.t);
         uint32_t *w = word_ptr(top);
-        const int rc = without_gil([&] { return lib.add_rmsnorm_bf16(px, pd, pg, eps, rows, cols, ld, ph, py, w, stream); });
+        const at::Tensor ws = producer_workspace(*x);
+        void *pw = ws.data_ptr();
+        const int rc = without_gil([&] { return lib.add_rmsnorm_bf16(px, pd, pg, eps, rows, cols, ld, ph, py, w, pw, kProducerWorkspaceBytes, stream); });
         return checked(rc, "moss_add_rmsnorm_bf16") ? PyTuple_Pack(3, delta ? h.o : a[0], y.o, top.o) : nullptr;
     });
 }
@@ -450,7 +460,9 @@ PyObject *rmsnorm_bf16_backward(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t rows = h->size(0), cols = h->size(1), ld = h->stride(0);
         void *ph = ptr(h), *pg = ptr(gamma), *py = ptr(dy), *pr = ptr(d_res), *po = ptr(&d_h.t);
         uint32_t *w = word_ptr(top);
-        const int rc = without_gil([&] { return lib.rmsnorm_bf16_backward(ph, pg, py, pr, eps, rows, cols, ld, po, w, stream); });
+        const at::Tensor ws = producer_workspace(*h);
+        void *pw = ws.data_ptr();
+        const int rc = without_gil([&] { return lib.rmsnorm_bf16_backward(ph, pg, py, pr, eps, rows, cols, ld, po, w, pw, kProducerWorkspaceBytes, stream); });
         return checked(rc, "moss_rmsnorm_bf16_backward") ? PyTuple_Pack(2, d_h.o, top.o) : nullptr;
     });
 }

@@ -131,6 +131,73 @@ __device__ __forceinline__ void merge_max_word(uint32_t *word, uint32_t m, uint3
     if (m > seen) __hip_atomic_fetch_max(word, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The same without the word: where the caller has memory to spare and calls may be numbered (moss_may_number_calls), each
+// workgroup leaves its maxima (WORDS of them, BF16 magnitudes in thread 0) beside the number of the call in slots of its own,
+// and the last of the grid, which waits for nobody that waits, reads them all and writes the caller's words.  No launch to
+// clear the words ahead, no queue of atomics, no look.  red: WORDS per wave.
+struct MaxSlots {
+    uint64_t *words;
+    uint64_t call;           // 0: merge into the words, which a launch ahead has cleared
+};
+constexpr int kMaxSlotBlocks = 2048;
+
+static inline MaxSlots max_slots(void *workspace, size_t bytes, int blocks, int words, hipStream_t st)
+{
+    const bool fits = workspace && moss_aligned16(workspace) && blocks <= kMaxSlotBlocks && bytes >= (size_t)blocks * words * 8;
+    return MaxSlots{(uint64_t *)workspace, fits && moss_may_number_calls(st) ? moss_next_call() : 0};
+}
+
+template <int WORDS, int THREADS>
+__device__ __forceinline__ void finish_max_in_slots(const MaxSlots &s, const uint32_t (&m)[WORDS], uint32_t *const (&out)[WORDS], uint32_t *red)
+{
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 0; w < WORDS; w++)
+            __hip_atomic_store(s.words + (size_t)blockIdx.x * WORDS + w, s.call << 16 | m[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (blockIdx.x != gridDim.x - 1) return;
+    constexpr int kLooks = 4;
+    const int n = (int)gridDim.x * WORDS;
+    uint32_t top = 0;                // (THREADS % WORDS == 0: a thread's words are all of one kind)
+    for (int i0 = threadIdx.x; i0 < n; i0 += THREADS * kLooks) {
+        uint64_t v[kLooks];
+        bool there;
+        do {
+            there = true;
+#pragma unroll
+            for (int u = 0; u < kLooks; u++) {
+                v[u] = s.call << 16;
+                if (i0 + u * THREADS < n) v[u] = __hip_atomic_load(s.words + i0 + u * THREADS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int u = 0; u < kLooks; u++) there = there && (v[u] >> 16) == s.call;
+            if (!there) __builtin_amdgcn_s_sleep(1);
+        } while (!there);
+#pragma unroll
+        for (int u = 0; u < kLooks; u++) {
+            const uint32_t x = (uint32_t)v[u] & 0xFFFFu;
+            top = x > top ? x : top;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= WORDS; off >>= 1) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)top, off, 64);
+        top = o > top ? o : top;
+    }
+    __syncthreads();                 // (red is free: thread 0 has read what the workgroup's own reduction left)
+    if ((threadIdx.x & 63) < WORDS) red[(threadIdx.x >> 6) * WORDS + (threadIdx.x & 63)] = top;
+    __syncthreads();
+    if (threadIdx.x < WORDS) {
+        for (int k = 0; k < THREADS / 64; k++) {
+            const uint32_t o = red[k * WORDS + threadIdx.x];
+            top = o > top ? o : top;
+        }
+#pragma unroll
+        for (int w = 0; w < WORDS; w++)
+            if ((int)threadIdx.x == w) *out[w] = top;
+    }
+}
+
 // Two FP32 values -> two E4M3 bytes in the low half of the result.  The hardware
 // converter rounds to nearest even; values are clamped to +-448 first so that the
 // cast saturates instead of producing the NaN code.

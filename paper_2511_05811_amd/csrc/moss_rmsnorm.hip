@@ -9,9 +9,11 @@
 // in registers between the row's reduction (sum of squares; in the backward also sum of dy gamma h) and the
 // output, so every input is read once.  Arithmetic in FP32 (sums of a few thousand terms: relative error
 // ~1e-6, far below half a BF16 step), one rounding to BF16 per output by V_CVT_PK_BF16_F32.  The maximum is
-// taken over the bit patterns actually written and merged into the caller's word by one atomic per
-// workgroup; a one-thread kernel clears the word first (no memset: the call can be captured into a graph).
+// taken over the bit patterns actually written and left in slots that the last workgroup folds into the
+// caller's word, or merged into it by one atomic per workgroup behind a one-thread kernel that clears it (callers
+// without a workspace, captured calls; no memset: the call can be captured into a graph).
 #include "moss_internal.h"
+#include "moss_producer.h"
 
 namespace moss {
 namespace {
@@ -56,13 +58,21 @@ __device__ __forceinline__ void block_sum2(float &a, float &b, float (*red)[2])
     }
 }
 
-__device__ __forceinline__ void merge_max(uint32_t m, uint32_t *word, int look, uint32_t *red)
+__device__ __forceinline__ void merge_max(uint32_t m, uint32_t *word, int look, const MaxSlots &slots, uint32_t *red)
 {
     m = (m & 0xFFFFu) > (m >> 16) ? (m & 0xFFFFu) : (m >> 16);
     m = wave_max_u32(m);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
+    if (slots.call) {
+        if (threadIdx.x == 0)
+            for (int i = 1; i < kRnThreads / kWave; i++) m = red[i] > m ? red[i] : m;
+        const uint32_t top[1] = {m};
+        uint32_t *const out[1] = {word};
+        finish_max_in_slots<1, kRnThreads>(slots, top, out, red);
+        return;
+    }
     if (threadIdx.x == 0) {
         const uint32_t seen = look_at_word(word, look);
         for (int i = 1; i < kRnThreads / kWave; i++) m = red[i] > m ? red[i] : m;
@@ -82,11 +92,12 @@ __global__ __launch_bounds__(kRnThreads) void k_add_rmsnorm(const uint16_t *__re
                                                             const uint16_t *__restrict__ gamma, float eps, int64_t rows,
                                                             int chunks_per_row, int64_t ld, float inv_cols, int flags,
                                                             uint16_t *__restrict__ h_out, uint16_t *__restrict__ y,
-                                                            uint32_t *__restrict__ y_max)
+                                                            uint32_t *__restrict__ y_max, MaxSlots slots)
 {
     __shared__ float red[kRnThreads / kWave][2];
     __shared__ uint32_t redm[kRnThreads / kWave];
     uint32_t m = 0;
+    asm volatile("" ::"s"(slots.words), "s"(slots.call));      // (fetched here, not at the end in front of the slots)
     uint4 gm[CHUNKS];
 #pragma unroll
     for (int k = 0; k < CHUNKS; k++) {
@@ -133,7 +144,7 @@ __global__ __launch_bounds__(kRnThreads) void k_add_rmsnorm(const uint16_t *__re
             st_producer16(y + r * ld + (int64_t)c * 8, make_uint4(o[0], o[1], o[2], o[3]), flags & kProducerStream);
         }
     }
-    merge_max(m, y_max, flags & kProducerLook, redm);
+    merge_max(m, y_max, flags & kProducerLook, slots, redm);
 }
 
 // d_h = d_res + (g - n mean(g n)) / rms with g = dy gamma, n = h / rms, rms = sqrt(mean(h^2) + eps).
@@ -143,11 +154,12 @@ __global__ __launch_bounds__(kRnThreads) void k_rmsnorm_backward(const uint16_t 
                                                                  const uint16_t *__restrict__ dy, const uint16_t *__restrict__ d_res,
                                                                  float eps, int64_t rows, int chunks_per_row, int64_t ld,
                                                                  float inv_cols, int flags, uint16_t *__restrict__ d_h,
-                                                                 uint32_t *__restrict__ dh_max)
+                                                                 uint32_t *__restrict__ dh_max, MaxSlots slots)
 {
     __shared__ float red[kRnThreads / kWave][2];
     __shared__ uint32_t redm[kRnThreads / kWave];
     uint32_t m = 0;
+    asm volatile("" ::"s"(slots.words), "s"(slots.call));      // (fetched here, not at the end in front of the slots)
     uint4 gm[CHUNKS];
 #pragma unroll
     for (int k = 0; k < CHUNKS; k++) {
@@ -204,7 +216,7 @@ __global__ __launch_bounds__(kRnThreads) void k_rmsnorm_backward(const uint16_t 
             st_producer16(d_h + off, make_uint4(o[0], o[1], o[2], o[3]), flags & kProducerStream);
         }
     }
-    merge_max(m, dh_max, flags & kProducerLook, redm);
+    merge_max(m, dh_max, flags & kProducerLook, slots, redm);
 }
 
 int check_rows(int64_t rows, int64_t cols, int64_t ld, float eps)
@@ -249,6 +261,13 @@ extern "C" int moss_internal_rmsnorm_looks(int64_t rows, int64_t cols) { return 
 extern "C" int moss_add_rmsnorm_bf16(const void *x, const void *delta, const void *gamma, float eps, int64_t rows, int64_t cols,
                                      int64_t ld, void *h_out, void *y, uint32_t *y_absmax_bits, void *stream)
 {
+    return moss_internal_add_rmsnorm_bf16(x, delta, gamma, eps, rows, cols, ld, h_out, y, y_absmax_bits, nullptr, 0, stream);
+}
+
+extern "C" int moss_internal_add_rmsnorm_bf16(const void *x, const void *delta, const void *gamma, float eps, int64_t rows,
+                                              int64_t cols, int64_t ld, void *h_out, void *y, uint32_t *y_absmax_bits,
+                                              void *workspace, size_t workspace_bytes, void *stream)
+{
     using namespace moss;
     if (!x || !gamma || !y || !y_absmax_bits || (delta && !h_out)) return MOSS_ERR_NULL;
     int rc = check_rows(rows, cols, ld, eps);
@@ -260,11 +279,14 @@ extern "C" int moss_add_rmsnorm_bf16(const void *x, const void *delta, const voi
     const float inv_cols = 1.0f / (float)cols;
     const int flags = producer_flags(rows, cols, looks(rows, cols));
     const dim3 grid(rows_grid(rows)), block(kRnThreads);
-    hipLaunchKernelGGL(k_rmsnorm_clear, dim3(1), dim3(64), 0, st, y_absmax_bits);
-    MOSS_LAUNCH_CHECK();
+    const MaxSlots slots = max_slots(workspace, workspace_bytes, (int)grid.x, 1, st);
+    if (!slots.call) {
+        hipLaunchKernelGGL(k_rmsnorm_clear, dim3(1), dim3(64), 0, st, y_absmax_bits);
+        MOSS_LAUNCH_CHECK();
+    }
 #define MOSS_RN_FWD(A, C)                                                                                                    \
     hipLaunchKernelGGL((k_add_rmsnorm<A, C>), grid, block, 0, st, (const uint16_t *)x, (const uint16_t *)delta,                \
-                       (const uint16_t *)gamma, eps, rows, cpr, ld, inv_cols, flags, (uint16_t *)h_out, (uint16_t *)y, y_absmax_bits)
+                       (const uint16_t *)gamma, eps, rows, cpr, ld, inv_cols, flags, (uint16_t *)h_out, (uint16_t *)y, y_absmax_bits, slots)
     if (delta) {
         if (chunks <= 1) MOSS_RN_FWD(true, 1); else if (chunks <= 2) MOSS_RN_FWD(true, 2); else if (chunks <= 4) MOSS_RN_FWD(true, 4); else MOSS_RN_FWD(true, 8);
     } else {
@@ -279,6 +301,13 @@ extern "C" int moss_rmsnorm_bf16_backward(const void *h, const void *gamma, cons
                                           int64_t rows, int64_t cols, int64_t ld, void *d_h, uint32_t *d_h_absmax_bits,
                                           void *stream)
 {
+    return moss_internal_rmsnorm_bf16_backward(h, gamma, dy, d_res, eps, rows, cols, ld, d_h, d_h_absmax_bits, nullptr, 0, stream);
+}
+
+extern "C" int moss_internal_rmsnorm_bf16_backward(const void *h, const void *gamma, const void *dy, const void *d_res, float eps,
+                                                   int64_t rows, int64_t cols, int64_t ld, void *d_h, uint32_t *d_h_absmax_bits,
+                                                   void *workspace, size_t workspace_bytes, void *stream)
+{
     using namespace moss;
     if (!h || !gamma || !dy || !d_h || !d_h_absmax_bits) return MOSS_ERR_NULL;
     int rc = check_rows(rows, cols, ld, eps);
@@ -290,12 +319,15 @@ extern "C" int moss_rmsnorm_bf16_backward(const void *h, const void *gamma, cons
     const float inv_cols = 1.0f / (float)cols;
     const int flags = producer_flags(rows, cols, looks(rows, cols));
     const dim3 grid(rows_grid(rows)), block(kRnThreads);
-    hipLaunchKernelGGL(k_rmsnorm_clear, dim3(1), dim3(64), 0, st, d_h_absmax_bits);
-    MOSS_LAUNCH_CHECK();
+    const MaxSlots slots = max_slots(workspace, workspace_bytes, (int)grid.x, 1, st);
+    if (!slots.call) {
+        hipLaunchKernelGGL(k_rmsnorm_clear, dim3(1), dim3(64), 0, st, d_h_absmax_bits);
+        MOSS_LAUNCH_CHECK();
+    }
 #define MOSS_RN_BWD(R, C)                                                                                                    \
     hipLaunchKernelGGL((k_rmsnorm_backward<R, C>), grid, block, 0, st, (const uint16_t *)h, (const uint16_t *)gamma,           \
                        (const uint16_t *)dy, (const uint16_t *)d_res, eps, rows, cpr, ld, inv_cols, flags, (uint16_t *)d_h,     \
-                       d_h_absmax_bits)
+                       d_h_absmax_bits, slots)
     if (d_res) {
         if (chunks <= 1) MOSS_RN_BWD(true, 1); else if (chunks <= 2) MOSS_RN_BWD(true, 2); else if (chunks <= 4) MOSS_RN_BWD(true, 4); else MOSS_RN_BWD(true, 8);
     } else {

@@ -9,9 +9,11 @@
 // elements; arithmetic in FP32 with the hardware's exp2 and reciprocal approximations (1 ulp each),
 // one rounding to BF16 (round to nearest even) by V_CVT_PK_BF16_F32.  The maximum is taken over the
 // bit patterns actually written (unsigned maximum of the 15 magnitude bits), folded per wave and per
-// workgroup, and merged into the caller's word by one atomic per workgroup; a one-thread kernel clears
-// the word first (no memset, so the call can be captured into a graph).
+// workgroup, and either left in slots that the last workgroup folds into the caller's word, or merged into it by
+// one atomic per workgroup behind a one-thread kernel that clears it (callers without a workspace, captured
+// calls; no memset, so the call can be captured into a graph).
 #include "moss_internal.h"
+#include "moss_producer.h"
 
 namespace moss {
 namespace {
@@ -53,6 +55,18 @@ __device__ __forceinline__ void fold_max(uint32_t m, uint32_t *word, int look, u
     __syncthreads();
 }
 
+// maximum of the workgroup in thread 0 (red: a word per wave)
+__device__ __forceinline__ uint32_t block_max(uint32_t m, uint32_t *red)
+{
+    m = (m & 0xFFFFu) > (m >> 16) ? (m & 0xFFFFu) : (m >> 16);
+    m = wave_max_u32(m);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int i = 1; i < kSwThreads / kWave; i++) m = red[i] > m ? red[i] : m;
+    return m;
+}
+
 __global__ void k_swiglu_clear(uint32_t *a, uint32_t *b)
 {
     if (threadIdx.x == 0) {
@@ -72,10 +86,11 @@ __device__ __forceinline__ int64_t chunk_offset(int64_t id, int chunks_per_row, 
 template <int CHUNKS>
 __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restrict__ gate, const uint16_t *__restrict__ up,
                                                        int64_t n_chunks, int chunks_per_row, int64_t ld, int dense, int flags,
-                                                       uint16_t *__restrict__ h, uint32_t *__restrict__ h_max)
+                                                       uint16_t *__restrict__ h, uint32_t *__restrict__ h_max, MaxSlots slots)
 {
     __shared__ uint32_t red[kSwThreads / kWave];
     uint32_t m = 0;
+    asm volatile("" ::"s"(slots.words), "s"(slots.call));      // (fetched here, not at the end in front of the slots)
     const int64_t stride = (int64_t)gridDim.x * kSwThreads * CHUNKS;
     for (int64_t id0 = (int64_t)blockIdx.x * kSwThreads * CHUNKS + threadIdx.x; id0 < n_chunks; id0 += stride) {
         uint4 g[CHUNKS], u[CHUNKS];
@@ -104,7 +119,13 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restric
             st_producer16(h + off[k], make_uint4(o[0], o[1], o[2], o[3]), flags & kProducerStream);
         }
     }
-    fold_max(m, h_max, flags & kProducerLook, red);
+    if (slots.call) {
+        const uint32_t top[1] = {block_max(m, red)};
+        uint32_t *const out[1] = {h_max};
+        finish_max_in_slots<1, kSwThreads>(slots, top, out, red);
+    } else {
+        fold_max(m, h_max, flags & kProducerLook, red);
+    }
 }
 
 template <int CHUNKS>
@@ -112,10 +133,12 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu_backward(const uint16_t *
                                                                 const uint16_t *__restrict__ dh, int64_t n_chunks,
                                                                 int chunks_per_row, int64_t ld, int dense, int flags,
                                                                 uint16_t *__restrict__ d_gate, uint16_t *__restrict__ d_up,
-                                                                uint32_t *__restrict__ dg_max, uint32_t *__restrict__ du_max)
+                                                                uint32_t *__restrict__ dg_max, uint32_t *__restrict__ du_max,
+                                                                MaxSlots slots)
 {
-    __shared__ uint32_t red[kSwThreads / kWave];
+    __shared__ uint32_t red[kSwThreads / kWave], red_u[kSwThreads / kWave], red_all[2 * kSwThreads / kWave];
     uint32_t mg = 0, mu = 0;
+    asm volatile("" ::"s"(slots.words), "s"(slots.call));      // (fetched here, not at the end in front of the slots)
     const int64_t stride = (int64_t)gridDim.x * kSwThreads * CHUNKS;
     for (int64_t id0 = (int64_t)blockIdx.x * kSwThreads * CHUNKS + threadIdx.x; id0 < n_chunks; id0 += stride) {
         uint4 gc[CHUNKS], uc[CHUNKS], dc[CHUNKS];
@@ -158,8 +181,14 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu_backward(const uint16_t *
             st_producer16(d_up + off, make_uint4(ou[0], ou[1], ou[2], ou[3]), flags & kProducerStream);
         }
     }
-    fold_max(mg, dg_max, flags & kProducerLook, red);
-    fold_max(mu, du_max, flags & kProducerLook, red);
+    if (slots.call) {
+        const uint32_t top[2] = {block_max(mg, red), block_max(mu, red_u)};
+        uint32_t *const out[2] = {dg_max, du_max};
+        finish_max_in_slots<2, kSwThreads>(slots, top, out, red_all);
+    } else {
+        fold_max(mg, dg_max, flags & kProducerLook, red);
+        fold_max(mu, du_max, flags & kProducerLook, red);
+    }
 }
 
 int check_common(int64_t rows, int64_t cols, int64_t ld)
@@ -214,6 +243,12 @@ extern "C" int moss_internal_swiglu_chunks(int64_t rows, int64_t cols) { return 
 extern "C" int moss_swiglu_bf16(const void *gate, const void *up, int64_t rows, int64_t cols, int64_t ld,
                                 void *h, uint32_t *h_absmax_bits, void *stream)
 {
+    return moss_internal_swiglu_bf16(gate, up, rows, cols, ld, h, h_absmax_bits, nullptr, 0, stream);
+}
+
+extern "C" int moss_internal_swiglu_bf16(const void *gate, const void *up, int64_t rows, int64_t cols, int64_t ld, void *h,
+                                         uint32_t *h_absmax_bits, void *workspace, size_t workspace_bytes, void *stream)
+{
     using namespace moss;
     if (!gate || !up || !h || !h_absmax_bits) return MOSS_ERR_NULL;
     int rc = check_common(rows, cols, ld);
@@ -222,13 +257,16 @@ extern "C" int moss_swiglu_bf16(const void *gate, const void *up, int64_t rows, 
     hipStream_t st = (hipStream_t)stream;
     const int chunks_per_row = (int)(cols / 8);
     const int64_t n_chunks = rows * chunks_per_row;
-    hipLaunchKernelGGL(k_swiglu_clear, dim3(1), dim3(64), 0, st, h_absmax_bits, (uint32_t *)nullptr);
-    MOSS_LAUNCH_CHECK();
     const int grid = grid_for(n_chunks), per_thread = chunks_per_thread(n_chunks);
+    const MaxSlots slots = max_slots(workspace, workspace_bytes, grid, 1, st);
+    if (!slots.call) {
+        hipLaunchKernelGGL(k_swiglu_clear, dim3(1), dim3(64), 0, st, h_absmax_bits, (uint32_t *)nullptr);
+        MOSS_LAUNCH_CHECK();
+    }
     const auto kern = per_thread == 1 ? k_swiglu<1> : per_thread == 2 ? k_swiglu<2> : k_swiglu<4>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kSwThreads), 0, st, (const uint16_t *)gate, (const uint16_t *)up, n_chunks,
                        chunks_per_row, ld, (int)(ld == cols), producer_flags(rows, cols, looks(grid)),
-                       (uint16_t *)h, h_absmax_bits);
+                       (uint16_t *)h, h_absmax_bits, slots);
     MOSS_LAUNCH_CHECK();
     return MOSS_OK;
 }
@@ -236,6 +274,14 @@ extern "C" int moss_swiglu_bf16(const void *gate, const void *up, int64_t rows, 
 extern "C" int moss_swiglu_bf16_backward(const void *gate, const void *up, const void *dh, int64_t rows, int64_t cols,
                                          int64_t ld, void *d_gate, void *d_up, uint32_t *d_gate_absmax_bits,
                                          uint32_t *d_up_absmax_bits, void *stream)
+{
+    return moss_internal_swiglu_bf16_backward(gate, up, dh, rows, cols, ld, d_gate, d_up, d_gate_absmax_bits, d_up_absmax_bits, nullptr, 0,
+                                              stream);
+}
+
+extern "C" int moss_internal_swiglu_bf16_backward(const void *gate, const void *up, const void *dh, int64_t rows, int64_t cols,
+                                                  int64_t ld, void *d_gate, void *d_up, uint32_t *d_gate_absmax_bits,
+                                                  uint32_t *d_up_absmax_bits, void *workspace, size_t workspace_bytes, void *stream)
 {
     using namespace moss;
     if (!gate || !up || !dh || !d_gate || !d_up || !d_gate_absmax_bits || !d_up_absmax_bits) return MOSS_ERR_NULL;
@@ -248,14 +294,17 @@ extern "C" int moss_swiglu_bf16_backward(const void *gate, const void *up, const
     hipStream_t st = (hipStream_t)stream;
     const int chunks_per_row = (int)(cols / 8);
     const int64_t n_chunks = rows * chunks_per_row;
-    hipLaunchKernelGGL(k_swiglu_clear, dim3(1), dim3(64), 0, st, d_gate_absmax_bits, d_up_absmax_bits);
-    MOSS_LAUNCH_CHECK();
     const int grid = grid_for(n_chunks), per_thread = chunks_per_thread(n_chunks);
+    const MaxSlots slots = max_slots(workspace, workspace_bytes, grid, 2, st);
+    if (!slots.call) {
+        hipLaunchKernelGGL(k_swiglu_clear, dim3(1), dim3(64), 0, st, d_gate_absmax_bits, d_up_absmax_bits);
+        MOSS_LAUNCH_CHECK();
+    }
     const auto kern = per_thread == 1 ? k_swiglu_backward<1> : per_thread == 2 ? k_swiglu_backward<2> : k_swiglu_backward<4>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kSwThreads), 0, st, (const uint16_t *)gate, (const uint16_t *)up,
                        (const uint16_t *)dh, n_chunks, chunks_per_row, ld, (int)(ld == cols),
                        producer_flags(rows, cols, looks(grid)), (uint16_t *)d_gate, (uint16_t *)d_up,
-                       d_gate_absmax_bits, d_up_absmax_bits);
+                       d_gate_absmax_bits, d_up_absmax_bits, slots);
     MOSS_LAUNCH_CHECK();
     return MOSS_OK;
 }

@@ -172,3 +172,31 @@ def test_swiglu_feeds_the_quantizer_in_one_pass(oracle):
     assert scalar(got["s"]) == s
     assert np.array_equal(u8(got["q_row"]), qr) and np.array_equal(u8(got["e_row"]), er)
     assert np.array_equal(u8(got["q_col"]), qc) and np.array_equal(u8(got["e_col"]), ec)
+
+
+@pytest.mark.parametrize("rows,cols,pad", [(1, 8, 0), (32, 256, 8), (640, 1024, 0), (1033, 2056, 64), (4096, 2048, 0), (8192, 4096, 0)])
+def test_maximum_words_from_slots_are_those_of_the_atomics(rows, cols, pad):
+    """An eager call folds the maxima of up to 2048 workgroups in scratch of its own, a captured one merges them into the
+    words: same tensors and same words, twice in a row, and the words are the largest magnitudes written."""
+    gen = torch.Generator(device="cuda:0").manual_seed(rows + cols)
+    make = lambda: torch.randn(rows, cols + pad, generator=gen, device="cuda:0").bfloat16()[:, :cols]
+    a, b, c = make(), make(), make()
+    gamma = torch.randn(cols, generator=gen, device="cuda:0").bfloat16()
+    calls = (lambda: moss.swiglu_bf16(a, b), lambda: moss.swiglu_bf16_backward(a, b, c), lambda: moss.add_rmsnorm_bf16(a, gamma, 1e-5, delta=b),
+             lambda: moss.rmsnorm_bf16_backward(a, gamma, b, 1e-5, d_res=c))
+    for k, call in enumerate(calls):
+        graph = torch.cuda.CUDAGraph()
+        call()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            want = call()
+        graph.replay()
+        for again in range(2):
+            got = call()
+            torch.cuda.synchronize()
+            for x, y in zip(got, want):
+                assert torch.equal(x, y), (k, again)
+        tensors = [t for t in got if t.dtype == torch.bfloat16][-2 if k == 1 else -1:]
+        words = [t for t in got if t.dtype == torch.int32]
+        for t, w in zip(tensors, words):
+            assert int(w) == int((t.contiguous().view(torch.int16).int() & 0x7FFF).max()), k
