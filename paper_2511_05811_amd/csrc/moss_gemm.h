@@ -88,10 +88,22 @@ __device__ __forceinline__ void store_fragment(const v16f &acc, float scale, voi
                 for (int g = 0; g < 4; g++) *reinterpret_cast<float4 *>(o + 8 * g) = make_float4(r[4 * g], r[4 * g + 1], r[4 * g + 2], r[4 * g + 3]);
             }
         } else if (row < M) {
+            // the matrix ends inside the fragment, or its rows are not 16-byte aligned
 #pragma unroll
-            for (int v = 0; v < 16; v++) {
-                const int c = 8 * (v / 4) + v % 4;
-                if (n + 4 * h + c < N) o[c] = accumulate ? r[v] + o[c] : r[v];
+            for (int g = 0; g < 4; g++) {
+                const int64_t left = N - (n + 4 * h + 8 * g);
+                if (left >= 4 && ld % 4 == 0) {
+                    float4 v = make_float4(r[4 * g], r[4 * g + 1], r[4 * g + 2], r[4 * g + 3]);
+                    if (accumulate) {
+                        const float4 q = *reinterpret_cast<const float4 *>(o + 8 * g);
+                        v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+                    }
+                    *reinterpret_cast<float4 *>(o + 8 * g) = v;
+                } else {
+#pragma unroll
+                    for (int x = 0; x < 4; x++)
+                        if (x < left) o[8 * g + x] = accumulate ? r[4 * g + x] + o[8 * g + x] : r[4 * g + x];
+                }
             }
         }
         return;
@@ -113,10 +125,18 @@ __device__ __forceinline__ void store_fragment(const v16f &acc, float scale, voi
             if (row < M) *reinterpret_cast<uint4 *>(o + 16 * g + 8 * h) = make_uint4(w[4 * g], w[4 * g + 1], w[4 * g + 2], w[4 * g + 3]);
         }
     } else if (row < M) {
+        // the matrix ends inside the fragment, or its rows are not 16-byte aligned
 #pragma unroll
-        for (int v = 0; v < 16; v++) {
-            const int c = 8 * (v / 4) + 4 * h + v % 4;
-            if (n + c < N) o[c] = (uint16_t)(w[v / 2] >> (16 * (v & 1)));
+        for (int g = 0; g < 4; g++) {
+            const int at = 8 * g + 4 * h;
+            const int64_t left = N - (n + at);
+            if (left >= 4 && ld % 4 == 0) {
+                *reinterpret_cast<uint2 *>(o + at) = make_uint2(w[2 * g], w[2 * g + 1]);
+            } else {
+#pragma unroll
+                for (int x = 0; x < 4; x++)
+                    if (x < left) o[at + x] = (uint16_t)(w[2 * g + x / 2] >> (16 * (x & 1)));
+            }
         }
     }
 }

@@ -25,6 +25,10 @@ int moss_internal_cu_count();
 // Numbers of calls, for words in a workspace of unknown contents that carry their own validity: a word that holds the number of
 // the call in its upper 48 bits has been written by that call.  Never zero, never used again by this process.
 uint64_t moss_next_call();
+// A workgroup that looks for such words of workgroups that wait for nothing stops after kMaxLooks looks (most of a second)
+// all the same and takes what is there: a workspace that two overlapping calls share then gives a wrong result, as it always
+// has, and not a kernel that never ends.
+constexpr uint32_t kMaxLooks = 1u << 20;
 // false where a launch on the stream is being captured: a replay would use the number again, and find the words of the replay
 // before it.
 bool moss_may_number_calls(hipStream_t st);
@@ -161,8 +165,8 @@ __device__ __forceinline__ void finish_max_in_slots(const MaxSlots &s, const uin
     uint32_t top = 0;                // (THREADS % WORDS == 0: a thread's words are all of one kind)
     for (int i0 = threadIdx.x; i0 < n; i0 += THREADS * kLooks) {
         uint64_t v[kLooks];
-        bool there;
-        do {
+        bool there = false;
+        for (uint32_t looks = 0; !there && looks < kMaxLooks; looks++) {
             there = true;
 #pragma unroll
             for (int u = 0; u < kLooks; u++) {
@@ -172,7 +176,7 @@ __device__ __forceinline__ void finish_max_in_slots(const MaxSlots &s, const uin
 #pragma unroll
             for (int u = 0; u < kLooks; u++) there = there && (v[u] >> 16) == s.call;
             if (!there) __builtin_amdgcn_s_sleep(1);
-        } while (!there);
+        }
 #pragma unroll
         for (int u = 0; u < kLooks; u++) {
             const uint32_t x = (uint32_t)v[u] & 0xFFFFu;

@@ -327,6 +327,7 @@ __device__ __forceinline__ uint32_t scan_max(const uint16_t *__restrict__ x, int
 // takes the maximum over X by itself, so every wave ends whatever the scheduler does, with the same outputs.
 constexpr int kMaxSlots = kMaxPartials / 2;      // they lie where the two-launch path has its partial maxima
 constexpr uint32_t kNotMet = ~0u;
+constexpr uint32_t kMeetPolls = 1u << 12;        // most looks of the kernels below 16 MiB, and of row groupings
 
 // m: this thread's maximum.  Returns the maximum over the grid in every thread, or kNotMet.  red: 2 * THREADS / 64 words.
 template <int THREADS>
@@ -1255,7 +1256,9 @@ static int launch_meeting(const uint16_t *x, int64_t rows, int64_t cols, int64_t
 {
     using namespace moss;
     const int64_t n_chunks = rows * (cols / 8), cus = moss_internal_cu_count();
-    const uint32_t polls = g_poll_limit.load();
+    // (other kernels may hold the compute units where calls overlap on several streams; the search that ends the wait is short
+    // for tensors of this size, so the wait is too: some milliseconds)
+    const uint32_t limit = g_poll_limit.load(), polls = limit < kMeetPolls ? limit : kMeetPolls;
     if (!want_col) {
         static std::atomic<int> cached[2][6];
         const int k = row_meet_unroll_log2(n_chunks);

@@ -153,15 +153,15 @@ __device__ __forceinline__ void block_reduce_end(WCounts c, void *ws, int64_t sl
     WCounts all;
     for (int i = threadIdx.x; i < n; i += kWThreads) {
         uint64_t w[kFoldWords];
-        bool there;
-        do {
+        bool there = false;
+        for (uint32_t looks = 0; !there && looks < kMaxLooks; looks++) {
             there = true;
 #pragma unroll
             for (int j = 0; j < kFoldWords; j++) w[j] = __hip_atomic_load(words + i * kFoldWords + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
             for (int j = 0; j < kFoldWords; j++) there = there && (w[j] >> 16) == end.call;
             if (!there) __builtin_amdgcn_s_sleep(1);
-        } while (!there);
+        }
         auto value = [&](int j) { return ((uint32_t)w[j] & 0xFFFFu) | (uint32_t)w[j + 1] << 16; };
         all.amax = fmaxf(all.amax, __uint_as_float(value(0)));
         all.over += value(2);
