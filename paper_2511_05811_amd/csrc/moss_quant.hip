@@ -330,9 +330,13 @@ constexpr uint32_t kNotMet = ~0u;
 constexpr uint32_t kMeetPolls = 1u << 12;        // most looks of the kernels below 16 MiB, and of row groupings
 
 // m: this thread's maximum.  Returns the maximum over the grid in every thread, or kNotMet.  red: 2 * THREADS / 64 words.
-template <int THREADS>
+// meanwhile: what the workgroup does between leaving its word and looking for the others'.
+struct Nothing {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <int THREADS, typename F = Nothing>
 __device__ __forceinline__ uint32_t meet_in_slots(uint64_t *slots, int n, int mine, uint64_t call, uint32_t m, uint32_t poll_limit,
-                                                  uint32_t *red)
+                                                  uint32_t *red, F meanwhile = F())
 {
     constexpr int kWaves = THREADS / kWave, kLooks = 4;
     m = wave_max_u32(m);
@@ -340,12 +344,14 @@ __device__ __forceinline__ uint32_t meet_in_slots(uint64_t *slots, int n, int mi
     __syncthreads();
     if (n == 1) {                // nobody to meet
         for (int i = 0; i < kWaves; i++) m = red[i] > m ? red[i] : m;
+        meanwhile();
         return m;
     }
     if (threadIdx.x == 0) {
         for (int i = 1; i < kWaves; i++) m = red[i] > m ? red[i] : m;
         __hip_atomic_store(slots + mine, call << 16 | m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    meanwhile();
     uint32_t top = 0;
     for (int i0 = threadIdx.x; i0 < n; i0 += THREADS * kLooks) {
         uint64_t w[kLooks];
@@ -640,6 +646,10 @@ __device__ __forceinline__ void tile_group_maxima(const uint4 (&raw)[8], uint32_
     }
 }
 
+struct TileMaxima {
+    uint32_t r[8], c[8];
+};
+
 struct TileShape {
     int64_t rows, cols, ld;
 };
@@ -696,8 +706,9 @@ __device__ __forceinline__ uint32_t tile_absmax(const uint4 (&raw)[8])
 // The two forms never sit side by side in a loop body: a kernel runs the fast form over its tiles and the
 // general form afterwards for the (rare) tiles that need it, so that the fast form's registers stay few.
 // The body contains one workgroup barrier; the LDS staging area stays in use until the caller's next barrier.
-template <bool ROW, bool COL, bool CEIL, bool FAST, bool FULL, int W>
-__device__ __forceinline__ bool quant_tile_body(const uint4 (&raw)[8], const TileShape &sh, int64_t r0, int64_t c0,
+// maxima(mx) leaves the tile's group maxima (taken here, or kept from before).
+template <bool ROW, bool COL, bool CEIL, bool FAST, bool FULL, int W, typename F>
+__device__ __forceinline__ bool quant_tile_body(const uint4 (&raw)[8], F maxima, const TileShape &sh, int64_t r0, int64_t c0,
                                                 const GlobalScale &g, uint8_t *__restrict__ q_row,
                                                 uint8_t *__restrict__ e_row, uint8_t *__restrict__ q_col,
                                                 uint8_t *__restrict__ e_col, TileLds<W> &lds)
@@ -715,8 +726,9 @@ __device__ __forceinline__ bool quant_tile_body(const uint4 (&raw)[8], const Til
     uint32_t rbytes[2] = {0, 0}, cbytes[2] = {0, 0};
     bool redo = false;
     {
-        uint32_t rmax[8], cmax[8];
-        tile_group_maxima<ROW, COL>(raw, rmax, cmax);
+        TileMaxima mx;
+        maxima(mx);
+        const uint32_t (&rmax)[8] = mx.r, (&cmax)[8] = mx.c;
         if (FAST) {
             uint32_t sub_min = ~0u, min_fb = 255u;
 #pragma unroll
@@ -833,17 +845,19 @@ __device__ __forceinline__ bool tile_of_workgroup(uint32_t id, int tiles_x, int 
 }
 
 // A workgroup's only tile: the fast form, and the general one where that says so.  (lds.redo is zero, and a barrier ago.)
-template <bool ROW, bool CEIL, int W>
-__device__ __forceinline__ void quant_one_tile(const uint4 (&raw)[8], const TileShape &sh, int64_t r0, int64_t c0, const GlobalScale &g,
-                                               uint8_t *__restrict__ q_row, uint8_t *__restrict__ e_row,
+// maxima: see quant_tile_body; called by each form, so that a kernel short of registers can take them again (held across both
+// forms they spill at 4 waves per SIMD: 8192 x 11008 103 -> 135 us).
+template <bool ROW, bool CEIL, int W, typename F>
+__device__ __forceinline__ void quant_one_tile(const uint4 (&raw)[8], F maxima, const TileShape &sh, int64_t r0, int64_t c0,
+                                               const GlobalScale &g, uint8_t *__restrict__ q_row, uint8_t *__restrict__ e_row,
                                                uint8_t *__restrict__ q_col, uint8_t *__restrict__ e_col, TileLds<W> &lds)
 {
     const bool redo = tile_is_full<W>(sh, r0, c0)
-                          ? quant_tile_body<ROW, true, CEIL, true, true, W>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds)
-                          : quant_tile_body<ROW, true, CEIL, true, false, W>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
+                          ? quant_tile_body<ROW, true, CEIL, true, true, W>(raw, maxima, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds)
+                          : quant_tile_body<ROW, true, CEIL, true, false, W>(raw, maxima, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
     if (redo && (threadIdx.x & 63) == 0) atomicOr(&lds.redo, 1u);
     __syncthreads();
-    if (lds.redo) quant_tile_body<ROW, true, CEIL, false, false, W>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
+    if (lds.redo) quant_tile_body<ROW, true, CEIL, false, false, W>(raw, maxima, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
 }
 
 template <bool ROW, bool CEIL, bool SCAN>
@@ -869,7 +883,7 @@ __global__ __launch_bounds__(kQuantThreads, 4) void k_quant_tile(const uint16_t 
     const int64_t r0 = (int64_t)ty * kTile, c0 = (int64_t)tx * kTile;
     uint4 raw[8];
     load_tile<4>(raw, x, sh, r0, c0);
-    quant_one_tile<ROW, CEIL, 4>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
+    quant_one_tile<ROW, CEIL, 4>(raw, [&](TileMaxima &mx) { tile_group_maxima<ROW, true>(raw, mx.r, mx.c); }, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
 }
 
 // The same in one launch: a workgroup of W waves keeps its tile of 32 W rows x 128 columns in registers while the workgroups
@@ -893,14 +907,18 @@ __global__ __launch_bounds__(W *kWave, 2) void k_quant_tile_meet(const uint16_t 
     const int64_t r0 = (int64_t)ty * (W * kGroup), c0 = (int64_t)(t - ty * tiles_x) * kTile;
     uint4 raw[8];
     load_tile<W>(raw, x, sh, r0, c0);
-    uint32_t m = meet_in_slots<W * kWave>(slots, (int)total, t, call, tile_absmax(raw), poll_limit, red);
+    // (the group maxima do not need the scale: taken while the first words travel; 1024 x 4096 10.8 -> 9.2 us, 64 x 512 5.3 -> 5.15)
+    const uint32_t mine = tile_absmax(raw);
+    TileMaxima kept;
+    auto groups = [&]() { tile_group_maxima<ROW, true>(raw, kept.r, kept.c); };
+    uint32_t m = meet_in_slots<W * kWave>(slots, (int)total, t, call, mine, poll_limit, red, groups);
     if (m == kNotMet) {
         __syncthreads();
         m = scan_max<W * kWave>(x, (int)(rows * (cols / 8)), (int)(cols / 8), ld, ld == cols, red);
     }
     const GlobalScale g = make_global_scale<CEIL>(m);
     if (t == 0 && threadIdx.x == 0) *s_global = g.s;
-    quant_one_tile<ROW, CEIL, W>(raw, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
+    quant_one_tile<ROW, CEIL, W>(raw, [&](TileMaxima &mx) { mx = kept; }, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1079,7 +1097,8 @@ __global__ __launch_bounds__(kQuantThreads, 2) void k_quant_persist(const uint16
             int64_t r0, c0;
             origin(t, r0, c0);
             if (tile_is_full<4>(sh, r0, c0)) {
-                if (quant_tile_body<ROW, COL, CEIL, true, true, 4>(keep[k], sh, r0, c0, g, q_row, e_row, q_col, e_col, lds) &&
+                const auto maxima = [&](TileMaxima &mx) { tile_group_maxima<ROW, COL>(keep[k], mx.r, mx.c); };
+                if (quant_tile_body<ROW, COL, CEIL, true, true, 4>(keep[k], maxima, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds) &&
                     (threadIdx.x & 63) == 0)
                     atomicOr(&lds.redo, 1u << k);
                 __syncthreads();
@@ -1098,7 +1117,8 @@ __global__ __launch_bounds__(kQuantThreads, 2) void k_quant_persist(const uint16
         origin(kept_tile(k), r0, c0);
         uint4 ra[8];
         load_tile<4>(ra, x, sh, r0, c0);
-        quant_tile_body<ROW, COL, CEIL, false, false, 4>(ra, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
+        const auto maxima = [&](TileMaxima &mx) { tile_group_maxima<ROW, COL>(ra, mx.r, mx.c); };
+        quant_tile_body<ROW, COL, CEIL, false, false, 4>(ra, maxima, sh, r0, c0, g, q_row, e_row, q_col, e_col, lds);
         __syncthreads();
     }
     // the last of a flag's users (the group's members and the publisher) leaves flag and count at zero
@@ -1183,7 +1203,7 @@ static int64_t meet_tiles(int64_t rows, int64_t cols, int k)
 // (64 x 256 5.0 us with one wave, 6.4 with four), more workgroups take longer to meet (512 x 4096: 10.0 / 9.0 / 7.8 us with 512 /
 // 256 / 128).  From 512 tiles of 128 x 128 on the kernel below, which keeps up to four, takes as long or less (2048 x 4096 17.0
 // against 16.2, 4096 x 4096 30 against 22).
-// Against the launches it replaces: 64 x 256 7.0 -> 5.0 us, 256 x 2048 10.2 -> 6.0, 1024 x 4096 15.3 -> 10.5, 1600 x 4160 19.5 -> 16.2.
+// Against the launches it replaces: 64 x 256 7.0 -> 4.9 us, 256 x 2048 10.2 -> 5.6, 1024 x 4096 15.3 -> 9.0, 1600 x 4160 19.5 -> 14.0.
 static int tile_meet_waves_log2(int64_t rows, int64_t cols)
 {
     int k = 0;
