@@ -8,17 +8,19 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 // wave-wide direct global->LDS copy: every lane moves 16 bytes from base + off to
-// lds_addr + 16 * lane (lds_addr is wave-uniform and goes through M0)
+// lds_addr + 16 * lane (lds_addr is wave-uniform and goes through M0).  A copy into LDS that follows a scalar write of M0 needs
+// one wait state in between, or it may go where M0 pointed before; the compiler, which puts it there itself elsewhere, does not
+// look into an asm block.
 __device__ __forceinline__ void dma16(const uint8_t *base, uint32_t off, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(off), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
 
 // the same to lds_addr + at, which is added in the move to M0 (`at` is a constant once loops are unrolled)
 __device__ __forceinline__ void dma16_at(const uint8_t *base, uint32_t off, uint32_t lds_addr, int at)
 {
-    asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1"
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(off), "s"(base), "s"(lds_addr), "i"(at) : "memory", "m0", "scc");
 }
 
