@@ -25,10 +25,11 @@ int moss_internal_cu_count();
 // Numbers of calls, for words in a workspace of unknown contents that carry their own validity: a word that holds the number of
 // the call in its upper 48 bits has been written by that call.  Never zero, never used again by this process.
 uint64_t moss_next_call();
-// A workgroup that looks for such words of workgroups that wait for nothing stops after kMaxLooks looks (most of a second)
-// all the same and takes what is there: a workspace that two overlapping calls share then gives a wrong result, as it always
-// has, and not a kernel that never ends.
-constexpr uint32_t kMaxLooks = 1u << 20;
+// A workgroup that looks for such words of others stops after so many looks (some milliseconds), or moss_quant_set_poll_limit's
+// if that is less, and hands over what it waits for (moss::fold_is_ours): every kernel ends, whatever the others wait for.
+constexpr uint32_t kMaxLooks = 1u << 12;
+uint32_t moss_poll_limit();
+static inline uint32_t moss_looks() { return moss_poll_limit() < kMaxLooks ? moss_poll_limit() : kMaxLooks; }
 // false where a launch on the stream is being captured: a replay would use the number again, and find the words of the replay
 // before it.
 bool moss_may_number_calls(hipStream_t st);
@@ -133,6 +134,39 @@ __device__ __forceinline__ uint32_t look_at_word(const uint32_t *word, int look)
 __device__ __forceinline__ void merge_max_word(uint32_t *word, uint32_t m, uint32_t seen)
 {
     if (m > seen) __hip_atomic_fetch_max(word, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Words of a call that one workgroup folds.  Each workgroup leaves its own, the last of the grid, which mostly starts last, looks
+// for them all and folds them.  The others wait for nothing, but they may be kept off the machine for any time (the workgroups
+// are dealt to the XCDs in turn, and another stream's kernel may fill some of them), so that the last stops looking after a
+// while.  It then leaves a word that says so, `handed`, and looks once more; each of the others looks at that word behind its own
+// words, and if it is there looks at all words once.  Of the words and `handed`, all written before their writers look, whoever
+// wrote the last sees the others, so somebody finds all of them; the exchange makes that one workgroup.  Two calls that
+// share the words by mistake may leave them unfolded, as words of each are missing; nobody waits for them.
+//
+// The looking wave: true if the fold is its own.  It has stored its workgroup's words itself.  all_there: looks once at this
+// lane's share of the words.
+__device__ __forceinline__ uint64_t look_at_call(const uint64_t *word)
+{
+    return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void leave_for_call(uint64_t *word, uint64_t call, uint32_t value)
+{
+    __hip_atomic_store(word, call << 16 | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename F>
+__device__ __forceinline__ bool fold_is_ours(uint64_t *handed, uint64_t call, bool hand_over, F all_there)
+{
+    constexpr uint32_t kHanded = 1, kFolded = 2;
+    const int lane = threadIdx.x & 63;
+    if (hand_over && lane == 0) leave_for_call(handed, call, kHanded);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what this wave has left is there for everyone
+    if (!hand_over && !__any(look_at_call(handed) == (call << 16 | kHanded))) return false;
+    if (!__all(all_there())) return false;
+    uint64_t was = call << 16 | kHanded;
+    return __any(lane == 0 && __hip_atomic_compare_exchange_strong(handed, &was, call << 16 | kFolded, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                                  __HIP_MEMORY_SCOPE_AGENT));
 }
 
 // The same without the word: where the caller has memory to spare and calls may be numbered (moss_may_number_calls), each

@@ -1166,6 +1166,8 @@ int groups_per_cu(const void *fn, int threads, std::atomic<int> &cached)
 
 extern "C" void moss_quant_set_poll_limit(unsigned polls) { g_poll_limit.store(polls); }
 
+uint32_t moss_poll_limit() { return g_poll_limit.load(); }
+
 extern "C" size_t moss_quant_workspace_bytes(int64_t rows, int64_t cols, unsigned flags)
 {
     (void)rows; (void)cols; (void)flags;

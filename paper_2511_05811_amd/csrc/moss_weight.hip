@@ -116,20 +116,39 @@ __device__ __forceinline__ void advance_state(moss_wscale_state *st, const WCoun
     st->clipped_count += c.clip;
 }
 
-// The fold inside the pass.  A workgroup leaves its partial as six 64-bit words, the number of the call in the upper 48 bits
-// and 16 bits of the partial in each: a word that holds the number is this call's (see moss_next_call), so nothing has to be
-// cleared or counted, and the words may arrive in any order.  The last workgroup of the grid, which is dispatched after all
-// others, reads the words until each holds the number and advances the state.  It waits for the others, which wait for
-// nothing, and all of them have read the state by then.  The launch behind the pass that this replaces took 2 us on the
+// The fold inside the pass.  A workgroup leaves its partial as four 64-bit words, the number of the call in the upper 48 bits
+// and in the others the maximum's lower and upper half and the two counts (it has fewer than 2^16 elements): a word that holds
+// the number is this call's (see moss_next_call), so nothing has to be cleared or counted, and the words may arrive in any
+// order.  The last workgroup of the grid, or whoever it hands over to (fold_is_ours), advances the state once all words are
+// there; by then all workgroups have read the state.  The launch behind the pass that this replaces took 2 us on the
 // device, with what lies between two kernels, and 2.3 on the host.  Steps back to back: 64 x 64 8.3 -> 6.7 us, 512 x 256 9.0 -> 7.2, 1024 x
 // 1024 10.8 -> 9.5, 1792 x 1792 27.1 -> 24.6, 2048 x 2048 28.0 -> 26.5, 4096 x 4096 103.4 -> 101.9.
 struct StepEnd {
     uint64_t call;            // 0: partials for the kernel behind
     int64_t step;
     double lr_term;
+    uint32_t looks;
 };
-constexpr int kFoldWords = 6;
-constexpr int kFoldBlocks = kWMaxBlocks * 12 / (8 * kFoldWords);       // what fits the workspace: 1024
+constexpr int kFoldWords = 4;
+constexpr int kFoldBlocks = 1024;
+static_assert((kFoldBlocks * kFoldWords + 1) * 8 <= kWMaxBlocks * 12, "the words, and one to hand over by, fit the smallest workspace");
+static_assert(kFoldBlocks < kWMaxBlocks && kWTile * kWTile < 1 << 16, "a workgroup's elements (flat: 16 per thread below kWMaxBlocks)");
+
+// one look at the partial of workgroup i, added to c if it is there
+__device__ __forceinline__ bool take_partial(const uint64_t *words, int i, uint64_t call, WCounts &c)
+{
+    uint64_t w[kFoldWords];
+    bool there = true;
+#pragma unroll
+    for (int j = 0; j < kFoldWords; j++) w[j] = look_at_call(words + i * kFoldWords + j);
+#pragma unroll
+    for (int j = 0; j < kFoldWords; j++) there = there && (w[j] >> 16) == call;
+    if (!there) return false;
+    c.amax = fmaxf(c.amax, __uint_as_float(((uint32_t)w[0] & 0xFFFFu) | (uint32_t)w[1] << 16));
+    c.over += (uint32_t)w[2] & 0xFFFFu;
+    c.clip += (uint32_t)w[3] & 0xFFFFu;
+    return true;
+}
 
 __device__ __forceinline__ void block_reduce_end(WCounts c, void *ws, int64_t slots, moss_wscale_state *st, const StepEnd &end)
 {
@@ -137,38 +156,46 @@ __device__ __forceinline__ void block_reduce_end(WCounts c, void *ws, int64_t sl
         block_reduce_store(c, ws, slots);
         return;
     }
+    __shared__ uint32_t late;
+    if (threadIdx.x == 0) late = 0;
     block_reduce<kWThreads>(c);
-    uint64_t *words = reinterpret_cast<uint64_t *>(ws);
+    uint64_t *words = reinterpret_cast<uint64_t *>(ws), *handed = words + kFoldBlocks * kFoldWords;
     const int n = (int)(gridDim.x * gridDim.y), mine = (int)(blockIdx.y * gridDim.x + blockIdx.x);
     if (threadIdx.x < kWave) {
-        const uint32_t part[3] = {(uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(c.amax)),
-                                  (uint32_t)__builtin_amdgcn_readfirstlane((int)c.over), (uint32_t)__builtin_amdgcn_readfirstlane((int)c.clip)};
+        const uint32_t amax = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(c.amax));
+        const uint32_t over = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.over), clip = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.clip);
         const int j = threadIdx.x;
-        const uint32_t v = j < 2 ? part[0] : j < 4 ? part[1] : part[2];
-        if (j < kFoldWords)
-            __hip_atomic_store(words + mine * kFoldWords + j, end.call << 16 | (j & 1 ? v >> 16 : v & 0xFFFFu), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+        if (j < kFoldWords) leave_for_call(words + mine * kFoldWords + j, end.call, j == 0 ? amax & 0xFFFFu : j == 1 ? amax >> 16 : j == 2 ? over : clip);
     }
-    if (mine != n - 1) return;
+    const bool last = mine == n - 1;
     WCounts all;
-    for (int i = threadIdx.x; i < n; i += kWThreads) {
-        uint64_t w[kFoldWords];
-        bool there = false;
-        for (uint32_t looks = 0; !there && looks < kMaxLooks; looks++) {
-            there = true;
-#pragma unroll
-            for (int j = 0; j < kFoldWords; j++) w[j] = __hip_atomic_load(words + i * kFoldWords + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-            for (int j = 0; j < kFoldWords; j++) there = there && (w[j] >> 16) == end.call;
-            if (!there) __builtin_amdgcn_s_sleep(1);
+    if (last) {
+        for (int i = threadIdx.x; i < n; i += kWThreads) {
+            bool there = false;
+            for (uint32_t looks = 0; !there && looks < end.looks; looks++) {
+                there = take_partial(words, i, end.call, all);
+                if (!there) __builtin_amdgcn_s_sleep(1);
+            }
+            if (!there) late = 1;
         }
-        auto value = [&](int j) { return ((uint32_t)w[j] & 0xFFFFu) | (uint32_t)w[j + 1] << 16; };
-        all.amax = fmaxf(all.amax, __uint_as_float(value(0)));
-        all.over += value(2);
-        all.clip += value(4);
+        __syncthreads();             // (and thread 0 has read what the first reduction left)
+        if (!late) {
+            block_reduce<kWThreads>(all);
+            if (threadIdx.x == 0) advance_state(st, all, end.lr_term, end.step);
+            return;
+        }
     }
-    __syncthreads();                 // (thread 0 has read what the first reduction left)
-    block_reduce<kWThreads>(all);
+    if (threadIdx.x >= kWave) return;
+    const bool ours = fold_is_ours(handed, end.call, last, [&]() {
+        bool there = true;
+        all = WCounts();
+        for (int i = threadIdx.x; i < n; i += kWave) there = take_partial(words, i, end.call, all) && there;
+        return there;
+    });
+    if (!ours) return;
+    all.amax = wave_max_f32(all.amax);
+    all.over = wave_sum_u32(all.over);
+    all.clip = wave_sum_u32(all.clip);
     if (threadIdx.x == 0) advance_state(st, all, end.lr_term, end.step);
 }
 
@@ -724,14 +751,14 @@ extern "C" int moss_weight_autoscale_cast(float *w, float *m, float *v, const vo
 
     if (rebase) {
         // AdamW alone (it yields amax(W_new)), re-base the scale from it, then cast with the new scale
-        launch_flat<false>(L, gb, w, m, v, g, a, StepEnd{0, 0, lr_term}, wq, kNextCast);
+        launch_flat<false>(L, gb, w, m, v, g, a, StepEnd{0, 0, lr_term, 0}, wq, kNextCast);
         MOSS_LAUNCH_CHECK();
         if ((rc = finalize(L, L.grid1d, kFinRebase, lr_term, args->step))) return rc;
         return cast_only(L, w, false, wq, wq_t);
     }
     const bool tiled = wq_t && tile_path_ok(rows, cols);
     const int blocks = tiled ? (int)(L.grid2d.x * L.grid2d.y) : L.grid1d;
-    const StepEnd end{folds_itself(blocks) && moss_may_number_calls(L.st) ? moss_next_call() : 0, args->step, lr_term};
+    const StepEnd end{folds_itself(blocks) && moss_may_number_calls(L.st) ? moss_next_call() : 0, args->step, lr_term, moss_looks()};
     if (tiled) launch_tile<true>(L, gb, w, m, v, g, a, end, wq, wq_t);
     else launch_flat<true>(L, gb, w, m, v, g, a, end, wq, wq_t && cols <= 256 ? kNextNarrowTranspose : kNextNothing);
     MOSS_LAUNCH_CHECK();

@@ -297,43 +297,66 @@ def test_step_number_that_disagrees_with_the_state_is_flagged():
 
 
 # one workgroup, a few, as many as fold their partials themselves, one more (the kernel behind); tiles of 32 and 128 rows, flat
-@pytest.mark.parametrize("rows,cols,transpose", [(16, 4, True), (1, 4, False), (96, 160, True), (4096, 4096, True), (4096, 4224, True),
-                                                 (1024, 4096, False), (1025, 4096, False)])
+FOLDS = [(16, 4, True), (1, 4, False), (96, 160, True), (4096, 4096, True), (4096, 4224, True), (1024, 4096, False), (1025, 4096, False)]
+
+
+def fold_steps(rows, cols, transpose, captured, steps=3):
+    """Outputs and state after each step, on a workspace of unknown contents."""
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev).manual_seed(rows + cols)
+    w = torch.randn(rows, cols, generator=gen, device=dev) * 0.02
+    grads = [torch.randn(rows, cols, generator=gen, device=dev) * 1e-3 for _ in range(3)]
+    m, v, g = torch.zeros_like(w), torch.zeros_like(w), torch.empty_like(w)
+    state = moss.new_wscale_state(dev)
+    ws = torch.full((moss.load().moss_weight_workspace_bytes(rows, cols),), 0xA5, dtype=torch.uint8, device=dev)
+    wq, wq_t = moss.weight_autoscale_init(w, state, want_transpose=transpose, workspace=ws)
+    out = []
+    for t in range(1, steps + 1):
+        g.copy_(grads[t % 3])
+        hp = mi.adamw_hparams(t, lr=1e-2, margin=1e-4)
+        args = moss.AdamWArgs(hp["lr"], hp["beta1"], hp["beta2"], hp["eps"], hp["weight_decay"], hp["one_minus_beta1"],
+                              hp["one_minus_beta2"], hp["bias_corr1"], hp["bias_corr2"], hp["margin"], 500, t)
+        step = lambda: moss.weight_autoscale_cast(w, m, v, g, args, state, wq=wq, wq_t=wq_t, workspace=ws)
+        if captured:
+            graph = torch.cuda.CUDAGraph()
+            torch.cuda.synchronize()
+            with torch.cuda.graph(graph):
+                step()
+            graph.replay()
+        else:
+            step()
+        torch.cuda.synchronize()
+        if t > steps - 3:
+            out.append([x.clone() for x in (w, m, v, wq, state)] + ([wq_t.clone()] if transpose else []))
+    return out
+
+
+@pytest.mark.parametrize("rows,cols,transpose", FOLDS)
 def test_the_fold_inside_the_pass_gives_what_the_kernel_behind_gives(rows, cols, transpose):
     """A captured step leaves its partials to the kernel behind, an eager one may fold them itself: same state (with counters
     that count: the bound is broken on purpose) and same outputs over three steps on a workspace of unknown contents."""
     print(f"[fold] {rows}x{cols} transpose={transpose}", flush=True)
-    dev = torch.device("cuda:0")
-    gen = torch.Generator(device=dev).manual_seed(rows + cols)
-    w0 = torch.randn(rows, cols, generator=gen, device=dev) * 0.02
-    grads = [torch.randn(rows, cols, generator=gen, device=dev) * 1e-3 for _ in range(3)]
-    runs = []
-    for captured in (False, True):
-        w, m, v, g = w0.clone(), torch.zeros_like(w0), torch.zeros_like(w0), torch.empty_like(w0)
-        state = moss.new_wscale_state(dev)
-        ws = torch.full((moss.load().moss_weight_workspace_bytes(rows, cols),), 0xA5, dtype=torch.uint8, device=dev)
-        wq, wq_t = moss.weight_autoscale_init(w, state, want_transpose=transpose, workspace=ws)
-        out = []
-        for t in range(1, 4):
-            g.copy_(grads[t - 1])
-            hp = mi.adamw_hparams(t, lr=1e-2, margin=1e-4)
-            args = moss.AdamWArgs(hp["lr"], hp["beta1"], hp["beta2"], hp["eps"], hp["weight_decay"], hp["one_minus_beta1"],
-                                  hp["one_minus_beta2"], hp["bias_corr1"], hp["bias_corr2"], hp["margin"], 500, t)
-            step = lambda: moss.weight_autoscale_cast(w, m, v, g, args, state, wq=wq, wq_t=wq_t, workspace=ws)
-            if captured:
-                graph = torch.cuda.CUDAGraph()
-                torch.cuda.synchronize()
-                with torch.cuda.graph(graph):
-                    step()
-                graph.replay()
-            else:
-                step()
-            torch.cuda.synchronize()
-            out.append([x.clone() for x in (w, m, v, wq, state)] + ([wq_t.clone()] if transpose else []))
-        runs.append(out)
+    runs = [fold_steps(rows, cols, transpose, captured) for captured in (False, True)]
     for eager, graphed in zip(*runs):
         for a, b in zip(eager, graphed):
             assert torch.equal(a, b)
     last = moss.read_wscale_state(runs[0][-1][4])
     assert last.step == 3 and last.flags == 0
     assert rows * cols < 100 or last.overflow_count > 0
+
+
+@pytest.mark.parametrize("rows,cols,transpose", FOLDS)
+def test_a_fold_that_is_handed_over_is_the_same(rows, cols, transpose):
+    """With no look at the others' partials (limit 0) the last workgroup hands the fold over at once, to itself or to whichever
+    comes later: same states and outputs, in every one of many steps."""
+    print(f"[fold handed over] {rows}x{cols} transpose={transpose}", flush=True)
+    want = fold_steps(rows, cols, transpose, False, steps=60)
+    moss.quant_set_poll_limit(0)
+    try:
+        got = fold_steps(rows, cols, transpose, False, steps=60)
+    finally:
+        moss.quant_set_poll_limit(32768)
+    for a, b in zip(want, got):
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
+    assert moss.read_wscale_state(got[-1][4]).step == 60
