@@ -122,7 +122,8 @@ int moss_quant_act_2level_noalloc(const void *x_bf16, int64_t rows, int64_t cols
  * grid may have to wait for them, and workgroups then fall back to the slow path after the
  * bound -- correct, but slow; quantizer calls that must overlap other work should be
  * serialised on one stream.  The bound holds as well for the workgroup of moss_weight_autoscale_cast
- * that collects what the others have counted: past it, one that comes later does. */
+ * and of the BF16 producers below that collects what the others have found: past it, one that comes
+ * later does. */
 void moss_quant_set_poll_limit(unsigned polls);
 
 /* The same quantizer for a tensor whose producer already knows a bound of |X| (Sec. 3.1, Eq. 2:

@@ -171,18 +171,19 @@ __device__ __forceinline__ bool fold_is_ours(uint64_t *handed, uint64_t call, bo
 
 // The same without the word: where the caller has memory to spare and calls may be numbered (moss_may_number_calls), each
 // workgroup leaves its maxima (WORDS of them, BF16 magnitudes in thread 0) beside the number of the call in slots of its own,
-// and the last of the grid, which waits for nobody that waits, reads them all and writes the caller's words.  No launch to
+// and the last of the grid, or whoever it hands over to, reads them all and writes the caller's words.  No launch to
 // clear the words ahead, no queue of atomics, no look.  red: WORDS per wave.
 struct MaxSlots {
     uint64_t *words;
     uint64_t call;           // 0: merge into the words, which a launch ahead has cleared
+    uint32_t looks;
 };
 constexpr int kMaxSlotBlocks = 2048;
 
 static inline MaxSlots max_slots(void *workspace, size_t bytes, int blocks, int words, hipStream_t st)
 {
-    const bool fits = workspace && moss_aligned16(workspace) && blocks <= kMaxSlotBlocks && bytes >= (size_t)blocks * words * 8;
-    return MaxSlots{(uint64_t *)workspace, fits && moss_may_number_calls(st) ? moss_next_call() : 0};
+    const bool fits = workspace && moss_aligned16(workspace) && blocks <= kMaxSlotBlocks && bytes >= ((size_t)blocks * words + 1) * 8;
+    return MaxSlots{(uint64_t *)workspace, fits && moss_may_number_calls(st) ? moss_next_call() : 0, moss_looks()};
 }
 
 template <int WORDS, int THREADS>
@@ -190,50 +191,84 @@ __device__ __forceinline__ void finish_max_in_slots(const MaxSlots &s, const uin
 {
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int w = 0; w < WORDS; w++)
-            __hip_atomic_store(s.words + (size_t)blockIdx.x * WORDS + w, s.call << 16 | m[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int w = 0; w < WORDS; w++) leave_for_call(s.words + (size_t)blockIdx.x * WORDS + w, s.call, m[w]);
     }
-    if (blockIdx.x != gridDim.x - 1) return;
     constexpr int kLooks = 4;
+    constexpr uint32_t kLate = ~0u;
+    static_assert(THREADS % WORDS == 0 && kWave % WORDS == 0, "a thread's slots are all of one kind");
     const int n = (int)gridDim.x * WORDS;
-    uint32_t top = 0;                // (THREADS % WORDS == 0: a thread's words are all of one kind)
-    for (int i0 = threadIdx.x; i0 < n; i0 += THREADS * kLooks) {
-        uint64_t v[kLooks];
-        bool there = false;
-        for (uint32_t looks = 0; !there && looks < kMaxLooks; looks++) {
-            there = true;
+    const bool last = blockIdx.x == gridDim.x - 1;
+    auto write = [&](int w, uint32_t top) {
 #pragma unroll
-            for (int u = 0; u < kLooks; u++) {
-                v[u] = s.call << 16;
-                if (i0 + u * THREADS < n) v[u] = __hip_atomic_load(s.words + i0 + u * THREADS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+        for (int k = 0; k < WORDS; k++)
+            if (w == k) *out[k] = top;
+    };
+    // the largest of each kind, in the first WORDS lanes of the wave
+    auto largest = [&](uint32_t top) {
 #pragma unroll
-            for (int u = 0; u < kLooks; u++) there = there && (v[u] >> 16) == s.call;
-            if (!there) __builtin_amdgcn_s_sleep(1);
-        }
-#pragma unroll
-        for (int u = 0; u < kLooks; u++) {
-            const uint32_t x = (uint32_t)v[u] & 0xFFFFu;
-            top = x > top ? x : top;
-        }
-    }
-#pragma unroll
-    for (int off = 32; off >= WORDS; off >>= 1) {
-        const uint32_t o = (uint32_t)__shfl_xor((int)top, off, 64);
-        top = o > top ? o : top;
-    }
-    __syncthreads();                 // (red is free: thread 0 has read what the workgroup's own reduction left)
-    if ((threadIdx.x & 63) < WORDS) red[(threadIdx.x >> 6) * WORDS + (threadIdx.x & 63)] = top;
-    __syncthreads();
-    if (threadIdx.x < WORDS) {
-        for (int k = 0; k < THREADS / 64; k++) {
-            const uint32_t o = red[k * WORDS + threadIdx.x];
+        for (int off = 32; off >= WORDS; off >>= 1) {
+            const uint32_t o = (uint32_t)__shfl_xor((int)top, off, 64);
             top = o > top ? o : top;
         }
+        return top;
+    };
+    if (last) {
+        uint32_t top = 0;
+        for (int i0 = threadIdx.x; i0 < n; i0 += THREADS * kLooks) {
+            uint64_t v[kLooks];
+            bool there = false;
+            for (uint32_t looks = 0; !there && looks < s.looks; looks++) {
+                there = true;
 #pragma unroll
-        for (int w = 0; w < WORDS; w++)
-            if ((int)threadIdx.x == w) *out[w] = top;
+                for (int u = 0; u < kLooks; u++) {
+                    v[u] = s.call << 16;
+                    if (i0 + u * THREADS < n) v[u] = look_at_call(s.words + i0 + u * THREADS);
+                }
+#pragma unroll
+                for (int u = 0; u < kLooks; u++) there = there && (v[u] >> 16) == s.call;
+                if (!there) __builtin_amdgcn_s_sleep(1);
+            }
+            if (!there) {
+                top = kLate;
+                break;
+            }
+#pragma unroll
+            for (int u = 0; u < kLooks; u++) {
+                const uint32_t x = (uint32_t)v[u] & 0xFFFFu;
+                top = x > top ? x : top;
+            }
+        }
+        top = largest(top);
+        __syncthreads();             // (red is free: thread 0 has read what the workgroup's own reduction left)
+        if ((threadIdx.x & 63) < WORDS) red[(threadIdx.x >> 6) * WORDS + (threadIdx.x & 63)] = top;
+        __syncthreads();
+        if (threadIdx.x >= kWave) return;
+        top = 0;
+        if (threadIdx.x < WORDS)
+            for (int k = 0; k < THREADS / kWave; k++) {
+                const uint32_t o = red[k * WORDS + threadIdx.x];
+                top = o > top ? o : top;
+            }
+        if (!__any(top == kLate)) {
+            if (threadIdx.x < WORDS) write((int)threadIdx.x, top);
+            return;
+        }
     }
+    if (threadIdx.x >= kWave) return;
+    uint32_t top = 0;
+    const bool ours = fold_is_ours(s.words + n, s.call, last, [&]() {
+        bool there = true;
+        for (int i = threadIdx.x; i < n; i += kWave) {
+            const uint64_t v = look_at_call(s.words + i);
+            const uint32_t x = (uint32_t)v & 0xFFFFu;
+            there = there && (v >> 16) == s.call;
+            top = x > top ? x : top;
+        }
+        return there;
+    });
+    if (!ours) return;
+    top = largest(top);
+    if (threadIdx.x < WORDS) write((int)threadIdx.x, top);
 }
 
 // Two FP32 values -> two E4M3 bytes in the low half of the result.  The hardware

@@ -5,7 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
-constexpr size_t kProducerWorkspaceBytes = 2 * 2048 * 8;       // two words for each workgroup of the largest grid
+constexpr size_t kProducerWorkspaceBytes = (2 * 2048 + 1) * 8;       // two words for each workgroup of the largest grid, one to hand over by
 
 extern "C" {
 int moss_internal_swiglu_bf16(const void *gate, const void *up, int64_t rows, int64_t cols, int64_t ld, void *h,

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu(const uint16_t *__restric
 {
     __shared__ uint32_t red[kSwThreads / kWave];
     uint32_t m = 0;
-    asm volatile("" ::"s"(slots.words), "s"(slots.call));      // (fetched here, not at the end in front of the slots)
+    asm volatile("" ::"s"(slots.words), "s"(slots.call), "s"(slots.looks));      // (fetched here, not at the end in front of the slots)
     const int64_t stride = (int64_t)gridDim.x * kSwThreads * CHUNKS;
     for (int64_t id0 = (int64_t)blockIdx.x * kSwThreads * CHUNKS + threadIdx.x; id0 < n_chunks; id0 += stride) {
         uint4 g[CHUNKS], u[CHUNKS];
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kSwThreads) void k_swiglu_backward(const uint16_t *
 {
     __shared__ uint32_t red[kSwThreads / kWave], red_u[kSwThreads / kWave], red_all[2 * kSwThreads / kWave];
     uint32_t mg = 0, mu = 0;
-    asm volatile("" ::"s"(slots.words), "s"(slots.call));      // (fetched here, not at the end in front of the slots)
+    asm volatile("" ::"s"(slots.words), "s"(slots.call), "s"(slots.looks));      // (fetched here, not at the end in front of the slots)
     const int64_t stride = (int64_t)gridDim.x * kSwThreads * CHUNKS;
     for (int64_t id0 = (int64_t)blockIdx.x * kSwThreads * CHUNKS + threadIdx.x; id0 < n_chunks; id0 += stride) {
         uint4 gc[CHUNKS], uc[CHUNKS], dc[CHUNKS];

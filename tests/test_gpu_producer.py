@@ -200,3 +200,27 @@ def test_maximum_words_from_slots_are_those_of_the_atomics(rows, cols, pad):
         words = [t for t in got if t.dtype == torch.int32]
         for t, w in zip(tensors, words):
             assert int(w) == int((t.contiguous().view(torch.int16).int() & 0x7FFF).max()), k
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 8), (32, 256), (1033, 2056), (8192, 4096)])
+def test_maximum_words_of_a_fold_that_is_handed_over(rows, cols):
+    """With no look at the others' slots (limit 0) the last workgroup hands the fold over at once, to itself or to whichever
+    comes later: the words are the largest magnitudes written, in every one of many calls."""
+    gen = torch.Generator(device="cuda:0").manual_seed(rows + cols)
+    a, b, c = (torch.randn(rows, cols, generator=gen, device="cuda:0").bfloat16() for _ in range(3))
+    gamma = torch.randn(cols, generator=gen, device="cuda:0").bfloat16()
+    calls = (lambda w: moss.swiglu_bf16(a, b, absmax_bits=w[0])[:1], lambda w: moss.swiglu_bf16_backward(a, b, c, d_gate_absmax_bits=w[0], d_up_absmax_bits=w[1])[:2],
+             lambda w: moss.add_rmsnorm_bf16(a, gamma, 1e-5, delta=b, absmax_bits=w[0])[1:2],
+             lambda w: moss.rmsnorm_bf16_backward(a, gamma, b, 1e-5, d_res=c, absmax_bits=w[0])[:1])
+    moss.quant_set_poll_limit(0)
+    try:
+        for k, call in enumerate(calls):
+            print(f"[fold handed over] {rows}x{cols} producer {k}", flush=True)
+            words = torch.full((50, 2, 1), -1, dtype=torch.int32, device="cuda:0")
+            for again in range(50):
+                tensors = call(words[again])
+            torch.cuda.synchronize()
+            for j, t in enumerate(tensors):
+                assert bool((words[:, j] == (t.view(torch.int16).int() & 0x7FFF).max()).all()), (k, j)
+    finally:
+        moss.quant_set_poll_limit(32768)
