@@ -117,11 +117,12 @@ int moss_quant_act_2level_noalloc(const void *x_bf16, int64_t rows, int64_t cols
  * maximum from X by itself, so the kernel ends even if its workgroups cannot all run at once;
  * the outputs are the same on either path.  Process-wide, takes effect from the next call; the
  * default is 32768.  0 makes every workgroup that finds the result not yet published take the
- * slow path (used by the tests).  The one-launch kernel assumes the device to itself: when other
- * kernels occupy compute units at the same time (calls on several streams at once) part of its
- * grid may have to wait for them, and workgroups then fall back to the slow path after the
- * bound -- correct, but slow; quantizer calls that must overlap other work should be
- * serialised on one stream.  The bound holds as well for the workgroup of moss_weight_autoscale_cast
+ * slow path (used by the tests).  The one-launch kernels assume that their grid fits the device: when
+ * other kernels occupy compute units at the same time (calls on several streams at once) part of it may
+ * have to wait for them, and workgroups then fall back to the slow path after the bound -- correct, but
+ * slow: four streams of calls of 16 MiB and more in turn take milliseconds a call, of 8 to 16 MiB with column
+ * groups 80 to 120 microseconds (smaller ones, two streams, and calls beside a GEMM lose little or nothing);
+ * such calls should be serialised on one stream.  The bound holds as well for the workgroup of moss_weight_autoscale_cast
  * and of the BF16 producers below that collects what the others have found: past it, one that comes
  * later does. */
 void moss_quant_set_poll_limit(unsigned polls);

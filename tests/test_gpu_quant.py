@@ -292,3 +292,23 @@ def test_meeting_in_slots_gives_the_outputs_of_a_captured_call(rows, cols, pad, 
 @pytest.mark.parametrize("shape", [(64, 256), (96, 160)])       # whole tiles, tiles over the right edge
 def test_meeting_in_slots_on_tensors_that_the_fast_form_does_not_cover(oracle, name, shape):
     check_against_oracle(oracle, mi.adversarial_activations(*shape)[name], 0, name)
+
+
+@pytest.mark.parametrize("rows,cols,flags", [(64, 512, ROW | COL), (1024, 4096, ROW), (1536, 4096, ROW | COL), (4096, 4096, ROW | COL)])
+def test_calls_that_overlap_on_four_streams_give_the_outputs_of_calls_in_turn(rows, cols, flags):
+    """Grids that meet and do not all fit the machine at once: each on tensors, outputs and scratch of its own."""
+    xs = [bf16_to_gpu(mi.heavy_tailed_activation(rows, cols, seed=rows + k)) for k in range(4)]
+    want = [moss.quant_act_2level(x, flags) for x in xs]
+    streams = [torch.cuda.Stream() for _ in xs]
+    spaces = [torch.full((moss.load().moss_quant_workspace_bytes(rows, cols, flags),), 0xA5, dtype=torch.uint8, device=x.device) for x in xs]
+    got = [[{k: torch.zeros_like(v) for k, v in w.items() if v is not None} for w in want] for _ in range(4)]
+    torch.cuda.synchronize()
+    for again in got:
+        for x, out, space, stream in zip(xs, again, spaces, streams):
+            with torch.cuda.stream(stream):
+                moss.quant_act_2level(x, flags, out=out, workspace=space)
+    torch.cuda.synchronize()
+    for again in got:
+        for out, w in zip(again, want):
+            for k in out:
+                assert torch.equal(out[k], w[k]), k
