@@ -248,28 +248,46 @@ extern "C" size_t moss_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
 //
 // The choice has two steps.  The first is made as if the large tiles took whole stages only (K % 128 == 0); the second gives
 // a problem whose K ends inside a stage to the large tiles all the same where they are faster than what the first has chosen.
-//
-// First step: the tile (rows * 1000 + columns) for a problem whose exponents, where given, are aligned; 0 for the general
-// kernel (the tests hold the choice by it)
+namespace {
+
+struct Choice {
+    int kind;         // small tiles, or -1
+    bool large_ok;    // the large tiles can take it: they do without small tiles, and otherwise if those cannot be launched
+    bool ragged;      // by the second step
+};
+
+Choice choose(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int64_t ld_out, int accumulate)
+{
+    if (K % 128 != 0 && moss_internal_gemm_big_ragged(M, N, K, a_e, b_e, accumulate, ld_out)) return Choice{-1, true, true};
+    const bool large_ok = moss_internal_gemm_big_ok(M, N, K, a_e, b_e, ld_out);
+    return Choice{moss_internal_gemm_mid_kind(M, N, K, a_e, b_e, accumulate, large_ok), large_ok, false};
+}
+
+Choice choose_for_aligned(int64_t M, int64_t N, int64_t K, int64_t has_a_e, int64_t has_b_e, int64_t ld_out, int64_t accumulate)
+{
+    static const uint8_t some[16] __attribute__((aligned(16))) = {};
+    return choose(M, N, K, has_a_e ? some : nullptr, has_b_e ? some : nullptr, ld_out, (int)accumulate);
+}
+
+int large_tile(int64_t M, int64_t N) { return moss_internal_gemm_big_narrow(M, N) ? 128256 : 256256; }
+
+}  // namespace
+
+// The tile (rows * 1000 + columns) that moss_gemm_fp8_mx takes for a problem whose exponents, where given, are aligned; 0 for
+// the general kernel (the tests hold the choice by it)
 extern "C" int moss_internal_gemm_tile(int64_t M, int64_t N, int64_t K, int64_t has_a_e, int64_t has_b_e, int64_t ld_out,
                                        int64_t accumulate)
 {
-    static const uint8_t some[16] __attribute__((aligned(16))) = {};
-    const uint8_t *a_e = has_a_e ? some : nullptr, *b_e = has_b_e ? some : nullptr;
-    const bool large_ok = moss_internal_gemm_big_ok(M, N, K, a_e, b_e, ld_out);
     static const int tiles[5] = {32032, 64064, 64128, 128128, 128192};
-    const int kind = moss_internal_gemm_mid_kind(M, N, K, a_e, b_e, (int)accumulate, large_ok);
-    if (kind >= 0) return tiles[kind];
-    return large_ok ? (moss_internal_gemm_big_narrow(M, N) ? 128256 : 256256) : 0;
+    const Choice c = choose_for_aligned(M, N, K, has_a_e, has_b_e, ld_out, accumulate);
+    return c.kind >= 0 ? tiles[c.kind] : c.large_ok ? large_tile(M, N) : 0;
 }
 
-// Second step: the large tile that takes a problem with K % 128 != 0, 0 if the first step's choice stands
+// The large tile that takes a problem by the second step, 0 if the first step's choice stands
 extern "C" int moss_internal_gemm_ragged_tile(int64_t M, int64_t N, int64_t K, int64_t has_a_e, int64_t has_b_e, int64_t ld_out,
                                               int64_t accumulate)
 {
-    static const uint8_t some[16] __attribute__((aligned(16))) = {};
-    if (!moss_internal_gemm_big_ragged(M, N, K, has_a_e ? some : nullptr, has_b_e ? some : nullptr, (int)accumulate, ld_out)) return 0;
-    return moss_internal_gemm_big_narrow(M, N) ? 128256 : 256256;
+    return choose_for_aligned(M, N, K, has_a_e, has_b_e, ld_out, accumulate).ragged ? large_tile(M, N) : 0;
 }
 
 extern "C" int moss_gemm_fp8_mx(int64_t M, int64_t N, int64_t K,
@@ -288,13 +306,11 @@ extern "C" int moss_gemm_fp8_mx(int64_t M, int64_t N, int64_t K,
     if (((uintptr_t)a_s & 3) || ((uintptr_t)b_s & 3)) return MOSS_ERR_ALIGN;
     if (K % 16) return MOSS_ERR_ALIGN;
     const int f32 = out_dtype == MOSS_DT_F32;
-    const bool ragged = K % 128 != 0 && moss_internal_gemm_big_ragged(M, N, K, a_e, b_e, accumulate, ld_out);
-    const bool large_ok = ragged || moss_internal_gemm_big_ok(M, N, K, a_e, b_e, ld_out);
-    const int kind = ragged ? -1 : moss_internal_gemm_mid_kind(M, N, K, a_e, b_e, accumulate, large_ok);
+    const Choice c = choose(M, N, K, a_e, b_e, ld_out, accumulate);
     int rc = MOSS_ERR_UNSUPPORTED;
-    if (kind >= 0)
-        rc = moss_internal_gemm_mid(kind, M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, f32, ld_out, accumulate, (hipStream_t)stream);
-    if (rc == MOSS_ERR_UNSUPPORTED && large_ok)
+    if (c.kind >= 0)
+        rc = moss_internal_gemm_mid(c.kind, M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, f32, ld_out, accumulate, (hipStream_t)stream);
+    if (rc == MOSS_ERR_UNSUPPORTED && c.large_ok)
         rc = moss_internal_gemm_big(M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, f32, ld_out, accumulate, (hipStream_t)stream);
     if (rc != MOSS_ERR_UNSUPPORTED) return rc;
     return launch_gemm<128, 128, 2, 2, kModeFp8Mx>(M, N, K, a_q, a_e, a_s, b_q, b_e, b_s, out, out_dtype == MOSS_DT_F32,
