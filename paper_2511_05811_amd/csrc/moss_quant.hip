@@ -325,7 +325,7 @@ __device__ __forceinline__ uint32_t scan_max(const uint16_t *__restrict__ x, int
 // call is never used again (a replay of a captured graph would use it again: captured calls take other paths).  The wait
 // is bounded: a workgroup that does not find a slot filled within poll_limit looks (the grid was not co-resident after all)
 // takes the maximum over X by itself, so every wave ends whatever the scheduler does, with the same outputs.
-constexpr int kMaxSlots = kMaxPartials / 2;      // they lie where the two-launch path has its partial maxima
+constexpr int kMaxSlots = kMaxPartials / 2;      // they lie where the two-launch path has its partial maxima (may_meet)
 constexpr uint32_t kNotMet = ~0u;
 constexpr uint32_t kMeetPolls = 1u << 12;        // most looks of the kernels below 16 MiB, and of row groupings
 
@@ -1181,6 +1181,11 @@ static bool scans(int64_t bytes, bool dense, bool want_col)
     return bytes <= (dense ? kScanBytesRow : kScanBytesRowStrided);
 }
 
+// Whether a grid may meet in slots: all of it runs at once (`held`: workgroups that the device holds), and each workgroup has a slot.
+static bool may_meet(int64_t grid, int64_t held) { return grid <= held && grid <= moss::kMaxSlots; }
+
+extern "C" int moss_internal_quant_may_meet(int64_t grid, int64_t held) { return may_meet(grid, held); }
+
 // log2 of the chunks per thread of k_quant_row_meet, -1 if the tensor is too large for it.  One workgroup per compute unit of
 // the 256 up to 8 MiB, two above: fewer workgroups meet sooner (2 MiB 6.3 us with 256 of them, 7.2 with 512; 4 MiB 6.9 and 8.3,
 // with 1024 11.0), more of them load faster (16 MiB 11.1 either way, 28 MiB 15.8 and 14.5, 64 MiB 24.8 and 23.5).
@@ -1292,7 +1297,7 @@ static int launch_meeting(const uint16_t *x, int64_t rows, int64_t cols, int64_t
                                       k_quant_row_meet<true, 8>, k_quant_row_meet<true, 16>, k_quant_row_meet<true, 32>}};
         const Fn fn = fns[ceil_mode][k];
         const int64_t grid = (n_chunks + (kQuantThreads << k) - 1) / (kQuantThreads << k);
-        if (grid > cus * groups_per_cu(reinterpret_cast<const void *>(fn), kQuantThreads, cached[ceil_mode][k])) return MOSS_ERR_UNSUPPORTED;
+        if (!may_meet(grid, cus * groups_per_cu(reinterpret_cast<const void *>(fn), kQuantThreads, cached[ceil_mode][k]))) return MOSS_ERR_UNSUPPORTED;
         hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kQuantThreads), 0, st, x, (int)n_chunks, (int)(cols / 8), ld, (int)(ld == cols),
                            slots, call, polls, q_row, e_row, s_global);
         MOSS_LAUNCH_CHECK();
@@ -1311,7 +1316,7 @@ static int launch_meeting(const uint16_t *x, int64_t rows, int64_t cols, int64_t
     const Fn fn = fns[want_row][ceil_mode][k];
     const int threads = kWave << k;
     const int64_t tiles = meet_tiles(rows, cols, k);
-    if (tiles > cus * groups_per_cu(reinterpret_cast<const void *>(fn), threads, cached[want_row][ceil_mode][k])) return MOSS_ERR_UNSUPPORTED;
+    if (!may_meet(tiles, cus * groups_per_cu(reinterpret_cast<const void *>(fn), threads, cached[want_row][ceil_mode][k]))) return MOSS_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(fn, dim3((unsigned)tiles), dim3(threads), 0, st, x, rows, cols, ld, (int)tiles_x, slots, call, polls, q_row,
                        e_row, q_col, e_col, s_global);
     MOSS_LAUNCH_CHECK();
@@ -1382,12 +1387,13 @@ static int quant_with_workspace(const void *x_bf16, int64_t rows, int64_t cols, 
         const int64_t grid = (int64_t)per_cu * moss_internal_cu_count();
         if (per_cu > 0 && n_tiles >= grid && n_tiles <= grid * kKeep) {
             uint32_t *sync = partial + kMaxPartials;
-            if (!call && !words_are_zero) {       // (the kernel leaves them at zero itself)
+            const uint64_t number = may_meet(grid, grid) ? call : 0;
+            if (!number && !words_are_zero) {       // (the kernel leaves them at zero itself)
                 hipLaunchKernelGGL(k_quant_sync_reset, dim3(1), dim3(kQuantThreads), 0, st, sync);
                 MOSS_LAUNCH_CHECK();
             }
             hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kQuantThreads), 0, st, x, rows, cols, ld, (int)tiles_x,
-                               (int)n_tiles, sync, (uint64_t *)workspace, call, g_poll_limit.load(), q_row, e_row, q_col, e_col, s_global);
+                               (int)n_tiles, sync, (uint64_t *)workspace, number, g_poll_limit.load(), q_row, e_row, q_col, e_col, s_global);
             MOSS_LAUNCH_CHECK();
             return MOSS_OK;
         }

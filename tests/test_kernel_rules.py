@@ -121,6 +121,12 @@ def test_workgroups_meet_where_their_tensor_fits_the_registers(L, rows, cols, ro
     assert ask(L.moss_internal_quant_meets, rows, cols, 1) == col
 
 
+@pytest.mark.parametrize("grid,held,meets", [(1, 1, 1), (512, 512, 1), (513, 512, 0), (1024, 4096, 1), (1025, 4096, 0), (4096, 4096, 0)])
+def test_a_grid_meets_where_all_of_it_runs_and_has_a_slot(L, grid, held, meets):
+    assert ask(L.moss_internal_quant_may_meet, grid, held) == meets
+    assert L.moss_quant_workspace_bytes(C.c_int64(1), C.c_int64(32), C.c_uint(1)) >= 1024 * 8
+
+
 # ragged K in the large tiles: where the first step of the choice has a slower kernel, with whole exponent dwords and outputs in
 # 16-byte pieces (0: the first step's kernel stands)
 @pytest.mark.parametrize("M,N,K,b_e,tile", [(11328, 3520, 2080, 0, 256256), (4160, 4480, 9824, 0, 256256), (2432, 6016, 2656, 1, 256256), (4096, 4096, 2080, 0, 256256),
