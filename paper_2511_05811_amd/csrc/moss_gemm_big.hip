@@ -289,8 +289,10 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
     for (int ti = 0; ti < n_my_tiles; ti++) {
         const bool has_next = ti + 1 < n_my_tiles;
         const int g0 = ti * T, sp0 = (ti * NB) & 1;      // global stage / scale block numbers of this tile's first
-        // Stage 0 and scale block 0 of this tile were issued two stages ago (or by the prologue),
-        // stage 1 just now: wait for all but the latter, then fetch the first fragments.
+        // Stage 0 and scale block 0 of this tile were issued two stages ago (or by the prologue).  Behind them came stage 1, in the
+        // prologue and behind a BF16 epilogue as the newest: all but it is waited for.  An FP32 epilogue issues stage 1 ahead
+        // of its stores: there the newest are the last kPiecesD stores, and stage 1 and the stores before them are waited
+        // for as well.  Then the first fragments are fetched.
         wait_vmcnt<kPiecesD>();
         wait_lds_and_barrier();
 #pragma unroll
@@ -416,8 +418,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm_mx_big(int64_t M, int64_t N, in
                 if (issue && (iP & 3) == 0) issue_scales(cx, iP >> 2, own ? (sp0 + (iP >> 2)) & 1 : (sp0 + NB) & 1);
             }
         }
-        // (stage 1 of the next tile belongs into the last stage's slot, which the epilogue uses first:
-        // it is issued after the epilogue)
+        // (stage 1 of the next tile belongs into the last stage's slot, through which a BF16 epilogue stages its outputs: it is
+        // issued behind that, or ahead of the stores of an FP32 epilogue, which does not use the slot)
         asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");   // let the last matrix instructions retire
 
         // ---- epilogue.  Accumulator register v of lane (i32, h) in fragment (i, j) is out[m, n] with
