@@ -90,7 +90,7 @@ def _check(rc, what):
         raise MossError(f"{what}: {load().moss_status_string(rc).decode()} (status {rc})")
 
 
-_calls = None      # the native calls, bound to the library; False if they have not been built for this torch
+_calls = None      # the native calls, bound to the library; False if they have not been built for this torch and this library
 
 
 def _bind_calls():
@@ -104,7 +104,11 @@ def _bind_calls():
         from . import _moss_calls as native
         get_device, get_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
         addresses = tuple(C.cast(getattr(L, n), C.c_void_p).value for n in names)
+        L.moss_internal_interface.restype = C.c_uint32
+        built_for_these = native.interface != 0 and (native.torch_version, native.interface) == (torch.__version__, L.moss_internal_interface())
     except (ImportError, AttributeError):
+        built_for_these = False
+    if not built_for_these:
         _calls = False
         return _calls
     native.bind(addresses, _check, AdamWArgs, get_device, get_stream)

@@ -1,5 +1,6 @@
 """Build libmoss_hip.so (gfx950) in-tree with hipcc, and the native calls of the binding, _moss_calls.so, with the host
 compiler.  `python -m paper_2511_05811_amd.build`."""
+import hashlib
 import os
 import subprocess
 import sys
@@ -19,9 +20,22 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Wno-unused-command-line-argument", "-Wno-inline-asm"]   # (the copies name M0 as clobbered: reserved, hence a warning)
 
 
+def interface():
+    """The number that the library and the native calls compiled against it share: of the headers that declare its functions."""
+    h = hashlib.sha256()
+    for path in (os.path.join(INCLUDE, "moss.h"), os.path.join(CSRC, "moss_producer.h")):
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return int(h.hexdigest()[:8], 16) | 1        # (never 0)
+
+
 def build(verbose=False):
+    """The library, and the native calls if they can be built: the binding works without them, so that hipcc is all it takes.  Native
+    calls of an earlier build do not stay beside the new library."""
+    if os.path.exists(CALLS):
+        os.remove(CALLS)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + FLAGS + ["-I", INCLUDE, "-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
+    cmd = [hipcc] + FLAGS + [f"-DMOSS_INTERFACE={interface()}u", "-I", INCLUDE, "-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
     if verbose:
         print(" ".join(cmd))
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -30,7 +44,10 @@ def build(verbose=False):
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err.strip():
         print(err, file=sys.stderr)
-    build_calls(verbose)
+    try:
+        build_calls(verbose)
+    except (OSError, ImportError, RuntimeError) as e:
+        print(f"no native calls for the binding ({e}): it makes them from Python", file=sys.stderr)
     return LIB
 
 
@@ -39,6 +56,7 @@ def build_calls(verbose=False):
     import torch
     home = os.path.dirname(torch.__file__)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           f"-DMOSS_INTERFACE={interface()}u", f'-DMOSS_TORCH_VERSION="{torch.__version__}"',
            "-I", INCLUDE, "-I", CSRC, "-isystem", os.path.join(home, "include"), "-isystem", sysconfig.get_paths()["include"], "-o", CALLS,
            os.path.join(CSRC, "moss_calls.cpp"), "-L", os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:

@@ -5,6 +5,7 @@
 #include <unistd.h>
 
 #include "moss_internal.h"
+#include "moss_producer.h"
 
 static std::atomic<int> g_cu_count[64];   // per device, 0 = not asked yet; racing first calls store the same value
 
@@ -45,6 +46,8 @@ bool moss_may_number_calls(hipStream_t st)
     }
     return status == hipStreamCaptureStatusNone;
 }
+
+extern "C" uint32_t moss_internal_interface(void) { return MOSS_INTERFACE; }
 
 extern "C" int moss_device_cu_count(void) { return moss_internal_cu_count(); }
 

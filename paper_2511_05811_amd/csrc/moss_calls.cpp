@@ -355,7 +355,7 @@ bool word(PyObject *o, Output &out, const at::Tensor &like)
     return true;
 }
 
-// BF16 rows of the stride of `like`: the caller's, or new ones (`checked_inner`: its columns have to be neighbours)
+// BF16 rows of the stride of `like`: the caller's (`check_stride`: of this very stride, columns neighbours), or new ones
 bool rows_out(PyObject *o, Output &out, const at::Tensor &like, bool check_stride)
 {
     const at::Tensor *t;
@@ -507,5 +507,12 @@ PyMODINIT_FUNC PyInit__moss_calls()
     k_e_col = PyUnicode_InternFromString("e_col");
     k_s = PyUnicode_InternFromString("s");
     if (!k_q_row || !k_e_row || !k_q_col || !k_e_col || !k_s) return nullptr;
-    return PyModule_Create(&module);
+    PyObject *m = PyModule_Create(&module);
+    // what this was compiled for: binding.py compares it with the torch and the library that it has before it binds anything
+    if (m && (PyModule_AddStringConstant(m, "torch_version", MOSS_TORCH_VERSION) < 0 ||
+              PyModule_AddObject(m, "interface", PyLong_FromUnsignedLong(MOSS_INTERFACE)) < 0)) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }

@@ -7,7 +7,14 @@
 
 constexpr size_t kProducerWorkspaceBytes = (2 * 2048 + 1) * 8;       // two words for each workgroup of the largest grid, one to hand over by
 
+// What the callers of this library's functions were compiled for: the build hands the library and the binding's native calls one number
+// made from moss.h and this file (0: built some other way, never the same as anything).
+#ifndef MOSS_INTERFACE
+#define MOSS_INTERFACE 0
+#endif
+
 extern "C" {
+uint32_t moss_internal_interface(void);
 int moss_internal_swiglu_bf16(const void *gate, const void *up, int64_t rows, int64_t cols, int64_t ld, void *h,
                               uint32_t *h_absmax_bits, void *workspace, size_t workspace_bytes, void *stream);
 int moss_internal_swiglu_bf16_backward(const void *gate, const void *up, const void *dh, int64_t rows, int64_t cols, int64_t ld,

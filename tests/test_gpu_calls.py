@@ -1,11 +1,14 @@
 """The binding's native calls give what its Python code gives: outputs, returned objects and refusals.  Every call below runs
 through both, on its own copies of the inputs."""
+import ctypes as C
+import types
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2511_05811_amd as moss
-from paper_2511_05811_amd import binding
+from paper_2511_05811_amd import binding, build
 
 ROW, COL = moss.MOSS_Q_ROW, moss.MOSS_Q_COL
 
@@ -48,6 +51,34 @@ def test_plain_arguments_are_what_the_native_calls_take():
     assert binding._calls.gemm_fp8_mx(x, None, x, x, None, x, None, False) is None
     with pytest.raises(AssertionError):
         moss.quant_act_2level(x)
+
+
+@pytest.mark.parametrize("other", ["torch_version", "interface", "interface of no build"])
+def test_native_calls_built_for_another_torch_or_library_are_left_alone(monkeypatch, other):
+    """They would read tensors of another layout, or call the library by another signature."""
+    lib = moss.load()
+    lib.moss_internal_interface.restype = C.c_uint32
+    marks = dict(torch_version=torch.__version__, interface=lib.moss_internal_interface())
+    bound = []
+    fake = types.SimpleNamespace(bind=lambda *a: bound.append(a), **marks)
+    monkeypatch.setattr(moss, "_moss_calls", fake, raising=False)
+    monkeypatch.setattr(binding, "_calls", None)
+    assert binding._bind_calls() is fake and len(bound) == 1            # (the marks as they are)
+    for name, value in {"torch_version": dict(torch_version="1.0"), "interface": dict(interface=marks["interface"] ^ 2),
+                        "interface of no build": dict(interface=0)}[other].items():
+        setattr(fake, name, value)
+    assert binding._bind_calls() is False and len(bound) == 1
+
+
+def test_the_library_builds_without_what_the_native_calls_need(monkeypatch, tmp_path, capsys):
+    lib, calls = tmp_path / "lib.so", tmp_path / "calls.so"
+    calls.write_text("of an earlier build")
+    monkeypatch.setattr(build, "LIB", str(lib))
+    monkeypatch.setattr(build, "CALLS", str(calls))
+    monkeypatch.setattr(build, "SOURCES", ["moss_api.hip"])
+    monkeypatch.setenv("CXX", str(tmp_path / "no compiler here"))
+    assert build.build() == str(lib)
+    assert lib.exists() and not calls.exists() and "no native calls" in capsys.readouterr().err
 
 
 @pytest.fixture
