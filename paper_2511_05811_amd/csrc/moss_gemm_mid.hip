@@ -440,40 +440,31 @@ __global__ __launch_bounds__(kMidThreads) void k_gemm_mx_mid(const MidArgs p)
         return;
     }
 
-    // ... and a single fragment: every wave leaves its sums in LDS (row pitch 32 floats, 16-byte chunks XOR-swizzled by row), then
-    // the workgroup walks the tile row by row, adds the KS parts in order, scales and stores.
-    // (accumulator register v of lane (i32, h) in fragment (i, j): row 32 i + i32, column 32 j + 8 (v / 4) + 4 h + v % 4)
-    constexpr int kChunks = 8 * NJ, kPart = 32 * MI * 32 * NJ;          // float4 per staged row; floats per wave
-    constexpr int kSwizzle = (kChunks & -kChunks) - 1;
+    // ... and a single fragment (32 x 32 tiles, a K group per wave): every wave leaves its sums in LDS (row pitch 32 floats, 16-byte
+    // chunks XOR-swizzled by row), then a thread adds the KS parts of four columns of a row in order, scales and stores.
+    // (accumulator register v of lane (i32, h): row i32, column 8 (v / 4) + 4 h + v % 4)
+    if (kFrags == 1) {
+        static_assert(kFrags > 1 || (WM * WN == 1 && S::kBM * S::kBN == 4 * kMidThreads), "four outputs per thread");
+        constexpr int kPart = 32 * 32;               // floats per wave
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[0][0]));   // the last matrix instructions retire
+        __syncthreads();                             // slots and exponents have been read
+        float *part = reinterpret_cast<float *>(mid_smem);
 #pragma unroll
-    for (int i = 0; i < MI; i++)
-#pragma unroll
-        for (int j = 0; j < NJ; j++) asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[i][j]));   // the last matrix instructions retire
-    __syncthreads();                             // slots and exponents have been read
-    float *part = reinterpret_cast<float *>(mid_smem);
-#pragma unroll
-    for (int i = 0; i < MI; i++)
-#pragma unroll
-        for (int j = 0; j < NJ; j++)
-#pragma unroll
-            for (int qd = 0; qd < 4; qd++)
-                *reinterpret_cast<float4 *>(part + wave * kPart + (i * 32 + i32) * 32 * NJ + (((8 * j + 2 * qd + h) ^ (i32 & kSwizzle)) << 2)) =
-                    make_float4(acc[i][j][4 * qd], acc[i][j][4 * qd + 1], acc[i][j][4 * qd + 2], acc[i][j][4 * qd + 3]);
-    __syncthreads();
-    const bool vec_ok = p.ld_out % 4 == 0;
-#pragma unroll 4
-    for (int id = tid; id < kBM * kBN / 4; id += kMidThreads) {
-        const int row = id / (kBN / 4), c4 = id % (kBN / 4);
-        const int rw = row / (32 * MI), rr = row % (32 * MI), cw = c4 / kChunks, cc = c4 % kChunks;
-        const float *src = part + (rw * WN + cw) * kPart + rr * 32 * NJ + ((cc ^ (rr & kSwizzle)) << 2);
+        for (int qd = 0; qd < 4; qd++)
+            *reinterpret_cast<float4 *>(part + wave * kPart + i32 * 32 + (((2 * qd + h) ^ (i32 & 7)) << 2)) =
+                make_float4(acc[0][0][4 * qd], acc[0][0][4 * qd + 1], acc[0][0][4 * qd + 2], acc[0][0][4 * qd + 3]);
+        __syncthreads();
+        const bool vec_ok = p.ld_out % 4 == 0;
+        const int row = tid / 8, c4 = tid % 8;
+        const float *src = part + row * 32 + ((c4 ^ (row & 7)) << 2);
         float4 t = *reinterpret_cast<const float4 *>(src);
 #pragma unroll
         for (int k = 1; k < KS; k++) {
-            const float4 u = *reinterpret_cast<const float4 *>(src + k * WM * WN * kPart);
+            const float4 u = *reinterpret_cast<const float4 *>(src + k * kPart);
             t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
         }
         const int64_t m = m0 + row, nn = n0 + 4 * c4;
-        if (m >= M || nn >= N) continue;
+        if (m >= M || nn >= N) return;
         const float r[4] = {t.x * scale, t.y * scale, t.z * scale, t.w * scale};
         if (p.out_f32) {
             float *o = reinterpret_cast<float *>(p.out) + m * p.ld_out + nn;
