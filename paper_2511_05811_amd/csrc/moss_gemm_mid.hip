@@ -529,17 +529,19 @@ static int launch_mid(MidArgs p, int budget, hipStream_t st)
 // units a fixed part (first latency, exponents, epilogue) and a part per iteration (stages of K = 128, dealt over the K groups
 // of a tile), each with a share that grows with how full the rounds are.  The constants are fits to 2200 random problems (M 32 to
 // 12000, N 256 to 12288, K 128 to 12288; calls back to back on two sets of operands, 256 compute units), each run in every
-// kernel that can take it; the fits miss by 2 to 7 % (mean), 10 % at the 10th and 90th percentile.  K % 128 != 0: the rows no longer start on lines and
+// kernel that can take it; the fits missed by 2 to 7 % (mean), 10 % at the 10th and 90th percentile.  K % 128 != 0: the rows no longer start on lines and
 // the exponents are cut out of two dwords, so that a stage costs more.  "b" marks exponents of b, whose outputs are FP32.
+// The fits are from before tiles of 64 x 128 and more, and FP32 outputs of the large ones, stored from the registers: a round of
+// these takes up to 3 us less by now, of the large ones up to 5.  What the kernels take now:
 //   tile        (M, N, K) measured / model
-//   32 x 32     (256, 1024, 1024) 4.2 / 4.5    (17, 11008, 4096) 10.2 / 10.1
-//   64 x 64     (1024, 1024, 1024) 6.5 / 7.0   (256, 4096, 4096) 12.0 / 12.3
-//   64 x 128    (512, 4096, 1024) 8.6 / 8.9    (512, 4096, 4096) 15.5 / 16.3
-//   128 x 128   (2048, 2048, 1024) 12.2 / 12.1 (2048, 2048, 4096) 23.8 / 24.0
-//   128 x 192   (2048, 3072, 1024) 15.4 / 15.5 (2048, 3072, 7168) 45.6 / 44.6
-//   large       (2048, 4096, 2048) 19.7 / 18.9 (4096, 4096, 4096) 56 / 58      (4096, 4096, 512) b 27.8 / 28.1
-//   ... ragged  (11328, 3520, 2080) 99.6 / 105 (1336, 4096, 4128) 38.6 / 36.4  (2432, 6016, 2656) b 55.4 / 57.3
-//   general     (4096, 4096, 2080) 62 / 62     (6321, 2424, 32) 15.7 / 15.9    (2528, 2912, 8032) b 136 / 131
+//   32 x 32     (256, 1024, 1024) 4.4 / 4.5    (17, 11008, 4096) 10.0 / 10.1
+//   64 x 64     (1024, 1024, 1024) 6.3 / 7.0   (256, 4096, 4096) 12.0 / 12.3
+//   64 x 128    (512, 4096, 1024) 7.8 / 8.9    (512, 4096, 4096) 14.7 / 16.3
+//   128 x 128   (2048, 2048, 1024) 10.0 / 12.1 (2048, 2048, 4096) 22.6 / 24.0
+//   128 x 192   (2048, 3072, 1024) 12.5 / 15.5 (2048, 3072, 7168) 43.4 / 44.6
+//   large       (2048, 4096, 2048) 19.7 / 18.9 (4096, 4096, 4096) 60 / 58      (4096, 4096, 512) b 23.7 / 28.1
+//   ... ragged  (11328, 3520, 2080) 105 / 105  (1336, 4096, 4128) 40.9 / 36.4  (2432, 6016, 2656) b 56.0 / 57.3
+//   general     (4096, 4096, 2080) 66 / 62     (6321, 2424, 32) 14.8 / 15.9    (2528, 2912, 8032) b 128 / 131
 namespace {
 
 double rounds_of(double tiles, double cus) { return tiles <= cus ? 1.0 : std::ceil(tiles / cus); }
@@ -573,12 +575,18 @@ MidPlan plan_mid(int64_t M, int64_t N, int64_t K, bool b_exponents, bool accumul
     const int r = K % 128 != 0, b = b_exponents;
     const int64_t C = (K + 127) / 128;
     const double it4 = (double)((C + 3) / 4), it2 = (double)((C + 1) / 2), t0 = tiles_of(M, N, 32, 32);
+    // (an accumulating round of 128 rows is charged 3 or 5 us, which is also from before: 3520 x 1540 x 1184 with exponents of b 25.0 us in
+    // 128 x 192 tiles, 29.1 in the general kernel, which has it)
     const double us[5] = {t0 <= cus ? one[r][b][0] + one[r][b][1] * it4 : 2.2 + rounds_of(t0, cus) * (more[r][b][0] + more[r][b][1] * it4),
                           us_of(cost[0][r][b], tiles_of(M, N, 64, 64), cus, it4), us_of(cost[1][r][b], tiles_of(M, N, 64, 128), cus, it2),
                           us_of(cost[2][r][b], tiles_of(M, N, 128, 128), cus, (double)C, accumulate ? 3.0 : 0.0),
                           us_of(cost[3][r][b], tiles_of(M, N, 128, 192), cus, (double)C, accumulate ? 5.0 : 0.0)};
     MidPlan best{0, us[0]};
-    for (int k = 1; k < (large_ok ? 4 : 5); k++)     // (large tiles, where they can take the problem, beat 128 x 192)
+    // (128 x 192 is left out where the large tiles can take the problem: they beat it before its loop became a quarter faster.  Since
+    // then they do not always: 1333 x 4096 x 11008 69.6 us in half tiles, 62.8 in 128 x 192; 1492 x 3360 x 9344 57.5, 51.1; 2272 x 7712 x
+    // 4992 116.0, 95.6; 1499 x 11168 x 3328 83.7, 67.2; but 2048 x 12288 x 4096 105.3, 109.8; 2048 x 4096 x 12288 89.6, 124.7;
+    // 8192 x 4096 x 4096 117.0, 160.9.)
+    for (int k = 1; k < (large_ok ? 4 : 5); k++)
         if (us[k] < 0.97 * best.us) best = MidPlan{k, us[k]};
     return best;
 }
@@ -622,10 +630,9 @@ MidPlan plan_small_or_other(int64_t M, int64_t N, int64_t K, const uint8_t *a_e,
 
 }  // namespace
 
-// The kind of tiles (0 .. 4), -1 to leave the problem to the kernel that would have it otherwise.  Over the 2200 problems the
-// kernels that this and the rule below choose take 0.5 % more than the fastest of each (mean), and 2.2 % less than those that
-// were chosen before; six take more than then, by 4 to 12 %.  (The fits are from before tiles of 64 x 128 and more stored from
-// the registers, which takes 0.6 to 2.5 us off each of their rounds: since then 1.3 % over 2000 other problems.)
+// The kind of tiles (0 .. 4), -1 to leave the problem to the kernel that would have it otherwise.  Over the 2200 problems, with the
+// kernels as they were when fitted, the ones that this and the rule below choose took 0.5 % more than the fastest of each
+// problem (mean).  With the kernels as they are now it is 1.3 % over 2000 other problems.
 int moss_internal_gemm_mid_kind(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int accumulate,
                                 bool large_ok)
 {
@@ -633,8 +640,8 @@ int moss_internal_gemm_mid_kind(int64_t M, int64_t N, int64_t K, const uint8_t *
 }
 
 // Whether k_gemm_mx_big takes a problem with K % 128 != 0 from the kernel that has it by the rule above: where it is
-// expected to be a fourteenth faster (a fifth for a short K with exponents of b, as above).  4096 x 4096 x 2080 62 -> 39 us, 11328 x 3520 x
-// 2080 169 -> 100, 4160 x 4480 x 9824 305 -> 217, 2432 x 6016 x 2656 with exponents of b 105 -> 55.
+// expected to be a fourteenth faster (a fifth for a short K with exponents of b, as above).  4096 x 4096 x 2080 66 -> 41 us, 11328 x 3520 x
+// 2080 175 -> 105, 4160 x 4480 x 9824 287 -> 223, 2432 x 6016 x 2656 with exponents of b 105 -> 56.
 bool moss_internal_gemm_big_ragged(int64_t M, int64_t N, int64_t K, const uint8_t *a_e, const uint8_t *b_e, int accumulate,
                                    int64_t ld_out)
 {
