@@ -235,9 +235,12 @@ int rows_grid(int64_t rows)
 {
     int cus = moss_internal_cu_count();
     if (cus <= 0) cus = 256;
-    // Four workgroups per compute unit: each ends on the caller's word, one after the other.  Norm forward and backward with
-    // their quantizers, 2 / 4 / 8 per compute unit: 2048 x 4096 63 / 68 / 88 us, 4096 x 4096 94 / 96 / 111, 8192 x 4096
-    // 168 / 154 / 165, 8192 x 8192 313 / 292 / 299.
+    // Four workgroups per compute unit, grid-stride beyond.  Norm forward and backward with their quantizers, us, 2 / 4 / 8 per
+    // compute unit, maxima in slots (two leave too little in flight, eight have more slots to fold):
+    //     1024 x 4096 47 / 45 / 45    2048 x 4096 61 / 57 / 57    4096 x 4096 92 / 86 / 87    8192 x 4096 167 / 148 / 150
+    //     8192 x 8192 314 / 280 / 283
+    // and merged into the caller's word, where the ends of the workgroups queue: 2048 x 4096 63 / 68 / 88, 4096 x 4096
+    // 94 / 96 / 111, 8192 x 4096 168 / 154 / 165, 8192 x 8192 313 / 292 / 299.
     const int64_t cap = (int64_t)cus * 4;
     return (int)(rows < cap ? rows : cap);
 }

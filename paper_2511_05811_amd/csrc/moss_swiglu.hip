@@ -217,8 +217,9 @@ int grid_for(int64_t n_chunks)
     const int64_t want = (n_chunks + (int64_t)kSwThreads * per_thread - 1) / ((int64_t)kSwThreads * per_thread);
     int cus = moss_internal_cu_count();
     if (cus <= 0) cus = 256;
-    // eight workgroups per compute unit, grid-stride beyond: every one ends on the caller's words (4096 x 11008 with the quantizers
-    // 259 us at 4, 8 and 16 per compute unit, 2048 x 11008 143 / 144 / 163)
+    // Eight workgroups per compute unit, grid-stride beyond, as many as have slots for their maxima (kMaxSlotBlocks).  Forward and backward
+    // with the quantizers, us, 4 and 8: 1024 x 11008 86 and 87, 2048 x 11008 138 both, 4096 x 11008 253 and 254; merged into the caller's
+    // words, 4 / 8 / 16: 2048 x 11008 143 / 144 / 163, 4096 x 11008 259 each.
     const int64_t cap = (int64_t)cus * 8;
     return (int)(want < cap ? want : cap);
 }
