@@ -120,9 +120,9 @@ int moss_quant_act_2level_noalloc(const void *x_bf16, int64_t rows, int64_t cols
  * slow path (used by the tests).  The one-launch kernels assume that their grid fits the device: when
  * other kernels occupy compute units at the same time (calls on several streams at once) part of it may
  * have to wait for them, and workgroups then fall back to the slow path after the bound -- correct, but
- * slow: four streams of calls of 16 MiB and more in turn take milliseconds a call, of 8 to 16 MiB with column
- * groups 80 to 120 microseconds (smaller ones, two streams, and calls beside a GEMM lose little or nothing);
- * such calls should be serialised on one stream.  The bound holds as well for the workgroup of moss_weight_autoscale_cast
+ * slow: three or four streams of calls of 16 MiB and more with column groups, or of 64 MiB without, take
+ * milliseconds a call, four of 12 to 16 MiB with column groups 30 to 120 microseconds (smaller ones, two
+ * streams, and calls beside a GEMM lose little or nothing); such calls should be serialised on one stream.  The bound holds as well for the workgroup of moss_weight_autoscale_cast
  * and of the BF16 producers below that collects what the others have found: past it, one that comes
  * later does. */
 void moss_quant_set_poll_limit(unsigned polls);
